@@ -3,25 +3,20 @@
 //   y = x w^T,   dx = dy w,   dw = dy^T x        x [M,K], w [N,K], y, dy [M,N], all bf16 row-major.
 // All three are C[I,J] = sum_r A(i,r) B(j,r) with each operand stored either with r contiguous
 // ("direct": x and w in the forward, dy in dx) or with its output index contiguous ("transposed":
-// w in dx, dy and x in dw), so one kernel template with two flags serves them.
+// w in dx, dy and x in dw), so kernel templates with two flags serve them.
 //
-// A workgroup of 8 wavefronts (two per SIMD, so that one wave's barrier and LDS waits are
-// covered by the other's MFMAs) computes one 256 x 256 tile of C at a time (the grid is one
-// workgroup per CU, each walking its share of the tiles); wave (wi, wj) owns 128 x 64 of it as
-// 4 x 2 blocks of v_mfma_f32_32x32x16_bf16 (128 accumulator registers).  The contraction runs
-// in steps of 64 through two LDS stages of 64 KiB filled by asynchronous global->LDS copies.
-// Tiles sit in LDS row-major with swizzled 16-byte chunks; a direct operand's
-// fragment is one 16-byte LDS read, a transposed operand's fragment two transpose loads.  The
-// products are formed transposed, C^T = B A^T (B's rows as the MFMA's row operand), so that a
-// lane ends up holding one row i of C with consecutive j in its registers and the epilogue
-// writes 16 bytes per lane.  Each k-step reads 4 + 2 fragments for 8 MFMAs: 0.75 KiB of LDS
-// reads per MFMA, plus 0.25 KiB of copy writes.  (Four waves
-// owning 128 x 128 each, 0.5 KiB of reads per MFMA, were tried both compiler-scheduled and with
-// a hand-written instruction order and a mid-stage barrier: with one wave per SIMD the barrier
-// and the issue cost of the copy instructions are exposed, and neither version was faster.)
+// Two kernels share the tile order, the copies and the fragment layouts.  linear_pp_kernel computes 256 x 256 tiles of C
+// and is the faster one per product; linear_ring_kernel computes smaller ones, down to 32 x 32, for outputs that
+// do not fill the chip with large tiles (pick_tile below chooses).  In both a workgroup is 8 wavefronts (two per SIMD),
+// one workgroup per CU, each walking its share of the tiles; operands reach LDS by asynchronous copies that run ahead
+// of the products across tile boundaries.  Tiles sit in LDS row-major with swizzled 16-byte chunks; a direct operand's
+// fragment is one 16-byte LDS read, a transposed operand's two transpose loads.  The products are formed transposed,
+// C^T = B A^T (B's rows as the MFMA's row operand), so that a lane ends up holding one row i of C with consecutive j.
 #include "../../include/ie_linear.h"
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "attn_common.hpp"
 #include "launch.hpp"
@@ -30,10 +25,6 @@ namespace ie {
 namespace {
 
 constexpr int kWaves = 8;
-constexpr int TI = 256, TJ = 256, TR = 64;
-constexpr int G_TILE_BYTES = TI * TR * 2;          // 32 KiB, either layout
-constexpr int G_STAGE_BYTES = 2 * G_TILE_BYTES;    // A tile | B tile
-constexpr int G_SMEM_BYTES = 2 * G_STAGE_BYTES;
 constexpr int kPanel = 8;                          // i-tiles that share a j-tile back to back
 
 struct GemmParams {
@@ -46,7 +37,7 @@ struct GemmParams {
   int tiles_i, tiles_j, tiles;
 };
 
-// Swizzle of a direct tile (256 rows of 128 bytes): the 16-byte chunk c of row r sits at chunk position
+// Swizzle of a direct tile (rows of 128 bytes): the 16-byte chunk c of row r sits at chunk position
 // c ^ dswz(r).  A 16-byte LDS read is served 16 lanes at a time across 256 bytes of banks, i.e. two rows
 // of this tile side by side, so the 16 consecutive rows of a fragment read must put the requested
 // chunk at 8 different positions for the even rows and 8 for the odd ones.  (The attention tiles'
@@ -54,50 +45,76 @@ struct GemmParams {
 // LDS cycles of the forward product were bank conflicts with it.)
 __device__ __forceinline__ uint32_t dswz(uint32_t r) { return (r >> 1) & 7u; }
 
-// Asynchronous copy of one operand tile into LDS.  `valid` = rows (direct) or 16-byte chunks
-// (transposed) of the tile that exist along the output index; lanes past it repeat the last one.
-// WAVES: how many of the workgroup's waves take part in a copy (8: all; 4: waves 0-3 or waves 4-7, see the kernel).
-template <bool T, int WAVES>
+// One wave's share of the copy of SUB consecutive 64-deep tiles of one operand, `ext` = tile extent along the output
+// index.  Instruction t of wave w is piece w + 8 t of the SUB * ext / 8 pieces of 1 KiB, in LDS order.  `subs` of the
+// SUB tiles exist (the others repeat the last one and are not used); `sub_step` = bytes between them.
+template <bool T, int EXT, int SUB>
 struct TileCopy {
-  static constexpr int NI = 32 / WAVES;   // 1 KiB instructions per wave per tile
-  uint32_t row;    // tile row this lane fetches in instruction 0: direct tiles add 8*WAVES per instruction, transposed 2*WAVES
-  uint32_t chunk;  // its 16-byte chunk POSITION inside the row
+  static constexpr int PIECES = EXT / 8;              // 1 KiB pieces of one 64-deep tile
+  static constexpr int NI = SUB * PIECES / kWaves;
+  static constexpr int CPR = T ? EXT / 8 : 8;         // 16-byte chunks per row
+  static constexpr int RPP = 64 / CPR;                // rows per piece
+  uint32_t row, chunk;   // this lane's row and chunk POSITION in piece 0
+  uint32_t voff;         // its byte offset in instruction 0 of a whole tile, and in the others up to whole rows
   int wave;
-  __device__ __forceinline__ void init(int tid) {
+  __device__ __forceinline__ void init(int tid, uint32_t pitch) {
     const int lane = tid & 63;
-    wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WAVES;
-    row = T ? 2 * wave + lane / 32 : 8 * wave + lane / 8;
-    chunk = T ? lane % 32 : lane % 8;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    row = lane / CPR;
+    chunk = lane % CPR;
+    // (from one instruction to the next a lane's row moves by a multiple of 16, which leaves the swizzle as it is)
+    const uint32_t r = row + (uint32_t)(wave % PIECES) * RPP;
+    voff = r * pitch + ((chunk ^ (T ? (uint32_t)swz<EXT>((int)r) : dswz(r))) << 4);
+    static_assert((kWaves % PIECES == 0 || kWaves * RPP % 16 == 0), "");
   }
-  // `g`: first byte of the tile in global memory (wave-uniform); `lds`: byte address of the tile.
-  __device__ __forceinline__ void issue(uint32_t lds, const char* g, uint32_t pitch, int valid) const {
+  // WHOLE: the tile exists in full, no per-lane arithmetic.
+  template <bool WHOLE>
+  __device__ __forceinline__ void issue(uint32_t lds, const char* g, uint32_t pitch, int valid, int64_t sub_step, int subs) const {
 #pragma unroll
     for (int t = 0; t < NI; ++t) {
-      uint32_t voff;
-      if (!T) {
-        const uint32_t r = row + 8 * WAVES * t;
-        const uint32_t lc = chunk ^ dswz(r);             // the logical chunk that belongs at this position
-        const uint32_t rc = r < (uint32_t)valid ? r : (uint32_t)valid - 1;
-        voff = rc * pitch + (lc << 4);
-      } else {
-        const uint32_t r = row + 2 * WAVES * t;
-        const uint32_t lc = chunk ^ swz<256>(r);
-        const uint32_t ch = lc < (uint32_t)valid ? lc : (uint32_t)valid - 1;
-        voff = r * pitch + (ch << 4);
+      const int piece = wave + kWaves * t;
+      int sub = piece / PIECES;
+      if (SUB > 1) sub = sub < subs ? sub : subs - 1;
+      const char* src = g + sub * sub_step;
+      const uint32_t dst = lds + (uint32_t)piece * 1024;
+      if constexpr (WHOLE) {
+        async_copy16(voff, src + (int64_t)(kWaves * t % PIECES * RPP) * pitch, dst);
+        continue;
       }
-      async_copy16(voff, g, lds + (uint32_t)(wave + WAVES * t) * 1024);
+      const uint32_t r = row + (uint32_t)(piece % PIECES) * RPP;
+      uint32_t v;
+      if (!T) {
+        v = (r < (uint32_t)valid ? r : (uint32_t)valid - 1) * pitch + ((chunk ^ dswz(r)) << 4);
+      } else {
+        const uint32_t lc = chunk ^ (uint32_t)swz<EXT>((int)r);
+        v = r * pitch + ((lc < (uint32_t)valid ? lc : (uint32_t)valid - 1) << 4);
+      }
+      async_copy16(v, src, dst);
     }
   }
 };
 
-// Fragment of the 32 output indices o .. o+31 of a tile for contraction step ks (16 values of r).
-template <bool T>
-__device__ __forceinline__ bf16x8 frag(const char* tile, int lane, int o, int ks) {
+// Operand of v_mfma_f32_32x32x16_bf16: output indices o .. o+31, 16-deep slice ks of one 64-deep tile of extent EXT
+// (pitch 128 bytes, or 2 EXT if transposed).
+template <bool T, int EXT>
+__device__ __forceinline__ bf16x8 ring_frag(const char* tile, int lane, int o, int ks) {
   const int n = lane & 31, h = lane >> 5;
   if (!T) return lds_read8(tile, (o + n) * 128 + (((2 * ks + h) ^ (int)dswz((uint32_t)(o + n))) << 4));
   const int c0 = o + 16 * ((lane >> 4) & 1), r0 = 16 * ks + 8 * h;
-  return cat4(lds_read_tr4(tile + tr_off<256>(lane, r0, c0)), lds_read_tr4(tile + tr_off<256>(lane, r0 + 4, c0)));
+  return cat4(lds_read_tr4(tile + tr_off<EXT>(lane, r0, c0)), lds_read_tr4(tile + tr_off<EXT>(lane, r0 + 4, c0)));
 }
+
+// Operand of v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, contraction indices 8 (l / 16) .. +7): output indices
+// o .. o+15, 32-deep slice ks.
+template <bool T, int EXT>
+__device__ __forceinline__ bf16x8 frag16(const char* tile, int lane, int o, int ks) {
+  const int n = lane & 15, g = lane >> 4;
+  if (!T) return lds_read8(tile, (o + n) * 128 + (((4 * ks + g) ^ (int)dswz((uint32_t)(o + n))) << 4));
+  const int r0 = 32 * ks + 8 * g;
+  return cat4(lds_read_tr4(tile + tr_off<EXT>(lane, r0, o)), lds_read_tr4(tile + tr_off<EXT>(lane, r0 + 4, o)));
+}
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
 // One lane's share of a 32 x 32 accumulator block: row i of C, 32 consecutive j, of which the
 // first `cols` (a multiple of 8) exist.  Same exchange as store_block32_bf16.
@@ -137,9 +154,9 @@ struct GemmTile {
   const char* gb;
   int64_t i0, j0;
   int i_valid, j_valid, a_valid, b_valid;
-  bool valid;
+  bool valid, whole;   // whole: TI x TJ outputs exist
 };
-template <bool A_T, bool B_T>
+template <bool A_T, bool B_T, int TI, int TJ>
 __device__ __forceinline__ GemmTile decode_gemm_tile(const GemmParams& p, int l) {
   GemmTile g;
   const int per = (p.tiles + 7) / 8;
@@ -155,6 +172,7 @@ __device__ __forceinline__ GemmTile decode_gemm_tile(const GemmParams& p, int l)
   g.j0 = (int64_t)tj * TJ;
   g.i_valid = (int)(p.I - g.i0 < TI ? p.I - g.i0 : TI);
   g.j_valid = (int)(p.J - g.j0 < TJ ? p.J - g.j0 : TJ);
+  g.whole = g.i_valid == TI && g.j_valid == TJ;
   g.ga = p.a + (A_T ? g.i0 * 2 : g.i0 * p.a_pitch);
   g.gb = p.b + (B_T ? g.j0 * 2 : g.j0 * p.b_pitch);
   g.a_valid = A_T ? g.i_valid / 8 : g.i_valid;
@@ -162,88 +180,346 @@ __device__ __forceinline__ GemmTile decode_gemm_tile(const GemmParams& p, int l)
   return g;
 }
 
+// ---- 256 x 256 tiles ------------------------------------------------------------------------------
+// Bound: the matrix pipeline at the clock that power management grants.  What an MFMA costs in power is why this
+// kernel is built on the 16x16x32 form (half the accumulator traffic per product of the 32x32x16 one): with the same
+// schedule the 32x32x16 form took 2-7 % longer at 8192 tokens x 4096, at a lower clock.
+// Wave (wi, wj) owns rows 64 wi .. +63 of both 128-row halves A0, A1 of the tile and columns 32 wj .. +31 of both
+// 128-column halves B0, B1 (128 accumulator registers).  The two waves of a SIMD (w and w + 4) alternate: while one
+// runs a cluster of 32 MFMAs, the other reads its next operands and issues copies; one workgroup barrier separates the
+// turns, waves 4-7 are one turn late.  A 64-deep step is two turns: read A0, B0, B1, products A0 B0 and A0 B1; read A1,
+// products A1 B1 and A1 B0.  A half that has been read is copied over at once with the step after next's, so a copy
+// has a whole step to arrive in two LDS stages of 64 KiB.  (Four turns of 16 MFMAs per step, copies behind the MFMAs
+// instead of behind the reads, 32-deep steps in a ring of four or five, and one turn of 64 per step were 3-4 %, 15-20 %,
+// 10-15 % and 40 % slower: every turn pays an LDS latency, and a copy that waits for the memory pipeline in a cluster
+// holds the MFMAs behind it.)
+// 8192 tokens, the twelve products of hidden 4096 / MLP 11008: 0.50-0.55 of the 2.5 PFLOP/s peak (forward products
+// 660 -> 602, 226 -> 208, 1178 -> 1102, 588 -> 528 us against eight waves in step at one barrier per 64-deep step;
+// dx 653 -> 607, 637 -> 588; dw 677 -> 658, 625 -> 607).
+constexpr int TI = 256, TJ = 256;
+constexpr int P_HALF_BYTES = 128 * 128;              // half an operand tile: 128 output indices x 64 deep
+constexpr int P_STAGE_BYTES = 4 * P_HALF_BYTES;      // A0 | A1 | B0 | B1
+constexpr int P_SMEM_BYTES = 2 * P_STAGE_BYTES;
 template <bool A_T, bool B_T>
-__global__ __launch_bounds__(kWaves * 64, 1) void linear_gemm_kernel(GemmParams p) {
-  constexpr int NJB = 2;   // 32-column blocks per wave: it owns 128 x 64 of the tile
+__global__ __launch_bounds__(kWaves * 64, 1) void linear_pp_kernel(GemmParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int n = lane & 31, h = lane >> 5;
-  // Persistent: this workgroup takes every (gridDim/8)-th tile of its XCD's share.  The first
-  // copy of the next tile is issued in the last contraction step of the current one, so the
-  // epilogue's stores overlap it; the stage parity simply keeps running across tiles.
-  int l = (int)(blockIdx.x >> 3);
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, g4 = lane >> 4;
+  const int wi = wv & 1, wj = (wv >> 1) & 3;
+  const bool late = wv >= 4;
   const int lstep = (int)(gridDim.x >> 3);
-  GemmTile cur = decode_gemm_tile<A_T, B_T>(p, l);
-  if (!cur.valid) return;
-  const int64_t a_step = A_T ? TR * p.a_pitch : TR * 2;
-  const int64_t b_step = B_T ? TR * p.b_pitch : TR * 2;
+  const int nkt = (int)(p.R / 64);
+  const int64_t a_step = A_T ? 64 * p.a_pitch : 128, b_step = B_T ? 64 * p.b_pitch : 128;
+  const int64_t a_half = A_T ? 256 : 128 * p.a_pitch, b_half = B_T ? 256 : 128 * p.b_pitch;
 
-  // With both operands direct (the forward product) the two waves of a SIMD (w and w + 4) take turns copying: one
-  // issues all 16 copy instructions of a stage while the other already has the matrix pipeline, instead of both
-  // issuing 8 in front of their first MFMAs (forward products +2-4 %; with a transposed operand the same
-  // arrangement loses 2-8 %, so those keep all eight waves copying).
-  constexpr bool kTakeTurns = !A_T && !B_T;
-  constexpr int kCopyWaves = kTakeTurns ? 4 : kWaves;
-  TileCopy<A_T, kCopyWaves> ca;
-  TileCopy<B_T, kCopyWaves> cb;
-  ca.init(tid);
-  cb.init(tid);
+  TileCopy<A_T, 128, 1> ca;
+  TileCopy<B_T, 128, 1> cb;
+  ca.init(tid, (uint32_t)p.a_pitch);
+  cb.init(tid, (uint32_t)p.b_pitch);
   const uint32_t lds0 = lds_address(smem);
-  auto copy_stage = [&](const GemmTile& g, int kt, int stage) __attribute__((always_inline)) {
-    if (kTakeTurns && (wv >> 2) != (stage & 1)) return;
-    const uint32_t base = lds0 + stage * G_STAGE_BYTES;
-    ca.issue(base, g.ga + kt * a_step, (uint32_t)p.a_pitch, g.a_valid);
-    cb.issue(base + G_TILE_BYTES, g.gb + kt * b_step, (uint32_t)p.b_pitch, g.b_valid);
-  };
 
-  const int wi = wv & 1, wj = wv >> 1;   // this wave's part of the tile
-  f32x16 acc[4][NJB];
-  const int nkt = (int)(p.R / TR);
-  int stage = 0;
-  copy_stage(cur, 0, 0);
+  int cl = (int)(blockIdx.x >> 3), ckt = 0, cslot = 0;
+  GemmTile ctile = decode_gemm_tile<A_T, B_T, TI, TJ>(p, cl);
+  if (!ctile.valid) return;
+  GemmTile cur = ctile;
+  int l = cl;
+  // Half `hf` of an operand tile; a half that lies past the end repeats the last row (chunk) of the first.  (One branch
+  // for all the copies of a turn: a branch per copy made the kernel 20 % slower.)
+  auto copy_a = [&](int hf, auto whole) __attribute__((always_inline)) {
+    constexpr int U = A_T ? 16 : 128;
+    const bool in = decltype(whole)::value || hf == 0 || ctile.a_valid > U;
+    ca.template issue<decltype(whole)::value>(lds0 + cslot * P_STAGE_BYTES + hf * P_HALF_BYTES, ctile.ga + ckt * a_step + (hf && in ? a_half : 0), (uint32_t)p.a_pitch,
+             hf && in ? ctile.a_valid - U : ctile.a_valid, 0, 1);
+  };
+  auto copy_b = [&](int hf, auto whole) __attribute__((always_inline)) {
+    constexpr int U = B_T ? 16 : 128;
+    const bool in = decltype(whole)::value || hf == 0 || ctile.b_valid > U;
+    cb.template issue<decltype(whole)::value>(lds0 + cslot * P_STAGE_BYTES + (2 + hf) * P_HALF_BYTES, ctile.gb + ckt * b_step + (hf && in ? b_half : 0), (uint32_t)p.b_pitch,
+             hf && in ? ctile.b_valid - U : ctile.b_valid, 0, 1);
+  };
+  auto advance = [&]() __attribute__((always_inline)) {
+    cslot ^= 1;
+    if (++ckt == nkt) {
+      ckt = 0;
+      cl += lstep;
+      ctile = decode_gemm_tile<A_T, B_T, TI, TJ>(p, cl);
+    }
+  };
+  auto copy_first = [&](auto whole) __attribute__((always_inline)) { copy_a(0, whole); copy_b(0, whole); copy_b(1, whole); };
+  auto copy_first_any = [&]() __attribute__((always_inline)) {
+    if (ctile.whole) copy_first(std::true_type{});
+    else copy_first(std::false_type{});
+  };
+  auto copy_last_any = [&]() __attribute__((always_inline)) {
+    if (ctile.whole) copy_a(1, std::true_type{});
+    else copy_a(1, std::false_type{});
+  };
+  copy_first_any();
+  copy_last_any();
+  advance();
+  bool pend = ctile.valid;   // the step at the copies' position lacks its A1
+  if (pend) copy_first_any();
+  async_wait_all();
+  __syncthreads();
+  auto bar = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto reads_done = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (late) bar();
+  int slot = 0;
   for (;;) {
-    l += lstep;
-    const GemmTile nxt = decode_gemm_tile<A_T, B_T>(p, l);
+    f32x4 acc[2][2][4][2];   // [A half][B half][ib][jb]
 #pragma unroll
-    for (int ib = 0; ib < 4; ++ib)
+    for (int x = 0; x < 32; ++x) acc[x >> 4][(x >> 3) & 1][(x >> 1) & 3][x & 1] = f32x4{0, 0, 0, 0};
+    bf16x8 fa[4][2], fb[2][2][2];
+    for (int kt = 0; kt < nkt; ++kt) {
+      const char* st = smem + slot * P_STAGE_BYTES;
+      auto read_a = [&](int hf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int ib = 0; ib < 4; ++ib) fa[ib][ks] = frag16<A_T, 128>(st + hf * P_HALF_BYTES, lane, wi * 64 + ib * 16, ks);
+      };
+      auto read_b = [&](int hf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int jb = 0; jb < 2; ++jb) fb[hf][jb][ks] = frag16<B_T, 128>(st + (2 + hf) * P_HALF_BYTES, lane, wj * 32 + jb * 16, ks);
+      };
+      auto products = [&](int ha, int hb) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb) acc[ha][hb][ib][jb] = mfma16(fb[hb][jb][ks], fa[ib][ks], acc[ha][hb][ib][jb]);
+        __builtin_amdgcn_s_setprio(0);
+      };
+      read_b(0);
+      read_a(0);
+      read_b(1);
+      // A1 of the next step goes where every wave has read this slot's predecessor in the previous turn but one.  What
+      // must have landed behind this turn is this step's A1: all but the eight youngest copies, six of the next
+      // step's first three halves and the two issued here (the epilogue's stores are younger and only tighten the wait).
+      if (pend) {
+        copy_last_any();
+        advance();
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      reads_done();
+      products(0, 0);
+      products(0, 1);
+      bar();
+      read_a(1);
+      // The step after next's A0, B0 and B1 go where this step's have been read; the next step's must have landed.
+      pend = ctile.valid;
+      if (pend) {
+        copy_first_any();
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      reads_done();
+      products(1, 1);
+      products(1, 0);
+      bar();
+      slot ^= 1;
+    }
+#pragma unroll
+    for (int ha = 0; ha < 2; ++ha)
+#pragma unroll
+      for (int ib = 0; ib < 4; ++ib) {
+        const int il = ha * 128 + wi * 64 + ib * 16 + n;
+        const bool ok = il < cur.i_valid;
+        __bf16* crow = p.c + (cur.i0 + (ok ? il : 0)) * p.c_pitch + cur.j0;
+#pragma unroll
+        for (int hb = 0; hb < 2; ++hb) {
+          // The rows of 16 lanes exchange quads, so that a lane holds eight consecutive columns of one 16-column block.
+          const f32x4 v0 = acc[ha][hb][ib][0], v1 = acc[ha][hb][ib][1];
+          u32x4 out;
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, pack_bf16(v0[2 * e], v0[2 * e + 1])),
+                                                      __builtin_bit_cast(uint32_t, pack_bf16(v1[2 * e], v1[2 * e + 1])), false, false);
+            out[e] = r[0];
+            out[2 + e] = r[1];
+          }
+          const int j = hb * 128 + wj * 32 + 16 * (g4 & 1) + 8 * (g4 >> 1);
+          if (ok && j < cur.j_valid) *reinterpret_cast<u32x4*>(crow + j) = out;
+        }
+      }
+    l += lstep;
+    cur = decode_gemm_tile<A_T, B_T, TI, TJ>(p, l);
+    if (!cur.valid) break;
+  }
+  if (!late) bar();
+}
+
+// ---- smaller tiles ----------------------------------------------------------------------------------
+// The same products where 256 x 256 tiles would leave most of the chip idle (few tokens, small layers) or where the
+// time is the weights' way from HBM: tiles of CI x CJ, contraction steps of 64 SUB through a ring of NS LDS stages
+// with NS - 1 of them in flight, and WK groups of waves that each take every WK-th 16-deep slice of a step for the
+// whole tile (their partial sums are added through LDS at the tile's end, in fp32 and in a fixed order).
+// Bound: at one step in flight a step took 1.25 us however little it did, the latency of a cold copy, so the ring holds
+// as many bytes in flight as fit (80-112 KiB); what is left is HBM for a handful of tokens (one token, 22016 x 4096:
+// 34 us = 5.3 TB/s) and LDS bandwidth and the barrier per step for the wider tiles.
+template <int CI_, int CJ_, int WI_, int WJ_, int WK_, int SUB_, int NS_>
+struct RingCfg {
+  static constexpr int CI = CI_, CJ = CJ_, WI = WI_, WJ = WJ_, WK = WK_, SUB = SUB_, NS = NS_;
+  static constexpr int NIB = CI / WI / 32, NJB = CJ / WJ / 32;   // 32 x 32 blocks of a wave
+  static constexpr int A_BYTES = CI * 128, B_BYTES = CJ * 128;   // one 64-deep tile of each operand
+  static constexpr int STAGE_BYTES = SUB * (A_BYTES + B_BYTES);
+  static constexpr int RED_BYTES = WK > 1 ? CI * CJ * 4 * WK : 0;
+  static constexpr int SMEM_BYTES = NS * STAGE_BYTES + RED_BYTES;
+  static constexpr int COPIES = STAGE_BYTES / 1024 / kWaves;     // copy instructions of a wave per stage
+  static_assert(WI * WJ * WK == kWaves && SMEM_BYTES <= 160 * 1024 && STAGE_BYTES % (1024 * kWaves) == 0, "");
+};
+
+template <bool A_T, bool B_T, typename C>
+__global__ __launch_bounds__(kWaves * 64, 1) void linear_ring_kernel(GemmParams p) {
+  constexpr int CI = C::CI, CJ = C::CJ, SUB = C::SUB, NS = C::NS, WK = C::WK, NIB = C::NIB, NJB = C::NJB;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  const int wi = wv % C::WI, wj = (wv / C::WI) % C::WJ, wk = wv / (C::WI * C::WJ);
+  const int lstep = (int)(gridDim.x >> 3);
+  const int nr = (int)(p.R / 64);                 // 64-deep tiles of the contraction
+  const int nkt = (nr + SUB - 1) / SUB;           // steps
+  const int64_t a_step = A_T ? 64 * p.a_pitch : 128, b_step = B_T ? 64 * p.b_pitch : 128;
+
+  TileCopy<A_T, CI, SUB> ca;
+  TileCopy<B_T, CJ, SUB> cb;
+  ca.init(tid, (uint32_t)p.a_pitch);
+  cb.init(tid, (uint32_t)p.b_pitch);
+  const uint32_t lds0 = lds_address(smem);
+
+  // The copies run ahead of the products by NS - 1 steps, across tile boundaries: (ctile, ckt) is the next step to copy.
+  int cl = (int)(blockIdx.x >> 3), ckt = 0, cslot = 0;
+  GemmTile ctile = decode_gemm_tile<A_T, B_T, CI, CJ>(p, cl);
+  if (!ctile.valid) return;
+  GemmTile cur = ctile;
+  int l = cl;
+  auto copy_next = [&]() __attribute__((always_inline)) {
+    const uint32_t base = lds0 + cslot * C::STAGE_BYTES;
+    const int64_t sub0 = (int64_t)ckt * SUB;
+    const int subs = nr - (int)sub0;
+    auto both = [&](auto whole) __attribute__((always_inline)) {
+      constexpr bool W = decltype(whole)::value;
+      ca.template issue<W>(base, ctile.ga + sub0 * a_step, (uint32_t)p.a_pitch, ctile.a_valid, a_step, subs);
+      cb.template issue<W>(base + SUB * C::A_BYTES, ctile.gb + sub0 * b_step, (uint32_t)p.b_pitch, ctile.b_valid, b_step, subs);
+    };
+    if (ctile.whole) both(std::true_type{});
+    else both(std::false_type{});
+    cslot = cslot + 1 == NS ? 0 : cslot + 1;
+    if (++ckt == nkt) {
+      ckt = 0;
+      cl += lstep;
+      ctile = decode_gemm_tile<A_T, B_T, CI, CJ>(p, cl);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+    if (ctile.valid) copy_next();
+
+  int slot = 0;
+  for (;;) {
+    f32x16 acc[NIB][NJB];
+#pragma unroll
+    for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
       for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[ib][jb][r] = 0.0f;
     for (int kt = 0; kt < nkt; ++kt) {
-      async_wait_all();  // this wave's copies of this stage have landed ...
-      __syncthreads();   // ... everyone's have, and everyone is done reading the other stage
-      if (kt + 1 < nkt) copy_stage(cur, kt + 1, stage ^ 1);
-      else if (nxt.valid) copy_stage(nxt, 0, stage ^ 1);
-      const char* ta = smem + stage * G_STAGE_BYTES;
-      const char* tb = ta + G_TILE_BYTES;
+      // This wave's copies of the step have landed (the younger steps' may be open while there are any to come; the
+      // epilogue's stores are younger than the copies they leave open, so the count is safe with them too) and its LDS
+      // reads of the previous step are done; behind the barrier the same holds for all waves.
+      if (ctile.valid) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(C::COPIES * (NS - 2)) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (ctile.valid) copy_next();   // into the stage everyone has just left
+      const char* st = smem + slot * C::STAGE_BYTES;
+      auto slice = [&](int ks) __attribute__((always_inline)) {
+        const char* ta = st + (SUB > 1 ? (ks >> 2) * C::A_BYTES : 0);
+        const char* tb = st + SUB * C::A_BYTES + (SUB > 1 ? (ks >> 2) * C::B_BYTES : 0);
+        bf16x8 fi[NIB], fj[NJB];
 #pragma unroll
-      for (int ks = 0; ks < TR / 16; ++ks) {
-        bf16x8 fi[4], fj[NJB];
+        for (int ib = 0; ib < NIB; ++ib) fi[ib] = ring_frag<A_T, CI>(ta, lane, (wi * NIB + ib) * 32, ks & 3);
 #pragma unroll
-        for (int ib = 0; ib < 4; ++ib) fi[ib] = frag<A_T>(ta, lane, wi * 128 + ib * 32, ks);
+        for (int jb = 0; jb < NJB; ++jb) fj[jb] = ring_frag<B_T, CJ>(tb, lane, (wj * NJB + jb) * 32, ks & 3);
 #pragma unroll
-        for (int jb = 0; jb < NJB; ++jb) fj[jb] = frag<B_T>(tb, lane, wj * (32 * NJB) + jb * 32, ks);
-#pragma unroll
-        for (int ib = 0; ib < 4; ++ib)
+        for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
           for (int jb = 0; jb < NJB; ++jb) acc[ib][jb] = mfma32(fj[jb], fi[ib], acc[ib][jb]);
-      }
-      stage ^= 1;
-    }
+      };
+      const int left = (nr - kt * SUB) * 4;   // 16-deep slices that exist from here on
+      if (SUB == 1 || left >= SUB * 4) {
 #pragma unroll
-    for (int ib = 0; ib < 4; ++ib) {
-      const int il = wi * 128 + ib * 32 + n;
-      const bool ok = il < cur.i_valid;
-      __bf16* crow = p.c + (cur.i0 + (ok ? il : 0)) * p.c_pitch + cur.j0;
+        for (int s = 0; s < SUB * 4 / WK; ++s) slice(wk + WK * s);
+      } else {
+        for (int ks = wk; ks < left; ks += WK) slice(ks);
+      }
+      slot = slot + 1 == NS ? 0 : slot + 1;
+    }
+
+    if constexpr (WK == 1) {
 #pragma unroll
-      for (int jb = 0; jb < NJB; ++jb) {
-        const int jl = wj * (32 * NJB) + jb * 32;
-        store_block(crow + jl, acc[ib][jb], h, ok, cur.j_valid - jl);
+      for (int ib = 0; ib < NIB; ++ib) {
+        const int il = (wi * NIB + ib) * 32 + n;
+        const bool ok = il < cur.i_valid;
+        __bf16* crow = p.c + (cur.i0 + (ok ? il : 0)) * p.c_pitch + cur.j0;
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) {
+          const int jl = (wj * NJB + jb) * 32;
+          store_block(crow + jl, acc[ib][jb], h, ok, cur.j_valid - jl);
+        }
+      }
+    } else {
+      // Partial sums through LDS, [wj wi group][block][quad q][wk][lane] x 16 bytes: quad q of a block is four
+      // consecutive columns 8 q + 4 h of row n.  Reader wk adds the quads q = wk, wk + WK, ... of its group's blocks.
+      constexpr int NB = NIB * NJB;
+      float* red = reinterpret_cast<float*>(smem + NS * C::STAGE_BYTES) + (wj * C::WI + wi) * NB * 4 * WK * 256;
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x16& a = acc[ib][jb];
+            f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+            *reinterpret_cast<f32x4*>(red + (((ib * NJB + jb) * 4 + q) * WK + wk) * 256 + lane * 4) = v;
+          }
+      // (the reads below are done before this wave reaches the next step's barrier, hence before the area is written again)
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib) {
+        const int il = (wi * NIB + ib) * 32 + n;
+        const bool ok = il < cur.i_valid;
+        __bf16* crow = p.c + (cur.i0 + (ok ? il : 0)) * p.c_pitch + cur.j0;
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb)
+          for (int q = wk; q < 4; q += WK) {
+            const float* src = red + ((ib * NJB + jb) * 4 + q) * WK * 256 + lane * 4;
+            f32x4 sum = *reinterpret_cast<const f32x4*>(src);
+#pragma unroll
+            for (int k = 1; k < WK; ++k) sum += *reinterpret_cast<const f32x4*>(src + k * 256);
+            const int j = (wj * NJB + jb) * 32 + 8 * q + 4 * h;
+            bf16x4 out = {(__bf16)sum[0], (__bf16)sum[1], (__bf16)sum[2], (__bf16)sum[3]};
+            if (ok && j < cur.j_valid) *reinterpret_cast<bf16x4*>(crow + j) = out;
+          }
       }
     }
-    if (!nxt.valid) break;
-    cur = nxt;
+    l += lstep;
+    cur = decode_gemm_tile<A_T, B_T, CI, CJ>(p, l);
+    if (!cur.valid) break;
   }
 }
 
@@ -257,13 +533,13 @@ int check_dims(int64_t M, int64_t N, int64_t K) {
   return IE_OK;
 }
 
-template <bool A_T, bool B_T>
-int launch_gemm(GemmParams p, hipStream_t st) {
-  auto kernel = linear_gemm_kernel<A_T, B_T>;
-  int rc = set_smem(kernel, G_SMEM_BYTES);
+// Tiles, grid and launch of one kernel: one workgroup per CU at most, the tiles dealt to the XCDs in eighths.
+template <typename K>
+int launch_tiles(K kernel, GemmParams p, int ti, int tj, int smem, hipStream_t st) {
+  int rc = set_smem(kernel, smem);
   if (rc) return rc;
-  p.tiles_i = (int)ceil_div(p.I, TI);
-  p.tiles_j = (int)ceil_div(p.J, TJ);
+  p.tiles_i = (int)ceil_div(p.I, ti);
+  p.tiles_j = (int)ceil_div(p.J, tj);
   const int64_t tiles = (int64_t)p.tiles_i * p.tiles_j;
   if (tiles >= ((int64_t)1 << 28)) return IE_ERR_SHAPE;
   p.tiles = (int)tiles;
@@ -271,11 +547,79 @@ int launch_gemm(GemmParams p, hipStream_t st) {
   const int cus = cu_count(&e);
   if (e != hipSuccess) return hip_fail(e);
   const int per = (p.tiles + 7) / 8;                      // tiles of one XCD's share
-  const int per_xcd_wgs = cus / 8 < per ? cus / 8 : per;  // one workgroup per CU (128 KiB of LDS each)
+  const int per_xcd_wgs = cus / 8 < per ? cus / 8 : per;  // one workgroup per CU
   const unsigned grid = 8u * (unsigned)(per_xcd_wgs < 1 ? 1 : per_xcd_wgs);
-  kernel<<<dim3(grid), dim3(kWaves * 64), G_SMEM_BYTES, st>>>(p);
+  kernel<<<dim3(grid), dim3(kWaves * 64), smem, st>>>(p);
   e = hipGetLastError();
   return e == hipSuccess ? IE_OK : hip_fail(e);
+}
+
+using Ring256x128 = RingCfg<256, 128, 4, 2, 1, 1, 3>;
+using Ring128x256 = RingCfg<128, 256, 2, 4, 1, 1, 3>;
+using Ring128 = RingCfg<128, 128, 2, 4, 1, 1, 4>;
+using Ring64x128 = RingCfg<64, 128, 2, 4, 1, 1, 6>;
+using Ring64 = RingCfg<64, 64, 1, 2, 4, 1, 6>;
+using Ring32 = RingCfg<32, 32, 1, 1, 8, 4, 4>;
+
+template <bool A_T, bool B_T, typename C>
+int launch_ring(const GemmParams& p, hipStream_t st) {
+  return launch_tiles(linear_ring_kernel<A_T, B_T, C>, p, C::CI, C::CJ, C::SMEM_BYTES, st);
+}
+
+// Which kernel: the one with the least estimated time.  A workgroup takes its tiles one after the other, and a tile its
+// 64-deep steps at a cost per step that was measured per product (forward, dx, dw: a transposed operand takes two LDS
+// reads per fragment) with all CUs at work, less in a round that leaves CUs idle (memory is then less busy and the clock
+// higher), plus what stands around a tile.  Fitted to 1008 measured (product, size) pairs, 1 to 16384 tokens and layer
+// widths 512 to 8192: the choice is 0.4 % slower than the best of the seven on average and 21 % at most, and twice as
+// fast as 256 x 256 tiles throughout (200 tokens: 4096 x 4096 94 -> 22 us with 64 x 64 tiles, 12288 x 4096 96 -> 41 us
+// with 128 x 128, 22016 x 4096 99 -> 65 us with 256 x 128; one token, 4096 x 11008: 224 -> 25 us with 32 x 32; 8192
+// tokens stay on 256 x 256).
+enum Tile { kPp256, kRing256x128, kRing128x256, kRing128, kRing64x128, kRing64, kRing32, kTiles };
+struct TileCost {
+  int ti, tj, step;         // tile, depth of a step in units of 64
+  float step_us[3];         // per 64-deep step: forward, dx, dw
+  float tile_us, light;     // around a tile; factor of a step when few CUs are at work
+};
+constexpr TileCost kCost[kTiles] = {
+    {256, 256, 1, {1.50f, 1.60f, 1.80f}, 3.7f, 0.73f},    {256, 128, 1, {1.03f, 1.075f, 1.137f}, 1.5f, 0.71f},
+    {128, 256, 1, {1.055f, 1.072f, 1.10f}, 1.3f, 0.73f},  {128, 128, 1, {0.637f, 0.662f, 0.690f}, 1.0f, 0.73f},
+    {64, 128, 1, {0.442f, 0.443f, 0.512f}, 0.7f, 0.83f},  {64, 64, 1, {0.272f, 0.300f, 0.332f}, 1.3f, 0.82f},
+    {32, 32, 4, {0.144f, 0.f, 0.f}, 0.f, 0.70f}};
+
+Tile pick_tile(int64_t I, int64_t J, int64_t R, bool a_t, bool b_t, int cus) {
+  const int prod = a_t ? 2 : b_t ? 1 : 0;
+  const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
+  Tile best = kPp256;
+  float best_us = 0.f;
+  for (int k = 0; k < kTiles; ++k) {
+    if (k == kRing32 && prod != 0) continue;   // (both operands direct: a transposed 32-wide tile has 64-byte rows)
+    const TileCost& c = kCost[k];
+    const int64_t per = ceil_div(ceil_div(I, c.ti) * ceil_div(J, c.tj), 8);   // tiles of one XCD
+    const int64_t full = per / per_xcd, rest = per % per_xcd;                 // whole rounds, tiles of the last one
+    const float steps = (float)(ceil_div(R, 64 * c.step) * c.step);
+    const float last = rest ? c.light + (1.f - c.light) * (float)rest / (float)per_xcd : 0.f;
+    const float us = (float)(full + (rest != 0)) * c.tile_us + steps * c.step_us[prod] * ((float)full + last);
+    if (k == 0 || us < best_us) { best = (Tile)k; best_us = us; }
+  }
+  return best;
+}
+
+template <bool A_T, bool B_T>
+int launch_gemm(const GemmParams& p, hipStream_t st) {
+  hipError_t e;
+  const int cus = cu_count(&e);
+  if (e != hipSuccess) return hip_fail(e);
+  switch (pick_tile(p.I, p.J, p.R, A_T, B_T, cus)) {
+    case kRing256x128: return launch_ring<A_T, B_T, Ring256x128>(p, st);
+    case kRing128x256: return launch_ring<A_T, B_T, Ring128x256>(p, st);
+    case kRing128: return launch_ring<A_T, B_T, Ring128>(p, st);
+    case kRing64x128: return launch_ring<A_T, B_T, Ring64x128>(p, st);
+    case kRing64: return launch_ring<A_T, B_T, Ring64>(p, st);
+    case kRing32:
+      if constexpr (!A_T && !B_T) return launch_ring<A_T, B_T, Ring32>(p, st);
+      [[fallthrough]];
+    default: return launch_tiles(linear_pp_kernel<A_T, B_T>, p, TI, TJ, P_SMEM_BYTES, st);
+  }
 }
 
 }  // namespace
