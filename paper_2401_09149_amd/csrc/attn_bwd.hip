@@ -95,22 +95,12 @@ struct DqCfg {
   template <int D> static constexpr int smem_bytes() { return 2 * 2 * BN * D * 2; }   // two stages of a K and a V tile
 };
 template <int D, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(AttnParams p) {
+__device__ __forceinline__ void dq_item(const AttnParams& p, char* smem, int* scratch, const int item) {
   constexpr int BM = DqCfg<WAVES>::BM, BN = DqCfg<WAVES>::BN, THREADS = DqCfg<WAVES>::THREADS;
   constexpr int NKS = D / 16, NDB = D / 32;
   constexpr int TILE_BYTES = BN * D * 2;
   constexpr int STAGE_BYTES = 2 * TILE_BYTES;
   constexpr int ROW_BYTES = D * 2;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ int scratch[2 * WAVES + 2];
-
-  __shared__ QueueState s_work;
-  queue_init(p, &s_work);
-  const uint32_t xcc = xcc_id();
-  int skip = 0;
-  for (;;) {   // persistent: one item (batch, head, query tile) per iteration (tile_queue.hpp)
-  const int item = next_work(p, &s_work, xcc, skip);
-  if (item < 0) break;
   // (an opaque copy of the thread index: per-lane offsets are recomputed per item rather than
   // hoisted out of this loop and kept in registers through the main loop)
   int tid = threadIdx.x;
@@ -119,7 +109,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(Attn
   const int n = lane & 31, h = lane >> 5, grp = lane >> 4;
 
   TileCoord tc = decode_tile<BM, THREADS>(p, p.Hq, true, scratch, item, tid);
-  if (!tc.valid) continue;
+  if (!tc.valid) return;
   // (the tile coordinates may have come through LDS: wave-uniform values are moved to scalar registers explicitly)
   const int g = tc.h / (p.Hq / p.Hkv);
   const int64_t q0 = uniform(tc.t0), doc_end = uniform(tc.doc_end);
@@ -282,7 +272,21 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(Attn
                                            tok_off(p, k_begin + row_rel_late, q_stride * 2));
 #pragma unroll
   for (int db = 0; db < NDB; ++db) store_block32_bf16(drow + 32 * db, acc[db], p.scale, h, wave_row_min + n < rows_rel_end);
-  }  // next item
+}
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(AttnParams p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ int scratch[2 * WAVES + 2];
+
+  __shared__ QueueState s_work;
+  queue_init(p, &s_work);
+  const uint32_t xcc = xcc_id();
+  int skip = 0;
+  for (;;) {   // persistent: one item (batch, head, query tile) per iteration (tile_queue.hpp)
+    const int item = next_work(p, &s_work, xcc, skip);
+    if (item < 0) break;
+    dq_item<D, WAVES>(p, smem, scratch, item);
+  }
 }
 
 // ---- dK, dV ------------------------------------------------------------------------------
@@ -305,24 +309,14 @@ struct DkdvCfg {
 
 // CHUNKED: q, k, v, dk, dv are chunks of a sequence-parallel exchange buffer (tok_off in attn_common.hpp) instead of
 // contiguous tensors: a separate instantiation, so that the contiguous case keeps its simpler address arithmetic.
-template <int D, bool STORE_DS, bool CHUNKED = false>
-__global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p) {
+template <int D, bool STORE_DS, bool CHUNKED>
+__device__ __forceinline__ void dkdv_item(const AttnParams& p, char* smem, int* scratch, const int item) {
   static_assert(!(STORE_DS && CHUNKED), "the stored-dS path takes contiguous tensors");
   using C = DkdvCfg<D>;
   constexpr int BK = C::BK, BQ = C::BQ, NB = C::NB;
   constexpr int NKS = D / 16, NDB = D / 32;
   constexpr int TILE_BYTES = C::TILE_BYTES, STAGE_BYTES = C::STAGE_BYTES;
   constexpr int ROW_BYTES = D * 2;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ int scratch[8];
-
-  __shared__ QueueState s_work;
-  queue_init(p, &s_work);
-  const uint32_t xcc = xcc_id();
-  int skip = 0;
-  for (;;) {   // persistent: one item (batch, kv head, key block) per iteration (tile_queue.hpp)
-  const int item = next_work(p, &s_work, xcc, skip);
-  if (item < 0) break;
   // (an opaque copy of the thread index: per-lane offsets are recomputed per item rather than
   // hoisted out of this loop and kept in registers through the main loop)
   int tid = threadIdx.x;
@@ -331,7 +325,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p
   const int n = lane & 31, h = lane >> 5, grp = lane >> 4;
 
   TileCoord tc = decode_tile<BK>(p, p.Hkv, false, scratch, item, tid);
-  if (!tc.valid) continue;
+  if (!tc.valid) return;
   // The tile coordinates may have come through LDS (packed input): they are the same in every lane, and are moved
   // to scalar registers here so that everything derived from them between two steps (the description of the next
   // query tile: three 64-bit addresses) is scalar arithmetic instead of vector multiplies and lane reads.
@@ -821,7 +815,55 @@ __global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p
     store_block32_bf16(dkrow + 32 * db, dkacc[db], p.scale, h, key_ok);
     store_block32_bf16(dvrow + 32 * db, dvacc[db], 1.0f, h, key_ok);
   }
-  }  // next item
+}
+template <int D, bool STORE_DS, bool CHUNKED = false>
+__global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ int scratch[8];
+
+  __shared__ QueueState s_work;
+  queue_init(p, &s_work);
+  const uint32_t xcc = xcc_id();
+  int skip = 0;
+  for (;;) {   // persistent: one item (batch, kv head, key block) per iteration (tile_queue.hpp)
+    const int item = next_work(p, &s_work, xcc, skip);
+    if (item < 0) break;
+    dkdv_item<D, STORE_DS, CHUNKED>(p, smem, scratch, item);
+  }
+}
+
+// ---- dK, dV and dQ in one launch -------------------------------------------------------------
+// The two main kernels depend on the delta kernel only, so where neither needs the whole register file (head
+// dimension 64) or the whole chip (a launch whose items of both kinds are all resident at once) their items run side
+// by side: the launch is as long as the longer kind and there is one tail instead of two.  `ONCE`: every workgroup
+// does the one item of its index, dK/dV items first, without the queues' atomics; otherwise a workgroup takes dK/dV
+// items until there are none and then dQ items (128 rows each).
+template <int D, bool CHUNKED, bool ONCE>
+__global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_bwd_both_kernel(AttnParams pkv, AttnParams pq) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ int scratch[10];
+  if constexpr (ONCE) {
+    const int b = (int)blockIdx.x;
+    if (b < pkv.q_total) dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, b);
+    else dq_item<D, 4>(pq, smem, scratch, b - pkv.q_total);
+  } else {
+    __shared__ QueueState s_kv, s_q;
+    queue_init(pkv, &s_kv);
+    queue_init(pq, &s_q);
+    const uint32_t xcc = xcc_id();
+    int skip = 0;
+    for (;;) {
+      const int item = next_work(pkv, &s_kv, xcc, skip);
+      if (item < 0) break;
+      dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, item);
+    }
+    skip = 0;
+    for (;;) {
+      const int item = next_work(pq, &s_q, xcc, skip);
+      if (item < 0) break;
+      dq_item<D, 4>(pq, smem, scratch, item);
+    }
+  }
 }
 
 // ---- dQ from a materialised dS ---------------------------------------------------------------
@@ -975,6 +1017,9 @@ constexpr int kCountersDq = 0, kCountersDkdv = kQueueBytes / 4;
 constexpr int kDqWaves = 8;   // waves per workgroup of the recomputing dQ kernel at head dimension 128 (four: 2 % slower)
 
 template <int D>
+constexpr int kBothSmem = DkdvCfg<D>::SMEM_BYTES > DqCfg<4>::template smem_bytes<D>() ? DkdvCfg<D>::SMEM_BYTES : DqCfg<4>::template smem_bytes<D>();
+
+template <int D>
 static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
   hipError_t e;
   if (phases & 1) {  // delta
@@ -1050,8 +1095,51 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
     return 0;
   };
+  // Both main kernels in one launch.  ONCE: a workgroup per item, no queue.
+  auto both_phase = [&](auto chunked_c, auto once_c, const int64_t tiles, const int per_cu) -> int {
+    constexpr bool kChunked = decltype(chunked_c)::value, kOnce = decltype(once_c)::value;
+    static KernelSetup setup;
+    int fits = 1;
+    int rc = kernel_setup(setup, attn_bwd_both_kernel<D, kChunked, kOnce>, kBothSmem<D>, &fits);
+    if (rc) return rc;
+    AttnParams kv = p, q = p;
+    kv.tiles = q.tiles = (int32_t)tiles;
+    kv.q_total = (int32_t)(tiles * p.B * p.Hkv);
+    q.q_total = (int32_t)(tiles * p.B * p.Hq);
+    int64_t grid = (int64_t)kv.q_total + q.q_total;
+    if constexpr (!kOnce) {
+      const QueueLaunch qk = tile_queue_prepare(kv, p.ws_counters + kCountersDkdv, kv.q_total, kv.Hkv, per_cu, st, cleared_by_delta);
+      if (qk.err != hipSuccess) return hip_fail(qk.err);
+      const QueueLaunch qq = tile_queue_prepare(q, p.ws_counters + kCountersDq, q.q_total, q.Hq, per_cu, st, cleared_by_delta);
+      if (qq.err != hipSuccess) return hip_fail(qq.err);
+      hipError_t e;
+      const int64_t cap = (int64_t)cu_count(&e) * per_cu;
+      if (e != hipSuccess) return hip_fail(e);
+      grid = grid < cap ? grid : cap;
+    }
+    attn_bwd_both_kernel<D, kChunked, kOnce><<<dim3((unsigned)grid), dim3(kThreads), kBothSmem<D>, st>>>(kv, q);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
+    return 0;
+  };
   const bool chunked = p.tok_shift < 63;
   int rc = 0;
+  if (!from_ds && (phases & 6) == 6) {
+    const int cus = cu_count(&e);
+    if (e != hipSuccess) return hip_fail(e);
+    const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs);
+    const int64_t items = tiles * p.B * ((int64_t)p.Hq + p.Hkv);
+    constexpr int per_cu = D == 64 ? 2 : 1;
+    const bool once = items <= (int64_t)cus * per_cu;
+    if (once && (D == 64 || tile_rows_setting.load(std::memory_order_relaxed) != 256)) {
+      return chunked ? both_phase(std::true_type{}, std::true_type{}, tiles, per_cu)
+                     : both_phase(std::false_type{}, std::true_type{}, tiles, per_cu);
+    }
+    if constexpr (D == 64) {
+      if (items >= ((int64_t)1 << 31)) return kErrShape;
+      return chunked ? both_phase(std::true_type{}, std::false_type{}, tiles, per_cu)
+                     : both_phase(std::false_type{}, std::false_type{}, tiles, per_cu);
+    }
+  }
   if (from_ds) {
     if constexpr (D == 128) {
       if ((phases & 4) && (rc = dkdv_phase(std::true_type{}, std::false_type{}))) return rc;

@@ -1,0 +1,42 @@
+"""dK/dV and dQ in one launch (attn_bwd_both_kernel) against the same pass in two: the same item bodies, so the same
+bits.  The one-launch form is taken where all items of both kinds are resident at once, and always at head dimension 64;
+a call that names the phases one by one takes the kernels of their own."""
+import pytest
+
+from parity_util import randn_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,D,causal,lens", [
+    (1, 512, 2, 2, 64, True, None),       # 16 items, one per workgroup
+    (1, 4096, 8, 8, 64, True, None),      # 512 items: the last size with one per workgroup
+    (1, 4097, 8, 8, 64, True, None),      # one tile more per head: work queues, one-row tiles
+    (4, 2000, 16, 16, 64, False, None),   # work queues, several items per workgroup
+    (1, 1, 3, 1, 64, True, None),
+    (1, 1000, 4, 2, 64, True, [300, 0, 1, 699]),
+    (1, 2047, 8, 8, 128, True, None),     # 256 items
+    (2, 300, 6, 2, 128, False, None),
+    (1, 1000, 4, 1, 128, True, [300, 0, 1, 699]),
+])
+def test_one_launch_gives_the_bits_of_two(B, S, Hq, Hkv, D, causal, lens):
+    import torch
+    from paper_2401_09149_amd import binding
+    print(f"case B{B} S{S} Hq{Hq} Hkv{Hkv} D{D} {causal} {lens}", flush=True)
+    dev, scale = "cuda:0", D ** -0.5
+    q, do = (randn_bf16((B, S, Hq, D), 300 + j).to(dev) for j in range(2))
+    k, v = (randn_bf16((B, S, Hkv, D), 302 + j).to(dev) for j in range(2))
+    cu = None
+    if lens:
+        cu = torch.tensor([0] + lens, dtype=torch.int32).cumsum(0).to(torch.int32).to(dev)
+    o, lse = binding.attn_fwd(q, k, v, scale, causal, cu)
+    ws = binding.alloc_bwd_workspace(q, k, cu)
+    want = [torch.full_like(t, float("nan")) for t in (q, k, v)]
+    for phase in (binding.BWD_DELTA, binding.BWD_DQ, binding.BWD_DKDV):
+        binding.ie_attn_bwd_phases(q, k, v, o, do, lse, *want, cu, scale, causal, ws, phase)
+    for _ in range(2):
+        got = [torch.full_like(t, float("nan")) for t in (q, k, v)]
+        binding.ie_attn_bwd(q, k, v, o, do, lse, *got, cu, scale, causal, ws)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
