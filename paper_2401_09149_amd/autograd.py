@@ -18,6 +18,7 @@ class _Attention(torch.autograd.Function):
             ctx.save_for_backward(q, k, v, o, lse)
         ctx.cu_seqlens, ctx.scale, ctx.causal, ctx.workspace, ctx.stored_ds = cu_seqlens, scale, causal, workspace, stored_ds
         ctx.mark_non_differentiable(lse)
+        ctx.set_materialize_grads(False)   # no fill kernel for the gradient that lse never has
         return o, lse
 
     @staticmethod
@@ -27,6 +28,8 @@ class _Attention(torch.autograd.Function):
             o, lse = binding.attn_fwd(q, k, v, ctx.scale, ctx.causal, ctx.cu_seqlens)
         else:
             q, k, v, o, lse = ctx.saved_tensors
+        if dout is None:
+            dout = torch.zeros_like(o)
         dq, dk, dv = binding.attn_bwd(q, k, v, o, dout.contiguous(), lse, ctx.scale, ctx.causal, ctx.cu_seqlens,
                                       workspace=ctx.workspace, stored_ds=ctx.stored_ds)
         return dq, dk, dv, None, None, None, None, None, None
@@ -50,23 +53,25 @@ class _Linear(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, w):
         lead = x.shape[:-1]
-        x2 = x.reshape(-1, x.shape[-1]).contiguous()
+        x2 = x if x.dim() == 2 else x.reshape(-1, x.shape[-1])
+        x2 = x2.contiguous()
         w = w.contiguous()
         y = torch.empty((x2.shape[0], w.shape[0]), dtype=torch.bfloat16, device=x.device)
         binding.ie_linear_fwd(x2, w, y)
         ctx.save_for_backward(x2, w)
         ctx.lead = lead
-        return y.reshape(*lead, w.shape[0])
+        return y if len(lead) == 1 else y.reshape(*lead, w.shape[0])
 
     @staticmethod
     def backward(ctx, dy):
         x2, w = ctx.saved_tensors
-        dy2 = dy.reshape(-1, dy.shape[-1]).contiguous()
+        dy2 = (dy if dy.dim() == 2 else dy.reshape(-1, dy.shape[-1])).contiguous()
         dx = dw = None
         if ctx.needs_input_grad[0]:
             dx = torch.empty_like(x2)
             binding.ie_linear_bwd_input(dy2, w, dx)
-            dx = dx.reshape(*ctx.lead, x2.shape[1])
+            if len(ctx.lead) != 1:
+                dx = dx.reshape(*ctx.lead, x2.shape[1])
         if ctx.needs_input_grad[1]:
             dw = torch.empty_like(w)
             binding.ie_linear_bwd_weight(dy2, x2, dw)

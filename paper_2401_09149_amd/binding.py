@@ -105,7 +105,11 @@ def _ptr(t, dtype, what):
 
 
 def _stream(stream):
-    return (stream if stream is not None else torch.cuda.current_stream()).cuda_stream
+    """The handle of `stream`, or of the current device's current stream (asked for directly: building a
+    torch.cuda.Stream for it takes 2.9 us, a third of a small call)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _shape(q, k, **others):
