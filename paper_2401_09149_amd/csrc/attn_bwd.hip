@@ -273,6 +273,216 @@ __device__ __forceinline__ void dq_item(const AttnParams& p, char* smem, int* sc
 #pragma unroll
   for (int db = 0; db < NDB; ++db) store_block32_bf16(drow + 32 * db, acc[db], p.scale, h, wave_row_min + n < rows_rel_end);
 }
+// The same item on v_mfma_f32_16x16x32_bf16, for head dimension 128: half the accumulator traffic per product of the
+// 32x32x16 form, which the power limit turns into time.  A 32 x 32 block of scores is 2 x 2 MFMA blocks, so a lane
+// has TWO query columns (16 qb + lane % 16) and, with g = lane / 16, the keys 16 kb + key4(g) + 0..3 of each; the
+// eight of both key blocks are one B operand of the dQ product.  key4 swaps the middle two groups (0, 8, 4, 12): the
+// transpose loads of two neighbouring lane groups then address rows 0..3 and 8..11, which the tile's swizzle keeps on
+// different banks (rows 0..3 and 4..7 collide).
+template <int D, int WAVES>
+__device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int* scratch, const int item) {
+  constexpr int BM = DqCfg<WAVES>::BM, BN = DqCfg<WAVES>::BN, THREADS = DqCfg<WAVES>::THREADS;
+  constexpr int NKS = D / 32, NDB = D / 16;   // 32-deep slices, 16-wide blocks of the head dimension
+  constexpr int TILE_BYTES = BN * D * 2;
+  constexpr int STAGE_BYTES = 2 * TILE_BYTES;
+  constexpr int ROW_BYTES = D * 2;
+  // (an opaque copy of the thread index: per-lane offsets are recomputed per item rather than
+  // hoisted out of this loop and kept in registers through the main loop)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wv = tid >> 6;
+  const int n = lane & 15, g4 = lane >> 4;
+  const int key4 = 4 * (((g4 & 1) << 1) | (g4 >> 1));
+
+  TileCoord tc = decode_tile<BM, THREADS>(p, p.Hq, true, scratch, item, tid);
+  if (!tc.valid) return;
+  // (the tile coordinates may have come through LDS: wave-uniform values are moved to scalar registers explicitly)
+  const int g = tc.h / (p.Hq / p.Hkv);
+  const int64_t q0 = uniform(tc.t0), doc_end = uniform(tc.doc_end);
+  const int64_t q_end = (q0 + BM < doc_end) ? q0 + BM : doc_end;
+  const int64_t k_begin = uniform(tc.doc_begin);
+  const int64_t k_end = p.causal ? q_end : doc_end;
+  const int nk = (int)(k_end - k_begin);
+  const int nkt = (nk + BN - 1) / BN;
+  const int nfull = nk / BN;
+
+  const int64_t q_stride = (int64_t)p.Hq * D;
+  const int64_t kv_pitch = (int64_t)p.Hkv * D * 2;
+  const int64_t qhead = ((int64_t)tc.b * p.S * p.Hq + tc.h) * D;   // for dout (always contiguous)
+  const char* kbase = uniform(reinterpret_cast<const char*>(p.k + g * D) + tc.b * p.kv_bstride);   // key tile kt starts at token k_begin + kt * BN
+  const char* vbase = uniform(reinterpret_cast<const char*>(p.v + g * D) + tc.b * p.kv_bstride);
+  auto key_tile_off = [&](const int kt) __attribute__((always_inline)) { return tok_off(p, k_begin + (int64_t)kt * BN, kv_pitch); };
+
+  const uint32_t lds0 = lds_address(smem);
+  AsyncTile<D, WAVES> ld;
+  ld.init(tid, kv_pitch);
+  // Asynchronous copy of key tile kt, of which `rows` >= 1 rows exist, into the stage at LDS address `lds`, in
+  // 64-row parts; a part that lies past the end repeats the last valid row (masked later).
+  auto load_kv = [&](const uint32_t lds, const int kt, const int rows, auto full) __attribute__((always_inline)) {
+    const int64_t off = key_tile_off(kt);
+#pragma unroll
+    for (int part = 0; part < BN / 64; ++part) {
+      const uint32_t dst = lds + part * 64 * ROW_BYTES;
+      if (full) {
+        ld.load_full(dst, kbase + off + (int64_t)(64 * part) * kv_pitch);
+        ld.load_full(dst + TILE_BYTES, vbase + off + (int64_t)(64 * part) * kv_pitch);
+      } else {
+        const int first = rows > 64 * part ? 64 * part : rows - 1;
+        const int valid = rows > 64 * part ? rows - 64 * part : 1;
+        ld.load(dst, kbase + off + (int64_t)first * kv_pitch, valid);
+        ld.load(dst + TILE_BYTES, vbase + off + (int64_t)first * kv_pitch, valid);
+      }
+    }
+  };
+  load_kv(lds0, 0, nk, std::false_type{});
+
+  // This lane's query row, as a 32-bit position inside the document (rows past the tile's end repeat its last row and
+  // are not written).
+  const int rows_rel_end = (int)(q_end - k_begin);
+  int row_rel[2];
+  bf16x8 qf[2][NKS], dof[2][NKS];
+  float nlse2[2], ndelta[2];           // -lse * log2(e) and -delta of this lane's queries
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int raw = (int)(q0 - k_begin) + wv * 32 + qb * 16 + n;
+    row_rel[qb] = raw < rows_rel_end ? raw : rows_rel_end - 1;
+    const int64_t row = k_begin + row_rel[qb];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      qf[qb][ks] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(p.q + tc.h * D) + tc.b * p.q_bstride +
+                                                    tok_off(p, row, q_stride * 2) + (ks * 32 + g4 * 8) * 2);
+      dof[qb][ks] = *reinterpret_cast<const bf16x8*>(p.dout + qhead + row * q_stride + ks * 32 + g4 * 8);
+    }
+    const int64_t stat = ((int64_t)tc.b * p.Hq + tc.h) * p.S + row;
+    nlse2[qb] = p.lse2[stat];
+    ndelta[qb] = p.delta[stat];
+  }
+
+  const char* nat_ptr[NKS];  // A operand, K or V rows: row key4 + n % 4 of a 16-key block (n / 4 permuted as key4), chunk 4 ks + g4
+  const int nat_row = 4 * (((n >> 2 & 1) << 1) | (n >> 3)) + (n & 3);
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) nat_ptr[ks] = smem + tile_off<D>(nat_row, 4 * ks + g4);
+  const char* tr_ptr[NDB];   // transpose loads on the K tile: keys key4 .. +3, columns 16 db ..
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) tr_ptr[db] = smem + tr_off<D>(lane, key4, 16 * db);
+
+  // The dP chain starts from -delta (the same value in all 16 rows: one query per lane), so it
+  // delivers dP - delta.
+  const float c = p.scale_log2;
+  f32x4 acc[NDB][2];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) acc[db][qb] = f32x4{0, 0, 0, 0};
+
+  const int wave_row_min = (int)(q0 - k_begin) + wv * 32;
+
+  auto tile_step = [&](const int kt, const int stage, auto full_next) __attribute__((always_inline)) {
+    const int kb = kt * BN;
+    const uint32_t next_lds = lds0 + (STAGE_BYTES - stage);
+    if (full_next) load_kv(next_lds, kt + 1, BN, std::true_type{});
+    else if (kt + 1 < nkt) load_kv(next_lds, kt + 1, nk - kb - BN, std::false_type{});
+    const bool need_mask = (p.causal && kb + BN - 1 > wave_row_min) || (kb + BN > nk);
+    const int lim[2] = {(p.causal ? row_rel[0] : nk - 1) - kb - key4, (p.causal ? row_rel[1] : nk - 1) - kb - key4};
+
+#pragma unroll
+    for (int j = 0; j < BN / 32; ++j) {
+      const int blk = stage + 32 * j * ROW_BYTES;
+      f32x4 s[2][2], dp[2][2];   // [16-key block][query block]
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          s[kk][qb] = f32x4{0, 0, 0, 0};
+          dp[kk][qb] = f32x4{ndelta[qb], ndelta[qb], ndelta[qb], ndelta[qb]};
+        }
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const bf16x8 kf = lds_read8(nat_ptr[ks], blk + 16 * kk * ROW_BYTES);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) s[kk][qb] = mfma16(kf, qf[qb][ks], s[kk][qb]);
+        }
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const bf16x8 vf = lds_read8(nat_ptr[ks], blk + TILE_BYTES + 16 * kk * ROW_BYTES);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) dp[kk][qb] = mfma16(vf, dof[qb][ks], dp[kk][qb]);
+        }
+      // K^T fragments for the dQ product: half of them are requested before the elementwise work, the others behind
+      // the first query block's
+      bf16x8 ktf[NDB];
+      auto load_ktf = [&](int half) __attribute__((always_inline)) {
+#pragma unroll
+        for (int db = half * NDB / 2; db < (half + 1) * NDB / 2; ++db)
+          ktf[db] = cat4(lds_read_tr4(tr_ptr[db] + blk), lds_read_tr4(tr_ptr[db] + blk + 16 * ROW_BYTES));
+      };
+      load_ktf(0);
+      if (need_mask) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (32 * j + 16 * kk + r > lim[qb]) s[kk][qb][r] = -INFINITY;
+      }
+      bf16x8 dsf[2];
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        if (qb == 1) load_ktf(1);
+        bf16x2 pr[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int kk = t >> 1, r = 2 * (t & 1);
+          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kk][qb][r], c, nlse2[qb]));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kk][qb][r + 1], c, nlse2[qb]));
+          pr[t] = pack_bf16(p0 * dp[kk][qb][r], p1 * dp[kk][qb][r + 1]);
+        }
+        dsf[qb] = cat_pairs(pr[0], pr[1], pr[2], pr[3]);
+      }
+      // dQ^T += K^T dS^T over this block's 32 keys
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) acc[db][qb] = mfma16(ktf[db], dsf[qb], acc[db][qb]);
+    }
+    async_wait_all();
+    __syncthreads();
+  };
+
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) { consume(qf[qb][ks]); consume(dof[qb][ks]); }
+    consume(nlse2[qb]);
+    consume(ndelta[qb]);
+  }
+  async_wait_all();
+  __syncthreads();
+  int kt = 0;
+  for (; kt + 2 < nfull; kt += 2) {
+    tile_step(kt, 0, std::true_type{});
+    tile_step(kt + 1, STAGE_BYTES, std::true_type{});
+  }
+  for (; kt < nkt; ++kt) tile_step(kt, (kt & 1) * STAGE_BYTES, std::false_type{});
+
+  // (the rows are formed again from their 32-bit positions: 64-bit row indices kept alive through the main loop are
+  // registers this kernel does not have)
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    int row_rel_late = row_rel[qb];
+    asm volatile("" : "+v"(row_rel_late));   // (opaque: otherwise the address is formed in the prologue all the same)
+    __bf16* drow = reinterpret_cast<__bf16*>(reinterpret_cast<char*>(p.dq + tc.h * D) + tc.b * p.q_bstride +
+                                             tok_off(p, k_begin + row_rel_late, q_stride * 2));
+    const bool ok = wave_row_min + qb * 16 + n < rows_rel_end;
+#pragma unroll
+    for (int db = 0; db < NDB; db += 2) store_pair16_bf16(drow + 16 * db, acc[db][qb], acc[db + 1][qb], p.scale, g4, ok);
+  }
+}
 template <int D, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -285,7 +495,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(Attn
   for (;;) {   // persistent: one item (batch, head, query tile) per iteration (tile_queue.hpp)
     const int item = next_work(p, &s_work, xcc, skip);
     if (item < 0) break;
-    dq_item<D, WAVES>(p, smem, scratch, item);
+    if constexpr (D == 128) dq_item_16<D, WAVES>(p, smem, scratch, item);
+    else dq_item<D, WAVES>(p, smem, scratch, item);
   }
 }
 
@@ -845,6 +1056,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_bwd_both_kerne
   if constexpr (ONCE) {
     const int b = (int)blockIdx.x;
     if (b < pkv.q_total) dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, b);
+    else if constexpr (D == 128) dq_item_16<D, 4>(pq, smem, scratch, b - pkv.q_total);
     else dq_item<D, 4>(pq, smem, scratch, b - pkv.q_total);
   } else {
     __shared__ QueueState s_kv, s_q;

@@ -206,6 +206,30 @@ __device__ __forceinline__ void store_block32_bf16(__bf16* dst, const f32x16& ac
   }
 }
 
+// v_mfma_f32_16x16x32_bf16: A: lane holds row lane % 16, k = 8 (lane / 16) .. +7; B: column lane % 16, the same k;
+// C: column lane % 16, register r is row 4 (lane / 16) + r.
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// Writes one lane's share of two 16-row blocks of C-layout accumulator columns (v0: rows 4 g + r, v1: rows 16 + 4 g + r,
+// g = lane / 16) as bf16 to the 32 contiguous elements `dst`, scaled by `mul`, if `ok`.  The rows of 16 lanes exchange
+// quads first, so that a lane writes eight consecutive elements: 16 (g % 2) + 8 (g / 2) .. +7.
+__device__ __forceinline__ u32x4 exchange_pair16(f32x4 v0, f32x4 v1) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  u32x4 out;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const bf16x2_t a = {(__bf16)v0[2 * e], (__bf16)v0[2 * e + 1]}, b = {(__bf16)v1[2 * e], (__bf16)v1[2 * e + 1]};
+    auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    out[e] = r[0];
+    out[2 + e] = r[1];
+  }
+  return out;
+}
+__device__ __forceinline__ void store_pair16_bf16(__bf16* dst, f32x4 v0, f32x4 v1, float mul, int g, bool ok) {
+  const u32x4 out = exchange_pair16(v0 * mul, v1 * mul);
+  if (ok) *reinterpret_cast<u32x4*>(dst + 16 * (g & 1) + 8 * (g >> 1)) = out;
+}
+
 // ---- LDS tile layout -------------------------------------------------------------------
 // A tile is ROWS x D bf16, row pitch D*2 bytes, no padding.  The 16-byte chunk c of row r
 // sits at chunk position c ^ swz(r), which keeps both access patterns spread over the

@@ -114,8 +114,6 @@ __device__ __forceinline__ bf16x8 frag16(const char* tile, int lane, int o, int 
   return cat4(lds_read_tr4(tile + tr_off<EXT>(lane, r0, o)), lds_read_tr4(tile + tr_off<EXT>(lane, r0 + 4, o)));
 }
 
-__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-
 // One lane's share of a 32 x 32 accumulator block: row i of C, 32 consecutive j, of which the
 // first `cols` (a multiple of 8) exist.  Same exchange as store_block32_bf16.
 __device__ __forceinline__ void store_block(__bf16* dst, const f32x16& acc, int h, bool ok, int cols) {
@@ -343,16 +341,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_pp_kernel(GemmParams p)
         __bf16* crow = p.c + (cur.i0 + (ok ? il : 0)) * p.c_pitch + cur.j0;
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
-          // The rows of 16 lanes exchange quads, so that a lane holds eight consecutive columns of one 16-column block.
-          const f32x4 v0 = acc[ha][hb][ib][0], v1 = acc[ha][hb][ib][1];
-          u32x4 out;
-#pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, pack_bf16(v0[2 * e], v0[2 * e + 1])),
-                                                      __builtin_bit_cast(uint32_t, pack_bf16(v1[2 * e], v1[2 * e + 1])), false, false);
-            out[e] = r[0];
-            out[2 + e] = r[1];
-          }
+          const u32x4 out = exchange_pair16(acc[ha][hb][ib][0], acc[ha][hb][ib][1]);   // eight consecutive columns per lane
           const int j = hb * 128 + wj * 32 + 16 * (g4 & 1) + 8 * (g4 >> 1);
           if (ok && j < cur.j_valid) *reinterpret_cast<u32x4*>(crow + j) = out;
         }
