@@ -483,7 +483,9 @@ __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int*
     for (int db = 0; db < NDB; db += 2) store_pair16_bf16(drow + 16 * db, acc[db][qb], acc[db + 1][qb], p.scale, g4, ok);
   }
 }
-template <int D, int WAVES>
+// F16: the 16x16x32 form.  It gains where the launch runs into the power limit and costs a few per cent where it does not
+// (700 tokens x 40 heads, 240 items: 34.9 -> 36.2 us), so launches without a 128-row item for every CU keep the other.
+template <int D, int WAVES, bool F16>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ int scratch[2 * WAVES + 2];
@@ -495,7 +497,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(Attn
   for (;;) {   // persistent: one item (batch, head, query tile) per iteration (tile_queue.hpp)
     const int item = next_work(p, &s_work, xcc, skip);
     if (item < 0) break;
-    if constexpr (D == 128) dq_item_16<D, WAVES>(p, smem, scratch, item);
+    if constexpr (F16) dq_item_16<D, WAVES>(p, smem, scratch, item);
     else dq_item<D, WAVES>(p, smem, scratch, item);
   }
 }
@@ -1056,7 +1058,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_bwd_both_kerne
   if constexpr (ONCE) {
     const int b = (int)blockIdx.x;
     if (b < pkv.q_total) dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, b);
-    else if constexpr (D == 128) dq_item_16<D, 4>(pq, smem, scratch, b - pkv.q_total);
     else dq_item<D, 4>(pq, smem, scratch, b - pkv.q_total);
   } else {
     __shared__ QueueState s_kv, s_q;
@@ -1268,26 +1269,34 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
         return 0;
       }
     }
-    auto recompute = [&](auto waves_c) -> int {
+    auto recompute = [&](auto waves_c, auto f16_c) -> int {
       constexpr int W = decltype(waves_c)::value;
+      constexpr bool F16 = decltype(f16_c)::value;
       constexpr int smem = DqCfg<W>::template smem_bytes<D>();
       static KernelSetup setup;
       int per_cu = 1;
-      int rc = kernel_setup(setup, attn_bwd_dq_kernel<D, W>, smem, &per_cu, 64 * W);
+      int rc = kernel_setup(setup, attn_bwd_dq_kernel<D, W, F16>, smem, &per_cu, 64 * W);
       if (rc) return rc;
       tiles = tiles_per_head(p.S, DqCfg<W>::BM, p.cu, p.num_docs);
       items = tiles * p.B * p.Hq;
       a.tiles = (int32_t)tiles;
       const QueueLaunch ql = tile_queue_prepare(a, p.ws_counters + kCountersDq, items, a.Hq, per_cu, st, cleared_by_delta);
       if (ql.err != hipSuccess) return hip_fail(ql.err);
-      attn_bwd_dq_kernel<D, W><<<dim3((unsigned)ql.grid), dim3(64 * W), smem, st>>>(a);
+      attn_bwd_dq_kernel<D, W, F16><<<dim3((unsigned)ql.grid), dim3(64 * W), smem, st>>>(a);
       if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
       return 0;
     };
     if constexpr (D == 128) {
-      if (!dq_prefers_128_rows(ceil_div(p.S, DqCfg<kDqWaves>::BM) * p.B * p.Hq, p.S, p.cu != nullptr)) return recompute(std::integral_constant<int, kDqWaves>{});
+      const int cus = cu_count(&e);
+      if (e != hipSuccess) return hip_fail(e);
+      const bool wide = !dq_prefers_128_rows(ceil_div(p.S, DqCfg<kDqWaves>::BM) * p.B * p.Hq, p.S, p.cu != nullptr);
+      using Wide = std::integral_constant<int, kDqWaves>;
+      using Narrow = std::integral_constant<int, 4>;
+      if (items <= cus) return wide ? recompute(Wide{}, std::false_type{}) : recompute(Narrow{}, std::false_type{});
+      return wide ? recompute(Wide{}, std::true_type{}) : recompute(Narrow{}, std::true_type{});
+    } else {
+      return recompute(std::integral_constant<int, 4>{}, std::false_type{});
     }
-    return recompute(std::integral_constant<int, 4>{});
   };
   auto dkdv_phase = [&](auto store_c, auto chunked_c) -> int {
     constexpr bool kStore = decltype(store_c)::value, kChunked = decltype(chunked_c)::value;
