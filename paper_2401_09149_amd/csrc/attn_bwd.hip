@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "attn_common.hpp"
+#include "dispatch.hpp"
 #include "launch.hpp"
 #include "mfma_asm.hpp"
 #include "tile_queue.hpp"
@@ -1051,8 +1052,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p
 // dimension 64) or the whole chip (a launch whose items of both kinds are all resident at once) their items run side
 // by side: the launch is as long as the longer kind and there is one tail instead of two.  `ONCE`: every workgroup
 // does the one item of its index, dK/dV items first, without the queues' atomics; otherwise a workgroup takes dK/dV
-// items until there are none and then dQ items (128 rows each).  4 x 2000 tokens x 16 heads, D = 64: 324 -> 290 us of
-// kernel time; 512 tokens x 4 heads, D = 128: 46.7 -> 23.5 us for the whole backward pass.
+// items until there are none and then dQ items (128 rows each).  The whole backward pass: 4 x 2000 tokens x 16 heads
+// bidirectional, D = 64: 334 -> 312 us; 512 tokens x 4 heads, D = 128: 47.3 -> 23.5 us.  Launches of many rounds keep two
+// kernels (bwd64_in_one_launch in dispatch.hpp).
 template <int D, bool CHUNKED, bool ONCE>
 __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_bwd_both_kernel(AttnParams pkv, AttnParams pq) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1318,12 +1320,16 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
     return 0;
   };
-  // Both main kernels in one launch.  ONCE: a workgroup per item, no queue.
-  auto both_phase = [&](auto chunked_c, auto once_c, const int64_t tiles, const int per_cu) -> int {
-    constexpr bool kChunked = decltype(chunked_c)::value, kOnce = decltype(once_c)::value;
+  // Both main kernels in one launch (ONCE: a workgroup per item, no queue): how many of its workgroups fit on a CU, and
+  // the launch.
+  auto both_fit = [&](auto chunked_c, auto once_c, int* per_cu) -> int {
     static KernelSetup setup;
-    int fits = 1;
-    int rc = kernel_setup(setup, attn_bwd_both_kernel<D, kChunked, kOnce>, kBothSmem<D>, &fits);
+    return kernel_setup(setup, attn_bwd_both_kernel<D, decltype(chunked_c)::value, decltype(once_c)::value>, kBothSmem<D>, per_cu);
+  };
+  auto both_phase = [&](auto chunked_c, auto once_c, const int64_t tiles) -> int {
+    constexpr bool kChunked = decltype(chunked_c)::value, kOnce = decltype(once_c)::value;
+    int per_cu = 1;
+    int rc = both_fit(chunked_c, once_c, &per_cu);
     if (rc) return rc;
     AttnParams kv = p, q = p;
     kv.tiles = q.tiles = (int32_t)tiles;
@@ -1349,18 +1355,19 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
   if (!from_ds && (phases & 6) == 6) {
     const int cus = cu_count(&e);
     if (e != hipSuccess) return hip_fail(e);
+    int per_cu = 1;
+    if ((rc = chunked ? both_fit(std::true_type{}, std::true_type{}, &per_cu) : both_fit(std::false_type{}, std::true_type{}, &per_cu))) return rc;
     const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs);
-    const int64_t items = tiles * p.B * ((int64_t)p.Hq + p.Hkv);
-    constexpr int per_cu = D == 64 ? 2 : 1;
-    const bool once = items <= (int64_t)cus * per_cu;
-    if (once && (D == 64 || tile_rows_setting.load(std::memory_order_relaxed) != 256)) {
-      return chunked ? both_phase(std::true_type{}, std::true_type{}, tiles, per_cu)
-                     : both_phase(std::false_type{}, std::true_type{}, tiles, per_cu);
+    const int64_t items = tiles * p.B * ((int64_t)p.Hq + p.Hkv), resident = (int64_t)cus * per_cu;
+    if (items <= resident && (D == 64 || tile_rows_setting.load(std::memory_order_relaxed) != 256)) {
+      return chunked ? both_phase(std::true_type{}, std::true_type{}, tiles)
+                     : both_phase(std::false_type{}, std::true_type{}, tiles);
     }
     if constexpr (D == 64) {
-      if (items >= ((int64_t)1 << 31)) return kErrShape;
-      return chunked ? both_phase(std::true_type{}, std::false_type{}, tiles, per_cu)
-                     : both_phase(std::false_type{}, std::false_type{}, tiles, per_cu);
+      if (items < ((int64_t)1 << 31) && bwd64_in_one_launch(p.B, p.S, p.Hq, p.Hkv, p.causal != 0, p.num_docs, cus, resident)) {
+        return chunked ? both_phase(std::true_type{}, std::false_type{}, tiles)
+                       : both_phase(std::false_type{}, std::false_type{}, tiles);
+      }
     }
   }
   if (from_ds) {

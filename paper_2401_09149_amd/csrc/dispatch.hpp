@@ -1,0 +1,38 @@
+// Which kernel serves which call: the rules that go by sizes alone.  Plain host code without the HIP runtime, so that a
+// test can compile it and ask.
+#pragma once
+#include <stdint.h>
+
+namespace ie {
+
+// Backward pass at head dimension 64: dK/dV and dQ items in one launch (attn_bwd_both_kernel), or a launch each?
+// `resident`: workgroups of the shared launch that the chip holds at once (two per CU).
+// The shared launch saves a launch and fills the other kind's tail; it costs dQ its third wave per SIMD, and dK/dV items
+// that would have a CU to themselves share it.  Kernel time of the whole pass, two launches against one, 256 CUs:
+//   all items resident: one launch always (128 to 4096 tokens, every head count and group: 1.05-2.9 times faster);
+//   a little more work than that: the queues' fixed cost decides (700 tokens x 48 heads 94 : 109 us, 384 x 96
+//   107 : 127, but 640 x 80 130 : 125 and 1600 x 24 112 : 99);
+//   fewer dK/dV items than CUs: one launch while the pass is short (4096 x 16, 2 per group, bidirectional 360 : 326 us;
+//   8192 x 8, 4 per group 1011 : 1090; 8192 x 8, 8 per group 1792 : 2113);
+//   one to two rounds of dK/dV items, the last of them nearly empty or causal: one launch at any length (8192 x 16, 2 per
+//   group, causal 780 : 612 us; 6000 x 24, 2 per group, bidirectional 993 : 831);
+//   more rounds: one launch up to about 150 pairs of 128 x 128 tiles per CU, twice that where groups make the
+//   heaviest dK/dV items longer (2000 x 64 bidirectional 343 : 325 us, 4096 x 64 causal 627 : 613; above it
+//   8192 x 32 bidirectional 1980 : 2010, 8192 x 64 causal 2022 : 2149, 8192 x 64 bidirectional 3875 : 4117).
+inline bool bwd64_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus,
+                                int64_t resident) {
+  const int64_t per_head = num_docs ? S / 128 + num_docs : (S + 127) / 128;   // items per (batch entry, head)
+  const int64_t nk = per_head * B * Hkv, nq = per_head * B * Hq;
+  if (nk + nq <= resident) return true;
+  double doc = num_docs ? (double)S / 128 / (double)num_docs : (double)per_head;   // tiles of a document (packed: on average)
+  if (doc < 1) doc = 1;
+  const double work = (double)nq * (causal ? (doc + 1) / 2 : doc) / (double)cus;   // pairs of tiles per CU
+  if (5 * (nk + nq) < 7 * resident && work < 7) return false;
+  const int64_t group = Hq / Hkv;
+  if (nk <= cus) return nk > cus / 4 && (work <= 24 || work <= (double)(nk - cus / 2));
+  if (causal) return nk < 2 * resident || work <= (group == 1 ? 150 : 300);
+  const int64_t rounds = (nk + resident - 1) / resident;
+  return work <= 150 || 10 * nk <= (group >= 4 ? 8 : 7) * resident * rounds;
+}
+
+}  // namespace ie
