@@ -485,8 +485,7 @@ __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int*
     for (int db = 0; db < NDB; db += 2) store_pair16_bf16(drow + 16 * db, acc[db][qb], acc[db + 1][qb], p.scale, g4, ok);
   }
 }
-// F16: the 16x16x32 form.  It gains where the launch runs into the power limit and costs a few per cent where it does not
-// (700 tokens x 40 heads, 240 items: 34.9 -> 36.2 us), so launches without a 128-row item for every CU keep the other.
+// F16: the 16x16x32 form (dq128_on_16x16x32 in dispatch.hpp chooses).
 template <int D, int WAVES, bool F16>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1293,11 +1292,13 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     if constexpr (D == 128) {
       const int cus = cu_count(&e);
       if (e != hipSuccess) return hip_fail(e);
-      const bool wide = !dq_prefers_128_rows(ceil_div(p.S, DqCfg<kDqWaves>::BM) * p.B * p.Hq, p.S, p.cu != nullptr);
+      const int64_t items_256 = ceil_div(p.S, DqCfg<kDqWaves>::BM) * p.B * p.Hq;
+      const bool wide = !dq_prefers_128_rows(items_256, p.S, p.cu != nullptr);
+      const bool f16 = dq128_on_16x16x32(items, items_256, wide, p.causal != 0, p.cu != nullptr, cus);
       using Wide = std::integral_constant<int, kDqWaves>;
       using Narrow = std::integral_constant<int, 4>;
-      if (items <= cus) return wide ? recompute(Wide{}, std::false_type{}) : recompute(Narrow{}, std::false_type{});
-      return wide ? recompute(Wide{}, std::true_type{}) : recompute(Narrow{}, std::true_type{});
+      if (f16) return wide ? recompute(Wide{}, std::true_type{}) : recompute(Narrow{}, std::true_type{});
+      return wide ? recompute(Wide{}, std::false_type{}) : recompute(Narrow{}, std::false_type{});
     } else {
       return recompute(std::integral_constant<int, 4>{}, std::false_type{});
     }

@@ -35,4 +35,20 @@ inline bool bwd64_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, b
   return work <= 150 || 10 * nk <= (group >= 4 ? 8 : 7) * resident * rounds;
 }
 
+// Recomputing dQ kernel at head dimension 128: products as 16x16x32 MFMAs (dq_item_16) instead of 32x32x16 (dq_item)?
+// The 16x16x32 form costs less power per product and more issue slots, so it gains where the launch keeps the chip at its
+// power limit and loses where most CUs wait for a few heavy items: dQ alone, 32x32x16 against it, 32768 x 16 causal
+// 5032 : 4831 us, 4096 x 32 343 : 324 (bidirectional 212 : 205 causal), but 6000 x 8 causal 181 : 195, 12000 x 3 causal
+// 282 : 327, 3001 x 16 causal 99 : 105.  The line lies where the mean load per CU is about 3/4 of the heaviest item: in
+// 256-row items per CU 1.25 causal (an item's mean is half its maximum; 2048 x 40 84 : 83, 3001 x 24 109 : 110) and 0.8
+// bidirectional (2048 x 32 111 : 106, 3001 x 16 119 : 120); with 128-row workgroups, two per CU, 1.0 and 0.7 (8192 x 8
+// causal 227 : 227, 8192 x 6 bidirectional 297 : 288); packed documents, whose lengths the host does not know, 2
+// (16384 x 8 ten mixes 0.98-1.01, 16384 x 4 44-56 to 219-232).
+inline bool dq128_on_16x16x32(int64_t items_128, int64_t items_256, bool wide, bool causal, bool packed, int64_t cus) {
+  if (items_128 <= cus) return false;
+  if (packed) return items_256 >= 2 * cus;
+  const int64_t percent = causal ? (wide ? 125 : 100) : (wide ? 80 : 70);
+  return 100 * items_256 >= percent * cus;
+}
+
 }  // namespace ie

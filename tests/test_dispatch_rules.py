@@ -12,6 +12,9 @@ SHIM = """
 extern "C" int one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
   return ie::bwd64_in_one_launch(B, S, Hq, Hkv, causal != 0, docs, 256, 512);
 }
+extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
+  return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
+}
 """
 
 
@@ -47,3 +50,24 @@ def rules(tmp_path_factory):
 def test_bwd64_launches(rules, B, S, Hq, Hkv, causal, docs, one):
     i64 = ctypes.c_int64
     assert bool(rules.one_launch(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))) == one
+
+
+@pytest.mark.parametrize("S,H,wide,causal,packed,on16", [
+    (32768, 16, 1, 1, 0, True),
+    (4096, 32, 1, 0, 0, True),
+    (2048, 40, 1, 1, 0, True),     # 320 items of 256 rows
+    (3001, 24, 1, 1, 0, False),    # 288
+    (6000, 8, 1, 1, 0, False),
+    (2048, 32, 1, 0, 0, True),     # 256
+    (3001, 16, 1, 0, 0, False),    # 192
+    (8192, 8, 0, 1, 0, True),
+    (12000, 3, 0, 1, 0, False),
+    (8192, 6, 0, 0, 0, True),
+    (12000, 3, 0, 0, 0, False),
+    (65536, 8, 1, 1, 1, True),
+    (16384, 4, 1, 1, 1, False),
+    (128, 250, 1, 0, 0, False),    # no 128-row item for every CU
+])
+def test_dq128_form(rules, S, H, wide, causal, packed, on16):
+    i64 = ctypes.c_int64
+    assert bool(rules.dq16(i64(-(-S // 128) * H), i64(-(-S // 256) * H), wide, causal, packed)) == on16
