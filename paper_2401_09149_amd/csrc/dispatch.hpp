@@ -51,4 +51,53 @@ inline bool dq128_on_16x16x32(int64_t items_128, int64_t items_256, bool wide, b
   return 100 * items_256 >= percent * cus;
 }
 
+// Which linear kernel: the one with the least estimated time.  A workgroup takes its tiles one after the other, and a tile
+// its 64-deep steps at a cost per step for each product (forward, dx, dw: a transposed operand takes two LDS reads per
+// fragment) with all CUs at work, less in a round that leaves CUs idle (memory is then less busy and the clock higher),
+// plus what stands around a tile; a round of tiles takes no less than their outputs' way to memory, which is what counts
+// in weight gradients over a few hundred tokens.  Fitted to 1500 measured (product, size) pairs, 1 to 16384 tokens, layer
+// widths 512 to 8192, whole tiles and ragged ones: the choice is 0.2 % slower than the best of the seven on average
+// (0.3 % on a third of the pairs that a fit had not seen) and 14 % at most, and never more than 1 % slower than the
+// 256 x 256 tiles of 32x32x16 products that once served every size (twice as fast on average; dw 8192 tokens
+// 9600 x 3200 447 -> 422 us, 128 tokens 8192 x 8192 55 -> 46, forward 200 tokens 4096 x 4096 94 -> 22).
+enum Tile { kPp256, kRing256x128, kRing128x256, kRing128, kRing64x128, kRing64, kRing32, kTiles };
+struct TileCost {
+  int ti, tj, step;         // tile, depth of a step in units of 64
+  float step_us[3];         // per 64-deep step: forward, dx, dw
+  float tile_us, light;     // around a tile; factor of a step when few CUs are at work
+  float write_us;           // least time of a round of tiles on all CUs
+};
+constexpr TileCost kCost[kTiles] = {
+    {256, 256, 1, {1.273f, 1.379f, 1.609f}, 5.55f, 0.68f, 7.27f},
+    {256, 128, 1, {0.901f, 0.930f, 1.027f}, 2.88f, 0.71f, 3.63f},
+    {128, 256, 1, {1.024f, 0.940f, 1.058f}, 2.33f, 0.70f, 4.70f},
+    {128, 128, 1, {0.625f, 0.607f, 0.683f}, 1.20f, 0.68f, 2.56f},
+    {64, 128, 1, {0.422f, 0.460f, 0.482f}, 0.76f, 0.88f, 2.10f},
+    {64, 64, 1, {0.254f, 0.281f, 0.264f}, 1.28f, 0.72f, 2.06f},
+    {32, 32, 4, {0.128f, 0.f, 0.f}, 0.49f, 0.95f, 0.00f}};
+
+// C[I][J] over a contraction of R; product: 0 forward, 1 dx, 2 dw.
+inline Tile pick_tile(int64_t I, int64_t J, int64_t R, int product, int64_t cus) {
+  const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
+  Tile best = kPp256;
+  float best_us = 0.f;
+  for (int k = 0; k < kTiles; ++k) {
+    if (k == kRing32 && product != 0) continue;   // (both operands direct: a transposed 32-wide tile has 64-byte rows)
+    const TileCost& c = kCost[k];
+    const int64_t per = ceil_div(ceil_div(I, c.ti) * ceil_div(J, c.tj), 8);   // tiles of one XCD
+    const int64_t full = per / per_xcd, rest = per % per_xcd;                 // whole rounds, tiles of the last one
+    const float steps = (float)(ceil_div(R, 64 * c.step) * c.step) * c.step_us[product];
+    const float whole = steps + c.tile_us > c.write_us ? steps + c.tile_us : c.write_us;
+    float us = (float)full * whole;
+    if (rest) {
+      const float part = (float)rest / (float)per_xcd;
+      const float last = steps * (c.light + (1.f - c.light) * part) + c.tile_us;
+      us += last > c.write_us * part ? last : c.write_us * part;
+    }
+    if (k == 0 || us < best_us) { best = (Tile)k; best_us = us; }
+  }
+  return best;
+}
+
 }  // namespace ie

@@ -7,7 +7,7 @@
 //
 // Two kernels share the tile order, the copies and the fragment layouts.  linear_pp_kernel computes 256 x 256 tiles of C
 // and is the faster one per product; linear_ring_kernel computes smaller ones, down to 32 x 32, for outputs that
-// do not fill the chip with large tiles (pick_tile below chooses).  In both a workgroup is 8 wavefronts (two per SIMD),
+// do not fill the chip with large tiles (pick_tile in dispatch.hpp chooses).  In both a workgroup is 8 wavefronts (two per SIMD),
 // one workgroup per CU, each walking its share of the tiles; operands reach LDS by asynchronous copies that run ahead
 // of the products across tile boundaries.  Tiles sit in LDS row-major with swizzled 16-byte chunks; a direct operand's
 // fragment is one 16-byte LDS read, a transposed operand's two transpose loads.  The products are formed transposed,
@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "attn_common.hpp"
+#include "dispatch.hpp"
 #include "launch.hpp"
 
 namespace ie {
@@ -45,51 +46,47 @@ struct GemmParams {
 // LDS cycles of the forward product were bank conflicts with it.)
 __device__ __forceinline__ uint32_t dswz(uint32_t r) { return (r >> 1) & 7u; }
 
-// One wave's share of the copy of SUB consecutive 64-deep tiles of one operand, `ext` = tile extent along the output
-// index.  Instruction t of wave w is piece w + 8 t of the SUB * ext / 8 pieces of 1 KiB, in LDS order.  `subs` of the
-// SUB tiles exist (the others repeat the last one and are not used); `sub_step` = bytes between them.
+// One wave's share of the copy of SUB consecutive 64-deep tiles of one operand, `EXT` = tile extent along the output index.
+// A lane's offsets are worked out once per output tile (set_tile), so that a step's copies are a base address and nothing
+// else, whole tile or not.  (Worked out in every step, with a path of its own for whole tiles, they were some 180
+// instructions ahead of a step's LDS reads: dw 8192 tokens 3200 x 3200 209 -> 168 us and 12288 x 4096 668 -> 633, dx 4096
+// tokens 17152 x 3200 426 -> 355, forward 2048 tokens 9600 x 3200 139 -> 123, all with 256 x 256 tiles; dw 6144 tokens
+// 512 x 1344, 64 x 64 tiles, 37 -> 29.)  Instruction t of wave w is piece w + 8 t of the SUB * EXT / 8 pieces of 1 KiB, in LDS order.
 template <bool T, int EXT, int SUB>
 struct TileCopy {
-  static constexpr int PIECES = EXT / 8;              // 1 KiB pieces of one 64-deep tile
+  static constexpr uint32_t PIECES = EXT / 8;         // 1 KiB pieces of one 64-deep tile
   static constexpr int NI = SUB * PIECES / kWaves;
-  static constexpr int CPR = T ? EXT / 8 : 8;         // 16-byte chunks per row
-  static constexpr int RPP = 64 / CPR;                // rows per piece
-  uint32_t row, chunk;   // this lane's row and chunk POSITION in piece 0
-  uint32_t voff;         // its byte offset in instruction 0 of a whole tile, and in the others up to whole rows
-  int wave;
-  __device__ __forceinline__ void init(int tid, uint32_t pitch) {
-    const int lane = tid & 63;
-    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    row = lane / CPR;
-    chunk = lane % CPR;
-    // (from one instruction to the next a lane's row moves by a multiple of 16, which leaves the swizzle as it is)
-    const uint32_t r = row + (uint32_t)(wave % PIECES) * RPP;
-    voff = r * pitch + ((chunk ^ (T ? (uint32_t)swz<EXT>((int)r) : dswz(r))) << 4);
-    static_assert((kWaves % PIECES == 0 || kWaves * RPP % 16 == 0), "");
+  static constexpr uint32_t CPR = T ? EXT / 8 : 8;    // 16-byte chunks per row
+  static constexpr uint32_t RPP = 64 / CPR;           // rows per piece
+  static constexpr int NV = SUB > 1 ? 1 : NI;         // (SUB > 1: a lane's instructions differ in the 64-deep tile only)
+  static_assert(SUB == 1 || kWaves % PIECES == 0, "");
+  uint32_t wave;
+  uint32_t voff[NV];     // byte offset of this lane's 16 bytes of instruction t
+  __device__ __forceinline__ void init(int tid) { wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6); }
+  // `valid`: rows (direct) or 16-byte chunks (transposed) that exist along the output index; what lies past them repeats
+  // the last.  `first`: the tile starts at that row or chunk.
+  __device__ __forceinline__ void set_tile(int tid, uint32_t pitch, int valid, uint32_t first = 0) {
+    const uint32_t lane = tid & 63, last = (uint32_t)valid - 1;
+    auto clamp = [&](uint32_t x) __attribute__((always_inline)) { return x + first < last ? x + first : last; };
+#pragma unroll
+    for (int t = 0; t < NV; ++t) {
+      const uint32_t r = lane / CPR + (wave + kWaves * t) % PIECES * RPP;
+      const uint32_t chunk = lane % CPR ^ (T ? (uint32_t)swz<EXT>((int)r) : dswz(r));
+      voff[t] = T ? r * pitch + (clamp(chunk) << 4) : clamp(r) * pitch + (chunk << 4);
+    }
   }
-  // WHOLE: the tile exists in full, no per-lane arithmetic.
-  template <bool WHOLE>
-  __device__ __forceinline__ void issue(uint32_t lds, const char* g, uint32_t pitch, int valid, int64_t sub_step, int subs) const {
+  // `g`: first byte of the step; `subs` of its SUB tiles exist (the others repeat the last one and are not used);
+  // `sub_step`: bytes between them.
+  __device__ __forceinline__ void issue(uint32_t lds, const char* g, int64_t sub_step = 0, int subs = 1) const {
 #pragma unroll
     for (int t = 0; t < NI; ++t) {
-      const int piece = wave + kWaves * t;
-      int sub = piece / PIECES;
-      if (SUB > 1) sub = sub < subs ? sub : subs - 1;
-      const char* src = g + sub * sub_step;
-      const uint32_t dst = lds + (uint32_t)piece * 1024;
-      if constexpr (WHOLE) {
-        async_copy16(voff, src + (int64_t)(kWaves * t % PIECES * RPP) * pitch, dst);
-        continue;
+      const uint32_t piece = wave + kWaves * t;
+      const char* src = g;
+      if constexpr (SUB > 1) {
+        const uint32_t sub = piece / PIECES;
+        src += (int64_t)(sub < (uint32_t)subs ? sub : (uint32_t)subs - 1) * sub_step;
       }
-      const uint32_t r = row + (uint32_t)(piece % PIECES) * RPP;
-      uint32_t v;
-      if (!T) {
-        v = (r < (uint32_t)valid ? r : (uint32_t)valid - 1) * pitch + ((chunk ^ dswz(r)) << 4);
-      } else {
-        const uint32_t lc = chunk ^ (uint32_t)swz<EXT>((int)r);
-        v = r * pitch + ((lc < (uint32_t)valid ? lc : (uint32_t)valid - 1) << 4);
-      }
-      async_copy16(v, src, dst);
+      async_copy16(voff[NV == 1 ? 0 : t], src, lds + piece * 1024);
     }
   }
 };
@@ -148,11 +145,11 @@ __device__ __forceinline__ void store_block(__bf16* dst, const f32x16& acc, int 
 // workgroups that run together on an XCD share a few A and B panels in its L2.  `l` numbers the
 // tiles of one XCD's eighth.
 struct GemmTile {
-  const char* ga;  // first byte of the A tile of contraction step 0
+  const char* ga;  // first byte of the A tile of contraction step 0 (the copies' position moves it on step by step)
   const char* gb;
   int64_t i0, j0;
   int i_valid, j_valid, a_valid, b_valid;
-  bool valid, whole;   // whole: TI x TJ outputs exist
+  bool valid;
 };
 template <bool A_T, bool B_T, int TI, int TJ>
 __device__ __forceinline__ GemmTile decode_gemm_tile(const GemmParams& p, int l) {
@@ -170,7 +167,6 @@ __device__ __forceinline__ GemmTile decode_gemm_tile(const GemmParams& p, int l)
   g.j0 = (int64_t)tj * TJ;
   g.i_valid = (int)(p.I - g.i0 < TI ? p.I - g.i0 : TI);
   g.j_valid = (int)(p.J - g.j0 < TJ ? p.J - g.j0 : TJ);
-  g.whole = g.i_valid == TI && g.j_valid == TJ;
   g.ga = p.a + (A_T ? g.i0 * 2 : g.i0 * p.a_pitch);
   g.gb = p.b + (B_T ? g.j0 * 2 : g.j0 * p.b_pitch);
   g.a_valid = A_T ? g.i_valid / 8 : g.i_valid;
@@ -208,12 +204,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_pp_kernel(GemmParams p)
   const int lstep = (int)(gridDim.x >> 3);
   const int nkt = (int)(p.R / 64);
   const int64_t a_step = A_T ? 64 * p.a_pitch : 128, b_step = B_T ? 64 * p.b_pitch : 128;
-  const int64_t a_half = A_T ? 256 : 128 * p.a_pitch, b_half = B_T ? 256 : 128 * p.b_pitch;
-
-  TileCopy<A_T, 128, 1> ca;
-  TileCopy<B_T, 128, 1> cb;
-  ca.init(tid, (uint32_t)p.a_pitch);
-  cb.init(tid, (uint32_t)p.b_pitch);
+  TileCopy<A_T, 128, 1> ca[2];   // the two halves of the operand tile
+  TileCopy<B_T, 128, 1> cb[2];
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) { ca[hf].init(tid); cb[hf].init(tid); }
   const uint32_t lds0 = lds_address(smem);
 
   int cl = (int)(blockIdx.x >> 3), ckt = 0, cslot = 0;
@@ -221,42 +215,37 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_pp_kernel(GemmParams p)
   if (!ctile.valid) return;
   GemmTile cur = ctile;
   int l = cl;
-  // Half `hf` of an operand tile; a half that lies past the end repeats the last row (chunk) of the first.  (One branch
-  // for all the copies of a turn: a branch per copy made the kernel 20 % slower.)
-  auto copy_a = [&](int hf, auto whole) __attribute__((always_inline)) {
-    constexpr int U = A_T ? 16 : 128;
-    const bool in = decltype(whole)::value || hf == 0 || ctile.a_valid > U;
-    ca.template issue<decltype(whole)::value>(lds0 + cslot * P_STAGE_BYTES + hf * P_HALF_BYTES, ctile.ga + ckt * a_step + (hf && in ? a_half : 0), (uint32_t)p.a_pitch,
-             hf && in ? ctile.a_valid - U : ctile.a_valid, 0, 1);
+  auto set_tile = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      ca[hf].set_tile(tid, (uint32_t)p.a_pitch, ctile.a_valid, hf * (A_T ? 16 : 128));
+      cb[hf].set_tile(tid, (uint32_t)p.b_pitch, ctile.b_valid, hf * (B_T ? 16 : 128));
+    }
   };
-  auto copy_b = [&](int hf, auto whole) __attribute__((always_inline)) {
-    constexpr int U = B_T ? 16 : 128;
-    const bool in = decltype(whole)::value || hf == 0 || ctile.b_valid > U;
-    cb.template issue<decltype(whole)::value>(lds0 + cslot * P_STAGE_BYTES + (2 + hf) * P_HALF_BYTES, ctile.gb + ckt * b_step + (hf && in ? b_half : 0), (uint32_t)p.b_pitch,
-             hf && in ? ctile.b_valid - U : ctile.b_valid, 0, 1);
+  // A step's copies: A0, B0 and B1 first, A1 a turn later, which then moves on to the next step.
+  auto copy_first = [&]() __attribute__((always_inline)) {
+    const uint32_t base = lds0 + cslot * P_STAGE_BYTES;
+    ca[0].issue(base, ctile.ga);
+    cb[0].issue(base + 2 * P_HALF_BYTES, ctile.gb);
+    cb[1].issue(base + 3 * P_HALF_BYTES, ctile.gb);
   };
-  auto advance = [&]() __attribute__((always_inline)) {
+  auto copy_last = [&]() __attribute__((always_inline)) {
+    ca[1].issue(lds0 + cslot * P_STAGE_BYTES + P_HALF_BYTES, ctile.ga);
     cslot ^= 1;
+    ctile.ga += a_step;
+    ctile.gb += b_step;
     if (++ckt == nkt) {
       ckt = 0;
       cl += lstep;
       ctile = decode_gemm_tile<A_T, B_T, TI, TJ>(p, cl);
+      if (ctile.valid) set_tile();
     }
   };
-  auto copy_first = [&](auto whole) __attribute__((always_inline)) { copy_a(0, whole); copy_b(0, whole); copy_b(1, whole); };
-  auto copy_first_any = [&]() __attribute__((always_inline)) {
-    if (ctile.whole) copy_first(std::true_type{});
-    else copy_first(std::false_type{});
-  };
-  auto copy_last_any = [&]() __attribute__((always_inline)) {
-    if (ctile.whole) copy_a(1, std::true_type{});
-    else copy_a(1, std::false_type{});
-  };
-  copy_first_any();
-  copy_last_any();
-  advance();
+  set_tile();
+  copy_first();
+  copy_last();
   bool pend = ctile.valid;   // the step at the copies' position lacks its A1
-  if (pend) copy_first_any();
+  if (pend) copy_first();
   async_wait_all();
   __syncthreads();
   auto bar = [&]() __attribute__((always_inline)) {
@@ -307,8 +296,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_pp_kernel(GemmParams p)
       // must have landed behind this turn is this step's A1: all but the eight youngest copies, six of the next
       // step's first three halves and the two issued here (the epilogue's stores are younger and only tighten the wait).
       if (pend) {
-        copy_last_any();
-        advance();
+        copy_last();
         asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       } else {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -321,7 +309,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_pp_kernel(GemmParams p)
       // The step after next's A0, B0 and B1 go where this step's have been read; the next step's must have landed.
       pend = ctile.valid;
       if (pend) {
-        copy_first_any();
+        copy_first();
         asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       } else {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -387,8 +375,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_ring_kernel(GemmParams 
 
   TileCopy<A_T, CI, SUB> ca;
   TileCopy<B_T, CJ, SUB> cb;
-  ca.init(tid, (uint32_t)p.a_pitch);
-  cb.init(tid, (uint32_t)p.b_pitch);
+  ca.init(tid);
+  cb.init(tid);
   const uint32_t lds0 = lds_address(smem);
 
   // The copies run ahead of the products by NS - 1 steps, across tile boundaries: (ctile, ckt) is the next step to copy.
@@ -397,22 +385,24 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_ring_kernel(GemmParams 
   if (!ctile.valid) return;
   GemmTile cur = ctile;
   int l = cl;
+  ca.set_tile(tid, (uint32_t)p.a_pitch, ctile.a_valid);
+  cb.set_tile(tid, (uint32_t)p.b_pitch, ctile.b_valid);
   auto copy_next = [&]() __attribute__((always_inline)) {
     const uint32_t base = lds0 + cslot * C::STAGE_BYTES;
-    const int64_t sub0 = (int64_t)ckt * SUB;
-    const int subs = nr - (int)sub0;
-    auto both = [&](auto whole) __attribute__((always_inline)) {
-      constexpr bool W = decltype(whole)::value;
-      ca.template issue<W>(base, ctile.ga + sub0 * a_step, (uint32_t)p.a_pitch, ctile.a_valid, a_step, subs);
-      cb.template issue<W>(base + SUB * C::A_BYTES, ctile.gb + sub0 * b_step, (uint32_t)p.b_pitch, ctile.b_valid, b_step, subs);
-    };
-    if (ctile.whole) both(std::true_type{});
-    else both(std::false_type{});
+    const int subs = nr - ckt * SUB;
+    ca.issue(base, ctile.ga, a_step, subs);
+    cb.issue(base + SUB * C::A_BYTES, ctile.gb, b_step, subs);
+    ctile.ga += SUB * a_step;
+    ctile.gb += SUB * b_step;
     cslot = cslot + 1 == NS ? 0 : cslot + 1;
     if (++ckt == nkt) {
       ckt = 0;
       cl += lstep;
       ctile = decode_gemm_tile<A_T, B_T, CI, CJ>(p, cl);
+      if (ctile.valid) {
+        ca.set_tile(tid, (uint32_t)p.a_pitch, ctile.a_valid);
+        cb.set_tile(tid, (uint32_t)p.b_pitch, ctile.b_valid);
+      }
     }
   };
 #pragma unroll
@@ -555,50 +545,12 @@ int launch_ring(const GemmParams& p, hipStream_t st) {
   return launch_tiles(linear_ring_kernel<A_T, B_T, C>, p, C::CI, C::CJ, C::SMEM_BYTES, st);
 }
 
-// Which kernel: the one with the least estimated time.  A workgroup takes its tiles one after the other, and a tile its
-// 64-deep steps at a cost per step that was measured per product (forward, dx, dw: a transposed operand takes two LDS
-// reads per fragment) with all CUs at work, less in a round that leaves CUs idle (memory is then less busy and the clock
-// higher), plus what stands around a tile.  Fitted to 1008 measured (product, size) pairs, 1 to 16384 tokens and layer
-// widths 512 to 8192: the choice is 0.4 % slower than the best of the seven on average and 21 % at most, and twice as
-// fast as 256 x 256 tiles throughout (200 tokens: 4096 x 4096 94 -> 22 us with 64 x 64 tiles, 12288 x 4096 96 -> 41 us
-// with 128 x 128, 22016 x 4096 99 -> 65 us with 256 x 128; one token, 4096 x 11008: 224 -> 25 us with 32 x 32; 8192
-// tokens stay on 256 x 256).
-enum Tile { kPp256, kRing256x128, kRing128x256, kRing128, kRing64x128, kRing64, kRing32, kTiles };
-struct TileCost {
-  int ti, tj, step;         // tile, depth of a step in units of 64
-  float step_us[3];         // per 64-deep step: forward, dx, dw
-  float tile_us, light;     // around a tile; factor of a step when few CUs are at work
-};
-constexpr TileCost kCost[kTiles] = {
-    {256, 256, 1, {1.50f, 1.60f, 1.80f}, 3.7f, 0.73f},    {256, 128, 1, {1.03f, 1.075f, 1.137f}, 1.5f, 0.71f},
-    {128, 256, 1, {1.055f, 1.072f, 1.10f}, 1.3f, 0.73f},  {128, 128, 1, {0.637f, 0.662f, 0.690f}, 1.0f, 0.73f},
-    {64, 128, 1, {0.442f, 0.443f, 0.512f}, 0.7f, 0.83f},  {64, 64, 1, {0.272f, 0.300f, 0.332f}, 1.3f, 0.82f},
-    {32, 32, 4, {0.144f, 0.f, 0.f}, 0.f, 0.70f}};
-
-Tile pick_tile(int64_t I, int64_t J, int64_t R, bool a_t, bool b_t, int cus) {
-  const int prod = a_t ? 2 : b_t ? 1 : 0;
-  const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
-  Tile best = kPp256;
-  float best_us = 0.f;
-  for (int k = 0; k < kTiles; ++k) {
-    if (k == kRing32 && prod != 0) continue;   // (both operands direct: a transposed 32-wide tile has 64-byte rows)
-    const TileCost& c = kCost[k];
-    const int64_t per = ceil_div(ceil_div(I, c.ti) * ceil_div(J, c.tj), 8);   // tiles of one XCD
-    const int64_t full = per / per_xcd, rest = per % per_xcd;                 // whole rounds, tiles of the last one
-    const float steps = (float)(ceil_div(R, 64 * c.step) * c.step);
-    const float last = rest ? c.light + (1.f - c.light) * (float)rest / (float)per_xcd : 0.f;
-    const float us = (float)(full + (rest != 0)) * c.tile_us + steps * c.step_us[prod] * ((float)full + last);
-    if (k == 0 || us < best_us) { best = (Tile)k; best_us = us; }
-  }
-  return best;
-}
-
 template <bool A_T, bool B_T>
 int launch_gemm(const GemmParams& p, hipStream_t st) {
   hipError_t e;
   const int cus = cu_count(&e);
   if (e != hipSuccess) return hip_fail(e);
-  switch (pick_tile(p.I, p.J, p.R, A_T, B_T, cus)) {
+  switch (pick_tile(p.I, p.J, p.R, A_T ? 2 : B_T ? 1 : 0, cus)) {
     case kRing256x128: return launch_ring<A_T, B_T, Ring256x128>(p, st);
     case kRing128x256: return launch_ring<A_T, B_T, Ring128x256>(p, st);
     case kRing128: return launch_ring<A_T, B_T, Ring128>(p, st);

@@ -15,7 +15,9 @@ extern "C" int one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int cau
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
+extern "C" int tile(int64_t I, int64_t J, int64_t R, int product) { return ie::pick_tile(I, J, R, product, 256); }
 """
+TILES = [(256, 256), (256, 128), (128, 256), (128, 128), (64, 128), (64, 64), (32, 32)]   # enum Tile
 
 
 @pytest.fixture(scope="module")
@@ -71,3 +73,26 @@ def test_bwd64_launches(rules, B, S, Hq, Hkv, causal, docs, one):
 def test_dq128_form(rules, S, H, wide, causal, packed, on16):
     i64 = ctypes.c_int64
     assert bool(rules.dq16(i64(-(-S // 128) * H), i64(-(-S // 256) * H), wide, causal, packed)) == on16
+
+
+def linear_tile(rules, product, M, N, K):
+    """Output tile of a product of y = x w^T (x [M,K], w [N,K]) on 256 CUs."""
+    I, J, R = {"fwd": (M, N, K), "dx": (M, K, N), "dw": (N, K, M)}[product]
+    i64 = ctypes.c_int64
+    return TILES[rules.tile(i64(I), i64(J), i64(R), ["fwd", "dx", "dw"].index(product))]
+
+
+@pytest.mark.parametrize("product,M,N,K,tile", [
+    # weight gradients over a few tokens: the outputs' way to memory, for which larger tiles do better
+    ("dw", 128, 8192, 8192, (256, 256)),
+    ("dw", 64, 4096, 4096, (256, 256)),
+    ("dw", 192, 30720, 5120, (256, 256)),
+    ("dw", 8192, 9600, 3200, (256, 256)),
+    ("dw", 512, 2048, 2048, (128, 128)),
+    ("dx", 4096, 17152, 3200, (256, 256)),
+    ("fwd", 8192, 12288, 4096, (256, 256)),
+    ("fwd", 200, 4096, 4096, (64, 64)),
+    ("fwd", 1, 4096, 11008, (32, 32)),
+])
+def test_linear_tile(rules, product, M, N, K, tile):
+    assert linear_tile(rules, product, M, N, K) == tile
