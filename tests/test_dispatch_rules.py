@@ -96,3 +96,14 @@ def linear_tile(rules, product, M, N, K):
 ])
 def test_linear_tile(rules, product, M, N, K, tile):
     assert linear_tile(rules, product, M, N, K) == tile
+
+
+def test_every_linear_route_has_a_gpu_case(rules):
+    """The cases of test_gpu_linear_tiles take the tiles they name, and together every kernel of every product."""
+    from test_gpu_linear_tiles import BACKWARD, FORWARD
+    cases = [("fwd", M, N, K, t) for M, N, K, t in FORWARD]
+    cases += [(p, M, N, K, t) for M, N, K, dx, dw in BACKWARD for p, t in (("dx", dx), ("dw", dw)) if t]
+    for p, M, N, K, t in cases:
+        assert linear_tile(rules, p, M, N, K) == t, (p, M, N, K)
+    routes = {(p, t) for p in ("fwd", "dx", "dw") for t in TILES} - {("dx", (32, 32)), ("dw", (32, 32))}
+    assert {(p, t) for p, *_, t in cases} == routes
