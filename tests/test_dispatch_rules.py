@@ -107,3 +107,20 @@ def test_every_linear_route_has_a_gpu_case(rules):
         assert linear_tile(rules, p, M, N, K) == t, (p, M, N, K)
     routes = {(p, t) for p in ("fwd", "dx", "dw") for t in TILES} - {("dx", (32, 32)), ("dw", (32, 32))}
     assert {(p, t) for p, *_, t in cases} == routes
+
+
+def test_dq_full_chip_cases_take_the_16x16x32_form(rules):
+    from test_gpu_dq_full_chip import CASES
+    i64 = ctypes.c_int64
+    for name, (B, S, Hq, Hkv, causal, lens) in CASES.items():
+        packed = lens is not None
+        items = [-(-S // rows) * B * Hq for rows in (128, 256)]
+        assert not packed or sum(lens) == S
+        for wide in (0, 1):
+            assert rules.dq16(i64(items[0]), i64(items[1]), wide, int(causal), int(packed)), (name, wide)
+
+
+def test_fused_sequence_parallel_cases_take_both_forms(rules):
+    i64 = ctypes.c_int64
+    assert rules.one_launch(i64(1), i64(2048), i64(24), i64(24), 1, i64(0)) and 16 * 48 > 512
+    assert not rules.one_launch(i64(1), i64(512), i64(80), i64(80), 1, i64(0))

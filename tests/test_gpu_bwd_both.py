@@ -1,6 +1,7 @@
 """dK/dV and dQ in one launch (attn_bwd_both_kernel) against the same pass in two: the same item bodies, so the same
-bits.  The one-launch form is taken where all items of both kinds are resident at once, and always at head dimension 64;
-a call that names the phases one by one takes the kernels of their own."""
+bits.  The one-launch form is taken where all items of both kinds are resident at once, and at head dimension 64 also
+where bwd64_in_one_launch (csrc/dispatch.hpp) says so; a call that names the phases one by one takes the kernels of
+their own."""
 import pytest
 
 from parity_util import randn_bf16
@@ -13,6 +14,8 @@ pytestmark = pytest.mark.gpu
     (1, 4096, 8, 8, 64, True, None),      # 512 items: the last size with one per workgroup
     (1, 4097, 8, 8, 64, True, None),      # one tile more per head: work queues, one-row tiles
     (4, 2000, 16, 16, 64, False, None),   # work queues, several items per workgroup
+    (1, 700, 48, 48, 64, True, None),     # 576 short items: two launches either way
+    (1, 8192, 4, 1, 64, False, None),     # fewer dK/dV items than CUs
     (1, 1, 3, 1, 64, True, None),
     (1, 1000, 4, 2, 64, True, [300, 0, 1, 699]),
     (1, 2047, 8, 8, 128, True, None),     # 256 items

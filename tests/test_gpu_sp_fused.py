@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
     (2, 512, 8, 4, 128, 2, True),      # batch entries interleaved with peers, GQA widths
     (1, 1024, 4, 4, 128, 4, False),    # not causal
     (2, 256, 4, 2, 64, 2, True),       # head dimension 64 (the other forward kernel)
+    (1, 1024, 48, 48, 64, 2, True),    # head dimension 64, 768 backward items: the shared launch with its queues
+    (1, 256, 160, 160, 64, 2, True),   # 640 short ones: a launch each for dK/dV and dQ
     (1, 2048, 16, 16, 128, 8, True),   # two local heads, eight peers
     (1, 8192, 32, 32, 128, 4, True),   # the paper's own plan for 7B at 32K (s_sp = 4: 8 heads per GPU), full size
 ])
