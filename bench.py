@@ -209,11 +209,11 @@ def linear_bench(iters, with_cpu, profiled_with):
     big = {"M": M2, "N": N2, "K": K2, "tflops": [flop2 / t / 1e9 for t in ours], "library_tflops": [flop2 / t / 1e9 for t in lib]}
     del x, w, dy, y, dx, dw
     achieved = flop_total / ms_total / 1e9
-    out = {"workload": "7b_linear_m8192", "M": M, "dtype": "bf16", "kernel": "linear_gemm_kernel",
+    out = {"workload": "7b_linear_m8192", "M": M, "dtype": "bf16", "kernel": "linear_pp_kernel",
            "order": ["fwd", "bwd_input", "bwd_weight"], "per_module": per, "ms_per_layer": ms_total,
            "library_ms_per_layer": lib_ms_total, "gate_up_65b_m16384": big,
            "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                        "frac": achieved / PEAK_BF16_TFLOPS, "traffic": measured_traffic(profiled_with, "linear_gemm_kernel"),
+                        "frac": achieved / PEAK_BF16_TFLOPS, "traffic": measured_traffic(profiled_with, "linear_pp_kernel"),
                         "note": "all twelve products of one layer: FLOP / time; traffic: HBM bytes per launch, mean over the three instantiations' means"}}
     if with_cpu:
         import numpy as np
