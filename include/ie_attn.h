@@ -184,9 +184,11 @@ int ie_attn_bwd_static(const void* q, const void* k, const void* v, const void* 
  * work per item, which wins when a launch has few items per CU or the sequence is short).  rows = 0
  * (the initial setting) lets every call choose from its shape: dense input of up to 4096 tokens, or
  * up to 8192 tokens with fewer than two 256-row items per CU, takes the 128-row forward; dense input
- * of 8192 tokens or more with fewer than two 256-row items per CU takes the 128-row dQ.  rows = 128
- * or 256 fixes the choice for all later calls of the process (measurements, tests); the results of
- * the two differ only in rounding order.  Returns the previous setting, or IE_ERR_UNSUPPORTED for any
+ * of 8192 tokens or more with fewer than two 256-row items per CU takes the 128-row dQ.  A backward
+ * call whose dK/dV and dQ items of 128 rows all fit on the chip at once, dense or packed, runs them in
+ * one launch, with 128-row dQ items, unless rows = 256.  rows = 128 or 256 fixes the choice for all
+ * later calls of the process (measurements, tests); the results of the two differ only in rounding
+ * order.  Returns the previous setting, or IE_ERR_UNSUPPORTED for any
  * other value.  Head dimension 64 always works on 128-row items.  (Sec. 4.2: self-atten is profiled
  * over shapes from 4K x 40 heads to 256K x 1 head per GPU.)
  */

@@ -275,12 +275,13 @@ __device__ __forceinline__ void dq_item(const AttnParams& p, char* smem, int* sc
   for (int db = 0; db < NDB; ++db) store_block32_bf16(drow + 32 * db, acc[db], p.scale, h, wave_row_min + n < rows_rel_end);
 }
 // The same item on v_mfma_f32_16x16x32_bf16, for head dimension 128: half the accumulator traffic per product of the
-// 32x32x16 form, which the power limit turns into time (10.39 -> 9.79 ms at 32K x 32 heads, 380 -> 364 us at 2 x 4K x 32;
-// 227 instead of 253 registers).  A 32 x 32 block of scores is 2 x 2 MFMA blocks, so a lane
-// has TWO query columns (16 qb + lane % 16) and, with g = lane / 16, the keys 16 kb + key4(g) + 0..3 of each; the
-// eight of both key blocks are one B operand of the dQ product.  key4 swaps the middle two groups (0, 8, 4, 12): the
-// transpose loads of two neighbouring lane groups then address rows 0..3 and 8..11, which the tile's swizzle keeps on
-// different banks (rows 0..3 and 4..7 collide).
+// 32x32x16 form, which the power limit turns into time (10.39 -> 9.79 ms at 32K x 32 heads, 343 -> 324 us at 4K x 32
+// bidirectional; 227 instead of 253 registers; dq128_on_16x16x32 in dispatch.hpp has the sizes where it loses).  A 32 x 32
+// block of scores is 2 x 2 MFMA blocks, so a lane has TWO query columns (16 qb + lane % 16) and, with g = lane / 16, the
+// keys 16 kb + key4(g) + 0..3 of each; the eight of both key blocks are one B operand of the dQ product.  key4 swaps the
+// middle two groups (0, 8, 4, 12): the transpose loads of two neighbouring lane groups then address rows 0..3 and 8..11,
+// which the tile's swizzle keeps on different banks (rows 0..3 and 4..7 collide).  By the counters 40 % of the kernel's LDS
+// cycles are bank conflicts all the same (none in the 32x32x16 form), with LDS busy 54 % of the time.
 template <int D, int WAVES>
 __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int* scratch, const int item) {
   constexpr int BM = DqCfg<WAVES>::BM, BN = DqCfg<WAVES>::BN, THREADS = DqCfg<WAVES>::THREADS;
@@ -338,7 +339,7 @@ __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int*
   };
   load_kv(lds0, 0, nk, std::false_type{});
 
-  // This lane's query row, as a 32-bit position inside the document (rows past the tile's end repeat its last row and
+  // This lane's two query rows, as 32-bit positions inside the document (rows past the tile's end repeat its last row and
   // are not written).
   const int rows_rel_end = (int)(q_end - k_begin);
   int row_rel[2];
@@ -368,8 +369,8 @@ __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int*
 #pragma unroll
   for (int db = 0; db < NDB; ++db) tr_ptr[db] = smem + tr_off<D>(lane, key4, 16 * db);
 
-  // The dP chain starts from -delta (the same value in all 16 rows: one query per lane), so it
-  // delivers dP - delta.
+  // The dP chains start from -delta (the same value in a block's four rows: one query column per block), so they
+  // deliver dP - delta.
   const float c = p.scale_log2;
   f32x4 acc[NDB][2];
 #pragma unroll

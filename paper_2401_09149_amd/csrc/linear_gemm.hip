@@ -187,9 +187,9 @@ __device__ __forceinline__ GemmTile decode_gemm_tile(const GemmParams& p, int l)
 // instead of behind the reads, 32-deep steps in a ring of four or five, and one turn of 64 per step were 3-4 %, 15-20 %,
 // 10-15 % and 40 % slower: every turn pays an LDS latency, and a copy that waits for the memory pipeline in a cluster
 // holds the MFMAs behind it.)
-// 8192 tokens, the twelve products of hidden 4096 / MLP 11008: 0.50-0.55 of the 2.5 PFLOP/s peak (forward products
-// 660 -> 602, 226 -> 208, 1178 -> 1102, 588 -> 528 us against eight waves in step at one barrier per 64-deep step;
-// dx 653 -> 607, 637 -> 588; dw 677 -> 658, 625 -> 607).
+// 8192 tokens, the twelve products of hidden 4096 / MLP 11008: 0.47-0.62 of the 2.5 PFLOP/s peak, the matrix pipeline busy
+// 83 % (forward), 76 % (dx) and 64 % (dw) of the time (eight waves in step at one barrier per 64-deep step: QKV 664, 649,
+// 688 us; these turns: 571, 578, 668; with the copies' offsets worked out once per tile: 543, 563, 633).
 constexpr int TI = 256, TJ = 256;
 constexpr int P_HALF_BYTES = 128 * 128;              // half an operand tile: 128 output indices x 64 deep
 constexpr int P_STAGE_BYTES = 4 * P_HALF_BYTES;      // A0 | A1 | B0 | B1
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_pp_kernel(GemmParams p)
 // with NS - 1 of them in flight, and WK groups of waves that each take every WK-th 16-deep slice of a step for the
 // whole tile (their partial sums are added through LDS at the tile's end, in fp32 and in a fixed order).
 // Bound: at one step in flight a step took 1.25 us however little it did, the latency of a cold copy, so the ring holds
-// as many bytes in flight as fit (80-112 KiB); what is left is HBM for a handful of tokens (one token, 22016 x 4096:
+// as many bytes in flight as fit (80-120 KiB); what is left is HBM for a handful of tokens (one token, 22016 x 4096:
 // 34 us = 5.3 TB/s) and LDS bandwidth and the barrier per step for the wider tiles.
 template <int CI_, int CJ_, int WI_, int WJ_, int WK_, int SUB_, int NS_>
 struct RingCfg {
