@@ -96,7 +96,7 @@ struct DqCfg {
   template <int D> static constexpr int smem_bytes() { return 2 * 2 * BN * D * 2; }   // two stages of a K and a V tile
 };
 template <int D, int WAVES>
-__device__ __forceinline__ void dq_item(const AttnParams& p, char* smem, int* scratch, const int item) {
+__device__ __forceinline__ unsigned int dq_item(const AttnParams& p, char* smem, int* scratch, const int item, QueueState* queue) {
   constexpr int BM = DqCfg<WAVES>::BM, BN = DqCfg<WAVES>::BN, THREADS = DqCfg<WAVES>::THREADS;
   constexpr int NKS = D / 16, NDB = D / 32;
   constexpr int TILE_BYTES = BN * D * 2;
@@ -110,7 +110,7 @@ __device__ __forceinline__ void dq_item(const AttnParams& p, char* smem, int* sc
   const int n = lane & 31, h = lane >> 5, grp = lane >> 4;
 
   TileCoord tc = decode_tile<BM, THREADS>(p, p.Hq, true, scratch, item, tid);
-  if (!tc.valid) return;
+  if (!tc.valid) return kNotClaimed;
   // (the tile coordinates may have come through LDS: wave-uniform values are moved to scalar registers explicitly)
   const int g = tc.h / (p.Hq / p.Hkv);
   const int64_t q0 = uniform(tc.t0), doc_end = uniform(tc.doc_end);
@@ -267,12 +267,14 @@ __device__ __forceinline__ void dq_item(const AttnParams& p, char* smem, int* sc
 
   // (the row is formed again from its 32-bit position: a 64-bit row index kept alive through the main loop is two
   // registers this kernel does not have)
+  const unsigned int claimed = queue ? queue_claim(queue) : kNotClaimed;
   int row_rel_late = row_rel;
   asm volatile("" : "+v"(row_rel_late));   // (opaque: otherwise the address is formed in the prologue all the same)
   __bf16* drow = reinterpret_cast<__bf16*>(reinterpret_cast<char*>(p.dq + tc.h * D) + tc.b * p.q_bstride +
                                            tok_off(p, k_begin + row_rel_late, q_stride * 2));
 #pragma unroll
   for (int db = 0; db < NDB; ++db) store_block32_bf16(drow + 32 * db, acc[db], p.scale, h, wave_row_min + n < rows_rel_end);
+  return claimed;
 }
 // The same item on v_mfma_f32_16x16x32_bf16, for head dimension 128: half the accumulator traffic per product of the
 // 32x32x16 form, which the power limit turns into time (10.39 -> 9.79 ms at 32K x 32 heads, 343 -> 324 us at 4K x 32
@@ -283,7 +285,7 @@ __device__ __forceinline__ void dq_item(const AttnParams& p, char* smem, int* sc
 // which the tile's swizzle keeps on different banks (rows 0..3 and 4..7 collide).  By the counters 40 % of the kernel's LDS
 // cycles are bank conflicts all the same (none in the 32x32x16 form), with LDS busy 54 % of the time.
 template <int D, int WAVES>
-__device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int* scratch, const int item) {
+__device__ __forceinline__ unsigned int dq_item_16(const AttnParams& p, char* smem, int* scratch, const int item, QueueState* queue) {
   constexpr int BM = DqCfg<WAVES>::BM, BN = DqCfg<WAVES>::BN, THREADS = DqCfg<WAVES>::THREADS;
   constexpr int NKS = D / 32, NDB = D / 16;   // 32-deep slices, 16-wide blocks of the head dimension
   constexpr int TILE_BYTES = BN * D * 2;
@@ -298,7 +300,7 @@ __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int*
   const int key4 = 4 * (((g4 & 1) << 1) | (g4 >> 1));
 
   TileCoord tc = decode_tile<BM, THREADS>(p, p.Hq, true, scratch, item, tid);
-  if (!tc.valid) return;
+  if (!tc.valid) return kNotClaimed;
   // (the tile coordinates may have come through LDS: wave-uniform values are moved to scalar registers explicitly)
   const int g = tc.h / (p.Hq / p.Hkv);
   const int64_t q0 = uniform(tc.t0), doc_end = uniform(tc.doc_end);
@@ -475,6 +477,7 @@ __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int*
 
   // (the rows are formed again from their 32-bit positions: 64-bit row indices kept alive through the main loop are
   // registers this kernel does not have)
+  const unsigned int claimed = queue ? queue_claim(queue) : kNotClaimed;
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     int row_rel_late = row_rel[qb];
@@ -485,6 +488,7 @@ __device__ __forceinline__ void dq_item_16(const AttnParams& p, char* smem, int*
 #pragma unroll
     for (int db = 0; db < NDB; db += 2) store_pair16_bf16(drow + 16 * db, acc[db][qb], acc[db + 1][qb], p.scale, g4, ok);
   }
+  return claimed;
 }
 // F16: the 16x16x32 form (dq128_on_16x16x32 in dispatch.hpp chooses).
 template <int D, int WAVES, bool F16>
@@ -494,13 +498,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(Attn
 
   __shared__ QueueState s_work;
   queue_init(p, &s_work);
-  const uint32_t xcc = xcc_id();
-  int skip = 0;
+  unsigned int claimed = kNotClaimed;
   for (;;) {   // persistent: one item (batch, head, query tile) per iteration (tile_queue.hpp)
-    const int item = next_work(p, &s_work, xcc, skip);
+    const int item = next_work(&s_work, claimed);
     if (item < 0) break;
-    if constexpr (F16) dq_item_16<D, WAVES>(p, smem, scratch, item);
-    else dq_item<D, WAVES>(p, smem, scratch, item);
+    if constexpr (F16) claimed = dq_item_16<D, WAVES>(p, smem, scratch, item, &s_work);
+    else claimed = dq_item<D, WAVES>(p, smem, scratch, item, &s_work);
   }
 }
 
@@ -525,7 +528,7 @@ struct DkdvCfg {
 // CHUNKED: q, k, v, dk, dv are chunks of a sequence-parallel exchange buffer (tok_off in attn_common.hpp) instead of
 // contiguous tensors: a separate instantiation, so that the contiguous case keeps its simpler address arithmetic.
 template <int D, bool STORE_DS, bool CHUNKED>
-__device__ __forceinline__ void dkdv_item(const AttnParams& p, char* smem, int* scratch, const int item) {
+__device__ __forceinline__ unsigned int dkdv_item(const AttnParams& p, char* smem, int* scratch, const int item, QueueState* queue) {
   static_assert(!(STORE_DS && CHUNKED), "the stored-dS path takes contiguous tensors");
   using C = DkdvCfg<D>;
   constexpr int BK = C::BK, BQ = C::BQ, NB = C::NB;
@@ -540,7 +543,7 @@ __device__ __forceinline__ void dkdv_item(const AttnParams& p, char* smem, int* 
   const int n = lane & 31, h = lane >> 5, grp = lane >> 4;
 
   TileCoord tc = decode_tile<BK>(p, p.Hkv, false, scratch, item, tid);
-  if (!tc.valid) return;
+  if (!tc.valid) return kNotClaimed;
   // The tile coordinates may have come through LDS (packed input): they are the same in every lane, and are moved
   // to scalar registers here so that everything derived from them between two steps (the description of the next
   // query tile: three 64-bit addresses) is scalar arithmetic instead of vector multiplies and lane reads.
@@ -1022,6 +1025,7 @@ __device__ __forceinline__ void dkdv_item(const AttnParams& p, char* smem, int* 
   if (pending) flush_pending();
   mfma_result_fence();  // the last assembly MFMAs have retired before the accumulators are read
 
+  const unsigned int claimed = queue ? queue_claim(queue) : kNotClaimed;
   const int64_t key_st = key_ok ? key : tc.doc_end - 1;  // (address only formed for rows that exist)
   __bf16* dkrow = reinterpret_cast<__bf16*>(reinterpret_cast<char*>(p.dk) + kvhead + kv_row_off(key_st));
   __bf16* dvrow = reinterpret_cast<__bf16*>(reinterpret_cast<char*>(p.dv) + kvhead + kv_row_off(key_st));
@@ -1030,6 +1034,7 @@ __device__ __forceinline__ void dkdv_item(const AttnParams& p, char* smem, int* 
     store_block32_bf16(dkrow + 32 * db, dkacc[db], p.scale, h, key_ok);
     store_block32_bf16(dvrow + 32 * db, dvacc[db], 1.0f, h, key_ok);
   }
+  return claimed;
 }
 template <int D, bool STORE_DS, bool CHUNKED = false>
 __global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p) {
@@ -1038,12 +1043,11 @@ __global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p
 
   __shared__ QueueState s_work;
   queue_init(p, &s_work);
-  const uint32_t xcc = xcc_id();
-  int skip = 0;
+  unsigned int claimed = kNotClaimed;
   for (;;) {   // persistent: one item (batch, kv head, key block) per iteration (tile_queue.hpp)
-    const int item = next_work(p, &s_work, xcc, skip);
+    const int item = next_work(&s_work, claimed);
     if (item < 0) break;
-    dkdv_item<D, STORE_DS, CHUNKED>(p, smem, scratch, item);
+    claimed = dkdv_item<D, STORE_DS, CHUNKED>(p, smem, scratch, item, &s_work);
   }
 }
 
@@ -1061,24 +1065,23 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_bwd_both_kerne
   __shared__ int scratch[10];
   if constexpr (ONCE) {
     const int b = (int)blockIdx.x;
-    if (b < pkv.q_total) dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, b);
-    else dq_item<D, 4>(pq, smem, scratch, b - pkv.q_total);
+    if (b < pkv.q_total) dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, b, nullptr);
+    else dq_item<D, 4>(pq, smem, scratch, b - pkv.q_total, nullptr);
   } else {
     __shared__ QueueState s_kv, s_q;
     queue_init(pkv, &s_kv);
     queue_init(pq, &s_q);
-    const uint32_t xcc = xcc_id();
-    int skip = 0;
+    unsigned int claimed = kNotClaimed;
     for (;;) {
-      const int item = next_work(pkv, &s_kv, xcc, skip);
+      const int item = next_work(&s_kv, claimed);
       if (item < 0) break;
-      dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, item);
+      claimed = dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, item, &s_kv);
     }
-    skip = 0;
+    claimed = kNotClaimed;
     for (;;) {
-      const int item = next_work(pq, &s_q, xcc, skip);
+      const int item = next_work(&s_q, claimed);
       if (item < 0) break;
-      dq_item<D, 4>(pq, smem, scratch, item);
+      claimed = dq_item<D, 4>(pq, smem, scratch, item, &s_q);
     }
   }
 }
@@ -1107,11 +1110,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_from_ds_kernel(AttnPa
 
   __shared__ QueueState s_work;
   queue_init(p, &s_work);
-  const uint32_t xcc = xcc_id();
-  int skip = 0;
+  unsigned int claimed = kNotClaimed;
   for (;;) {   // persistent: one item (batch, head, pair of query tiles) per iteration (tile_queue.hpp)
-  const int item = next_work(p, &s_work, xcc, skip);
+  const int item = next_work(&s_work, claimed);
   if (item < 0) break;
+  claimed = kNotClaimed;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wv = tid >> 6;
@@ -1217,6 +1220,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bwd_dq_from_ds_kernel(AttnPa
   if (kt < nkt) step(kt, std::integral_constant<int, 0>{});
   if (kt + 1 < nkt) step(kt + 1, std::integral_constant<int, 1>{});
 
+  claimed = queue_claim(&s_work);
   // column 32 wv + n of a tile is its query 32 wv + 8 (e / 4) + 4 hh + e % 4 with hh = n / 16, e = n % 16
   const int e = n & 15;
   const int64_t row = q0 + 32 * wv + 8 * (e >> 2) + 4 * (n >> 4) + (e & 3);
@@ -1316,7 +1320,10 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     if (items >= ((int64_t)1 << 31)) return kErrShape;
     AttnParams a = p;
     a.tiles = (int32_t)tiles;
-    const QueueLaunch ql = tile_queue_prepare(a, p.ws_counters + kCountersDkdv, items, a.Hkv, per_cu, st, cleared_by_delta);
+    // (grouped heads in one list keep the order in which the workgroups arrive: dealt by index, dK/dV 32046 x 16, 8 per
+    // group, took 7.2 ms instead of 6.9, 12520 x 32, 8 per group, 2.62 instead of 2.48)
+    const bool deal = a.Hq == a.Hkv || p.B * a.Hkv % 8 == 0;
+    const QueueLaunch ql = tile_queue_prepare(a, p.ws_counters + kCountersDkdv, items, a.Hkv, per_cu, st, cleared_by_delta, deal);
     if (ql.err != hipSuccess) return hip_fail(ql.err);
     attn_bwd_dkdv_kernel<D, kStore, kChunked><<<dim3((unsigned)ql.grid), dim3(kThreads), smem, st>>>(a);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
@@ -1347,6 +1354,8 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
       const int64_t cap = (int64_t)cu_count(&e) * per_cu;
       if (e != hipSuccess) return hip_fail(e);
       grid = grid < cap ? grid : cap;
+      kv.q_dealt = (uint32_t)grid;
+      q.q_dealt = 0;   // (a workgroup starts on them when it is done with the others)
     }
     attn_bwd_both_kernel<D, kChunked, kOnce><<<dim3((unsigned)grid), dim3(kThreads), kBothSmem<D>, st>>>(kv, q);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);

@@ -46,6 +46,7 @@ struct AttnParams {
   float scale, scale_log2;  // scale_log2 = scale * log2(e)
   int32_t causal;
   int32_t tiles;            // tiles per head the grid was sized for (upper bound when packed)
+  uint32_t q_dealt;         // persistent launches: workgroups whose first item goes by their index (0: all items are claimed)
   int32_t q_heavy, q_per_xcd, q_total;  // persistent launches (tile_queue.hpp): tiles per head in a list's head-by-head part, items per XCD list (0: one list), items
   __bf16* ds;               // optional workspace: dS written by the dK/dV kernel for the dQ kernel (see ds_matrix_offset), or NULL
   // Where token t of batch entry b lives in q/dq (pitch Hq*D) and k/v/dk/dv (pitch Hkv*D), see tok_off():
@@ -450,7 +451,8 @@ struct TileCoord {
 // Tiles of `TS` tokens never straddle documents.  `w` is the item number a persistent workgroup
 // drew from its queue (tile_queue.hpp): item w belongs to the list of XCD w & 7 and is that
 // list's entry number w >> 3.  When B*H is a multiple of 8, list x holds the heads x, x+8, ... .
-// Its first part walks the heads one after the other, the heavier 5/8 of each head's tiles from
+// Its first part (empty where a workgroup gets two items at most, see tile_queue_prepare) walks the heads one after the
+// other, the heavier 5/8 of each head's tiles from
 // the heaviest down: the workgroups of an XCD then stream the SAME head's K/V (or Q/dO) through
 // its L2 nearly in lock-step, and each is fetched from HBM once per group of co-resident tiles.
 // Its last part holds the lighter 3/8 of the tiles of all its heads, interleaved by weight, so that

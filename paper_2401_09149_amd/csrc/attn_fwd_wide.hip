@@ -65,11 +65,11 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_wide_kernel(AttnParams p
 
   __shared__ QueueState s_work;
   queue_init(p, &s_work);
-  const uint32_t xcc = xcc_id();
-  int skip = 0;
+  unsigned int claimed = kNotClaimed;
   for (;;) {   // persistent: one item (batch, head, query tile) per iteration
-  const int item = next_work(p, &s_work, xcc, skip);
+  const int item = next_work(&s_work, claimed);
   if (item < 0) break;
+  claimed = kNotClaimed;
   // Everything below is derived from an opaque copy of the thread index, so that the compiler
   // recomputes the per-lane offsets for every item instead of hoisting them out of this loop and
   // keeping them in registers through the main loop, which has none to spare.
@@ -539,6 +539,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_wide_kernel(AttnParams p
     if (!barrier_first) end_of_tile();
   }
   mfma_result_fence();
+  claimed = queue_claim(&s_work);
 
   // Epilogue: normalise, write O (bf16) and LSE (natural log).
   auto store = [&](const f32x16 (&o)[NDB], const ColState& st, const int64_t row, const bool ok) __attribute__((always_inline)) {
