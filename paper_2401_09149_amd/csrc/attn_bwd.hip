@@ -1370,7 +1370,12 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     if ((rc = chunked ? both_fit(std::true_type{}, std::true_type{}, &per_cu) : both_fit(std::false_type{}, std::true_type{}, &per_cu))) return rc;
     const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs);
     const int64_t items = tiles * p.B * ((int64_t)p.Hq + p.Hkv), resident = (int64_t)cus * per_cu;
-    if (items <= resident && (D == 64 || tile_rows_setting.load(std::memory_order_relaxed) != 256)) {
+    bool once = items <= resident;
+    if constexpr (D == 128) {
+      if (tile_rows_setting.load(std::memory_order_relaxed) == 256) once = false;   // (its dQ items are 128 rows)
+      else if (!once && items < ((int64_t)1 << 31)) once = bwd128_in_one_launch(p.B, p.S, p.Hq, p.Hkv, p.causal != 0, p.num_docs, cus);
+    }
+    if (once) {
       return chunked ? both_phase(std::true_type{}, std::true_type{}, tiles)
                      : both_phase(std::false_type{}, std::true_type{}, tiles);
     }

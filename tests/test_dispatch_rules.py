@@ -12,6 +12,9 @@ SHIM = """
 extern "C" int one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
   return ie::bwd64_in_one_launch(B, S, Hq, Hkv, causal != 0, docs, 256, 512);
 }
+extern "C" int one_launch_128(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
+  return ie::bwd128_in_one_launch(B, S, Hq, Hkv, causal != 0, docs, 256);
+}
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
@@ -52,6 +55,26 @@ def rules(tmp_path_factory):
 def test_bwd64_launches(rules, B, S, Hq, Hkv, causal, docs, one):
     i64 = ctypes.c_int64
     assert bool(rules.one_launch(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))) == one
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,causal,docs,one", [
+    (1, 2048, 16, 16, 1, 0, True),     # a dK/dV item and a dQ item per CU
+    (1, 4096, 8, 8, 1, 0, True),
+    (1, 8192, 4, 4, 1, 0, True),
+    (1, 300, 128, 128, 1, 0, True),    # the GPU test's sizes (test_gpu_bwd_both.py)
+    (2, 200, 160, 40, 0, 0, True),
+    (1, 260, 150, 150, 1, 2, True),
+    (1, 3001, 32, 8, 1, 0, True),      # fewer dK/dV items than CUs, each of 4 heads
+    (1, 14426, 16, 2, 1, 0, True),
+    (1, 4096, 32, 32, 1, 0, False),
+    (2, 4096, 32, 32, 1, 0, False),
+    (1, 32768, 32, 32, 1, 0, False),
+    (2, 6144, 10, 10, 0, 0, False),
+    (1, 65536, 8, 8, 1, 20, False),
+])
+def test_bwd128_launches(rules, B, S, Hq, Hkv, causal, docs, one):
+    i64 = ctypes.c_int64
+    assert bool(rules.one_launch_128(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))) == one
 
 
 @pytest.mark.parametrize("S,H,wide,causal,packed,on16", [

@@ -1,10 +1,12 @@
 """dK/dV and dQ in one launch (attn_bwd_both_kernel) against the same pass in two: the same item bodies, so the same
-bits.  The one-launch form is taken where all items of both kinds are resident at once, and at head dimension 64 also
-where bwd64_in_one_launch (csrc/dispatch.hpp) says so; a call that names the phases one by one takes the kernels of
-their own."""
+bits.  The one-launch form is taken where all items of both kinds are resident at once, and also where
+bwd64_in_one_launch or bwd128_in_one_launch (csrc/dispatch.hpp) says so; a call that names the phases one by one takes the
+kernels of their own."""
+import numpy as np
 import pytest
+from oracle import attention as ora
 
-from parity_util import randn_bf16
+from parity_util import compare_all, randn_bf16, to64
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +45,31 @@ def test_one_launch_gives_the_bits_of_two(B, S, Hq, Hkv, D, causal, lens):
         torch.cuda.synchronize()
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,causal,lens", [
+    (1, 300, 128, 128, True, None),   # 384 items of each kind
+    (2, 200, 160, 40, False, None),   # 160 dK/dV items of four heads each, 640 of dQ
+    (1, 260, 150, 150, True, [1, 259]),
+])
+def test_more_items_than_cus_in_one_launch(B, S, Hq, Hkv, causal, lens):
+    """Head dimension 128, dealt out by the hardware: all kv heads hold the same data, so every group of heads has to show
+    the bits of the first, which is checked against the oracle."""
+    import torch
+    from paper_2401_09149_amd import binding
+    print(f"case B{B} S{S} Hq{Hq} Hkv{Hkv} {causal} {lens}", flush=True)
+    dev, D, g = "cuda:0", 128, Hq // Hkv
+    scale = D ** -0.5
+    q1, do1 = (randn_bf16((B, S, g, D), 800 + j) for j in range(2))
+    k1, v1 = (randn_bf16((B, S, 1, D), 802 + j) for j in range(2))
+    q, k, v, do = (t.to(dev).repeat(1, 1, Hkv, 1) for t in (q1, k1, v1, do1))
+    cu = None if lens is None else torch.tensor([0] + lens, dtype=torch.int32).cumsum(0).to(torch.int32).to(dev)
+    o, lse = binding.attn_fwd(q, k, v, scale, causal, cu)
+    got = [torch.full_like(t, float("nan")) for t in (q, k, v)]
+    binding.ie_attn_bwd(q, k, v, o, do, lse, *got, cu, scale, causal, binding.alloc_bwd_workspace(q, k, cu))
+    torch.cuda.synchronize()
+    first = [t[:, :, :n] for t, n in zip((o, *got), (g, g, 1, 1))]
+    for t, f in zip((o, *got), first):
+        assert torch.equal(t, f.repeat(1, 1, Hkv, 1))
+    ref = ora.attn_fwd_bwd(*(to64(t) for t in (q1, k1, v1, do1)), scale, causal, None if cu is None else np.asarray(cu.cpu()))
+    compare_all((first[0], lse[:, :g], *first[1:]), ref, f"S{S} Hq{Hq}")
