@@ -490,6 +490,221 @@ __device__ __forceinline__ unsigned int dq_item_16(const AttnParams& p, char* sm
   }
   return claimed;
 }
+// The same item for launches whose workgroups have a CU to themselves (the shared launch at head dimension 128, whose dK/dV
+// items take the whole register file): one wave per SIMD, so its MFMAs and everything else are interleaved instruction by
+// instruction (mfma_asm.hpp).  Per 32-key block b there are three chains, S(b) and dP(b) into one register block each and
+// dQ(b) into four accumulators; a phase runs S(b + 1), dP(b + 1) and dQ(b - 1) in turn, one MFMA of each at a time, and
+// between them the elementwise work of block b: 2 (fma, exp2, multiply) and a pack per three MFMAs.  Every LDS read lands in
+// the register its predecessor has just left: the K and V rows of block b + 2, the K^T fragments of block b.  K/V tiles of 64
+// keys in a ring of four stages: two are read, two are on their way, one barrier per tile.
+// Bound: a step of 128 keys takes 2.0 us (21 ns per MFMA) while a few CUs work and 2.8 us with all of them at the power
+// limit, 0.3 us of it copies (eight instructions per wave and tile; the dQ kernel's 256-row workgroups copy half as much per
+// product and take 2.4).  The compiler-scheduled item at one wave per SIMD took 4.1 us: backward 4096 x 8 144 -> 131 us,
+// 8192 x 4 262 -> 235, 8192 x 8 473 -> 433.
+template <int D>
+struct DqSeqCfg {
+  static constexpr int BM = 128, BN = 64, STAGES = 4;
+  static constexpr int TILE_BYTES = BN * D * 2, STAGE_BYTES = 2 * TILE_BYTES;   // K tile, then V tile
+  static constexpr int SMEM_BYTES = STAGES * STAGE_BYTES;
+};
+template <int D>
+__device__ __forceinline__ void dq_item_seq(const AttnParams& p, char* smem, int* scratch, const int item) {
+  using C = DqSeqCfg<D>;
+  constexpr int BM = C::BM, BN = C::BN, TILE_BYTES = C::TILE_BYTES, STAGE_BYTES = C::STAGE_BYTES, ROW_BYTES = D * 2;
+  constexpr int NKS = D / 16, NDB = D / 32;
+  static_assert(D == 128 && NKS == 2 * NDB, "one MFMA of each chain per slot");
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wv = tid >> 6;
+  const int n = lane & 31, h = lane >> 5, grp = lane >> 4;
+
+  TileCoord tc = decode_tile<BM>(p, p.Hq, true, scratch, item, tid);
+  if (!tc.valid) return;
+  const int g = tc.h / (p.Hq / p.Hkv);
+  const int64_t q0 = uniform(tc.t0), doc_end = uniform(tc.doc_end);
+  const int64_t q_end = (q0 + BM < doc_end) ? q0 + BM : doc_end;
+  const int64_t k_begin = uniform(tc.doc_begin);
+  const int64_t k_end = p.causal ? q_end : doc_end;
+  const int nk = (int)(k_end - k_begin);
+  const int nkt = (nk + BN - 1) / BN;
+
+  const int64_t q_stride = (int64_t)p.Hq * D;
+  const int64_t kv_pitch = (int64_t)p.Hkv * D * 2;
+  const int64_t qhead = ((int64_t)tc.b * p.S * p.Hq + tc.h) * D;   // for dout (always contiguous)
+  const char* kbase = uniform(reinterpret_cast<const char*>(p.k + g * D) + tc.b * p.kv_bstride);
+  const char* vbase = uniform(reinterpret_cast<const char*>(p.v + g * D) + tc.b * p.kv_bstride);
+  const uint32_t lds0 = lds_address(smem);
+  AsyncTile<D> ld;
+  ld.init(tid, kv_pitch);
+  // Tile T's copy: eight instructions per wave, all at once (any number of valid rows) or one by one (a whole tile).
+  constexpr int kPieces = 2 * AsyncTile<D>::NI;
+  static_assert(kPieces == NKS, "one piece per slot of a phase");
+  struct Copy { const char* k; const char* v; uint32_t lds; };
+  auto describe = [&](const int T) __attribute__((always_inline)) {
+    const int64_t off = tok_off(p, k_begin + (int64_t)T * BN, kv_pitch);
+    return Copy{kbase + off, vbase + off, lds0 + (uint32_t)(T % C::STAGES) * STAGE_BYTES};
+  };
+  auto copy_all = [&](const int T) __attribute__((always_inline)) {
+    const Copy c = describe(T);
+    ld.load(c.lds, c.k, nk - T * BN);
+    ld.load(c.lds + TILE_BYTES, c.v, nk - T * BN);
+  };
+  for (int T = 0; T < C::STAGES - 1 && T < nkt; ++T) copy_all(T);
+
+  const int rows_rel_end = (int)(q_end - k_begin);
+  const int row_rel_raw = (int)(q0 - k_begin) + wv * 32 + n;
+  const int row_rel = row_rel_raw < rows_rel_end ? row_rel_raw : rows_rel_end - 1;
+  const int64_t row = k_begin + row_rel;
+  bf16x8 qf[NKS], dof[NKS];   // live in AGPRs
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) {
+    qf[ks] = global_load_to_agpr(reinterpret_cast<const char*>(p.q + tc.h * D) + tc.b * p.q_bstride +
+                                 tok_off(p, row, q_stride * 2) + (ks * 16 + h * 8) * 2);
+    dof[ks] = global_load_to_agpr(p.dout + qhead + row * q_stride + ks * 16 + h * 8);
+  }
+  const int64_t stat = ((int64_t)tc.b * p.Hq + tc.h) * p.S + row;
+  const float nlse2 = p.lse2[stat];    // -lse * log2(e) of this lane's query
+  const float ndelta = p.delta[stat];  // -delta
+
+  const char* nat_ptr[NKS];  // row n of a tile, chunk 2ks + h (A operand: K or V rows)
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) nat_ptr[ks] = smem + tile_off<D>(n, 2 * ks + h);
+  const char* tr_ptr0[NDB];  // transpose loads on the K tile
+  const char* tr_ptr8[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) {
+    tr_ptr0[db] = smem + tr_off<D>(lane, 4 * (grp >> 1), 32 * db + 16 * (grp & 1));
+    tr_ptr8[db] = smem + tr_off<D>(lane, 8 + 4 * (grp >> 1), 32 * db + 16 * (grp & 1));
+  }
+  const float c = p.scale_log2;
+  f32x16 dp_init;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) dp_init[r] = ndelta;
+  f32x16 acc[NDB];   // live in AGPRs
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+
+  bf16x8 kf[NKS], vf[NKS];       // rows of the block whose scores come next
+  bf16x8 ktf[2][NDB];            // K^T fragments of the block whose dQ product comes next (zeros: there is none yet)
+  bf16x8 dsf[2];                 // its dS
+  f32x16 s[2], dp[2];            // by block parity
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) dsf[i][t] = (__bf16)0.f;
+    // (opaque: known to be zeros, they would be written in front of the MFMAs that read them, without the wait states)
+    asm volatile("" : "+v"(dsf[i]));
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) { ktf[i][db] = dsf[i]; asm volatile("" : "+v"(ktf[i][db])); }
+  }
+  agpr_loads_wait();   // Q, dO and the first tiles
+  consume(nlse2);
+  consume(ndelta);
+  __syncthreads();
+
+  // One phase: block `PAR` of the current tile, at LDS byte offset `cur`; `next`: the following tile's.
+  auto phase = [&](auto par_c, auto masked_c, auto last_c, const int cur, const int next, const bool copying, const Copy& cp,
+                   const int lim) __attribute__((always_inline)) {
+    constexpr int PAR = decltype(par_c)::value;
+    constexpr bool MASKED = decltype(masked_c)::value, LAST = decltype(last_c)::value;
+    constexpr bool HAS_S = !(LAST && PAR == 1);
+    constexpr int BLK = 32 * ROW_BYTES;
+    uint32_t dw[8];
+    float pr[16], d0, d1;
+    auto p_elem = [&](int e) __attribute__((always_inline)) {
+      if (MASKED) softmax_elem_masked(pr[e], s[PAR][e], c, nlse2, 8 * (e >> 2) + (e & 3), lim);
+      else softmax_elem<false>(pr[e], s[PAR][e], c, nlse2);
+    };
+    auto d_pair = [&](int w) __attribute__((always_inline)) {
+      mul_elem<false>(d0, pr[2 * w], dp[PAR][2 * w]);
+      mul_elem<false>(d1, pr[2 * w + 1], dp[PAR][2 * w + 1]);
+      pack_pair(dw[w], d0, d1);
+    };
+#pragma unroll
+    for (int m = 0; m < NKS; ++m) {
+      if (HAS_S) {
+        if (m == 0) mfma_first_b_agpr(s[PAR ^ 1], kf[0], qf[0]);
+        else mfma_next_b_agpr(s[PAR ^ 1], kf[m], qf[m]);
+      }
+      if (!LAST) kf[m] = lds_read8(nat_ptr[m] + next, PAR * BLK);
+      p_elem(2 * m);
+      asm_fence();
+      if (HAS_S) {
+        if (m == 0) mfma_first_cin_b_agpr(dp[PAR ^ 1], vf[0], dof[0], dp_init);
+        else mfma_next_b_agpr(dp[PAR ^ 1], vf[m], dof[m]);
+      }
+      if (!LAST) vf[m] = lds_read8(nat_ptr[m] + next, PAR * BLK + TILE_BYTES);
+      if (m > 0) d_pair(m - 1);
+      asm_fence();
+      mfma_acc_agpr(acc[m % NDB], ktf[m / NDB][m % NDB], dsf[m / NDB]);
+      {
+        const int off = PAR * BLK + 16 * (m / NDB) * ROW_BYTES;
+        ktf[m / NDB][m % NDB] = cat4(lds_read_tr4(tr_ptr0[m % NDB] + cur + off), lds_read_tr4(tr_ptr8[m % NDB] + cur + off));
+      }
+      p_elem(2 * m + 1);
+      if (PAR == 0 && copying) {
+        constexpr int NI = AsyncTile<D>::NI;
+        ld.load_full_piece(cp.lds + (m / NI) * TILE_BYTES, m / NI ? cp.v : cp.k, m % NI);
+      }
+      asm_fence();
+    }
+    asm volatile("s_nop 0");   // (element 15's exponential is the previous instruction but for copies)
+    d_pair(NKS - 1);
+    dsf[0] = frag_from_words(dw[0], dw[1], dw[2], dw[3]);
+    dsf[1] = frag_from_words(dw[4], dw[5], dw[6], dw[7]);
+    asm_fence();
+  };
+  auto tile = [&](const int T, auto masked_c, auto last_c) __attribute__((always_inline)) {
+    if (T > 0) {
+      // Tile T + 1 has landed (all but the eight copies of tile T + 2), and everyone has read what tile T + 3 replaces.
+      if (T + 2 < nkt) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+    const int T3 = T + C::STAGES - 1;
+    const bool spread = (T3 + 1) * BN <= nk;
+    Copy cp{};
+    if (spread) cp = describe(T3);
+    else if (T3 < nkt) copy_all(T3);
+    const int cur = (T % C::STAGES) * STAGE_BYTES, next = ((T + 1) % C::STAGES) * STAGE_BYTES;
+    const int lim = (p.causal ? row_rel : nk - 1) - T * BN - 4 * h;   // last visible key relative to the lane's first key
+    phase(std::integral_constant<int, 0>{}, masked_c, last_c, cur, next, spread, cp, lim);
+    phase(std::integral_constant<int, 1>{}, masked_c, last_c, cur, next, false, cp, lim - 32);
+  };
+
+  // S(0) and dP(0), with the rows of block 1 read behind them
+#pragma unroll
+  for (int m = 0; m < NKS; ++m) { kf[m] = lds_read8(nat_ptr[m], 0); vf[m] = lds_read8(nat_ptr[m], TILE_BYTES); }
+  asm_fence();
+#pragma unroll
+  for (int m = 0; m < NKS; ++m) {
+    if (m == 0) mfma_first_b_agpr(s[0], kf[0], qf[0]);
+    else mfma_next_b_agpr(s[0], kf[m], qf[m]);
+    kf[m] = lds_read8(nat_ptr[m], 32 * ROW_BYTES);
+    asm_fence();
+    if (m == 0) mfma_first_cin_b_agpr(dp[0], vf[0], dof[0], dp_init);
+    else mfma_next_b_agpr(dp[0], vf[m], dof[m]);
+    vf[m] = lds_read8(nat_ptr[m], 32 * ROW_BYTES + TILE_BYTES);
+    asm_fence();
+  }
+  mfma_result_fence();
+  int T = 0;
+  const int first_masked = p.causal ? (int)(q0 - k_begin) / BN : nk / BN;   // tiles before it are visible to all rows
+  for (; T < first_masked && T + 1 < nkt; ++T) tile(T, std::false_type{}, std::false_type{});
+  for (; T + 1 < nkt; ++T) tile(T, std::true_type{}, std::false_type{});
+  tile(T, std::true_type{}, std::true_type{});
+#pragma unroll
+  for (int m = 0; m < NKS; ++m) mfma_acc_agpr(acc[m % NDB], ktf[m / NDB][m % NDB], dsf[m / NDB]);
+  mfma_results_ready(acc);
+
+  int row_rel_late = row_rel;
+  asm volatile("" : "+v"(row_rel_late));   // (opaque: otherwise the address is formed in the prologue)
+  __bf16* drow = reinterpret_cast<__bf16*>(reinterpret_cast<char*>(p.dq + tc.h * D) + tc.b * p.q_bstride +
+                                           tok_off(p, k_begin + row_rel_late, q_stride * 2));
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) store_block32_bf16(drow + 32 * db, acc[db], p.scale, h, row_rel_raw < rows_rel_end);
+}
 // F16: the 16x16x32 form (dq128_on_16x16x32 in dispatch.hpp chooses).
 template <int D, int WAVES, bool F16>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void attn_bwd_dq_kernel(AttnParams p) {
@@ -1023,7 +1238,8 @@ __device__ __forceinline__ unsigned int dkdv_item(const AttnParams& p, char* sme
   }
   if (st < total) step_fn(st, std::integral_constant<int, 0>{});
   if (pending) flush_pending();
-  mfma_result_fence();  // the last assembly MFMAs have retired before the accumulators are read
+  mfma_results_ready(dkacc);  // the last assembly MFMAs have retired before the accumulators are read
+  mfma_results_ready(dvacc);
 
   const unsigned int claimed = queue ? queue_claim(queue) : kNotClaimed;
   const int64_t key_st = key_ok ? key : tc.doc_end - 1;  // (address only formed for rows that exist)
@@ -1057,8 +1273,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_bwd_dkdv_kernel(AttnParams p
 // by side: the launch is as long as the longer kind and there is one tail instead of two.  `ONCE`: every workgroup
 // does the one item of its index, dK/dV items first, without the queues' atomics; otherwise a workgroup takes dK/dV
 // items until there are none and then dQ items (128 rows each).  The whole backward pass: 4 x 2000 tokens x 16 heads
-// bidirectional, D = 64: 334 -> 312 us; 512 tokens x 4 heads, D = 128: 47.3 -> 23.5 us.  Launches of many rounds keep two
-// kernels (bwd64_in_one_launch in dispatch.hpp).
+// bidirectional, D = 64: 334 -> 312 us; 512 tokens x 4 heads, D = 128: 47.3 -> 22.4 us.  Launches of many rounds keep two
+// kernels (bwd64_in_one_launch and bwd128_in_one_launch in dispatch.hpp).
 template <int D, bool CHUNKED, bool ONCE>
 __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_bwd_both_kernel(AttnParams pkv, AttnParams pq) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1066,6 +1282,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_bwd_both_kerne
   if constexpr (ONCE) {
     const int b = (int)blockIdx.x;
     if (b < pkv.q_total) dkdv_item<D, false, CHUNKED>(pkv, smem, scratch, b, nullptr);
+    else if constexpr (D == 128) dq_item_seq<D>(pq, smem, scratch, b - pkv.q_total);
     else dq_item<D, 4>(pq, smem, scratch, b - pkv.q_total, nullptr);
   } else {
     __shared__ QueueState s_kv, s_q;
@@ -1238,7 +1455,9 @@ constexpr int kCountersDq = 0, kCountersDkdv = kQueueBytes / 4;
 constexpr int kDqWaves = 8;   // waves per workgroup of the recomputing dQ kernel at head dimension 128 (four: 2 % slower)
 
 template <int D>
-constexpr int kBothSmem = DkdvCfg<D>::SMEM_BYTES > DqCfg<4>::template smem_bytes<D>() ? DkdvCfg<D>::SMEM_BYTES : DqCfg<4>::template smem_bytes<D>();
+constexpr int kDqInBothSmem = D == 128 ? DqSeqCfg<D>::SMEM_BYTES : DqCfg<4>::template smem_bytes<D>();
+template <int D>
+constexpr int kBothSmem = DkdvCfg<D>::SMEM_BYTES > kDqInBothSmem<D> ? DkdvCfg<D>::SMEM_BYTES : kDqInBothSmem<D>;
 
 template <int D>
 static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {

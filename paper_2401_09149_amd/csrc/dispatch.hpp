@@ -37,19 +37,19 @@ inline bool bwd64_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, b
 
 // Backward pass at head dimension 128: all dK/dV and dQ items in one launch that the hardware deals out (the ONCE form of
 // attn_bwd_both_kernel), or a persistent kernel each?  The shared launch starts dQ items wherever dK/dV items have run
-// out, so it has one tail instead of two and no queues; its dQ items run one wave per SIMD and take 1.7 times as long per
-// pair of tiles as in their own kernel.  So it wins while a launch of either kind leaves CUs idle for long, and the choice
-// goes by the estimated times of both: the longest item or the work per CU, whichever is longer, with items priced per
-// 128 x 128 pair of tiles and per item.  Backward pass, two launches : one: 2048 x 16 138 : 87 us, 4096 x 8 232 : 142,
-// 8192 x 4 372 : 262, 3001 x 32, 4 per group, 406 : 311, 14426 x 16, 8 per group, 3653 : 3138; but 4096 x 32 476 : 498
-// (bidirectional 6144 x 10 x 2 1128 : 1294).
-// Fitted to 220 shapes, 128 to 16384 tokens: 0.15 % slower than the better form on average, 11 % at most (packed documents
-// of 125 to 7136 tokens, whose lengths the host does not know), and 7 % slower than two launches at most (497 x 25 x 4).
+// out, so it has one tail instead of two and no queues; its dQ items (dq_item_seq) take a quarter longer per pair of tiles
+// than those of the dQ kernel.  So it wins while a launch of either kind leaves CUs idle, and the choice goes by the
+// estimated times of both: the longest item or the work per CU, whichever is longer, with items priced per 128 x 128 pair
+// of tiles and per item.  Backward pass, two launches : one: 2048 x 16 140 : 83 us, 4096 x 8 231 : 131, 8192 x 4 377 : 235,
+// 8192 x 8 492 : 433, 3001 x 32, 4 per group, 400 : 328, 10180 x 8 x 4, 8 per group, bidirectional 6134 : 5102; but
+// 2 x 4096 x 32 890 : 920, 14443 x 37 5860 : 6222.
+// Fitted to 220 shapes, 128 to 16384 tokens: 0.2 % slower than the better form on average, 7 % at most, and 5 % slower than
+// two launches at most (3143 x 16, 2 per group, bidirectional); on 160 others the same.
 inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus) {
-  constexpr double kKvStep = 2.92, kKvItem = 18.8;     // dK/dV: us per pair of tiles, per item
-  constexpr double kQStep = 4.08;                      // dQ in the shared launch
-  constexpr double kQ2Step = 4.86, kQ2Item = 5.3;      // dQ in its own: two rows of tiles per item
-  constexpr double kLaunch = 9.8, kTail = 0.69;
+  constexpr double kKvStep = 2.87, kKvItem = 19.4;     // dK/dV: us per pair of tiles, per item
+  constexpr double kQStep = 3.23, kQItem = 0.34;       // dQ in the shared launch
+  constexpr double kQ2Step = 5.18, kQ2Item = 7.8;      // dQ in its own: two rows of tiles per item
+  constexpr double kLaunch = 2.5, kTail = 0.35;
   const double per_head = num_docs ? (double)(S / 128 + num_docs) : (double)((S + 127) / 128), group = (double)(Hq / Hkv);
   double doc = num_docs ? (double)S / 128 / (double)num_docs : per_head;   // tiles of a document (packed: on average)
   if (doc < 1) doc = 1;
@@ -61,14 +61,14 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
     return work / C > longest ? work / C : longest;
   };
   const double kv = doc * group * kKvStep + kKvItem, kv_work = nk * (mean * group * kKvStep + kKvItem);
-  const double q = doc * kQStep, q_work = nq * mean * kQStep;
+  const double q = doc * kQStep + kQItem, q_work = nq * (mean * kQStep + kQItem);
   double one = kv > q ? kv : q;
   if (nk + nq > C) {
     const double even = (kv_work + q_work) / C;
-    one = (even > kv ? even : kv) + kTail * (causal ? kQStep : q);
+    one = (even > kv ? even : kv) + kTail * (causal ? kQStep + kQItem : q);
   }
   const double two = span(nk, kv, kv_work) + span(nq / 2, doc * kQ2Step + kQ2Item, nq / 2 * (mean * kQ2Step + kQ2Item)) + kLaunch;
-  return one < two;
+  return one * (num_docs ? 1.06 : 1.02) < two;   // (documents differ: their longest items are longer than the mean's)
 }
 
 // Recomputing dQ kernel at head dimension 128: products as 16x16x32 MFMAs (dq_item_16) instead of 32x32x16 (dq_item)?

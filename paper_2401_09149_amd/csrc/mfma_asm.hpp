@@ -42,6 +42,13 @@ __device__ __forceinline__ void mfma_acc_agpr_after_moves(f32x16& acc, const bf1
 // Pins the compiler's own memory instructions (LDS reads) to this point of the sequence.
 __device__ __forceinline__ void asm_fence() { asm volatile("" ::: "memory"); }
 __device__ __forceinline__ void mfma_result_fence() { asm volatile("s_nop 15\n\ts_nop 3" ::: "memory"); }
+// The same in front of the compiler's own reads of these accumulators, which it might otherwise place ahead of the wait.
+template <int N>
+__device__ __forceinline__ void mfma_results_ready(f32x16 (&acc)[N]) {
+  mfma_result_fence();
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+a"(acc[i]));
+}
 
 // p0 = exp2(s0*c - l0), p1 = exp2(s1*c - l1), packed = {bf16(p0), bf16(p1)}
 template <bool LEAD>
@@ -79,6 +86,11 @@ template <bool LEAD>
 __device__ __forceinline__ void softmax_elem(float& p, float s, float c, float nl) {
   if (LEAD) asm volatile("s_nop 9");
   asm volatile("v_fma_f32 %0, %1, %2, %3\n\tv_exp_f32 %0, %0" : "=&v"(p) : "v"(s), "s"(c), "v"(nl));
+}
+// The same for element `key` of a lane's keys, of which those past `lim` are not visible (p = 0).
+__device__ __forceinline__ void softmax_elem_masked(float& p, float s, float c, float nl, int key, int lim) {
+  asm volatile("v_fma_f32 %0, %1, %2, %3\n\tv_cmp_gt_i32 vcc, %4, %5\n\tv_cndmask_b32 %0, %0, %6, vcc\n\tv_exp_f32 %0, %0"
+               : "=&v"(p) : "v"(s), "s"(c), "v"(nl), "s"(key), "v"(lim), "v"(-__builtin_inff()) : "vcc");
 }
 // d = p * dp  (the dP chain started from -delta)
 template <bool LEAD>
