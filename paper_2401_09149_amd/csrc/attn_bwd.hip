@@ -1087,10 +1087,14 @@ __device__ __forceinline__ unsigned int dkdv_item(const AttnParams& p, char* sme
     pending = true;
   };
 
-  // Generic tile (diagonal, document end, D = 64): compiler-scheduled, with masks.
+  // Generic tile (diagonal, document end, D = 64): compiler-scheduled, with masks where the tile needs one.  At head
+  // dimension 64, where it is the only tile, the masks (four VALU instructions per score) stand behind a branch, and the
+  // delta is the dP chain's C operand: 150 -> 95 VALU instructions per block of 16 MFMAs, dK/dV 4 x 8192 x 16 bidirectional
+  // 2332 -> 1927 us, 8192 x 16 331 -> 273.  (A body of its own for unmasked tiles spills; MFMAs left to the compiler copy the
+  // K and V fragments out of the AGPRs in front of each.)  Bound: VALU and the clock at the power limit, 1.8 GHz.
   // kPin keeps LDS reads from crossing the phase boundaries but lets ALU and MFMA instructions move.
   constexpr int kPin = 0x1 | 0x2 | 0x4 | 0x8 | 0x400;
-  auto generic_tile = [&](const StagePtrs& sp_, const int i0) __attribute__((always_inline)) {
+  auto generic_tile = [&](const StagePtrs& sp_, const int i0, const bool masked) __attribute__((always_inline)) {
     if (pending) {
       flush_pending();
       mfma_result_fence();  // the compiler's own instructions may touch dkacc next
@@ -1116,7 +1120,22 @@ __device__ __forceinline__ unsigned int dkdv_item(const AttnParams& p, char* sme
           dotf[sblk][db] = cat4(lds_read_tr4(sp_.tr0[db] + off), lds_read_tr4(sp_.tr8[db] + off));
         }
       __builtin_amdgcn_sched_barrier(kPin);
-      f32x16 dp = mfma_chain_b_in_agpr<NKS>(don, vf);
+      // row statistics (-lse*log2e, -delta) of the block's 16 rows held by this lane; at head dimension 64 -delta is the C
+      // operand of the dP chain, as in the hand-sequenced tile
+      f32x4 l4[4], d4[4];
+      f32x16 dp;
+      if constexpr (D == 64) {
+        f32x16 nd;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x4 t = *reinterpret_cast<const f32x4*>(sp_.stat + (BQ + 32 * rb + 8 * q4) * 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) nd[4 * q4 + e] = t[e];
+        }
+        dp = mfma_chain_cin_b_in_agpr(don, vf, nd);
+      } else {
+        dp = mfma_chain_b_in_agpr<NKS>(don, vf);
+      }
       bf16x8 qtg[2][NDB];
 #pragma unroll
       for (int sblk = 0; sblk < 2; ++sblk)
@@ -1125,15 +1144,13 @@ __device__ __forceinline__ unsigned int dkdv_item(const AttnParams& p, char* sme
           const int off = blk + 16 * sblk * ROW_BYTES;
           qtg[sblk][db] = cat4(lds_read_tr4(sp_.tr0[db] + off), lds_read_tr4(sp_.tr8[db] + off));
         }
-      // row statistics (-lse*log2e, -delta) of the block's 16 rows held by this lane
-      f32x4 l4[4], d4[4];
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         l4[q4] = *reinterpret_cast<const f32x4*>(sp_.stat + (32 * rb + 8 * q4) * 4);
-        d4[q4] = *reinterpret_cast<const f32x4*>(sp_.stat + (BQ + 32 * rb + 8 * q4) * 4);
+        if (D != 64) d4[q4] = *reinterpret_cast<const f32x4*>(sp_.stat + (BQ + 32 * rb + 8 * q4) * 4);
       }
       __builtin_amdgcn_sched_barrier(kPin);
-      {
+      if (D == 128 || masked) {
         const int lim_c = p.causal ? key_rel - i0 - 32 * rb - 4 * h : -(1 << 30);  // rows below this see no key of the lane
         const int lim_e = nq - i0 - 32 * rb - 4 * h;                                // rows from here on do not exist
 #pragma unroll
@@ -1167,7 +1184,8 @@ __device__ __forceinline__ unsigned int dkdv_item(const AttnParams& p, char* sme
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int r = 8 * sblk + 2 * t;
-          dd[t] = pack_bf16(pr[r] * (dp[r] + d4[r >> 2][r & 3]), pr[r + 1] * (dp[r + 1] + d4[r >> 2][(r & 3) + 1]));
+          if constexpr (D == 64) dd[t] = pack_bf16(pr[r] * dp[r], pr[r + 1] * dp[r + 1]);
+          else dd[t] = pack_bf16(pr[r] * (dp[r] + d4[r >> 2][r & 3]), pr[r + 1] * (dp[r + 1] + d4[r >> 2][(r & 3) + 1]));
         }
         dsf[sblk] = cat_pairs(dd[0], dd[1], dd[2], dd[3]);
       }
@@ -1205,14 +1223,14 @@ __device__ __forceinline__ unsigned int dkdv_item(const AttnParams& p, char* sme
     const bool next_full = has_next && nq - next_tile * BQ >= BQ;
     const int i0 = tile_idx * BQ;
     // Mask when a key of this wave can exceed a row of the tile (causal) or rows run past the document.
-    const bool need_mask = (p.causal && wv * 32 + 31 > i0) || (i0 + BQ > nq);
+    const bool need_mask = (p.causal && (D == 64 ? wave_u : wv) * 32 + 31 > i0) || (i0 + BQ > nq);
     const bool fast = D == 128 && !need_mask;
     if (fast && next_full) {
       fast_tile(sp[slot], make_next, std::true_type{});
     } else {
       if (has_next) copy_all(make_next());
       if (fast) fast_tile(sp[slot], make_next, std::false_type{});
-      else generic_tile(sp[slot], i0);
+      else generic_tile(sp[slot], i0, need_mask);
     }
     // The next tile's copies have landed; vector memory operations complete in issue order, and after a
     // hand-sequenced tile that copied piece by piece the six youngest are the dS stores of its last three

@@ -124,6 +124,20 @@ __device__ __forceinline__ f32x16 mfma_chain_b_in_agpr(const bf16x8 (&a)[NKS], c
   return acc;
 }
 
+// The same for head dimension 64 with a C operand: acc = cin + sum_ks A[ks] * B[ks].
+__device__ __forceinline__ f32x16 mfma_chain_cin_b_in_agpr(const bf16x8 (&a)[4], const bf16x8 (&b)[4], const f32x16& cin) {
+  f32x16 acc;
+  asm volatile(
+      "v_mfma_f32_32x32x16_bf16 %0, %1, %5, %9\n\t"
+      "v_mfma_f32_32x32x16_bf16 %0, %2, %6, %0\n\t"
+      "v_mfma_f32_32x32x16_bf16 %0, %3, %7, %0\n\t"
+      "v_mfma_f32_32x32x16_bf16 %0, %4, %8, %0\n\t"
+      "s_nop 15"
+      : "=&v"(acc)
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "a"(b[0]), "a"(b[1]), "a"(b[2]), "a"(b[3]), "v"(cin));
+  return acc;
+}
+
 // 16-byte global load straight into accumulation registers (for operands that stay there
 // for the whole kernel).  The compiler does not know this is a load: call agpr_loads_wait()
 // before the first use.
@@ -238,6 +252,10 @@ __device__ __forceinline__ void store_pair16_bf16(__bf16* dst, f32x4 v0, f32x4 v
 // the transpose loads that read 4 consecutive rows x 64 contiguous bytes.
 template <int D>
 __device__ __forceinline__ int swz(int r) {
+  // Rows of 128 bytes: two of them lie side by side on the banks, so of 16 consecutive rows the eight even ones have to
+  // show a chunk at eight positions, and so have the odd ones; and rows r and r + 2 of a transpose load's four, whose
+  // 64-byte pieces share a half, have to differ in the position's highest bit.  Bits 1 to 3 of the row, reversed.
+  if constexpr (D == 64) return ((r << 1) & 4) | ((r >> 1) & 2) | ((r >> 3) & 1);
   int f = ((r & 3) << 2) | (((r >> 2) ^ r) & 3);
   return f & (D / 8 - 1);
 }
