@@ -1607,8 +1607,14 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     if ((rc = chunked ? both_fit(std::true_type{}, std::true_type{}, &per_cu) : both_fit(std::false_type{}, std::true_type{}, &per_cu))) return rc;
     const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs);
     const int64_t items = tiles * p.B * ((int64_t)p.Hq + p.Hkv), resident = (int64_t)cus * per_cu;
-    bool once = items <= resident;
-    if constexpr (D == 128) {
+    bool once = items <= resident, queued = false;
+    if constexpr (D == 64) {
+      if (!once && items < ((int64_t)1 << 31)) {
+        const Bwd64 route = bwd64_route(p.B, p.S, p.Hq, p.Hkv, p.causal != 0, p.num_docs, cus, resident);
+        once = route == Bwd64::kDealt;
+        queued = route == Bwd64::kQueued;
+      }
+    } else {
       if (tile_rows_setting.load(std::memory_order_relaxed) == 256) once = false;   // (its dQ items are 128 rows)
       else if (!once && items < ((int64_t)1 << 31)) once = bwd128_in_one_launch(p.B, p.S, p.Hq, p.Hkv, p.causal != 0, p.num_docs, cus);
     }
@@ -1617,7 +1623,7 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
                      : both_phase(std::false_type{}, std::true_type{}, tiles);
     }
     if constexpr (D == 64) {
-      if (items < ((int64_t)1 << 31) && bwd64_in_one_launch(p.B, p.S, p.Hq, p.Hkv, p.causal != 0, p.num_docs, cus, resident)) {
+      if (queued) {
         return chunked ? both_phase(std::true_type{}, std::false_type{}, tiles)
                        : both_phase(std::false_type{}, std::false_type{}, tiles);
       }

@@ -5,7 +5,10 @@
 
 namespace ie {
 
-// Backward pass at head dimension 64: dK/dV and dQ items in one launch (attn_bwd_both_kernel), or a launch each?
+// Backward pass at head dimension 64, work queues: dK/dV and dQ items in one queued launch (attn_bwd_both_kernel), or a
+// queued launch each?  bwd64_route below decides first whether queues serve the call at all; the figures here are from before
+// the queues became cheap to enter and leave and dK/dV lost its masks, and the line between the two has not moved for the
+// calls that still come here.
 // `resident`: workgroups of the shared launch that the chip holds at once (two per CU).
 // The shared launch saves a launch and fills the other kind's tail; it costs dQ its third wave per SIMD, and dK/dV items
 // that would have a CU to themselves share it.  Kernel time of the whole pass, two launches against one, 256 CUs:
@@ -33,6 +36,38 @@ inline bool bwd64_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, b
   if (causal) return nk < 2 * resident || work <= (group == 1 ? 150 : 300);
   const int64_t rounds = (nk + resident - 1) / resident;
   return work <= 150 || 10 * nk <= (group >= 4 ? 8 : 7) * resident * rounds;
+}
+
+// Backward pass at head dimension 64: a persistent launch for each kind of item (kTwo), one launch that the hardware deals out
+// (kDealt, two workgroups per CU) or one with queues (kQueued)?  As at head dimension 128 (below) the shared launch has one
+// tail instead of two, and its dQ items run at two waves per SIMD instead of three.  The estimated time of one launch is
+// its longest item or the work per resident workgroup, whichever is longer; two launches come to 2.3 times the dK/dV items
+// alone.  Before (queued or two) : now: 8192 x 8, 8 per group, bidirectional 1791 : 1144 us, 8192 x 8, 4 per group, 1009 : 621,
+// 700 x 48 93 : 44, 640 x 80 126 : 57, 4096 x 16 x 4 605 : 520 (two), 8192 x 16 x 4 1970 : 1759 (two).
+// Fitted to 220 shapes, 128 to 16384 tokens: 0.2 % slower than the better of one and two launches on average, 13 % at most
+// (packed documents of 221 to 3749 tokens); 0.3 % and 9 % on 140 others.
+// Queues keep the order that shares K and V in L2, which pays in long bidirectional items of many heads per group (12800 x
+// 12, 8 per group, 4225 : 4037 us, 8600 x 20, 4 per group, 2024 : 1962); elsewhere the dealt launch is 1 % behind at most
+// or ahead by up to 50 %.
+enum class Bwd64 { kTwo, kDealt, kQueued };
+inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus, int64_t resident) {
+  constexpr double kKvStep = 2.46, kKvItem = 18.2, kQStep = 4.82, kQItem = 0.23;   // us per pair of tiles, per item
+  constexpr double kAlone = 0.91, kTwoLaunches = 2.31, kLaunch = 1.4;
+  const double per_head = num_docs ? (double)(S / 128 + num_docs) : (double)((S + 127) / 128), group = (double)(Hq / Hkv);
+  double doc = num_docs ? (double)S / 128 / (double)num_docs : per_head;   // tiles of a document (packed: on average)
+  if (doc < 1) doc = 1;
+  const double mean = causal ? (doc + 1) / 2 : doc, R = (double)resident;
+  const double nk = per_head * (double)(B * Hkv), nq = per_head * (double)(B * Hq);
+  const double kv = doc * group * kKvStep + kKvItem, kv_work = nk * (mean * group * kKvStep + kKvItem);
+  const double q = doc * kQStep + kQItem, q_work = nq * (mean * kQStep + kQItem);
+  const auto longer = [](double x, double y) { return x > y ? x : y; };
+  const double one = nk + nq > (double)cus ? longer(kAlone * kv, (kv_work + q_work) / R) : kAlone * longer(kv, q);
+  double two = kAlone * kv;   // dK/dV items: an item per CU, all of them resident, or rounds of them
+  if (nk > R && !causal) two = (double)(int64_t)((nk + R - 1) / R) * kv;
+  else if (nk > (double)cus) two = longer(two, kv_work / R);
+  if (one >= kTwoLaunches * two + kLaunch) return Bwd64::kTwo;
+  const bool long_groups = !causal && num_docs == 0 && group >= 4 && per_head * group >= 200 && nk + nq >= 5 * R;
+  return long_groups && bwd64_in_one_launch(B, S, Hq, Hkv, causal, num_docs, cus, resident) ? Bwd64::kQueued : Bwd64::kDealt;
 }
 
 // Backward pass at head dimension 128: all dK/dV and dQ items in one launch that the hardware deals out (the ONCE form of

@@ -12,6 +12,9 @@ SHIM = """
 extern "C" int one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
   return ie::bwd64_in_one_launch(B, S, Hq, Hkv, causal != 0, docs, 256, 512);
 }
+extern "C" int route_64(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
+  return (int)ie::bwd64_route(B, S, Hq, Hkv, causal != 0, docs, 256, 512);
+}
 extern "C" int one_launch_128(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
   return ie::bwd128_in_one_launch(B, S, Hq, Hkv, causal != 0, docs, 256);
 }
@@ -55,6 +58,30 @@ def rules(tmp_path_factory):
 def test_bwd64_launches(rules, B, S, Hq, Hkv, causal, docs, one):
     i64 = ctypes.c_int64
     assert bool(rules.one_launch(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))) == one
+
+
+TWO, DEALT, QUEUED = 0, 1, 2   # enum Bwd64
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,causal,docs,route", [
+    (1, 700, 48, 48, 1, 0, DEALT),      # a little over one round of short items
+    (1, 640, 80, 80, 1, 0, DEALT),
+    (1, 8192, 8, 1, 0, 0, DEALT),       # fewer dK/dV items than CUs
+    (1, 8192, 8, 2, 0, 0, DEALT),
+    (1, 8192, 16, 8, 1, 0, DEALT),      # one to two rounds
+    (1, 1000, 80, 80, 1, 0, DEALT),     # the GPU test's sizes (test_gpu_bwd_both.py)
+    (1, 1300, 80, 20, 0, 0, DEALT),
+    (4, 2000, 16, 16, 0, 0, TWO),       # several rounds
+    (4, 4096, 16, 16, 1, 0, TWO),
+    (4, 8192, 16, 16, 0, 0, TWO),
+    (1, 13900, 24, 3, 0, 0, QUEUED),    # long items of grouped heads
+    (1, 6400, 56, 14, 0, 0, QUEUED),
+    (1, 13900, 24, 3, 1, 0, DEALT),
+    (1, 16384, 16, 16, 1, 31, DEALT),
+])
+def test_bwd64_route(rules, B, S, Hq, Hkv, causal, docs, route):
+    i64 = ctypes.c_int64
+    assert rules.route_64(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs)) == route
 
 
 @pytest.mark.parametrize("B,S,Hq,Hkv,causal,docs,one", [

@@ -47,18 +47,21 @@ def test_one_launch_gives_the_bits_of_two(B, S, Hq, Hkv, D, causal, lens):
             assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("B,S,Hq,Hkv,causal,lens", [
-    (1, 300, 128, 128, True, None),   # 384 items of each kind
-    (2, 200, 160, 40, False, None),   # 160 dK/dV items of four heads each, 640 of dQ
-    (1, 260, 150, 150, True, [1, 259]),
+@pytest.mark.parametrize("B,S,Hq,Hkv,D,causal,lens", [
+    (1, 300, 128, 128, 128, True, None),   # 384 items of each kind
+    (2, 200, 160, 40, 128, False, None),   # 160 dK/dV items of four heads each, 640 of dQ
+    (1, 260, 150, 150, 128, True, [1, 259]),
+    (1, 1000, 80, 80, 64, True, None),     # 640 items of each kind
+    (1, 1300, 80, 20, 64, False, None),
+    (1, 500, 150, 150, 64, True, [1, 499]),
 ])
-def test_more_items_than_cus_in_one_launch(B, S, Hq, Hkv, causal, lens):
-    """Head dimension 128, dealt out by the hardware: all kv heads hold the same data, so every group of heads has to show
-    the bits of the first, which is checked against the oracle."""
+def test_more_items_than_cus_in_one_launch(B, S, Hq, Hkv, D, causal, lens):
+    """Dealt out by the hardware: all kv heads hold the same data, so every group of heads has to show the bits of the
+    first, which is checked against the oracle."""
     import torch
     from paper_2401_09149_amd import binding
-    print(f"case B{B} S{S} Hq{Hq} Hkv{Hkv} {causal} {lens}", flush=True)
-    dev, D, g = "cuda:0", 128, Hq // Hkv
+    print(f"case B{B} S{S} Hq{Hq} Hkv{Hkv} D{D} {causal} {lens}", flush=True)
+    dev, g = "cuda:0", Hq // Hkv
     scale = D ** -0.5
     q1, do1 = (randn_bf16((B, S, g, D), 800 + j) for j in range(2))
     k1, v1 = (randn_bf16((B, S, 1, D), 802 + j) for j in range(2))
@@ -73,3 +76,22 @@ def test_more_items_than_cus_in_one_launch(B, S, Hq, Hkv, causal, lens):
         assert torch.equal(t, f.repeat(1, 1, Hkv, 1))
     ref = ora.attn_fwd_bwd(*(to64(t) for t in (q1, k1, v1, do1)), scale, causal, None if cu is None else np.asarray(cu.cpu()))
     compare_all((first[0], lse[:, :g], *first[1:]), ref, f"S{S} Hq{Hq}")
+
+
+def test_queued_launch_gives_the_bits_of_two():
+    """Long bidirectional items of grouped heads at head dimension 64 (bwd64_route)."""
+    import torch
+    from paper_2401_09149_amd import binding
+    B, S, Hq, Hkv, D = 1, 6400, 56, 14, 64
+    dev, scale = "cuda:0", D ** -0.5
+    q, do = (randn_bf16((B, S, Hq, D), 900 + j).to(dev) for j in range(2))
+    k, v = (randn_bf16((B, S, Hkv, D), 902 + j).to(dev) for j in range(2))
+    o, lse = binding.attn_fwd(q, k, v, scale, False)
+    ws = binding.alloc_bwd_workspace(q, k)
+    want, got = ([torch.full_like(t, float("nan")) for t in (q, k, v)] for _ in range(2))
+    for phase in (binding.BWD_DELTA, binding.BWD_DQ, binding.BWD_DKDV):
+        binding.ie_attn_bwd_phases(q, k, v, o, do, lse, *want, None, scale, False, ws, phase)
+    binding.ie_attn_bwd(q, k, v, o, do, lse, *got, None, scale, False, ws)
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
