@@ -20,7 +20,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-tar
 # has arrived), at both head dimensions: they must compile without scratch.  The recomputing dQ
 # kernel at head dimension 128 is listed because a spill in it has only ever meant a per-item invariant hoisted
 # out of the item loop, which is cheaper to recompute.
-NO_SCRATCH = ("attn_fwd_wide_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_both_kernel", "attn_bwd_dq_kernelILi128E")
+NO_SCRATCH = ("attn_fwd_wide_kernel", "attn_fwd_seq_kernel", "attn_bwd_dkdv_kernel", "attn_bwd_both_kernel", "attn_bwd_dq_kernelILi128E")
 # Persistent kernels loop over work items around a body that leaves no register free: with machine LICM the
 # compiler hoists per-lane invariants of the item prologue out of that loop and spills to keep them.
 SOURCE_FLAGS = {"attn_fwd_wide.hip": ["-mllvm", "-disable-machine-licm"], "attn_bwd.hip": ["-mllvm", "-disable-machine-licm"]}

@@ -48,6 +48,7 @@ struct AttnParams {
   int32_t tiles;            // tiles per head the grid was sized for (upper bound when packed)
   uint32_t q_dealt;         // persistent launches: workgroups whose first item goes by their index (0: all items are claimed)
   int32_t q_heavy, q_per_xcd, q_total;  // persistent launches (tile_queue.hpp): tiles per head in a list's head-by-head part, items per XCD list (0: one list), items
+  int32_t flip_lo, flip_hi; // 128-row forward: items (multiples of 8) that run in the opposite order
   __bf16* ds;               // optional workspace: dS written by the dK/dV kernel for the dQ kernel (see ds_matrix_offset), or NULL
   // Where token t of batch entry b lives in q/dq (pitch Hq*D) and k/v/dk/dv (pitch Hkv*D), see tok_off():
   // contiguous [B,S,heads,D] tensors, or the chunks of a sequence-parallel exchange buffer (one chunk per peer).

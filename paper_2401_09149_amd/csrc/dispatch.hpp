@@ -106,6 +106,47 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
   return one * (num_docs ? 1.06 : 1.02) < two;   // (documents differ: their longest items are longer than the mean's)
 }
 
+// Forward at head dimension 128: 256-row items in a persistent kernel (kWide, attn_fwd_wide_kernel), 128-row items two
+// workgroups to a CU (kNarrow, attn_fwd_kernel), or 128-row items of one hand-sequenced wave per SIMD (kSeq,
+// attn_fwd_seq_kernel)?  kWide has the fastest steady state and needs many items, kSeq the shortest items, kNarrow overlaps
+// one item's way in and out with the other's key loop.  The choice goes by the estimated times: the longest item or the
+// work per resident workgroup, with items priced per tile of 128 keys and per item; for causal launches of one to two items
+// per slot also the first pair of items that share one.  `prefer_narrow`: what sizes alone say (fwd_prefers_128_rows in
+// launch.hpp), left for another kernel where that is ahead by 4 % (bidirectional 8 %).  Packed documents longer than 12 tiles
+// on average count 1.3 times in 128-row items: their longest are longer than the mean says.
+// Wide or narrow as sizes alone say : now: 8192 x 8 175 : 148 us, 8192 x 4 146 : 121, 6000 x 8 117 : 96, 4096 x 16 91 : 81,
+// 29952 x 1 593 : 422; packed 8000 x 100 in 63 documents 74 : 30, 2222 x 2 in 4 44 : 24, 16384 x 2 in 24 53 : 32.
+// Fitted to 500 launches, 128 to 65536 tokens: 0.5 % slower than the best on average, 16 % faster than sizes alone would
+// have it (packed 34 %), 7 % slower at most (packed 3696 x 33).
+enum class Fwd128 { kWide, kNarrow, kSeq };
+inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_t num_docs, int64_t cus, bool prefer_narrow) {
+  struct Cost { double step, item, alone, per_cu; };
+  constexpr Cost kWideCost{2.37, 22.7, 1.0, 1}, kNarrowCost{3.18, 7.1, 0.84, 2}, kSeqCost{1.97, 8.0, 1.0, 1};
+  const double n128 = num_docs ? (double)(S / 128 + num_docs) : (double)((S + 127) / 128);
+  const double n256 = num_docs ? (double)(S / 256 + num_docs) : (double)((S + 255) / 256);
+  double doc = num_docs ? (double)S / 128 / (double)num_docs : n128;   // tiles of a document (packed: on average)
+  if (doc < 1) doc = 1;
+  const double mean = causal ? (doc + 1) / 2 : doc, heads = (double)(B * Hq);
+  const auto time = [&](const Cost& c, double per_head, double tiles, double mean_tiles) {
+    const double n = per_head * heads, slots = (double)cus * c.per_cu;
+    const double longest = c.step * tiles + c.item, work = n * (c.step * mean_tiles + c.item) / slots;
+    if (n <= (double)cus) return longest * c.alone;
+    if (n > slots && !causal) return (double)(int64_t)((n + slots - 1) / slots) * longest;
+    double t = work > longest * c.alone ? work : longest * c.alone;
+    if (n > slots && n <= 2 * slots) {
+      const double pair = 2 * (longest - c.step * tiles * slots / n);
+      t = pair > t ? pair : t;
+    }
+    return t;
+  };
+  const double margin = causal ? 1.04 : 1.08, spread = num_docs && doc > 12 ? 1.3 : 1.0;
+  const double wide = time(kWideCost, n256, doc + 1, mean + 0.5) * (prefer_narrow ? margin : 1.0);
+  const double narrow = time(kNarrowCost, n128, doc, mean) * spread * (prefer_narrow ? 1.0 : margin);
+  const double seq = time(kSeqCost, n128, doc, mean) * spread * margin;
+  if (wide <= narrow && wide <= seq) return Fwd128::kWide;
+  return narrow <= seq ? Fwd128::kNarrow : Fwd128::kSeq;
+}
+
 // Recomputing dQ kernel at head dimension 128: products as 16x16x32 MFMAs (dq_item_16) instead of 32x32x16 (dq_item)?
 // The 16x16x32 form costs less power per product and more issue slots, so it gains where the launch keeps the chip at its
 // power limit and loses where most CUs wait for a few heavy items: dQ alone, 32x32x16 against it, 32768 x 16 causal

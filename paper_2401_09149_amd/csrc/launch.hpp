@@ -51,6 +51,7 @@ inline bool few_items(int64_t items_256) {
   const int cus = cu_count(&e);
   return cus > 0 && items_256 < 2 * (int64_t)cus;
 }
+// (For the forward that is where fwd128_route in dispatch.hpp starts from.)
 // (`tile_rows_setting`: 0 = choose as above, 128 or 256 = the caller's choice, see ie_attn_set_tile_rows)
 inline std::atomic<int> tile_rows_setting{0};
 inline bool fwd_prefers_128_rows(int64_t items_256, int64_t S, bool packed) {

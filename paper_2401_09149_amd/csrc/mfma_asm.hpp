@@ -165,6 +165,11 @@ __device__ __forceinline__ void add_pack(float& l, float p_prev, uint32_t& packe
   asm volatile("v_add_f32 %0, %0, %2\n\tv_cvt_pk_bf16_f32 %1, %3, %2" : "+v"(l), "=v"(packed) : "v"(p_prev), "v"(p_prev2));
 }
 
+// The same for a pair whose sums are still open (masked blocks): l += p0 + p1, packed = {bf16(p0), bf16(p1)}.
+__device__ __forceinline__ void sum_pack_pair(float& l, uint32_t& packed, float p0, float p1) {
+  asm volatile("v_add_f32 %0, %0, %2\n\tv_cvt_pk_bf16_f32 %1, %2, %3\n\tv_add_f32 %0, %0, %3" : "+v"(l), "=&v"(packed) : "v"(p0), "v"(p1));
+}
+
 __device__ __forceinline__ bf16x8 frag_from_words(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   u32x4 w = {a, b, c, d};
   return __builtin_bit_cast(bf16x8, w);

@@ -18,6 +18,9 @@ extern "C" int route_64(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causa
 extern "C" int one_launch_128(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
   return ie::bwd128_in_one_launch(B, S, Hq, Hkv, causal != 0, docs, 256);
 }
+extern "C" int fwd_128(int64_t B, int64_t S, int64_t Hq, int causal, int64_t docs, int narrow) {
+  return (int)ie::fwd128_route(B, S, Hq, causal != 0, docs, 256, narrow != 0);
+}
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
@@ -58,6 +61,32 @@ def rules(tmp_path_factory):
 def test_bwd64_launches(rules, B, S, Hq, Hkv, causal, docs, one):
     i64 = ctypes.c_int64
     assert bool(rules.one_launch(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))) == one
+
+
+WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
+
+
+@pytest.mark.parametrize("B,S,Hq,causal,docs,narrow,route", [
+    (1, 8192, 8, 1, 0, 1, SEQ),         # up to two items per CU
+    (1, 8192, 4, 1, 0, 1, SEQ),
+    (1, 30000, 1, 1, 0, 0, SEQ),
+    (1, 3000, 8, 0, 0, 1, SEQ),
+    *((1, s, 2, c, 0, 1, SEQ) for s in (385, 449, 512, 513, 641) for c in (1,)),
+    *((1, s, 2, 0, 0, 1, SEQ) for s in (897, 960, 1024, 1025)),   # the GPU test's sizes (test_gpu_fwd_routes.py)
+    (2, 700, 3, 1, 0, 1, SEQ), (1, 1100, 4, 0, 0, 1, SEQ), (1, 2500, 2, 1, 4, 0, SEQ), (1, 2300, 2, 0, 4, 0, SEQ),
+    (2, 430, 40, 1, 0, 1, NARROW),      # short items, a second round
+    (1, 3000, 16, 0, 0, 1, NARROW),
+    (1, 3001, 32, 1, 0, 1, NARROW),
+    (1, 4096, 32, 1, 0, 1, NARROW),
+    (1, 32768, 32, 1, 0, 0, WIDE),
+    (1, 16384, 16, 1, 0, 0, WIDE),
+    (1, 8000, 100, 1, 63, 0, NARROW),   # packed: short documents
+    (1, 2222, 2, 1, 4, 0, SEQ),
+    (1, 65536, 8, 1, 17, 0, WIDE),      # long ones
+])
+def test_fwd128_route(rules, B, S, Hq, causal, docs, narrow, route):
+    i64 = ctypes.c_int64
+    assert rules.fwd_128(i64(B), i64(S), i64(Hq), causal, i64(docs), narrow) == route
 
 
 TWO, DEALT, QUEUED = 0, 1, 2   # enum Bwd64

@@ -1,0 +1,36 @@
+"""The forward kernel of one hand-sequenced wave per SIMD (attn_fwd_seq_kernel) at its edges: lengths around its 32-key
+blocks, 64-key tiles, the four stages of its ring and its 128-row items, against the oracle.  Calls of these sizes take it
+by fwd128_route (csrc/dispatch.hpp), which tests/test_dispatch_rules.py checks."""
+import numpy as np
+import pytest
+from oracle import attention as ora
+
+from parity_util import TOL_LSE, randn_bf16, to64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,causal,lens", [
+    *((1, s, 2, 1, c, None) for s in (385, 415, 416, 447, 449, 480, 511, 512, 513, 577, 639, 641) for c in (True,)),
+    *((1, s, 2, 1, False, None) for s in (897, 929, 960, 991, 1023, 1024, 1025)),
+    (2, 700, 3, 3, True, None),
+    (1, 1100, 4, 2, False, None),
+    (1, 2500, 2, 2, True, [1, 33, 66, 2400]),
+    (1, 2300, 2, 1, False, [64, 2200, 0, 36]),
+])
+def test_against_the_oracle(B, S, Hq, Hkv, causal, lens):
+    import torch
+    from paper_2401_09149_amd import binding
+    print(f"case B{B} S{S} Hq{Hq} Hkv{Hkv} {causal} {lens}", flush=True)
+    dev, D = "cuda:0", 128
+    # scores from small to far beyond the first block's: blocks that are done again are among them
+    q, k, v = (randn_bf16((B, S, h, D), 950 + j) for j, h in enumerate((Hq, Hkv, Hkv)))
+    k = (k.float() * torch.linspace(0.2, 6.0, S).view(1, S, 1, 1)).to(torch.bfloat16)
+    cu = None if lens is None else torch.tensor([0] + lens, dtype=torch.int32).cumsum(0).to(torch.int32)
+    o, lse = binding.attn_fwd(q.to(dev), k.to(dev), v.to(dev), D ** -0.5, causal, None if cu is None else cu.to(dev))
+    torch.cuda.synchronize()
+    ro, rlse = ora.attn_fwd(to64(q), to64(k), to64(v), D ** -0.5, causal, None if cu is None else np.asarray(cu))
+    # With scores as large as these a row is nearly one key's, and o nearly a value vector (up to 4.6 here).  bf16 rounds to
+    # within 2^-8 of a number: the probabilities cost 2^-8 max|v|, the result 2^-8 |o|; 1e-3 for the sums.
+    assert (np.abs(to64(o) - ro) <= 2.0 ** -8 * (np.abs(to64(v)).max() + np.abs(ro)) + 1e-3).all()
+    assert np.abs(to64(lse) - rlse).max() <= TOL_LSE * max(1.0, np.abs(rlse).max() / 8)   # (fp32: relative for large sums)
