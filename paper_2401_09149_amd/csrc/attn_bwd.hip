@@ -1535,7 +1535,7 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
       const int cus = cu_count(&e);
       if (e != hipSuccess) return hip_fail(e);
       const int64_t items_256 = ceil_div(p.S, DqCfg<kDqWaves>::BM) * p.B * p.Hq;
-      const bool wide = !dq_prefers_128_rows(items_256, p.S, p.cu != nullptr);
+      const bool wide = !dq_prefers_128_rows(items_256, p.S, p.num_docs);
       const bool f16 = dq128_on_16x16x32(items, items_256, wide, p.causal != 0, p.cu != nullptr, cus);
       using Wide = std::integral_constant<int, kDqWaves>;
       using Narrow = std::integral_constant<int, 4>;

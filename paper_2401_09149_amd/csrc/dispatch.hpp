@@ -79,7 +79,10 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
 // 8192 x 8 492 : 433, 3001 x 32, 4 per group, 400 : 328, 10180 x 8 x 4, 8 per group, bidirectional 6134 : 5102; but
 // 2 x 4096 x 32 890 : 920, 14443 x 37 5860 : 6222.
 // Fitted to 220 shapes, 128 to 16384 tokens: 0.2 % slower than the better form on average, 7 % at most, and 5 % slower than
-// two launches at most (3143 x 16, 2 per group, bidirectional); on 160 others the same.
+// two launches at most (3143 x 16, 2 per group, bidirectional); 0.2 % on 160 others.
+// Packed documents are priced by themselves (their items are short, and the longest of a call, whose lengths the host does
+// not know, counts as three times the mean): 109 calls of 2048 to 65536 tokens, 0.1 % slower than the better form on average,
+// 5 % at most; 22.7 tiles on average x 4 heads 579 (two) : 509 (one) us, 50000 x 8 in 2.1 tiles 350 : 426.
 inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus) {
   constexpr double kKvStep = 2.87, kKvItem = 19.4;     // dK/dV: us per pair of tiles, per item
   constexpr double kQStep = 3.23, kQItem = 0.34;       // dQ in the shared launch
@@ -90,6 +93,14 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
   if (doc < 1) doc = 1;
   const double mean = causal ? (doc + 1) / 2 : doc, C = (double)cus;
   const double nk = per_head * (double)(B * Hkv), nq = per_head * (double)(B * Hq);
+  if (num_docs) {
+    constexpr double kKv = 5.06, kKvIt = 7.25, kQ = 5.69, kQIt = 1.76, kQOwn = 8.22, kQOwnIt = 1.26, kOwn = 6.5, kLongest = 3.14;
+    const auto longer = [](double x, double y) { return x > y ? x : y; };
+    const double kv = kLongest * doc * group * kKv + kKvIt, kv_all = nk * (mean * group * kKv + kKvIt) / C;
+    const double one = longer(longer(kv, kLongest * doc * kQ + kQIt), kv_all + nq * (mean * kQ + kQIt) / C);
+    const double two = longer(kv, kv_all) + longer(0.6 * kLongest * doc * kQOwn + kQOwnIt, nq * (mean * kQOwn + kQOwnIt) / (2 * C)) + kOwn;
+    return 1.02 * one < two;
+  }
   const auto span = [&](double n, double longest, double work) {   // of a launch of n items
     if (n <= C) return longest;
     if (!causal) { const double rounds = (double)(int64_t)((n + C - 1) / C); return rounds * longest; }
@@ -103,7 +114,7 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
     one = (even > kv ? even : kv) + kTail * (causal ? kQStep + kQItem : q);
   }
   const double two = span(nk, kv, kv_work) + span(nq / 2, doc * kQ2Step + kQ2Item, nq / 2 * (mean * kQ2Step + kQ2Item)) + kLaunch;
-  return one * (num_docs ? 1.06 : 1.02) < two;   // (documents differ: their longest items are longer than the mean's)
+  return 1.02 * one < two;
 }
 
 // Forward at head dimension 128: 256-row items in a persistent kernel (kWide, attn_fwd_wide_kernel), 128-row items two

@@ -127,6 +127,8 @@ def test_bwd64_route(rules, B, S, Hq, Hkv, causal, docs, route):
     (1, 32768, 32, 32, 1, 0, False),
     (2, 6144, 10, 10, 0, 0, False),
     (1, 65536, 8, 8, 1, 20, False),
+    (1, 50000, 8, 8, 1, 180, False),   # packed: short documents, many items
+    (1, 35000, 4, 4, 1, 12, True),     # long ones on few heads
 ])
 def test_bwd128_launches(rules, B, S, Hq, Hkv, causal, docs, one):
     i64 = ctypes.c_int64
