@@ -171,7 +171,7 @@ static inline int kernel_setup(KernelSetup& ks, K kernel, int smem_bytes, int* p
 
 // Host side: fills the queue fields of `p` for `total` items (= tiles per head x B x heads) with the
 // launch's own `counters` (device memory, kQueueBytes) and clears them on `st` (unless they are clear already).  Returns the grid size for
-// `per_cu` resident workgroups per CU.  `deal`: the first items go by workgroup index.
+// `per_cu` resident workgroups per CU.  `deal`: the first items may go by workgroup index.
 struct QueueLaunch { int grid; hipError_t err; };
 static inline QueueLaunch tile_queue_prepare(AttnParams& p, unsigned int* counters, int64_t total, int heads, int per_cu, hipStream_t st,
                                              bool already_clear = false, bool deal = true) {
@@ -184,7 +184,10 @@ static inline QueueLaunch tile_queue_prepare(AttnParams& p, unsigned int* counte
   p.q_per_xcd = (nH % 8 == 0) ? (int32_t)(total / 8) : 0;
   const int64_t want = (int64_t)cus * per_cu;
   r.grid = (int)(total < want ? total : want);
-  p.q_dealt = deal ? (uint32_t)r.grid : 0u;
+  // One list of more than two items per workgroup leaves the first round to the order of arrival too (start dealt : by
+  // arrival, dQ 65536 x 4 4885 : 4818 us, dK/dV 131072 x 1 6918 : 6793, forward 65536 x 3 2666 : 2646, but forward 9000 x 20
+  // 394 : 399; with two items or fewer dQ 16384 x 6 496 : 598).
+  p.q_dealt = deal && (p.q_per_xcd > 0 || total <= 2 * want) ? (uint32_t)r.grid : 0u;
   // Head by head for the heavier 5/8 of a head's tiles, so that an XCD's workgroups share a head's rows in its L2; from the
   // heaviest tile of all heads down where a workgroup gets two items at most and the balance is what counts (dQ 4096 x 32
   // 196 : 168 us, dQ 1600 x 24 x 2 at head dimension 64 54 : 48, 4096 x 16 71 : 71; above it dK/dV 2048 x 40 94 : 100,
