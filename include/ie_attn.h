@@ -182,11 +182,12 @@ int ie_attn_bwd_static(const void* q, const void* k, const void* v, const void* 
  * Query rows per work item at head dimension 128, for the forward and the recomputing dQ kernel: 256
  * (one persistent workgroup per CU; the faster steady state) or 128 (two workgroups per CU; half the
  * work per item, which wins when a launch has few items per CU or the sequence is short).  rows = 0
- * (the initial setting) lets every call choose from its shape: dense input of up to 4096 tokens, or
- * up to 8192 tokens with fewer than two 256-row items per CU, takes the 128-row forward; dense input
- * of 8192 tokens or more with fewer than two 256-row items per CU takes the 128-row dQ.  A backward
- * call whose dK/dV and dQ items of 128 rows all fit on the chip at once, dense or packed, runs them in
- * one launch, with 128-row dQ items, unless rows = 256.  rows = 128 or 256 fixes the choice for all
+ * (the initial setting) lets every call choose from its shape: the forward by the estimated time of a
+ * launch with either (128-row items exist in two kernels, for few and for many items per CU); the dQ
+ * kernel takes 128 rows for dense input of 8192 tokens or more with fewer than two 256-row items per CU
+ * and for packed documents of up to 3072 tokens on average.  A backward call whose estimated time is
+ * the shorter for it runs its dK/dV and dQ items in one launch, with 128-row dQ items, unless rows =
+ * 256.  rows = 128 or 256 fixes the choice for all
  * later calls of the process (measurements, tests); the results of the two differ only in rounding
  * order.  Returns the previous setting, or IE_ERR_UNSUPPORTED for any
  * other value.  Head dimension 64 always works on 128-row items.  (Sec. 4.2: self-atten is profiled
