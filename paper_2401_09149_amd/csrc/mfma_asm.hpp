@@ -12,7 +12,10 @@
 //    an s_nop covering that distance, and the kernels place them at least two MFMAs behind
 //    the chain's last MFMA anyway;
 //  - a non-transcendental VALU instruction needs one wait state after the v_exp_f32 whose
-//    result it reads (s_nop 0 in softmax_pair).
+//    result it reads (s_nop 0 in softmax_pair);
+//  - a VALU instruction may read VCC, or a scalar register, only two wait states after the
+//    VALU instruction that wrote it (an fma and an s_nop in softmax_elem_masked).
+// tests/test_wait_states.py follows these through the assembly of every kernel.
 #pragma once
 #include "attn_common.hpp"
 
@@ -89,7 +92,7 @@ __device__ __forceinline__ void softmax_elem(float& p, float s, float c, float n
 }
 // The same for element `key` of a lane's keys, of which those past `lim` are not visible (p = 0).
 __device__ __forceinline__ void softmax_elem_masked(float& p, float s, float c, float nl, int key, int lim) {
-  asm volatile("v_fma_f32 %0, %1, %2, %3\n\tv_cmp_gt_i32 vcc, %4, %5\n\tv_cndmask_b32 %0, %0, %6, vcc\n\tv_exp_f32 %0, %0"
+  asm volatile("v_cmp_gt_i32 vcc, %4, %5\n\tv_fma_f32 %0, %1, %2, %3\n\ts_nop 0\n\tv_cndmask_b32 %0, %0, %6, vcc\n\tv_exp_f32 %0, %0"
                : "=&v"(p) : "v"(s), "s"(c), "v"(nl), "s"(key), "v"(lim), "v"(-__builtin_inff()) : "vcc");
 }
 // d = p * dp  (the dP chain started from -delta)
