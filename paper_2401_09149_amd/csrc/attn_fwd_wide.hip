@@ -257,13 +257,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_wide_kernel(AttnParams p
   // slots, PV of block i on odd slots), Y the one whose softmax runs (on s_y).  KLOAD / VLOAD: after a
   // K fragment's last use load the next block's (r = local block index in stage STG, or -1);
   // load the next block's V^T into the other buffer.
-  auto phase = [&](auto has_s, auto has_pv, auto has_sm, auto has_tail, const bf16x8 (&qx)[NKS], f32x16& s_x,
+  auto phase = [&](auto has_s, auto has_pv, auto has_sm, auto after_moves, const bf16x8 (&qx)[NKS], f32x16& s_x,
                    f32x16 (&o_x)[NDB], uint32_t (&pw_x)[8], float (&pr_x)[16], ColState& st_x, f32x16& s_y,
                    f32x16 (&o_y)[NDB], uint32_t (&pw_y)[8], float (&pr_y)[16], float& lsum_y, ColState& st_y, auto vpar_c,
                    auto kload_c, auto vload_c, const bool copying, const CopySrc& cs, auto slot_c)
       __attribute__((always_inline)) {
     constexpr bool HAS_S = decltype(has_s)::value, HAS_PV = decltype(has_pv)::value;
-    constexpr bool HAS_SM = decltype(has_sm)::value;
+    constexpr bool HAS_SM = decltype(has_sm)::value, AFTER_MOVES = decltype(after_moves)::value;
     constexpr int vpar = decltype(vpar_c)::value, kload_off = decltype(kload_c)::value;
     constexpr int vload_off = decltype(vload_c)::value;
     constexpr int copy_slot = decltype(slot_c)::value;
@@ -285,7 +285,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_wide_kernel(AttnParams p
         if (HAS_PV) {
           if (k == 0) pf0 = frag_from_words(pw_x[0], pw_x[1], pw_x[2], pw_x[3]);
           if (k == NDB) pf1 = frag_from_words(pw_x[4], pw_x[5], pw_x[6], pw_x[7]);
-          mfma_acc_agpr(o_x[k % NDB], vt[vpar][k / NDB][k % NDB], k < NDB ? pf0 : pf1);
+          if (AFTER_MOVES) mfma_acc_agpr_after_moves(o_x[k % NDB], vt[vpar][k / NDB][k % NDB], k < NDB ? pf0 : pf1);
+          else mfma_acc_agpr(o_x[k % NDB], vt[vpar][k / NDB][k % NDB], k < NDB ? pf0 : pf1);
         }
         if (vload_off >= 0) {
           const int off = vload_off + 16 * (k / NDB) * ROW_BYTES;
@@ -314,17 +315,18 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_wide_kernel(AttnParams p
   using None = std::integral_constant<int, -1>;
   bool copying = false;  // the current round copies the next tile piece by piece
   CopySrc cs{};
-  auto phase_a = [&](auto has_s, auto has_pv, auto has_sm, auto has_tail, auto vpar, auto vload_off, auto copy_slot)
+  auto phase_a = [&](auto has_s, auto has_pv, auto has_sm, auto after_moves, auto vpar, auto vload_off, auto copy_slot)
       __attribute__((always_inline)) {
-    phase(has_s, has_pv, has_sm, has_tail, qa, s_a, oa, pw_a, pr_a, sa, s_b, ob, pw_b, pr_b, lsum_b, sb, vpar, None{}, vload_off, copying, cs, copy_slot);
+    phase(has_s, has_pv, has_sm, after_moves, qa, s_a, oa, pw_a, pr_a, sa, s_b, ob, pw_b, pr_b, lsum_b, sb, vpar, None{}, vload_off, copying, cs, copy_slot);
   };
-  auto phase_b = [&](auto has_s, auto has_pv, auto has_sm, auto has_tail, auto vpar, auto kload_off, auto copy_slot)
+  auto phase_b = [&](auto has_s, auto has_pv, auto has_sm, auto after_moves, auto vpar, auto kload_off, auto copy_slot)
       __attribute__((always_inline)) {
-    phase(has_s, has_pv, has_sm, has_tail, qb, s_b, ob, pw_b, pr_b, sb, s_a, oa, pw_a, pr_a, lsum_a, sa, vpar, kload_off, None{}, copying, cs, copy_slot);
+    phase(has_s, has_pv, has_sm, after_moves, qb, s_b, ob, pw_b, pr_b, sb, s_a, oa, pw_a, pr_a, lsum_a, sa, vpar, kload_off, None{}, copying, cs, copy_slot);
   };
 
   // One round: the eight phases that read tile T (stage STG).  `copy_tile` is T + 1 when that
-  // tile is complete and is to be copied piece by piece during the round, else -1.
+  // tile is complete and is to be copied piece by piece during the round, else -1.  In an item's first round the compiler
+  // moves accumulators to where the other rounds have them, up to the instruction in front of the MFMA that adds to them.
   auto round = [&](auto stg_c, auto first_c, const int copy_tile) __attribute__((always_inline)) {
     copying = copy_tile >= 0;
     if (copying) cs = copy_src(copy_tile);
@@ -347,24 +349,24 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_wide_kernel(AttnParams p
       phase_a(Y{}, N{}, N{}, N{}, I1{}, O0{}, I1{});
       phase_b(Y{}, N{}, Y{}, N{}, I1{}, O1{}, std::integral_constant<int, 2>{});
     } else {
-      phase_b(Y{}, Y{}, Y{}, Y{}, I0{}, O0{}, I0{});                                  // B(prev 2)
-      phase_a(Y{}, Y{}, Y{}, Y{}, I1{}, O0{}, I1{});                                  // A(prev 3)
-      phase_b(Y{}, Y{}, Y{}, Y{}, I1{}, O1{}, std::integral_constant<int, 2>{});      // B(prev 3)
+      phase_b(Y{}, Y{}, Y{}, N{}, I0{}, O0{}, I0{});                                  // B(prev 2)
+      phase_a(Y{}, Y{}, Y{}, N{}, I1{}, O0{}, I1{});                                  // A(prev 3)
+      phase_b(Y{}, Y{}, Y{}, N{}, I1{}, O1{}, std::integral_constant<int, 2>{});      // B(prev 3)
     }
-    phase_a(Y{}, Y{}, Y{}, Y{}, I0{}, O1{}, std::integral_constant<int, 3>{});        // A(0)
-    phase_b(Y{}, Y{}, Y{}, Y{}, I0{}, O2{}, std::integral_constant<int, 4>{});        // B(0)
-    phase_a(Y{}, Y{}, Y{}, Y{}, I1{}, O2{}, std::integral_constant<int, 5>{});        // A(1)
-    phase_b(Y{}, Y{}, Y{}, Y{}, I1{}, O3{}, std::integral_constant<int, 6>{});        // B(1)
-    phase_a(Y{}, Y{}, Y{}, Y{}, I0{}, O3{}, std::integral_constant<int, 7>{});        // A(2)
+    phase_a(Y{}, Y{}, Y{}, first_c, I0{}, O1{}, std::integral_constant<int, 3>{});    // A(0)
+    phase_b(Y{}, Y{}, Y{}, first_c, I0{}, O2{}, std::integral_constant<int, 4>{});    // B(0)
+    phase_a(Y{}, Y{}, Y{}, first_c, I1{}, O2{}, std::integral_constant<int, 5>{});    // A(1)
+    phase_b(Y{}, Y{}, Y{}, first_c, I1{}, O3{}, std::integral_constant<int, 6>{});    // B(1)
+    phase_a(Y{}, Y{}, Y{}, first_c, I0{}, O3{}, std::integral_constant<int, 7>{});    // A(2)
   };
   // After a wave's last round: finish blocks 2 and 3 of that tile from registers.
   auto drain = [&]() __attribute__((always_inline)) {
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     copying = false;
-    phase_b(Y{}, Y{}, Y{}, Y{}, I0{}, None{}, I0{});   // B(2): S_b(3), PV_b(2), softmax of s_a(3)
-    phase_a(N{}, Y{}, Y{}, Y{}, I1{}, None{}, I0{});   // A(3): PV_a(3), softmax of s_b(3)
-    phase_b(N{}, Y{}, N{}, Y{}, I1{}, None{}, I0{});   // B(3): PV_b(3)
+    phase_b(Y{}, Y{}, Y{}, N{}, I0{}, None{}, I0{});   // B(2): S_b(3), PV_b(2), softmax of s_a(3)
+    phase_a(N{}, Y{}, Y{}, N{}, I1{}, None{}, I0{});   // A(3): PV_a(3), softmax of s_b(3)
+    phase_b(N{}, Y{}, N{}, N{}, I1{}, None{}, I0{});   // B(3): PV_b(3)
     mfma_result_fence();
   };
 

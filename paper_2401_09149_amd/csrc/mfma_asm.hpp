@@ -14,7 +14,9 @@
 //  - a non-transcendental VALU instruction needs one wait state after the v_exp_f32 whose
 //    result it reads (s_nop 0 in softmax_pair);
 //  - a VALU instruction may read VCC, or a scalar register, only two wait states after the
-//    VALU instruction that wrote it (an fma and an s_nop in softmax_elem_masked).
+//    VALU instruction that wrote it (an fma and an s_nop in softmax_elem_masked);
+//  - an MFMA may read a register only two wait states after the VALU instruction that wrote it
+//    (mfma_acc_agpr_after_moves where the compiler may have moved an accumulator).
 // tests/test_wait_states.py follows these through the assembly of every kernel.
 #pragma once
 #include "attn_common.hpp"
