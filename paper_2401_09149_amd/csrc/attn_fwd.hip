@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_seq_kernel(AttnParams p)
     asm volatile("s_nop 0");   // (element 15's exponential is the previous instruction but for copies)
     if (MASKED) sum_pack_pair(lsum, pw[7], pr[14], pr[15]);
     else add_pack(lsum, pr[15], pw[7], pr[14]);
-    if (__builtin_amdgcn_ballot_w64(!(lsum <= kRedo)) != 0) redo(s[PAR], pw, lsum, MASKED, lim);
+    if (__builtin_amdgcn_ballot_w64(sum_beyond(lsum, kRedo)) != 0) redo(s[PAR], pw, lsum, MASKED, lim);
     l += lsum;
     pf[0] = frag_from_words(pw[0], pw[1], pw[2], pw[3]);
     pf[1] = frag_from_words(pw[4], pw[5], pw[6], pw[7]);

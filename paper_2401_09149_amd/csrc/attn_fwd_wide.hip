@@ -302,7 +302,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_wide_kernel(AttnParams p
         if (pos >= 5 && pos <= 14) elem(pr_y, pw_y, s_y, st_y, lsum_y, pos + 1);
         if (pos == 15) {
           add_pack(lsum_y, pr_y[15], pw_y[7], pr_y[14]);
-          if (__builtin_amdgcn_ballot_w64(!(lsum_y <= kRedo)) != 0) redo(st_y, o_y, s_y, pw_y, lsum_y);
+          if (__builtin_amdgcn_ballot_w64(sum_beyond(lsum_y, kRedo)) != 0) redo(st_y, o_y, s_y, pw_y, lsum_y);
           st_y.l += lsum_y;
         }
       }

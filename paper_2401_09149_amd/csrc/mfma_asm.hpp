@@ -175,6 +175,12 @@ __device__ __forceinline__ void sum_pack_pair(float& l, uint32_t& packed, float 
   asm volatile("v_add_f32 %0, %0, %2\n\tv_cvt_pk_bf16_f32 %1, %2, %3\n\tv_add_f32 %0, %0, %3" : "+v"(l), "=&v"(packed) : "v"(p0), "v"(p1));
 }
 
+// Whether a block's sum of exponentials is beyond `limit` or not a number (scores of -inf against a reference that is not set
+// yet): compared as bits, since float comparisons are compiled for numbers only (FLAGS in build.py).
+__device__ __forceinline__ bool sum_beyond(float sum, float limit) {
+  return __builtin_bit_cast(uint32_t, sum) > __builtin_bit_cast(uint32_t, limit);
+}
+
 __device__ __forceinline__ bf16x8 frag_from_words(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   u32x4 w = {a, b, c, d};
   return __builtin_bit_cast(bf16x8, w);

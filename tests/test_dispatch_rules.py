@@ -71,7 +71,7 @@ WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
     (1, 8192, 4, 1, 0, 1, SEQ),
     (1, 30000, 1, 1, 0, 0, SEQ),
     (1, 3000, 8, 0, 0, 1, SEQ),
-    *((1, s, 2, c, 0, 1, SEQ) for s in (385, 449, 512, 513, 641) for c in (1,)),
+    *((1, s, 2, c, 0, 1, SEQ) for s in (385, 449, 512, 513, 640, 641) for c in (1,)),
     *((1, s, 2, 0, 0, 1, SEQ) for s in (897, 960, 1024, 1025)),   # the GPU test's sizes (test_gpu_fwd_routes.py)
     (2, 700, 3, 1, 0, 1, SEQ), (1, 1100, 4, 0, 0, 1, SEQ), (1, 2500, 2, 1, 4, 0, SEQ), (1, 2300, 2, 0, 4, 0, SEQ),
     (2, 430, 40, 1, 0, 1, NARROW),      # short items, a second round

@@ -1,11 +1,12 @@
 """The forward kernel of one hand-sequenced wave per SIMD (attn_fwd_seq_kernel) at its edges: lengths around its 32-key
 blocks, 64-key tiles, the four stages of its ring and its 128-row items, against the oracle.  Calls of these sizes take it
-by fwd128_route (csrc/dispatch.hpp), which tests/test_dispatch_rules.py checks."""
+by fwd128_route (csrc/dispatch.hpp), which tests/test_dispatch_rules.py checks.  And scores far below the others of their
+row, in all forward kernels."""
 import numpy as np
 import pytest
 from oracle import attention as ora
 
-from parity_util import TOL_LSE, randn_bf16, to64
+from parity_util import TOL_LSE, TOL_O, randn_bf16, to64
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +35,28 @@ def test_against_the_oracle(B, S, Hq, Hkv, causal, lens):
     # within 2^-8 of a number: the probabilities cost 2^-8 max|v|, the result 2^-8 |o|; 1e-3 for the sums.
     assert (np.abs(to64(o) - ro) <= 2.0 ** -8 * (np.abs(to64(v)).max() + np.abs(ro)) + 1e-3).all()
     assert np.abs(to64(lse) - rlse).max() <= TOL_LSE * max(1.0, np.abs(rlse).max() / 8)   # (fp32: relative for large sums)
+
+
+@pytest.mark.parametrize("rows", [0, 128, 256])
+@pytest.mark.parametrize("S,causal", [(640, True), (1024, False)])
+def test_scores_that_overflow_downwards(S, causal, rows):
+    """Keys whose fp32 scores are -inf, among finite ones of every row's first block and in both halves of the wave that holds
+    them: probability 0, and nothing else changes.  rows 0 takes the hand-sequenced kernel (tests/test_dispatch_rules.py), 128
+    and 256 the others."""
+    import torch
+    from paper_2401_09149_amd import binding
+    print(f"case S{S} {causal} rows {rows}", flush=True)
+    dev, D, H = "cuda:0", 128, 2
+    q, k, v = (randn_bf16((1, S, H, D), 970 + j) for j in range(3))
+    q[..., 0], k[..., 0] = 2.0 ** 100, 0.0
+    for key in (2, 5, 40, 300):   # (keys 0 to 3 and 4 to 7 lie in different halves)
+        k[:, key, :, 0] = -(2.0 ** 100)
+    before = binding.ie_attn_set_tile_rows(rows)
+    try:
+        o, lse = binding.attn_fwd(q.to(dev), k.to(dev), v.to(dev), D ** -0.5, causal)
+        torch.cuda.synchronize()
+    finally:
+        binding.ie_attn_set_tile_rows(before)
+    ro, rlse = ora.attn_fwd(to64(q), to64(k), to64(v), D ** -0.5, causal)
+    assert np.abs(to64(o) - ro).max() <= TOL_O
+    assert np.abs(to64(lse) - rlse).max() <= TOL_LSE
