@@ -20,7 +20,8 @@ namespace ie {
 
 // FLIP: items flip_lo .. flip_hi - 1 run in the opposite order, eight at a time (AttnParams; a kernel of its own, because the
 // order costs a small launch 0.4 us, 4 %, before its first copy).
-template <int D, bool FLIP>
+// LAZY (head dimension 64): unmasked blocks after a row's first look for no maximum (below).
+template <int D, bool FLIP, bool LAZY>
 __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
   constexpr int BM = 128, BN = 64;
   constexpr int NKS = D / 16;  // k-steps of the QK^T product
@@ -95,7 +96,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
   // first look for no maximum: their exponentials are taken against the reference as it is, and a block in which one lane's
   // 16 of them sum to more than this is done again with the true one.  Probabilities of up to 2^24 are as exact as others,
   // in fp32 and in bf16.  12 of 70 VALU instructions per block less: 8192 x 16 170 -> 161 us, 4 x 8192 x 16 bidirectional
-  // 1212 -> 1165 (at head dimension 128 within 1 %).
+  // 1212 -> 1165 (at head dimension 128 within 1 %).  The products then wait for the whole block's sum, which only other
+  // waves hide: fwd64_is_lazy in dispatch.hpp says where there are enough of them.
   constexpr float kRedo = 16777216.0f;
   float m = -INFINITY;  // reference maximum, raw (unscaled) score units
   float l = 0.f;        // this lane's share of the row sum (its half of the keys)
@@ -163,10 +165,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
       };
       bf16x8 pf[2];
       float block_sum = 0.f;
-      float& sum = D == 64 ? block_sum : l;
+      float& sum = LAZY ? block_sum : l;
       auto exponentials = [&]() __attribute__((always_inline)) {
         const float mc = m * c;
-        if (D == 64) sum = 0.f;
+        if (LAZY) sum = 0.f;
 #pragma unroll
         for (int sblk = 0; sblk < 2; ++sblk) {
           bf16x2 pr[4];
@@ -185,14 +187,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
         for (int r = 0; r < 16; ++r)
           if (32 * j + 8 * (r >> 2) + (r & 3) > lim) s[r] = -INFINITY;
       }
-      const bool search = D != 64 || need_mask || (j == 0 && kt == 0);
+      const bool search = !LAZY || need_mask || (j == 0 && kt == 0);
       if (search) move_reference(m + slack_raw);
       exponentials();
       if (!search && __builtin_amdgcn_ballot_w64(!(sum <= kRedo)) != 0) {
         move_reference(m);
         exponentials();
       }
-      if (D == 64) l += sum;
+      if (LAZY) l += sum;
       // O^T += V^T P^T
 #pragma unroll
       for (int sblk = 0; sblk < 2; ++sblk)
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_seq_kernel(AttnParams p)
   if (row_ok && h == 0) p.lse_out[((int64_t)tc.b * p.Hq + tc.h) * p.S + k_begin + row_rel] = (m * c + __builtin_amdgcn_logf(l_full)) * kLn2;
 }
 
-template <int D, bool SEQ, bool FLIP>
+template <int D, bool SEQ, bool FLIP, bool LAZY>
 static int launch_fwd_d(AttnParams p, int cus, hipStream_t st) {
   constexpr int smem = SEQ ? FwdSeqCfg::SMEM_BYTES : 2 * 2 * 64 * D * 2;   // (two stages of a K and a V tile)
   const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs);
@@ -470,7 +472,7 @@ static int launch_fwd_d(AttnParams p, int cus, hipStream_t st) {
     if (rc) return rc;
     attn_fwd_seq_kernel<<<dim3((unsigned)grid), dim3(kThreads), smem, st>>>(p);
   } else {
-    int rc = kernel_setup(setup, attn_fwd_kernel<D, FLIP>, smem, &per_cu);
+    int rc = kernel_setup(setup, attn_fwd_kernel<D, FLIP, LAZY>, smem, &per_cu);
     if (rc) return rc;
     // Of a causal launch's items, dealt from the heaviest down, the second one on each CU goes by the opposite order: the
     // heaviest with the lightest (4096 x 32 148 -> 142 us, 8192 x 16 at head dimension 64 166 -> 157).
@@ -478,7 +480,7 @@ static int launch_fwd_d(AttnParams p, int cus, hipStream_t st) {
       p.flip_lo = cus & ~7;
       p.flip_hi = (int32_t)(grid < 2 * p.flip_lo ? grid & ~(int64_t)7 : 2 * p.flip_lo);
     }
-    attn_fwd_kernel<D, FLIP><<<dim3((unsigned)grid), dim3(kThreads), smem, st>>>(p);
+    attn_fwd_kernel<D, FLIP, LAZY><<<dim3((unsigned)grid), dim3(kThreads), smem, st>>>(p);
   }
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : hip_fail(e);
@@ -486,8 +488,13 @@ static int launch_fwd_d(AttnParams p, int cus, hipStream_t st) {
 
 template <int D>
 static int launch_fwd_narrow(AttnParams p, int cus, hipStream_t st) {
-  const bool flip = p.causal && !p.cu && tiles_per_head(p.S, 128, nullptr, 0) * p.B * p.Hq > cus;
-  return flip ? launch_fwd_d<D, false, true>(p, cus, st) : launch_fwd_d<D, false, false>(p, cus, st);
+  const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs), items = tiles * p.B * p.Hq;
+  const bool flip = p.causal && !p.cu && items > cus;
+  if constexpr (D == 64) {
+    if (fwd64_is_lazy(items, p.causal != 0, p.cu != nullptr, cus))
+      return flip ? launch_fwd_d<D, false, true, true>(p, cus, st) : launch_fwd_d<D, false, false, true>(p, cus, st);
+  }
+  return flip ? launch_fwd_d<D, false, true, false>(p, cus, st) : launch_fwd_d<D, false, false, false>(p, cus, st);
 }
 
 int launch_fwd(AttnParams p, int D, hipStream_t st) {
@@ -500,7 +507,7 @@ int launch_fwd(AttnParams p, int D, hipStream_t st) {
   if (tile_rows_setting.load(std::memory_order_relaxed) == 0)   // (not the caller's choice)
     route = fwd128_route(p.B, p.S, p.Hq, p.causal != 0, p.num_docs, cus, narrow);
   if (route == Fwd128::kWide) return launch_fwd_wide(p, st);
-  return route == Fwd128::kSeq ? launch_fwd_d<128, true, false>(p, cus, st) : launch_fwd_narrow<128>(p, cus, st);
+  return route == Fwd128::kSeq ? launch_fwd_d<128, true, false, false>(p, cus, st) : launch_fwd_narrow<128>(p, cus, st);
 }
 
 }  // namespace ie

@@ -158,6 +158,13 @@ inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_
   return narrow <= seq ? Fwd128::kNarrow : Fwd128::kSeq;
 }
 
+// Forward at head dimension 64: unmasked blocks without a search for their maximum (LAZY in attn_fwd.hip)?  Where a wave has
+// its SIMD to itself the search is the shorter way (lazy : search, 165 x 40 6.34 : 6.12 us, 2911 x 4 41.9 : 39.9, 5374 x 1 72.3 :
+// 68.9); with several waves per SIMD it is work that can be left out.  Lazy against search in 200 launches, on average:
+// bidirectional, up to 256 items, 1.03, 256 to 384 0.995, 512 to 640 0.965, more 0.975; causal, where an item's mean is half its
+// longest, 256 to 384 1.03, 512 to 640 1.01, 640 to 800 1.00, more 0.98; packed 384 to 512 1.035, 800 to 1024 1.00, more 0.98.
+inline bool fwd64_is_lazy(int64_t items, bool causal, bool packed, int64_t cus) { return items > (causal || packed ? 3 : 1) * cus; }
+
 // Recomputing dQ kernel at head dimension 128: products as 16x16x32 MFMAs (dq_item_16) instead of 32x32x16 (dq_item)?
 // The 16x16x32 form costs less power per product and more issue slots, so it gains where the launch keeps the chip at its
 // power limit and loses where most CUs wait for a few heavy items: dQ alone, 32x32x16 against it, 32768 x 16 causal

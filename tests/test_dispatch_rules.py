@@ -21,6 +21,7 @@ extern "C" int one_launch_128(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int
 extern "C" int fwd_128(int64_t B, int64_t S, int64_t Hq, int causal, int64_t docs, int narrow) {
   return (int)ie::fwd128_route(B, S, Hq, causal != 0, docs, 256, narrow != 0);
 }
+extern "C" int lazy_64(int64_t items, int causal, int packed) { return ie::fwd64_is_lazy(items, causal != 0, packed != 0, 256); }
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
@@ -87,6 +88,29 @@ WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
 def test_fwd128_route(rules, B, S, Hq, causal, docs, narrow, route):
     i64 = ctypes.c_int64
     assert rules.fwd_128(i64(B), i64(S), i64(Hq), causal, i64(docs), narrow) == route
+
+
+@pytest.mark.parametrize("S,H,causal,packed,lazy", [
+    (512, 2, 1, 0, False),       # the smallest calls: a wave per SIMD
+    (4096, 8, 0, 0, False),      # 256 items
+    (4096, 9, 0, 0, True),
+    (8192, 12, 1, 0, False),     # 768
+    (8192, 13, 1, 0, True),
+    (2000, 64, 0, 0, True),
+    (8192, 12, 1, 1, False),
+    (8192, 12, 0, 1, False),
+    (8192, 13, 0, 1, True),
+])
+def test_fwd64_search(rules, S, H, causal, packed, lazy):
+    assert bool(rules.lazy_64(ctypes.c_int64(-(-S // 128) * H), causal, packed)) == lazy
+
+
+def test_cases_of_both_forward_bodies_at_head_dimension_64(rules):
+    from test_gpu_fwd_routes import LAZY_64, SEARCHING_64
+    for cases, lazy in ((LAZY_64, True), (SEARCHING_64, False)):
+        for S, H, causal, lens in cases:
+            tiles = S // 128 + len(lens) if lens else -(-S // 128)
+            assert bool(rules.lazy_64(ctypes.c_int64(tiles * H), int(causal), int(lens is not None))) == lazy, (S, H)
 
 
 TWO, DEALT, QUEUED = 0, 1, 2   # enum Bwd64

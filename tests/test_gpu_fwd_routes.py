@@ -1,7 +1,7 @@
 """The forward kernel of one hand-sequenced wave per SIMD (attn_fwd_seq_kernel) at its edges: lengths around its 32-key
 blocks, 64-key tiles, the four stages of its ring and its 128-row items, against the oracle.  Calls of these sizes take it
-by fwd128_route (csrc/dispatch.hpp), which tests/test_dispatch_rules.py checks.  And scores far below the others of their
-row, in all forward kernels."""
+by fwd128_route (csrc/dispatch.hpp), which tests/test_dispatch_rules.py checks.  And scores far below and far above the
+others of their row, in all forward kernels."""
 import numpy as np
 import pytest
 from oracle import attention as ora
@@ -60,3 +60,33 @@ def test_scores_that_overflow_downwards(S, causal, rows):
     ro, rlse = ora.attn_fwd(to64(q), to64(k), to64(v), D ** -0.5, causal)
     assert np.abs(to64(o) - ro).max() <= TOL_O
     assert np.abs(to64(lse) - rlse).max() <= TOL_LSE
+
+
+LAZY_64 = [(513, 160, True, None), (641, 60, False, None), (1500, 66, True, None),   # (the causal ones also in flipped order)
+           (1500, 64, True, [1, 65, 330, 1104]), (1500, 52, False, [64, 1400, 0, 36])]
+SEARCHING_64 = [(513, 2, True, None), (641, 3, False, None), (1500, 2, True, [1, 65, 330, 1104])]
+
+
+@pytest.mark.parametrize("S,H,causal,lens", LAZY_64 + SEARCHING_64)
+def test_blocks_beyond_the_reference_at_head_dimension_64(S, H, causal, lens):
+    """Scores far above those of their row's first block at head dimension 64, where launches of many items (LAZY_64) take
+    unmasked blocks against the maximum that is there, and again where a lane's sum passes 2^24: keys grow along the
+    sequence, so that it does.  All heads hold the same data and have to show the bits of the first."""
+    import torch
+    from paper_2401_09149_amd import binding
+    print(f"case S{S} H{H} {causal} {lens}", flush=True)
+    dev, D = "cuda:0", 64
+    q, k, v = (randn_bf16((1, S, 1, D), 980 + j) for j in range(3))
+    k = (k.float() * torch.linspace(0.2, 14.0, S).view(1, S, 1, 1)).to(torch.bfloat16)
+    cu = None if lens is None else torch.tensor([0] + lens, dtype=torch.int32).cumsum(0).to(torch.int32)
+    # scores of the last query (of the longest document, without the last 128 keys, where masks are) against its first block's
+    end, n = (S, S) if lens is None else (int(cu[lens.index(max(lens)) + 1]), max(lens))
+    s = to64(k)[0, end - n:end - 128, 0] @ to64(q)[0, end - 1, 0] * D ** -0.5 / np.log(2.0)
+    assert s.max() > s[:32].max() + 24
+    o, lse = binding.attn_fwd(*(t.to(dev).repeat(1, 1, H, 1) for t in (q, k, v)), D ** -0.5, causal, None if cu is None else cu.to(dev))
+    torch.cuda.synchronize()
+    assert torch.equal(o, o[:, :, :1].expand_as(o)) and torch.equal(lse, lse[:, :1].expand_as(lse))
+    ro, rlse = ora.attn_fwd(to64(q), to64(k), to64(v), D ** -0.5, causal, None if cu is None else np.asarray(cu))
+    # (the bounds of test_against_the_oracle, for the same reason)
+    assert (np.abs(to64(o[:, :, :1]) - ro) <= 2.0 ** -8 * (np.abs(to64(v)).max() + np.abs(ro)) + 1e-3).all()
+    assert np.abs(to64(lse[:, :1]) - rlse).max() <= TOL_LSE * max(1.0, np.abs(rlse).max() / 8)
