@@ -5,6 +5,10 @@
 
 namespace ie {
 
+// Items (workgroups of 256 threads) of a launch that the hardware deals out: a HIP launch has fewer than 2^32 threads.
+// Persistent launches draw up to 2^31 - 1 items from their queues, so a call of more than this goes to them.
+constexpr int64_t kDealtItems = ((int64_t)1 << 32) / 256 - 1;
+
 // Backward pass at head dimension 64, work queues: dK/dV and dQ items in one queued launch (attn_bwd_both_kernel), or a
 // queued launch each?  bwd64_route below decides first whether queues serve the call at all; the figures here are from before
 // the queues became cheap to enter and leave and dK/dV lost its masks, and the line between the two has not moved for the
@@ -58,6 +62,7 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
   if (doc < 1) doc = 1;
   const double mean = causal ? (doc + 1) / 2 : doc, R = (double)resident;
   const double nk = per_head * (double)(B * Hkv), nq = per_head * (double)(B * Hq);
+  if (nk + nq > (double)kDealtItems) return Bwd64::kTwo;
   const double kv = doc * group * kKvStep + kKvItem, kv_work = nk * (mean * group * kKvStep + kKvItem);
   const double q = doc * kQStep + kQItem, q_work = nq * (mean * kQStep + kQItem);
   const auto longer = [](double x, double y) { return x > y ? x : y; };
@@ -93,6 +98,7 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
   if (doc < 1) doc = 1;
   const double mean = causal ? (doc + 1) / 2 : doc, C = (double)cus;
   const double nk = per_head * (double)(B * Hkv), nq = per_head * (double)(B * Hq);
+  if (nk + nq > (double)kDealtItems) return false;
   if (num_docs) {
     constexpr double kKv = 5.06, kKvIt = 7.25, kQ = 5.69, kQIt = 1.76, kQOwn = 8.22, kQOwnIt = 1.26, kOwn = 6.5, kLongest = 3.14;
     const auto longer = [](double x, double y) { return x > y ? x : y; };
@@ -138,6 +144,7 @@ inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_
   double doc = num_docs ? (double)S / 128 / (double)num_docs : n128;   // tiles of a document (packed: on average)
   if (doc < 1) doc = 1;
   const double mean = causal ? (doc + 1) / 2 : doc, heads = (double)(B * Hq);
+  if (n128 * heads > (double)kDealtItems) return Fwd128::kWide;
   const auto time = [&](const Cost& c, double per_head, double tiles, double mean_tiles) {
     const double n = per_head * heads, slots = (double)cus * c.per_cu;
     const double longest = c.step * tiles + c.item, work = n * (c.step * mean_tiles + c.item) / slots;

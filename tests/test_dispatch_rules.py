@@ -159,6 +159,22 @@ def test_bwd128_launches(rules, B, S, Hq, Hkv, causal, docs, one):
     assert bool(rules.one_launch_128(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))) == one
 
 
+@pytest.mark.parametrize("B,S,Hq,Hkv,causal,docs", [
+    (2 ** 20, 1, 8, 8, 1, 0),              # 2^24 backward items, 2^23 in the forward
+    (2 ** 19, 100, 24, 12, 0, 0),
+    (1, 2 ** 22, 32, 32, 1, 2 ** 19),      # packed: 2^19 short documents
+])
+def test_more_items_than_a_launch_has_workgroups(rules, B, S, Hq, Hkv, causal, docs):
+    """A launch that the hardware deals out has fewer than 2^32 threads (2^24 workgroups); queues take what is beyond."""
+    i64 = ctypes.c_int64
+    args = (i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))
+    items = B * (S // 128 + docs if docs else -(-S // 128))
+    assert items * (Hq + Hkv) >= 2 ** 24
+    assert rules.route_64(*args) != DEALT and not rules.one_launch_128(*args)
+    if items * Hq >= 2 ** 24:
+        assert rules.fwd_128(i64(B), i64(S), i64(Hq), causal, i64(docs), 0) == WIDE
+
+
 @pytest.mark.parametrize("S,H,wide,causal,packed,on16", [
     (32768, 16, 1, 1, 0, True),
     (4096, 32, 1, 0, 0, True),
