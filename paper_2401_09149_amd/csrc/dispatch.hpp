@@ -9,39 +9,6 @@ namespace ie {
 // Persistent launches draw up to 2^31 - 1 items from their queues, so a call of more than this goes to them.
 constexpr int64_t kDealtItems = ((int64_t)1 << 32) / 256 - 1;
 
-// Backward pass at head dimension 64, work queues: dK/dV and dQ items in one queued launch (attn_bwd_both_kernel), or a
-// queued launch each?  bwd64_route below decides first whether queues serve the call at all; the figures here are from before
-// the queues became cheap to enter and leave and dK/dV lost its masks, and the line between the two has not moved for the
-// calls that still come here.
-// `resident`: workgroups of the shared launch that the chip holds at once (two per CU).
-// The shared launch saves a launch and fills the other kind's tail; it costs dQ its third wave per SIMD, and dK/dV items
-// that would have a CU to themselves share it.  Kernel time of the whole pass, two launches against one, 256 CUs:
-//   all items resident: one launch always (128 to 4096 tokens, every head count and group: 1.05-2.9 times faster);
-//   a little more work than that: the queues' fixed cost decides (700 tokens x 48 heads 94 : 109 us, 384 x 96
-//   107 : 127, but 640 x 80 130 : 125 and 1600 x 24 112 : 99);
-//   fewer dK/dV items than CUs: one launch while the pass is short (4096 x 16, 2 per group, bidirectional 360 : 326 us;
-//   8192 x 8, 4 per group 1011 : 1090; 8192 x 8, 8 per group 1792 : 2113);
-//   one to two rounds of dK/dV items, the last of them nearly empty or causal: one launch at any length (8192 x 16, 2 per
-//   group, causal 780 : 612 us; 6000 x 24, 2 per group, bidirectional 993 : 831);
-//   more rounds: one launch up to about 150 pairs of 128 x 128 tiles per CU, twice that where groups make the
-//   heaviest dK/dV items longer (2000 x 64 bidirectional 343 : 325 us, 4096 x 64 causal 627 : 613; above it
-//   8192 x 32 bidirectional 1980 : 2010, 8192 x 64 causal 2022 : 2149, 8192 x 64 bidirectional 3875 : 4117).
-inline bool bwd64_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus,
-                                int64_t resident) {
-  const int64_t per_head = num_docs ? S / 128 + num_docs : (S + 127) / 128;   // items per (batch entry, head)
-  const int64_t nk = per_head * B * Hkv, nq = per_head * B * Hq;
-  if (nk + nq <= resident) return true;
-  double doc = num_docs ? (double)S / 128 / (double)num_docs : (double)per_head;   // tiles of a document (packed: on average)
-  if (doc < 1) doc = 1;
-  const double work = (double)nq * (causal ? (doc + 1) / 2 : doc) / (double)cus;   // pairs of tiles per CU
-  if (5 * (nk + nq) < 7 * resident && work < 7) return false;
-  const int64_t group = Hq / Hkv;
-  if (nk <= cus) return nk > cus / 4 && (work <= 24 || work <= (double)(nk - cus / 2));
-  if (causal) return nk < 2 * resident || work <= (group == 1 ? 150 : 300);
-  const int64_t rounds = (nk + resident - 1) / resident;
-  return work <= 150 || 10 * nk <= (group >= 4 ? 8 : 7) * resident * rounds;
-}
-
 // Backward pass at head dimension 64: a persistent launch for each kind of item (kTwo), one launch that the hardware deals out
 // (kDealt, two workgroups per CU) or one with queues (kQueued)?  As at head dimension 128 (below) the shared launch has one
 // tail instead of two, and its dQ items run at two waves per SIMD instead of three.  The estimated time of one launch is
@@ -51,8 +18,9 @@ inline bool bwd64_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, b
 // Fitted to 220 shapes, 128 to 16384 tokens: 0.2 % slower than the better of one and two launches on average, 13 % at most
 // (packed documents of 221 to 3749 tokens); 0.3 % and 9 % on 140 others.
 // Queues keep the order that shares K and V in L2, which pays in long bidirectional items of many heads per group (12800 x
-// 12, 8 per group, 4225 : 4037 us, 8600 x 20, 4 per group, 2024 : 1962); elsewhere the dealt launch is 1 % behind at most
-// or ahead by up to 50 %.
+// 12, 8 per group, 4225 : 4037 us, 8600 x 20, 4 per group, 2024 : 1962); elsewhere, and where a call has no dK/dV item for
+// every CU, the dealt launch is 1 % behind at most or ahead by up to 50 %.
+// `resident`: workgroups of the shared launch that the chip holds at once (two per CU).
 enum class Bwd64 { kTwo, kDealt, kQueued };
 inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus, int64_t resident) {
   constexpr double kKvStep = 2.46, kKvItem = 18.2, kQStep = 4.82, kQItem = 0.23;   // us per pair of tiles, per item
@@ -72,7 +40,7 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
   else if (nk > (double)cus) two = longer(two, kv_work / R);
   if (one >= kTwoLaunches * two + kLaunch) return Bwd64::kTwo;
   const bool long_groups = !causal && num_docs == 0 && group >= 4 && per_head * group >= 200 && nk + nq >= 5 * R;
-  return long_groups && bwd64_in_one_launch(B, S, Hq, Hkv, causal, num_docs, cus, resident) ? Bwd64::kQueued : Bwd64::kDealt;
+  return long_groups && nk > (double)cus ? Bwd64::kQueued : Bwd64::kDealt;
 }
 
 // Backward pass at head dimension 128: all dK/dV and dQ items in one launch that the hardware deals out (the ONCE form of

@@ -9,9 +9,6 @@ import pytest
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2401_09149_amd", "csrc")
 SHIM = """
 #include "dispatch.hpp"
-extern "C" int one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
-  return ie::bwd64_in_one_launch(B, S, Hq, Hkv, causal != 0, docs, 256, 512);
-}
 extern "C" int route_64(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t docs) {
   return (int)ie::bwd64_route(B, S, Hq, Hkv, causal != 0, docs, 256, 512);
 }
@@ -38,30 +35,6 @@ def rules(tmp_path_factory):
         f.write(SHIM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
     return ctypes.CDLL(lib)
-
-
-@pytest.mark.parametrize("B,S,Hq,Hkv,causal,docs,one", [
-    (1, 512, 2, 2, 1, 0, True),       # everything resident
-    (1, 4096, 8, 8, 0, 0, True),      # exactly
-    (1, 700, 48, 48, 1, 0, False),    # 576 short items
-    (1, 640, 80, 80, 1, 0, True),
-    (1, 1600, 24, 24, 1, 0, True),
-    (1, 4096, 16, 8, 0, 0, True),     # fewer dK/dV items than CUs
-    (1, 8192, 8, 2, 0, 0, False),
-    (1, 8192, 8, 1, 0, 0, False),
-    (1, 8192, 16, 8, 1, 0, True),     # one to two rounds
-    (1, 6000, 24, 12, 0, 0, True),
-    (4, 2000, 16, 16, 0, 0, True),    # several rounds
-    (4, 4096, 16, 16, 1, 0, True),
-    (2, 8192, 16, 16, 0, 0, False),
-    (4, 8192, 16, 16, 1, 0, False),
-    (4, 8192, 16, 16, 0, 0, False),
-    (1, 65536, 16, 16, 1, 35, False),  # packed: by the mean document
-    (1, 16384, 16, 16, 1, 31, True),
-])
-def test_bwd64_launches(rules, B, S, Hq, Hkv, causal, docs, one):
-    i64 = ctypes.c_int64
-    assert bool(rules.one_launch(i64(B), i64(S), i64(Hq), i64(Hkv), causal, i64(docs))) == one
 
 
 WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
@@ -129,6 +102,10 @@ TWO, DEALT, QUEUED = 0, 1, 2   # enum Bwd64
     (4, 8192, 16, 16, 0, 0, TWO),
     (1, 13900, 24, 3, 0, 0, QUEUED),    # long items of grouped heads
     (1, 6400, 56, 14, 0, 0, QUEUED),
+    (1, 6400, 64, 16, 0, 0, QUEUED),
+    (1, 6400, 136, 17, 0, 0, TWO),      # dK/dV items that nearly fill their last round
+    (1, 2020, 192, 6, 0, 0, DEALT),     # fewer dK/dV items than CUs
+    (1, 13900, 24, 3, 0, 1, DEALT),     # packed
     (1, 13900, 24, 3, 1, 0, DEALT),
     (1, 16384, 16, 16, 1, 31, DEALT),
 ])
@@ -241,7 +218,35 @@ def test_dq_full_chip_cases_take_the_16x16x32_form(rules):
             assert rules.dq16(i64(items[0]), i64(items[1]), wide, int(causal), int(packed)), (name, wide)
 
 
-def test_fused_sequence_parallel_cases_take_both_forms(rules):
+def backward_form(rules, B, S, Hq, Hkv, D, causal, docs):
+    """"two" launches, one that the hardware deals out, or one with queues, as launch_bwd_d (csrc/attn_bwd.hip) chooses."""
     i64 = ctypes.c_int64
-    assert rules.one_launch(i64(1), i64(2048), i64(24), i64(24), 1, i64(0)) and 16 * 48 > 512
-    assert not rules.one_launch(i64(1), i64(512), i64(80), i64(80), 1, i64(0))
+    items = B * (S // 128 + docs if docs else -(-S // 128)) * (Hq + Hkv)
+    if items <= (512 if D == 64 else 256):   # all resident
+        return "dealt"
+    args = (i64(B), i64(S), i64(Hq), i64(Hkv), int(causal), i64(docs))
+    return ("two", "dealt", "queued")[rules.route_64(*args) if D == 64 else rules.one_launch_128(*args)]
+
+
+def test_launches_of_the_shared_launch_cases(rules):
+    """The cases of test_gpu_bwd_both take the launches that they are there for."""
+    from test_gpu_bwd_both import DEALT as dealt, MORE, QUEUED as queued
+    for B, S, Hq, Hkv, D, causal, lens in dealt + MORE:
+        assert backward_form(rules, B, S, Hq, Hkv, D, causal, len(lens) if lens else 0) == "dealt", (B, S, Hq)
+    B, S, Hq, Hkv, D, causal, _ = queued
+    assert backward_form(rules, B, S, Hq, Hkv, D, causal, 0) == "queued"
+
+
+def test_fused_sequence_parallel_cases_take_every_form(rules):
+    """The cases of test_gpu_sp_fused take the kernels that they name, and together every one that has a chunked form."""
+    from test_gpu_sp_fused import CASES
+    i64, seen = ctypes.c_int64, set()
+    for B, Sl, Hq, Hkv, D, P, causal, fwd, bwd in CASES:
+        S, Hql, Hkvl = P * Sl, Hq // P, Hkv // P
+        assert backward_form(rules, B, S, Hql, Hkvl, D, causal, 0) == bwd, (Sl, Hq, D)
+        if D == 128:
+            narrow = S <= 4096 or (S <= 8192 and -(-S // 256) * B * Hql < 512)   # fwd_prefers_128_rows (csrc/launch.hpp)
+            assert ("wide", "narrow", "seq")[rules.fwd_128(i64(B), i64(S), i64(Hql), int(causal), i64(0), int(narrow))] == fwd, (Sl, Hq)
+        seen |= {(D, "fwd", fwd), (D, "bwd", bwd)}
+    assert seen == {(64, "fwd", "narrow"), *((128, "fwd", f) for f in ("wide", "narrow", "seq")),
+                    *((64, "bwd", b) for b in ("two", "dealt", "queued")), *((128, "bwd", b) for b in ("two", "dealt"))}

@@ -1,7 +1,9 @@
-"""dK/dV and dQ in one launch (attn_bwd_both_kernel) against the same pass in two: the same item bodies, so the same
-bits.  The one-launch form is taken where all items of both kinds are resident at once, and also where
-bwd64_in_one_launch or bwd128_in_one_launch (csrc/dispatch.hpp) says so; a call that names the phases one by one takes the
-kernels of their own."""
+"""dK/dV and dQ in one launch (attn_bwd_both_kernel) against the same pass in two.  At head dimension 64 the item bodies
+are the same; at head dimension 128 the shared launch's dQ items (dq_item_seq) are others, which add the same products in
+the same order as dq_item: the same bits either way.  The one-launch form is taken where all items of both kinds are
+resident at once, and also where bwd64_route or bwd128_in_one_launch (csrc/dispatch.hpp) says so
+(tests/test_dispatch_rules.py holds the cases to it); a call that names the phases one by one takes the kernels of their
+own."""
 import numpy as np
 import pytest
 from oracle import attention as ora
@@ -11,18 +13,32 @@ from parity_util import compare_all, randn_bf16, to64
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,S,Hq,Hkv,D,causal,lens", [
+DEALT = [
     (1, 512, 2, 2, 64, True, None),       # 16 items, one per workgroup
-    (1, 4096, 8, 8, 64, True, None),      # 512 items: the last size with one per workgroup
-    (1, 4097, 8, 8, 64, True, None),      # one tile more per head: work queues, one-row tiles
-    (4, 2000, 16, 16, 64, False, None),   # work queues, several items per workgroup
-    (1, 700, 48, 48, 64, True, None),     # 576 short items: two launches either way
+    (1, 4096, 8, 8, 64, True, None),      # 512 items: the last size where all are resident
+    (1, 4097, 8, 8, 64, True, None),      # one tile more per head: a second round, one-row tiles
+    (4, 2000, 12, 12, 64, False, None),   # three rounds
+    (1, 700, 48, 48, 64, True, None),     # 576 short items
     (1, 8192, 4, 1, 64, False, None),     # fewer dK/dV items than CUs
     (1, 1, 3, 1, 64, True, None),
     (1, 1000, 4, 2, 64, True, [300, 0, 1, 699]),
     (1, 2047, 8, 8, 128, True, None),     # 256 items
     (2, 300, 6, 2, 128, False, None),
     (1, 1000, 4, 1, 128, True, [300, 0, 1, 699]),
+]
+MORE = [
+    (1, 300, 128, 128, 128, True, None),   # 384 items of each kind
+    (2, 200, 160, 40, 128, False, None),   # 160 dK/dV items of four heads each, 640 of dQ
+    (1, 260, 150, 150, 128, True, [1, 259]),
+    (1, 1000, 80, 80, 64, True, None),     # 640 items of each kind
+    (1, 1300, 80, 20, 64, False, None),
+    (1, 500, 150, 150, 64, True, [1, 499]),
+]
+QUEUED = (1, 6400, 56, 14, 64, False, None)   # long bidirectional items of grouped heads
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,D,causal,lens", DEALT + [
+    (4, 2000, 16, 16, 64, False, None),   # (several rounds, of which the call makes two launches as well)
 ])
 def test_one_launch_gives_the_bits_of_two(B, S, Hq, Hkv, D, causal, lens):
     import torch
@@ -47,14 +63,7 @@ def test_one_launch_gives_the_bits_of_two(B, S, Hq, Hkv, D, causal, lens):
             assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("B,S,Hq,Hkv,D,causal,lens", [
-    (1, 300, 128, 128, 128, True, None),   # 384 items of each kind
-    (2, 200, 160, 40, 128, False, None),   # 160 dK/dV items of four heads each, 640 of dQ
-    (1, 260, 150, 150, 128, True, [1, 259]),
-    (1, 1000, 80, 80, 64, True, None),     # 640 items of each kind
-    (1, 1300, 80, 20, 64, False, None),
-    (1, 500, 150, 150, 64, True, [1, 499]),
-])
+@pytest.mark.parametrize("B,S,Hq,Hkv,D,causal,lens", MORE)
 def test_more_items_than_cus_in_one_launch(B, S, Hq, Hkv, D, causal, lens):
     """Dealt out by the hardware: all kv heads hold the same data, so every group of heads has to show the bits of the
     first, which is checked against the oracle."""
@@ -79,19 +88,18 @@ def test_more_items_than_cus_in_one_launch(B, S, Hq, Hkv, D, causal, lens):
 
 
 def test_queued_launch_gives_the_bits_of_two():
-    """Long bidirectional items of grouped heads at head dimension 64 (bwd64_route)."""
     import torch
     from paper_2401_09149_amd import binding
-    B, S, Hq, Hkv, D = 1, 6400, 56, 14, 64
+    B, S, Hq, Hkv, D, causal, _ = QUEUED
     dev, scale = "cuda:0", D ** -0.5
     q, do = (randn_bf16((B, S, Hq, D), 900 + j).to(dev) for j in range(2))
     k, v = (randn_bf16((B, S, Hkv, D), 902 + j).to(dev) for j in range(2))
-    o, lse = binding.attn_fwd(q, k, v, scale, False)
+    o, lse = binding.attn_fwd(q, k, v, scale, causal)
     ws = binding.alloc_bwd_workspace(q, k)
     want, got = ([torch.full_like(t, float("nan")) for t in (q, k, v)] for _ in range(2))
     for phase in (binding.BWD_DELTA, binding.BWD_DQ, binding.BWD_DKDV):
-        binding.ie_attn_bwd_phases(q, k, v, o, do, lse, *want, None, scale, False, ws, phase)
-    binding.ie_attn_bwd(q, k, v, o, do, lse, *got, None, scale, False, ws)
+        binding.ie_attn_bwd_phases(q, k, v, o, do, lse, *want, None, scale, causal, ws, phase)
+    binding.ie_attn_bwd(q, k, v, o, do, lse, *got, None, scale, causal, ws)
     torch.cuda.synchronize()
     for a, b in zip(got, want):
         assert torch.equal(a, b)

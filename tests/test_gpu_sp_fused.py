@@ -7,20 +7,28 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,Sl,Hq,Hkv,D,P,causal", [
-    (1, 256, 8, 8, 128, 4, True),      # one tile per chunk in the forward
-    (2, 512, 8, 4, 128, 2, True),      # batch entries interleaved with peers, GQA widths
-    (1, 1024, 4, 4, 128, 4, False),    # not causal
-    (2, 256, 4, 2, 64, 2, True),       # head dimension 64 (the other forward kernel)
-    (1, 1024, 48, 48, 64, 2, True),    # head dimension 64, 768 backward items: the shared launch with its queues
-    (1, 256, 160, 160, 64, 2, True),   # 640 short ones: a launch each for dK/dV and dQ
-    (1, 2048, 16, 16, 128, 8, True),   # two local heads, eight peers
-    (1, 8192, 32, 32, 128, 4, True),   # the paper's own plan for 7B at 32K (s_sp = 4: 8 heads per GPU), full size
-])
-def test_fused_calls_equal_unpack_attention_pack(B, Sl, Hq, Hkv, D, P, causal):
+# What a call takes where it chooses by itself: its forward kernel and its backward launches (test_dispatch_rules.py).
+CASES = [
+    (1, 256, 8, 8, 128, 4, True, "seq", "dealt"),         # one tile per chunk in the forward
+    (2, 512, 8, 4, 128, 2, True, "seq", "dealt"),         # batch entries interleaved with peers, GQA widths
+    (1, 1024, 4, 4, 128, 4, False, "seq", "dealt"),       # not causal
+    (2, 256, 4, 2, 64, 2, True, "narrow", "dealt"),       # head dimension 64 (the other forward kernel)
+    (1, 1024, 48, 48, 64, 2, True, "narrow", "dealt"),    # 768 backward items on 512 slots
+    (1, 256, 160, 160, 64, 2, True, "narrow", "dealt"),   # 640 short ones
+    (4, 1024, 32, 32, 64, 2, False, "narrow", "two"),     # several rounds: a launch each for dK/dV and dQ
+    (1, 2048, 144, 18, 64, 2, False, "narrow", "queued"),  # long items of grouped heads: one launch with queues
+    (2, 1024, 64, 64, 128, 2, True, "narrow", "two"),     # many items of 128 rows
+    (1, 2048, 16, 16, 128, 8, True, "seq", "dealt"),      # two local heads, eight peers
+    (1, 8192, 32, 32, 128, 4, True, "wide", "two"),       # the paper's own plan for 7B at 32K (s_sp = 4: 8 heads per GPU), full size
+]
+
+
+@pytest.mark.parametrize("B,Sl,Hq,Hkv,D,P,causal,fwd,bwd", CASES)
+def test_fused_calls_equal_unpack_attention_pack(B, Sl, Hq, Hkv, D, P, causal, fwd, bwd):
     from paper_2401_09149_amd import binding
     try:
-        for rows in ((256, 128) if D == 128 else (0,)):   # both sizes of the forward's and dQ's work items
+        # head dimension 128: both sizes of the forward's and dQ's work items, and the choice by size
+        for rows in ((256, 128, 0) if D == 128 else (0,)):
             binding.ie_attn_set_tile_rows(rows)
             _fused_against_unfused(B, Sl, Hq, Hkv, D, P, causal)
     finally:
