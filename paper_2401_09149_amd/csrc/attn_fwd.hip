@@ -474,8 +474,7 @@ static int launch_fwd_d(AttnParams p, int cus, hipStream_t st) {
   } else {
     int rc = kernel_setup(setup, attn_fwd_kernel<D, FLIP, LAZY>, smem, &per_cu);
     if (rc) return rc;
-    // Of a causal launch's items, dealt from the heaviest down, the second one on each CU goes by the opposite order: the
-    // heaviest with the lightest (4096 x 32 148 -> 142 us, 8192 x 16 at head dimension 64 166 -> 157).
+    // The second item on each CU goes by the opposite order (fwd_flips in dispatch.hpp).
     if (FLIP) {
       p.flip_lo = cus & ~7;
       p.flip_hi = (int32_t)(grid < 2 * p.flip_lo ? grid & ~(int64_t)7 : 2 * p.flip_lo);
@@ -489,7 +488,7 @@ static int launch_fwd_d(AttnParams p, int cus, hipStream_t st) {
 template <int D>
 static int launch_fwd_narrow(AttnParams p, int cus, hipStream_t st) {
   const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs), items = tiles * p.B * p.Hq;
-  const bool flip = p.causal && !p.cu && items > cus;
+  const bool flip = fwd_flips(items, tiles, p.causal != 0, p.cu != nullptr, cus);
   if constexpr (D == 64) {
     if (fwd64_is_lazy(items, p.causal != 0, p.cu != nullptr, cus))
       return flip ? launch_fwd_d<D, false, true, true>(p, cus, st) : launch_fwd_d<D, false, false, true>(p, cus, st);

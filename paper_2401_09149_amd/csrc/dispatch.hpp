@@ -133,6 +133,16 @@ inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_
   return narrow <= seq ? Fwd128::kNarrow : Fwd128::kSeq;
 }
 
+// 128-row forward: the second item on each CU in the opposite order (FLIP in attn_fwd.hip), the heaviest with the lightest?
+// Causal launches dealt from the heaviest item down, of one to eight items per CU, a head of eight tiles or more.  In the same
+// order : in the opposite one, D = 128: 256 to 512 items of 16 tiles and more 1.057 on average, 768 to 1024 1.041 (4096 x 32
+// 148 : 142 us), up to 2048 1.00 to 1.01; D = 64 1.01 to 1.03.  Items of a few tiles differ little and lose more by the longer
+// way to the first copy (4 x 647 x 36 35.6 : 38.4, 4 x 524 x 38 29.7 : 31.0, 4 x 263 x 41 17.3 : 18.8); in longer launches
+// the second item is one of many, and the order of the lists shares more in L2 (64 tiles, 3000 items and more, 0.995).
+inline bool fwd_flips(int64_t items, int64_t tiles, bool causal, bool packed, int64_t cus) {
+  return causal && !packed && tiles >= 8 && items > cus && items <= 8 * cus;
+}
+
 // Forward at head dimension 64: unmasked blocks without a search for their maximum (LAZY in attn_fwd.hip)?  Where a wave has
 // its SIMD to itself the search is the shorter way (lazy : search, 165 x 40 6.34 : 6.12 us, 2911 x 4 41.9 : 39.9, 5374 x 1 72.3 :
 // 68.9); with several waves per SIMD it is work that can be left out.  Lazy against search in 200 launches, on average:

@@ -18,6 +18,7 @@ extern "C" int one_launch_128(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int
 extern "C" int fwd_128(int64_t B, int64_t S, int64_t Hq, int causal, int64_t docs, int narrow) {
   return (int)ie::fwd128_route(B, S, Hq, causal != 0, docs, 256, narrow != 0);
 }
+extern "C" int flips(int64_t items, int64_t tiles, int causal, int packed) { return ie::fwd_flips(items, tiles, causal != 0, packed != 0, 256); }
 extern "C" int lazy_64(int64_t items, int causal, int packed) { return ie::fwd64_is_lazy(items, causal != 0, packed != 0, 256); }
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
@@ -61,6 +62,25 @@ WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
 def test_fwd128_route(rules, B, S, Hq, causal, docs, narrow, route):
     i64 = ctypes.c_int64
     assert rules.fwd_128(i64(B), i64(S), i64(Hq), causal, i64(docs), narrow) == route
+
+
+@pytest.mark.parametrize("B,S,H,causal,packed,flips", [
+    (1, 4096, 32, 1, 0, True),
+    (2, 4096, 32, 1, 0, True),     # eight items per CU
+    (1, 4096, 65, 1, 0, False),
+    (1, 1024, 33, 1, 0, True),     # eight tiles
+    (1, 1024, 32, 1, 0, False),    # one item per CU
+    (4, 647, 36, 1, 0, False),     # short items
+    (4, 263, 41, 1, 0, False),
+    (1, 896, 60, 1, 0, False),
+    (1, 4096, 32, 0, 0, False),
+    (1, 4096, 32, 1, 1, False),
+    (1, 1100, 60, 1, 0, True),     # the GPU test's sizes (test_gpu_fwd_routes.py)
+    (1, 1100, 20, 1, 0, False),
+])
+def test_forward_order(rules, B, S, H, causal, packed, flips):
+    i64, tiles = ctypes.c_int64, -(-S // 128)
+    assert bool(rules.flips(i64(B * tiles * H), i64(tiles), causal, packed)) == flips
 
 
 @pytest.mark.parametrize("S,H,causal,packed,lazy", [

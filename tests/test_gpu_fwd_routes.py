@@ -62,7 +62,7 @@ def test_scores_that_overflow_downwards(S, causal, rows):
     assert np.abs(to64(lse) - rlse).max() <= TOL_LSE
 
 
-LAZY_64 = [(513, 160, True, None), (641, 60, False, None), (1500, 66, True, None),   # (the causal ones also in flipped order)
+LAZY_64 = [(513, 160, True, None), (641, 60, False, None), (1500, 66, True, None),   # (1500 x 66 also in flipped order)
            (1500, 64, True, [1, 65, 330, 1104]), (1500, 52, False, [64, 1400, 0, 36])]
 SEARCHING_64 = [(513, 2, True, None), (641, 3, False, None), (1500, 2, True, [1, 65, 330, 1104])]
 
@@ -90,3 +90,21 @@ def test_blocks_beyond_the_reference_at_head_dimension_64(S, H, causal, lens):
     # (the bounds of test_against_the_oracle, for the same reason)
     assert (np.abs(to64(o[:, :, :1]) - ro) <= 2.0 ** -8 * (np.abs(to64(v)).max() + np.abs(ro)) + 1e-3).all()
     assert np.abs(to64(lse[:, :1]) - rlse).max() <= TOL_LSE * max(1.0, np.abs(rlse).max() / 8)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_items_in_the_opposite_order(D):
+    """Launches that run the second item on each CU in the opposite order (fwd_flips in csrc/dispatch.hpp) do the same items
+    as launches of fewer heads, which do not."""
+    import torch
+    from paper_2401_09149_amd import binding
+    dev, S, H = "cuda:0", 1100, 60
+    q, k, v = (randn_bf16((1, S, H, D), 990 + j).to(dev) for j in range(3))
+    before = binding.ie_attn_set_tile_rows(128)
+    try:
+        o, lse = binding.attn_fwd(q, k, v, D ** -0.5, True)
+        parts = [binding.attn_fwd(*(t[:, :, h:h + 20].contiguous() for t in (q, k, v)), D ** -0.5, True) for h in (0, 20, 40)]
+        torch.cuda.synchronize()
+    finally:
+        binding.ie_attn_set_tile_rows(before)
+    assert torch.equal(o, torch.cat([a for a, _ in parts], 2)) and torch.equal(lse, torch.cat([b for _, b in parts], 1))
