@@ -101,12 +101,16 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
 // on average count 1.3 times in 128-row items: their longest are longer than the mean says.
 // Wide or narrow as sizes alone say : now: 8192 x 8 175 : 148 us, 8192 x 4 146 : 121, 6000 x 8 117 : 96, 4096 x 16 91 : 81,
 // 29952 x 1 593 : 422; packed 8000 x 100 in 63 documents 74 : 30, 2222 x 2 in 4 44 : 24, 16384 x 2 in 24 53 : 32.
-// Fitted to 500 launches, 128 to 65536 tokens: 0.5 % slower than the best on average, 16 % faster than sizes alone would
-// have it (packed 34 %), 7 % slower at most (packed 3696 x 33).
+// `last`: a last bidirectional round that leaves a slot of every CU free (4129 x 17 wide 228 : narrow 196 us, 5747 x 14 299 :
+// 269).  `first`, `again`: what kSeq's deep ring costs where it fills on many CUs at once, and where a CU's second item fills it
+// anew (seq : narrow, 555 x 47 20.5 : 17.5, 2 x 413 x 31 16.1 : 14.5; 2 x 652 x 27, 324 items, 24.2 : 20.2).
+// Dense, 2124 launches, 128 to 16384 tokens: 0.2 % slower than the best of the three on average, 12 % at most, and 4 % slower
+// than what sizes alone say at most (3 % faster on average); without `last`, `first` and `again` 0.35 %, 20 % and 20 %.  Packed,
+// 1608 calls of 1024 to 65536 tokens: 0.9 % slower than the best, 32 % faster than sizes alone, 5 % slower at most.
 enum class Fwd128 { kWide, kNarrow, kSeq };
 inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_t num_docs, int64_t cus, bool prefer_narrow) {
-  struct Cost { double step, item, alone, per_cu; };
-  constexpr Cost kWideCost{2.37, 22.7, 1.0, 1}, kNarrowCost{3.18, 7.1, 0.84, 2}, kSeqCost{1.97, 8.0, 1.0, 1};
+  struct Cost { double step, item, alone, per_cu, last, first, again; };
+  constexpr Cost kWideCost{2.37, 22.7, 1.0, 1, 1, 0, 0}, kNarrowCost{3.18, 7.1, 0.84, 2, 0.78, 0, 0}, kSeqCost{1.97, 8.0, 1.0, 1, 1, 1.5, 2};
   const double n128 = num_docs ? (double)(S / 128 + num_docs) : (double)((S + 127) / 128);
   const double n256 = num_docs ? (double)(S / 256 + num_docs) : (double)((S + 255) / 256);
   double doc = num_docs ? (double)S / 128 / (double)num_docs : n128;   // tiles of a document (packed: on average)
@@ -116,14 +120,19 @@ inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_
   const auto time = [&](const Cost& c, double per_head, double tiles, double mean_tiles) {
     const double n = per_head * heads, slots = (double)cus * c.per_cu;
     const double longest = c.step * tiles + c.item, work = n * (c.step * mean_tiles + c.item) / slots;
-    if (n <= (double)cus) return longest * c.alone;
-    if (n > slots && !causal) return (double)(int64_t)((n + slots - 1) / slots) * longest;
+    const double first = num_docs ? 0 : c.first, again = num_docs ? 0 : c.again;   // (fitted to dense input)
+    if (n <= (double)cus) return longest * c.alone + first * n / (double)cus;
+    if (n > slots && !causal) {
+      const double full = (double)(int64_t)(n / slots), rest = n - full * slots;
+      const double last = rest == 0 ? 0 : rest <= (double)cus && !num_docs ? c.last : 1;
+      return (full + last) * longest + again;
+    }
     double t = work > longest * c.alone ? work : longest * c.alone;
     if (n > slots && n <= 2 * slots) {
       const double pair = 2 * (longest - c.step * tiles * slots / n);
       t = pair > t ? pair : t;
     }
-    return t;
+    return n > slots ? t + again : t;
   };
   const double margin = causal ? 1.04 : 1.08, spread = num_docs && doc > 12 ? 1.3 : 1.0;
   const double wide = time(kWideCost, n256, doc + 1, mean + 0.5) * (prefer_narrow ? margin : 1.0);

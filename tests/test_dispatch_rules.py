@@ -52,6 +52,13 @@ WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
     (2, 430, 40, 1, 0, 1, NARROW),      # short items, a second round
     (1, 3000, 16, 0, 0, 1, NARROW),
     (1, 3001, 32, 1, 0, 1, NARROW),
+    (1, 4129, 17, 0, 0, 1, NARROW),     # a last round of a few items
+    (1, 5747, 14, 0, 0, 1, NARROW),
+    (1, 6917, 14, 0, 0, 1, WIDE),       # and one of many
+    (1, 555, 47, 0, 0, 1, NARROW),      # short items on nearly every CU
+    (2, 413, 31, 1, 0, 1, NARROW),
+    (1, 555, 8, 1, 0, 1, SEQ),
+    (2, 652, 27, 1, 0, 1, NARROW),      # and a second one on some
     (1, 4096, 32, 1, 0, 1, NARROW),
     (1, 32768, 32, 1, 0, 0, WIDE),
     (1, 16384, 16, 1, 0, 0, WIDE),
