@@ -505,7 +505,11 @@ int launch_fwd(AttnParams p, int D, hipStream_t st) {
   Fwd128 route = narrow ? Fwd128::kNarrow : Fwd128::kWide;
   if (tile_rows_setting.load(std::memory_order_relaxed) == 0)   // (not the caller's choice)
     route = fwd128_route(p.B, p.S, p.Hq, p.causal != 0, p.num_docs, cus, narrow);
-  if (route == Fwd128::kWide) return launch_fwd_wide(p, st);
+  if (route == Fwd128::kWide) {
+    const int rc = launch_fwd_wide(p, st);
+    if (rc != kErrBusy || !narrow) return rc;   // (what sizes alone give to 128-row items runs without a queue if none is free)
+    route = Fwd128::kNarrow;
+  }
   return route == Fwd128::kSeq ? launch_fwd_d<128, true, false, false>(p, cus, st) : launch_fwd_narrow<128>(p, cus, st);
 }
 

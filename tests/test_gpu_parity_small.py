@@ -384,6 +384,40 @@ def test_captured_forward_calls_pin_their_slots_and_the_rest_get_ie_err_busy():
     assert r.returncode == 0 and "pinned 256" in r.stdout
 
 
+_AND_A_CALL_THAT_CAN_DO_WITHOUT = r"""
+S, H = 6917, 14   # bidirectional: 256-row items by estimated time, 128-row items by sizes alone
+q, k, v = (torch.randn((1, S, H, D), generator=g).to(torch.bfloat16).to(dev) for _ in range(3))
+want = binding.attn_fwd(q, k, v, scale, False, None)
+binding.ie_attn_set_tile_rows(0)
+got = binding.attn_fwd(q, k, v, scale, False, None)
+captured = tuple(torch.zeros_like(t) for t in want)
+graph2 = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph2):
+    binding.ie_attn_fwd(q, k, v, *captured, None, scale, False)
+for _ in range(3):
+    for t in captured:
+        t.zero_()
+    graph2.replay()
+    torch.cuda.synchronize()
+    for a, b, c in zip(want, got, captured):
+        assert torch.equal(a, b) and torch.equal(a, c)
+print("served")
+"""
+
+
+def test_a_call_that_could_do_without_a_queue_runs_when_none_is_free():
+    """Calls that take the 256-row forward only because its estimated time is the shorter (fwd128_route in
+    csrc/dispatch.hpp) fall back on the 128-row one, which needs no slot.  In a process of its own, as above."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    script = _PIN_ALL_SLOTS.format(root=root) + _AND_A_CALL_THAT_CAN_DO_WITHOUT
+    r = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=100)
+    print(r.stdout[-2000:], r.stderr[-2000:], flush=True)
+    assert r.returncode == 0 and "served" in r.stdout
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_random_shapes(oracle, seed):
     """Shapes, head groupings, masks and document splits drawn from a seeded generator: whatever combination of ragged
