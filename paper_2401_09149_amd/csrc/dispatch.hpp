@@ -15,8 +15,13 @@ constexpr int64_t kDealtItems = ((int64_t)1 << 32) / 256 - 1;
 // its longest item or the work per resident workgroup, whichever is longer; two launches come to 2.3 times the dK/dV items
 // alone.  Before (queued or two) : now: 8192 x 8, 8 per group, bidirectional 1791 : 1144 us, 8192 x 8, 4 per group, 1009 : 621,
 // 700 x 48 93 : 44, 640 x 80 126 : 57, 4096 x 16 x 4 605 : 520 (two), 8192 x 16 x 4 1970 : 1759 (two).
-// Fitted to 220 shapes, 128 to 16384 tokens: 0.2 % slower than the better of one and two launches on average, 13 % at most
-// (packed documents of 221 to 3749 tokens); 0.3 % and 9 % on 140 others.
+// Fitted to 220 dense shapes, 128 to 16384 tokens; on 1486 others 0.4 % slower than the better of one and two launches on
+// average, 18 % at most, and 1 % slower than before at most but for one (3692 x 9, bidirectional, 4 %).
+// Packed documents have prices of their own: a call's longest document, whose length the host does not know, counts as 2.4
+// times the mean, and the dQ items of a launch of their own run three to a CU.  1530 calls of 1024 to 65536 tokens: 0.2 %
+// slower than the better form on average, 12 % at most, none slower than before; with the dense prices 2.3 %, 34 % and 17 %
+// (two : dealt, 52129 x 8, 4 per group, in 53 documents 439 : 339 us, 15593 x 24, 4 per group, in 11 600 : 449; 65065 x 136, 4
+// per group, in 261 3683 : 4130).
 // Queues keep the order that shares K and V in L2, which pays in long bidirectional items of many heads per group (12800 x
 // 12, 8 per group, 4225 : 4037 us, 8600 x 20, 4 per group, 2024 : 1962); elsewhere, and where a call has no dK/dV item for
 // every CU, the dealt launch is 1 % behind at most or ahead by up to 50 %.
@@ -31,15 +36,23 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
   const double mean = causal ? (doc + 1) / 2 : doc, R = (double)resident;
   const double nk = per_head * (double)(B * Hkv), nq = per_head * (double)(B * Hq);
   if (nk + nq > (double)kDealtItems) return Bwd64::kTwo;
+  const auto longer = [](double x, double y) { return x > y ? x : y; };
+  if (num_docs) {
+    constexpr double kKv = 2.38, kKvIt = 12.0, kQ = 6.81, kQIt = 0.5, kQOwn = 9.06, kQOwnIt = 1.83, kOwn = 14.6, kLongest = 2.38;
+    const double all = (double)S / 128, top = kLongest * doc < all ? kLongest * doc : longer(all, 1);   // tiles of the longest document
+    const double kv = top * group * kKv + kKvIt, kv_all = nk * (mean * group * kKv + kKvIt) / R;
+    const double one = longer(longer(kv, top * kQ + kQIt), kv_all + nq * (mean * kQ + kQIt) / R);
+    const double two = longer(kv, kv_all) + longer(0.69 * (top * kQOwn + kQOwnIt), nq * (mean * kQOwn + kQOwnIt) / (1.5 * R)) + kOwn;
+    return one < two ? Bwd64::kDealt : Bwd64::kTwo;
+  }
   const double kv = doc * group * kKvStep + kKvItem, kv_work = nk * (mean * group * kKvStep + kKvItem);
   const double q = doc * kQStep + kQItem, q_work = nq * (mean * kQStep + kQItem);
-  const auto longer = [](double x, double y) { return x > y ? x : y; };
   const double one = nk + nq > (double)cus ? longer(kAlone * kv, (kv_work + q_work) / R) : kAlone * longer(kv, q);
   double two = kAlone * kv;   // dK/dV items: an item per CU, all of them resident, or rounds of them
   if (nk > R && !causal) two = (double)(int64_t)((nk + R - 1) / R) * kv;
   else if (nk > (double)cus) two = longer(two, kv_work / R);
   if (one >= kTwoLaunches * two + kLaunch) return Bwd64::kTwo;
-  const bool long_groups = !causal && num_docs == 0 && group >= 4 && per_head * group >= 200 && nk + nq >= 5 * R;
+  const bool long_groups = !causal && group >= 4 && per_head * group >= 200 && nk + nq >= 5 * R;
   return long_groups && nk > (double)cus ? Bwd64::kQueued : Bwd64::kDealt;
 }
 

@@ -135,6 +135,11 @@ TWO, DEALT, QUEUED = 0, 1, 2   # enum Bwd64
     (1, 13900, 24, 3, 0, 1, DEALT),     # packed
     (1, 13900, 24, 3, 1, 0, DEALT),
     (1, 16384, 16, 16, 1, 31, DEALT),
+    (1, 52129, 8, 2, 1, 53, DEALT),     # packed: the longest document's tail
+    (1, 15593, 24, 6, 1, 11, DEALT),
+    (1, 10106, 40, 10, 1, 6, DEALT),
+    (1, 65065, 136, 34, 1, 261, TWO),   # and rounds enough to hide it
+    (1, 38376, 136, 34, 1, 74, TWO),
 ])
 def test_bwd64_route(rules, B, S, Hq, Hkv, causal, docs, route):
     i64 = ctypes.c_int64
