@@ -64,11 +64,14 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
 // of tiles and per item.  Backward pass, two launches : one: 2048 x 16 140 : 83 us, 4096 x 8 231 : 131, 8192 x 4 377 : 235,
 // 8192 x 8 492 : 433, 3001 x 32, 4 per group, 400 : 328, 10180 x 8 x 4, 8 per group, bidirectional 6134 : 5102; but
 // 2 x 4096 x 32 890 : 920, 14443 x 37 5860 : 6222.
-// Fitted to 220 shapes, 128 to 16384 tokens: 0.2 % slower than the better form on average, 7 % at most, and 5 % slower than
-// two launches at most (3143 x 16, 2 per group, bidirectional); 0.2 % on 160 others.
+// Fitted to 220 shapes; on 2124 others, 128 to 16384 tokens, 0.15 % slower than the better form on average, and none more than
+// 3 % slower than two launches.  Bidirectional calls, of equal items, take one launch for a gain of 4 % only: the estimate is out
+// by more where both forms fill their rounds (two : one, 13880 x 19 5694 : 6072 us, 2568 x 20, 2 per group, 248 : 266, 12173 x 17
+// 3901 : 4037).
 // Packed documents are priced by themselves (their items are short, and the longest of a call, whose lengths the host does
-// not know, counts as three times the mean): 109 calls of 2048 to 65536 tokens, 0.1 % slower than the better form on average,
-// 5 % at most; 22.7 tiles on average x 4 heads 579 (two) : 509 (one) us, 50000 x 8 in 2.1 tiles 350 : 426.
+// not know, counts as three times the mean, or as all of a call of fewer documents than that): 1608 calls of 1024 to 65536
+// tokens, 0.35 % slower than the better form on average; 22.7 tiles on average x 4 heads 579 (two) : 509 (one) us, 50000 x 8 in
+// 2.1 tiles 350 : 426, 13439 x 36, 4 per group, in two documents 3670 : 4060.
 inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus) {
   constexpr double kKvStep = 2.87, kKvItem = 19.4;     // dK/dV: us per pair of tiles, per item
   constexpr double kQStep = 3.23, kQItem = 0.34;       // dQ in the shared launch
@@ -83,9 +86,10 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
   if (num_docs) {
     constexpr double kKv = 5.06, kKvIt = 7.25, kQ = 5.69, kQIt = 1.76, kQOwn = 8.22, kQOwnIt = 1.26, kOwn = 6.5, kLongest = 3.14;
     const auto longer = [](double x, double y) { return x > y ? x : y; };
-    const double kv = kLongest * doc * group * kKv + kKvIt, kv_all = nk * (mean * group * kKv + kKvIt) / C;
-    const double one = longer(longer(kv, kLongest * doc * kQ + kQIt), kv_all + nq * (mean * kQ + kQIt) / C);
-    const double two = longer(kv, kv_all) + longer(0.6 * kLongest * doc * kQOwn + kQOwnIt, nq * (mean * kQOwn + kQOwnIt) / (2 * C)) + kOwn;
+    const double all = (double)((S + 127) / 128), top = kLongest * doc < all ? kLongest * doc : all;   // tiles of the longest document
+    const double kv = top * group * kKv + kKvIt, kv_all = nk * (mean * group * kKv + kKvIt) / C;
+    const double one = longer(longer(kv, top * kQ + kQIt), kv_all + nq * (mean * kQ + kQIt) / C);
+    const double two = longer(kv, kv_all) + longer(0.6 * top * kQOwn + kQOwnIt, nq * (mean * kQOwn + kQOwnIt) / (2 * C)) + kOwn;
     return 1.02 * one < two;
   }
   const auto span = [&](double n, double longest, double work) {   // of a launch of n items
@@ -101,7 +105,7 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
     one = (even > kv ? even : kv) + kTail * (causal ? kQStep + kQItem : q);
   }
   const double two = span(nk, kv, kv_work) + span(nq / 2, doc * kQ2Step + kQ2Item, nq / 2 * (mean * kQ2Step + kQ2Item)) + kLaunch;
-  return 1.02 * one < two;
+  return (causal ? 1.02 : 1.04) * one < two;
 }
 
 // Forward at head dimension 128: 256-row items in a persistent kernel (kWide, attn_fwd_wide_kernel), 128-row items two

@@ -162,6 +162,11 @@ def test_bwd64_route(rules, B, S, Hq, Hkv, causal, docs, route):
     (1, 65536, 8, 8, 1, 20, False),
     (1, 50000, 8, 8, 1, 180, False),   # packed: short documents, many items
     (1, 35000, 4, 4, 1, 12, True),     # long ones on few heads
+    (1, 13439, 36, 9, 1, 2, False),    # two documents: neither is three times their mean
+    (1, 18080, 28, 7, 1, 2, False),
+    (1, 13880, 19, 19, 0, 0, False),   # equal items: a gain of 4 % at least
+    (1, 2568, 20, 10, 0, 0, False),
+    (1, 12173, 17, 17, 0, 0, False),
 ])
 def test_bwd128_launches(rules, B, S, Hq, Hkv, causal, docs, one):
     i64 = ctypes.c_int64
