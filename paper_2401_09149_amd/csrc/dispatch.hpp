@@ -114,8 +114,10 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
 // one item's way in and out with the other's key loop.  The choice goes by the estimated times: the longest item or the
 // work per resident workgroup, with items priced per tile of 128 keys and per item; for causal launches of one to two items
 // per slot also the first pair of items that share one.  `prefer_narrow`: what sizes alone say (fwd_prefers_128_rows in
-// launch.hpp), left for another kernel where that is ahead by 4 % (bidirectional 8 %).  Packed documents longer than 12 tiles
-// on average count 1.3 times in 128-row items: their longest are longer than the mean says.
+// launch.hpp), left for another kernel where that is ahead by 4 % (bidirectional 8 %; kNarrow of more than eight dense items per CU
+// 10 %, for its price then runs into the power limit: 4 x 4621 x 36 wide 866 : narrow 917 us).  Packed documents longer than 12
+// tiles on average count 1.3 times in 128-row items (bidirectional, 10 tiles, 1.4: 50671 x 9 in 35 documents wide 792 : narrow
+// 873): their longest are longer than the mean says.
 // Wide or narrow as sizes alone say : now: 8192 x 8 175 : 148 us, 8192 x 4 146 : 121, 6000 x 8 117 : 96, 4096 x 16 91 : 81,
 // 29952 x 1 593 : 422; packed 8000 x 100 in 63 documents 74 : 30, 2222 x 2 in 4 44 : 24, 16384 x 2 in 24 53 : 32.
 // `last`: a last bidirectional round that leaves a slot of every CU free (4129 x 17 wide 228 : narrow 196 us, 5747 x 14 299 :
@@ -151,9 +153,10 @@ inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_
     }
     return n > slots ? t + again : t;
   };
-  const double margin = causal ? 1.04 : 1.08, spread = num_docs && doc > 12 ? 1.3 : 1.0;
+  const double margin = causal ? 1.04 : 1.08, spread = !num_docs ? 1.0 : causal ? (doc > 12 ? 1.3 : 1.0) : (doc > 10 ? 1.4 : 1.0);
+  const double many = !num_docs && n128 * heads > 8 * (double)cus ? 1.1 : margin;
   const double wide = time(kWideCost, n256, doc + 1, mean + 0.5) * (prefer_narrow ? margin : 1.0);
-  const double narrow = time(kNarrowCost, n128, doc, mean) * spread * (prefer_narrow ? 1.0 : margin);
+  const double narrow = time(kNarrowCost, n128, doc, mean) * spread * (prefer_narrow ? 1.0 : many);
   const double seq = time(kSeqCost, n128, doc, mean) * spread * margin;
   if (wide <= narrow && wide <= seq) return Fwd128::kWide;
   return narrow <= seq ? Fwd128::kNarrow : Fwd128::kSeq;

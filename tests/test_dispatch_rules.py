@@ -65,6 +65,8 @@ WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
     (1, 8000, 100, 1, 63, 0, NARROW),   # packed: short documents
     (1, 2222, 2, 1, 4, 0, SEQ),
     (1, 65536, 8, 1, 17, 0, WIDE),      # long ones
+    (1, 50671, 9, 0, 35, 0, WIDE),
+    (4, 4621, 36, 1, 0, 0, WIDE),       # many items
 ])
 def test_fwd128_route(rules, B, S, Hq, causal, docs, narrow, route):
     i64 = ctypes.c_int64
