@@ -31,7 +31,8 @@
  *     dimension 128, 256-row items) takes them from 256 slots of a device array inside the library, which
  *     every launch leaves cleared; a slot is handed out again only when the event recorded behind its
  *     previous launch has completed, or to a launch on the same stream, and when every slot is in flight on
- *     other streams the call returns IE_ERR_BUSY rather than share one.
+ *     other streams the call returns IE_ERR_BUSY rather than share one.  (Dense calls of up to 4096 tokens, or
+ *     8192 with fewer than two 256-row items per CU, then run on 128-row items, which need no slot.)
  *     A call enqueues kernel launches only (no memset, no copy, no allocation), so it may be recorded
  *     under stream capture; a forward call captured into a graph keeps its counter slot for the life of
  *     the process (at most 256 such calls), and two replays of one graph must not run at the same time.

@@ -278,7 +278,7 @@ __device__ __forceinline__ unsigned int dq_item(const AttnParams& p, char* smem,
 }
 // The same item on v_mfma_f32_16x16x32_bf16, for head dimension 128: half the accumulator traffic per product of the
 // 32x32x16 form, which the power limit turns into time (10.39 -> 9.79 ms at 32K x 32 heads, 343 -> 324 us at 4K x 32
-// bidirectional; 227 instead of 253 registers; dq128_on_16x16x32 in dispatch.hpp has the sizes where it loses).  A 32 x 32
+// bidirectional; 231 instead of 253 registers; dq128_on_16x16x32 in dispatch.hpp has the sizes where it loses).  A 32 x 32
 // block of scores is 2 x 2 MFMA blocks, so a lane has TWO query columns (16 qb + lane % 16) and, with g = lane / 16, the
 // keys 16 kb + key4(g) + 0..3 of each; the eight of both key blocks are one B operand of the dQ product.  key4 swaps the
 // middle two groups (0, 8, 4, 12): the transpose loads of two neighbouring lane groups then address rows 0..3 and 8..11,

@@ -232,9 +232,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
 // one element of the softmax of block b; K rows of block b + 2 and V^T fragments of block b land in the registers that
 // their predecessors have just left.  No running maximum: as in attn_fwd_wide.hip a block is done again, against its true
 // maximum, when its sum outgrows 2^24.  64-key K/V tiles in a ring of four stages, one barrier per tile.
-// Bound: VALU and MFMA issue of the one wave.  A lone item of 128 x 8192 takes 112 us against 134 compiler-scheduled with two
-// workgroups to a CU: 8192 x 8 175 -> 148 us, 6000 x 8 117 -> 96, 2500 x 20 54 -> 46; with more than two items per CU their ways
-// in and out, 8 us each, stand alone and it falls behind (3001 x 32 87 : 98; fwd128_route in dispatch.hpp).
+// Bound: the wave's one instruction stream; of all SIMDs' cycles at 8192 x 8, where the CUs are at work nine tenths of the time,
+// MFMAs take 39 % and VALU issue 32 %, the rest goes to 1.5 LDS reads per MFMA, copies and waits.  Against the compiler-scheduled kernel with two workgroups to a CU: 8192 x 1 (no
+// CU has two items) 144 -> 118 us, 8192 x 8 179 -> 154, 6000 x 8 116 -> 94, 2500 x 20 54 -> 46; with more than two items per CU
+// their ways in and out, 8 us each, stand alone and it falls behind (3001 x 32 87 : 98; fwd128_route in dispatch.hpp).
 struct FwdSeqCfg {
   static constexpr int D = 128, BM = 128, BN = 64, STAGES = 4;
   static constexpr int TILE_BYTES = BN * D * 2, STAGE_BYTES = 2 * TILE_BYTES;   // K tile, then V tile

@@ -65,11 +65,11 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
 // 8192 x 8 492 : 433, 3001 x 32, 4 per group, 400 : 328, 10180 x 8 x 4, 8 per group, bidirectional 6134 : 5102; but
 // 2 x 4096 x 32 890 : 920, 14443 x 37 5860 : 6222.
 // Fitted to 220 shapes; on 2124 others, 128 to 16384 tokens, 0.15 % slower than the better form on average, and none more than
-// 3 % slower than two launches.  Bidirectional calls, of equal items, take one launch for a gain of 4 % only: the estimate is out
+// 5 % slower than two launches.  Bidirectional calls, of equal items, take one launch for a gain of 4 % only: the estimate is out
 // by more where both forms fill their rounds (two : one, 13880 x 19 5694 : 6072 us, 2568 x 20, 2 per group, 248 : 266, 12173 x 17
 // 3901 : 4037).
 // Packed documents are priced by themselves (their items are short, and the longest of a call, whose lengths the host does
-// not know, counts as three times the mean, or as all of a call of fewer documents than that): 1608 calls of 1024 to 65536
+// not know, counts as three times the mean, though not as more than the call): 1608 calls of 1024 to 65536
 // tokens, 0.35 % slower than the better form on average; 22.7 tiles on average x 4 heads 579 (two) : 509 (one) us, 50000 x 8 in
 // 2.1 tiles 350 : 426, 13439 x 36, 4 per group, in two documents 3670 : 4060.
 inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus) {
@@ -118,8 +118,8 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
 // 10 %, for its price then runs into the power limit: 4 x 4621 x 36 wide 866 : narrow 917 us).  Packed documents longer than 12
 // tiles on average count 1.3 times in 128-row items (bidirectional, 10 tiles, 1.4: 50671 x 9 in 35 documents wide 792 : narrow
 // 873): their longest are longer than the mean says.
-// Wide or narrow as sizes alone say : now: 8192 x 8 175 : 148 us, 8192 x 4 146 : 121, 6000 x 8 117 : 96, 4096 x 16 91 : 81,
-// 29952 x 1 593 : 422; packed 8000 x 100 in 63 documents 74 : 30, 2222 x 2 in 4 44 : 24, 16384 x 2 in 24 53 : 32.
+// Wide or narrow as sizes alone say : now: 8192 x 8 179 : 154 us, 8192 x 4 145 : 121, 6000 x 8 116 : 94, 4096 x 16 90 : 79,
+// 29952 x 1 595 : 419; packed 8000 x 100 in 63 documents 74 : 30, 2222 x 2 in 4 44 : 24, 16384 x 2 in 24 53 : 32.
 // `last`: a last bidirectional round that leaves a slot of every CU free (4129 x 17 wide 228 : narrow 196 us, 5747 x 14 299 :
 // 269).  `first`, `again`: what kSeq's deep ring costs where it fills on many CUs at once, and where a CU's second item fills it
 // anew (seq : narrow, 555 x 47 20.5 : 17.5, 2 x 413 x 31 16.1 : 14.5; 2 x 652 x 27, 324 items, 24.2 : 20.2).

@@ -40,8 +40,8 @@ inline int64_t tiles_per_head(int64_t S, int64_t ts, const int32_t* cu, int32_t 
   return cu ? S / ts + num_docs : ceil_div(S, ts);
 }
 
-// Head dimension 128 has two forward kernels and two workgroup sizes of the recomputing dQ kernel: 256-row items
-// (one persistent workgroup per CU, the faster steady state) and 128-row items (two workgroups per CU).  With few
+// Head dimension 128 has 256-row items (one persistent workgroup per CU, the faster steady state) and 128-row items in the
+// forward (the latter in two kernels, two workgroups per CU or one) and in the recomputing dQ kernel (two per CU).  With few
 // 256-row items per CU a launch is as long as its heaviest item, and a 256-row item costs about 15 us around its
 // key loop, as much as four of its key tiles; measured on dense causal shapes from 4K x 24 heads to 16K x 16 heads,
 // the 128-row forward wins up to 4K tokens at any head count and at 8K below 2 items per CU, the 128-row dQ only at

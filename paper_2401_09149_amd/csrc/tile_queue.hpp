@@ -8,7 +8,7 @@
 // clock (6 % apart in the same kernel), so the slowest XCD finishes late while the others idle.
 // Here every XCD has its own list (the items of "its" heads, in the order decode_tile defines, so
 // that the workgroups of an XCD still stream the same head's K/V through its L2 together), and a
-// workgroup whose list is empty takes from the next XCD's list.
+// workgroup whose list is empty takes from whichever of the others still have entries (next_work).
 //
 // The counters of a launch (kQueueBytes, `AttnParams::q_counters`) are memory that belongs to
 // that launch alone: the backward kernels take them from the caller's workspace, the forward from
