@@ -1556,9 +1556,9 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     if (items >= ((int64_t)1 << 31)) return kErrShape;
     AttnParams a = p;
     a.tiles = (int32_t)tiles;
-    // (grouped heads in one list keep the order in which the workgroups arrive: dealt by index, dK/dV 32046 x 16, 8 per
-    // group, took 7.2 ms instead of 6.9, 12520 x 32, 8 per group, 2.62 instead of 2.48)
-    const bool deal = a.Hq == a.Hkv || p.B * a.Hkv % 8 == 0;
+    const int cus = cu_count(&e);
+    if (e != hipSuccess) return hip_fail(e);
+    const bool deal = dkdv_deals(items, p.B * a.Hkv % 8 != 0, a.Hq != a.Hkv, kStore, cus);
     const QueueLaunch ql = tile_queue_prepare(a, p.ws_counters + kCountersDkdv, items, a.Hkv, per_cu, st, cleared_by_delta, deal);
     if (ql.err != hipSuccess) return hip_fail(ql.err);
     attn_bwd_dkdv_kernel<D, kStore, kChunked><<<dim3((unsigned)ql.grid), dim3(kThreads), smem, st>>>(a);

@@ -108,6 +108,14 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
   return (causal ? 1.02 : 1.04) * one < two;
 }
 
+// dK/dV items of a persistent launch: may the first ones go by workgroup index (tile_queue.hpp)?  One list (a head count that
+// is no multiple of eight) keeps the order in which the workgroups arrive where heads are grouped (dealt : by arrival, 32046 x
+// 16, 8 per group, 7.2 : 6.9 ms, 12520 x 32, 8 per group, 2.62 : 2.48), and with dS stored from five items per four CUs (9984 x 6
+// 332 : 318 us, 6528 x 10 244 : 235, 3328 x 15 123 : 118; 320 items, 8192 x 5, 235 : 234, 288, 12288 x 3, 326 : 329).
+inline bool dkdv_deals(int64_t items, bool one_list, bool grouped, bool stores_ds, int64_t cus) {
+  return !one_list || !(grouped || (stores_ds && 4 * items > 5 * cus));
+}
+
 // Forward at head dimension 128: 256-row items in a persistent kernel (kWide, attn_fwd_wide_kernel), 128-row items two
 // workgroups to a CU (kNarrow, attn_fwd_kernel), or 128-row items of one hand-sequenced wave per SIMD (kSeq,
 // attn_fwd_seq_kernel)?  kWide has the fastest steady state and needs many items, kSeq the shortest items, kNarrow overlaps

@@ -18,6 +18,7 @@ extern "C" int one_launch_128(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int
 extern "C" int fwd_128(int64_t B, int64_t S, int64_t Hq, int causal, int64_t docs, int narrow) {
   return (int)ie::fwd128_route(B, S, Hq, causal != 0, docs, 256, narrow != 0);
 }
+extern "C" int deals(int64_t items, int one_list, int grouped, int stores) { return ie::dkdv_deals(items, one_list != 0, grouped != 0, stores != 0, 256); }
 extern "C" int flips(int64_t items, int64_t tiles, int causal, int packed) { return ie::fwd_flips(items, tiles, causal != 0, packed != 0, 256); }
 extern "C" int lazy_64(int64_t items, int causal, int packed) { return ie::fwd64_is_lazy(items, causal != 0, packed != 0, 256); }
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
@@ -189,6 +190,20 @@ def test_more_items_than_a_launch_has_workgroups(rules, B, S, Hq, Hkv, causal, d
     assert rules.route_64(*args) != DEALT and not rules.one_launch_128(*args)
     if items * Hq >= 2 ** 24:
         assert rules.fwd_128(i64(B), i64(S), i64(Hq), causal, i64(docs), 0) == WIDE
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,stores,deals", [
+    (9984, 6, 6, 1, False),      # one list, dS stored
+    (3328, 15, 15, 1, False),
+    (8192, 5, 5, 1, True),       # 320 items
+    (9984, 6, 6, 0, True),
+    (4096, 16, 16, 1, True),     # eight lists
+    (32046, 16, 2, 0, False),    # one list of grouped heads
+    (32046, 64, 8, 0, True),
+])
+def test_first_dkdv_items(rules, S, Hq, Hkv, stores, deals):
+    i64 = ctypes.c_int64
+    assert bool(rules.deals(i64(-(-S // 128) * Hkv), int(Hkv % 8 != 0), int(Hq != Hkv), stores)) == deals
 
 
 @pytest.mark.parametrize("S,H,wide,causal,packed,on16", [
