@@ -17,6 +17,9 @@ constexpr int64_t kDealtItems = ((int64_t)1 << 32) / 256 - 1;
 // 700 x 48 93 : 44, 640 x 80 126 : 57, 4096 x 16 x 4 605 : 520 (two), 8192 x 16 x 4 1970 : 1759 (two).
 // Fitted to 220 dense shapes, 128 to 16384 tokens; on 1486 others 0.4 % slower than the better of one and two launches on
 // average, 18 % at most, and 1 % slower than before at most but for one (3692 x 9, bidirectional, 4 %).
+// Very many short batch entries take two launches: what stands around an item that the hardware starts adds up (two : dealt, 153
+// x 886 x 24 2078 : 2528 us, 1127 x 193 x 16 1481 : 1625, 978 x 237 x 8, bidirectional, 823 : 931; entries of one tile, and of two
+// below 128 items per CU, 0.6 to 0.95).
 // Packed documents have prices of their own: a call's longest document, whose length the host does not know, counts as 2.4
 // times the mean, and the dQ items of a launch of their own run three to a CU.  1530 calls of 1024 to 65536 tokens: 0.2 %
 // slower than the better form on average, 12 % at most, none slower than before; with the dense prices 2.3 %, 34 % and 17 %
@@ -52,6 +55,7 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
   if (nk > R && !causal) two = (double)(int64_t)((nk + R - 1) / R) * kv;
   else if (nk > (double)cus) two = longer(two, kv_work / R);
   if (one >= kTwoLaunches * two + kLaunch) return Bwd64::kTwo;
+  if (per_head >= 2 && per_head <= 10 && (nk + nq) * per_head > 256 * (double)cus) return Bwd64::kTwo;
   const bool long_groups = !causal && group >= 4 && per_head * group >= 200 && nk + nq >= 5 * R;
   return long_groups && nk > (double)cus ? Bwd64::kQueued : Bwd64::kDealt;
 }
@@ -64,19 +68,21 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
 // of tiles and per item.  Backward pass, two launches : one: 2048 x 16 140 : 83 us, 4096 x 8 231 : 131, 8192 x 4 377 : 235,
 // 8192 x 8 492 : 433, 3001 x 32, 4 per group, 400 : 328, 10180 x 8 x 4, 8 per group, bidirectional 6134 : 5102; but
 // 2 x 4096 x 32 890 : 920, 14443 x 37 5860 : 6222.
-// Fitted to 220 shapes; on 2124 others, 128 to 16384 tokens, 0.15 % slower than the better form on average, and none more than
-// 5 % slower than two launches.  Bidirectional calls, of equal items, take one launch for a gain of 4 % only: the estimate is out
-// by more where both forms fill their rounds (two : one, 13880 x 19 5694 : 6072 us, 2568 x 20, 2 per group, 248 : 266, 12173 x 17
-// 3901 : 4037).
+// Where a call has rounds enough the persistent kernels are ahead for every size but one tile per head, where a 256-row dQ item
+// is half empty (two : one, 102 x 689 x 24 2038 : 2556 us, 387 x 141 x 16, bidirectional, 1025 : 1293, 13880 x 19, bidirectional,
+// 5694 : 6072; one tile: 1211 x 9 x 32, 4 per group, 1657 : 1482, 587 x 3 x 16 487 : 436), so a workgroup that the hardware starts costs more around its item than
+// one that draws it.  Fitted to 2840 dense calls, 2124 of them of 128 to 16384 tokens and the others of 4 to 2000 batch
+// entries of up to 1200: 0.1 % slower than the better form on average, 10 % at most; of 2174 others twelve were 3 % or more
+// slower than two launches had been, 9 % at most (268 x 188 x 3, bidirectional).
 // Packed documents are priced by themselves (their items are short, and the longest of a call, whose lengths the host does
 // not know, counts as three times the mean, though not as more than the call): 1608 calls of 1024 to 65536
-// tokens, 0.35 % slower than the better form on average; 22.7 tiles on average x 4 heads 579 (two) : 509 (one) us, 50000 x 8 in
+// tokens, 0.33 % slower than the better form on average; 22.7 tiles on average x 4 heads 579 (two) : 509 (one) us, 50000 x 8 in
 // 2.1 tiles 350 : 426, 13439 x 36, 4 per group, in two documents 3670 : 4060.
 inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool causal, int64_t num_docs, int64_t cus) {
-  constexpr double kKvStep = 2.87, kKvItem = 19.4;     // dK/dV: us per pair of tiles, per item
-  constexpr double kQStep = 3.23, kQItem = 0.34;       // dQ in the shared launch
-  constexpr double kQ2Step = 5.18, kQ2Item = 7.8;      // dQ in its own: two rows of tiles per item
-  constexpr double kLaunch = 2.5, kTail = 0.35;
+  constexpr double kKvStep = 2.756, kKvItem = 10.793, kQStep = 3.755, kQItem = 2.154;   // in the shared launch
+  constexpr double kKv2Step = 3.269, kKv2Item = 8.124;                                  // dK/dV in a launch of its own
+  constexpr double kQ2Step = 5.124, kQ2Item = 3.186;                                    // dQ: two rows of tiles per item
+  constexpr double kLaunch = 19.4, kTail = 0.587;
   const double per_head = num_docs ? (double)(S / 128 + num_docs) : (double)((S + 127) / 128), group = (double)(Hq / Hkv);
   double doc = num_docs ? (double)S / 128 / (double)num_docs : per_head;   // tiles of a document (packed: on average)
   if (doc < 1) doc = 1;
@@ -90,7 +96,7 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
     const double kv = top * group * kKv + kKvIt, kv_all = nk * (mean * group * kKv + kKvIt) / C;
     const double one = longer(longer(kv, top * kQ + kQIt), kv_all + nq * (mean * kQ + kQIt) / C);
     const double two = longer(kv, kv_all) + longer(0.6 * top * kQOwn + kQOwnIt, nq * (mean * kQOwn + kQOwnIt) / (2 * C)) + kOwn;
-    return 1.02 * one < two;
+    return (group > 1 ? 1.08 : 1.02) * one < two;   // (of few long items, whose lengths are a guess)
   }
   const auto span = [&](double n, double longest, double work) {   // of a launch of n items
     if (n <= C) return longest;
@@ -104,8 +110,10 @@ inline bool bwd128_in_one_launch(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, 
     const double even = (kv_work + q_work) / C;
     one = (even > kv ? even : kv) + kTail * (causal ? kQStep + kQItem : q);
   }
-  const double two = span(nk, kv, kv_work) + span(nq / 2, doc * kQ2Step + kQ2Item, nq / 2 * (mean * kQ2Step + kQ2Item)) + kLaunch;
-  return (causal ? 1.02 : 1.04) * one < two;
+  const double kv2 = doc * group * kKv2Step + kKv2Item, kv2_work = nk * (mean * group * kKv2Step + kKv2Item);
+  const double n2 = (double)(((S + 127) / 128 + 1) / 2) * (double)(B * Hq), mean2 = causal ? mean + 0.5 : doc;
+  const double two = span(nk, kv2, kv2_work) + span(n2, doc * kQ2Step + kQ2Item, n2 * (mean2 * kQ2Step + kQ2Item)) + kLaunch;
+  return (causal ? 1.02 : 1.012) * one < two;
 }
 
 // dK/dV items of a persistent launch: may the first ones go by workgroup index (tile_queue.hpp)?  One list (a head count that

@@ -137,6 +137,10 @@ TWO, DEALT, QUEUED = 0, 1, 2   # enum Bwd64
     (1, 2020, 192, 6, 0, 0, DEALT),     # fewer dK/dV items than CUs
     (1, 13900, 24, 3, 0, 1, DEALT),     # packed
     (1, 13900, 24, 3, 1, 0, DEALT),
+    (153, 886, 24, 24, 1, 0, TWO),      # many short batch entries
+    (1127, 193, 16, 16, 1, 0, TWO),
+    (1127, 100, 16, 16, 1, 0, DEALT),   # of one tile
+    (100, 193, 16, 16, 1, 0, DEALT),    # not so many
     (1, 16384, 16, 16, 1, 31, DEALT),
     (1, 52129, 8, 2, 1, 53, DEALT),     # packed: the longest document's tail
     (1, 15593, 24, 6, 1, 11, DEALT),
@@ -163,6 +167,10 @@ def test_bwd64_route(rules, B, S, Hq, Hkv, causal, docs, route):
     (1, 32768, 32, 32, 1, 0, False),
     (2, 6144, 10, 10, 0, 0, False),
     (1, 65536, 8, 8, 1, 20, False),
+    (102, 689, 24, 24, 1, 0, False),   # many short batch entries
+    (387, 141, 16, 16, 0, 0, False),
+    (561, 161, 8, 8, 0, 0, False),
+    (735, 100, 22, 22, 1, 0, True),    # of one tile
     (1, 50000, 8, 8, 1, 180, False),   # packed: short documents, many items
     (1, 35000, 4, 4, 1, 12, True),     # long ones on few heads
     (1, 13439, 36, 9, 1, 2, False),    # two documents: neither is three times their mean
