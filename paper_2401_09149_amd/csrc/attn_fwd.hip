@@ -491,7 +491,7 @@ static int launch_fwd_narrow(AttnParams p, int cus, hipStream_t st) {
   const int64_t tiles = tiles_per_head(p.S, 128, p.cu, p.num_docs), items = tiles * p.B * p.Hq;
   const bool flip = fwd_flips(items, tiles, p.causal != 0, p.cu != nullptr, cus);
   if constexpr (D == 64) {
-    if (fwd64_is_lazy(items, p.causal != 0, p.cu != nullptr, cus))
+    if (fwd64_is_lazy(items, p.causal != 0, p.cu != nullptr, cus, p.cu ? p.S / 128 / (p.num_docs > 0 ? p.num_docs : 1) : tiles))
       return flip ? launch_fwd_d<D, false, true, true>(p, cus, st) : launch_fwd_d<D, false, false, true>(p, cus, st);
   }
   return flip ? launch_fwd_d<D, false, true, false>(p, cus, st) : launch_fwd_d<D, false, false, false>(p, cus, st);

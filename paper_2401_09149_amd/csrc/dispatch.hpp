@@ -193,7 +193,12 @@ inline bool fwd_flips(int64_t items, int64_t tiles, bool causal, bool packed, in
 // 68.9); with several waves per SIMD it is work that can be left out.  Lazy against search in 200 launches, on average:
 // bidirectional, up to 256 items, 1.03, 256 to 384 0.995, 512 to 640 0.965, more 0.975; causal, where an item's mean is half its
 // longest, 256 to 384 1.03, 512 to 640 1.01, 640 to 800 1.00, more 0.98; packed 384 to 512 1.035, 800 to 1024 1.00, more 0.98.
-inline bool fwd64_is_lazy(int64_t items, bool causal, bool packed, int64_t cus) { return items > (causal || packed ? 3 : 1) * cus; }
+// `tiles`: of a head, or of a packed call's mean document.  Items of a few tiles are mostly masked blocks and first ones, which
+// search either way (lazy : search in 340 launches of many: one tile 1.01, two to four causal 1.015, bidirectional 1.005, from
+// five on as above; packed 1.012, from two on 1.005, from four on 0.99).
+inline bool fwd64_is_lazy(int64_t items, bool causal, bool packed, int64_t cus, int64_t tiles) {
+  return items > (causal || packed ? 3 : 1) * cus && tiles >= (packed ? 2 : 5);
+}
 
 // Recomputing dQ kernel at head dimension 128: products as 16x16x32 MFMAs (dq_item_16) instead of 32x32x16 (dq_item)?
 // The 16x16x32 form costs less power per product and more issue slots, so it gains where the launch keeps the chip at its

@@ -20,7 +20,7 @@ extern "C" int fwd_128(int64_t B, int64_t S, int64_t Hq, int causal, int64_t doc
 }
 extern "C" int deals(int64_t items, int one_list, int grouped, int stores) { return ie::dkdv_deals(items, one_list != 0, grouped != 0, stores != 0, 256); }
 extern "C" int flips(int64_t items, int64_t tiles, int causal, int packed) { return ie::fwd_flips(items, tiles, causal != 0, packed != 0, 256); }
-extern "C" int lazy_64(int64_t items, int causal, int packed) { return ie::fwd64_is_lazy(items, causal != 0, packed != 0, 256); }
+extern "C" int lazy_64(int64_t items, int causal, int packed, int64_t tiles) { return ie::fwd64_is_lazy(items, causal != 0, packed != 0, 256, tiles); }
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
@@ -103,9 +103,13 @@ def test_forward_order(rules, B, S, H, causal, packed, flips):
     (8192, 12, 1, 1, False),
     (8192, 12, 0, 1, False),
     (8192, 13, 0, 1, True),
+    (512, 400, 1, 0, False),     # four tiles
+    (513, 400, 1, 0, True),
+    (500, 400, 0, 0, False),
 ])
 def test_fwd64_search(rules, S, H, causal, packed, lazy):
-    assert bool(rules.lazy_64(ctypes.c_int64(-(-S // 128) * H), causal, packed)) == lazy
+    i64, tiles = ctypes.c_int64, -(-S // 128)
+    assert bool(rules.lazy_64(i64(tiles * H), causal, packed, i64(tiles))) == lazy
 
 
 def test_cases_of_both_forward_bodies_at_head_dimension_64(rules):
@@ -113,7 +117,8 @@ def test_cases_of_both_forward_bodies_at_head_dimension_64(rules):
     for cases, lazy in ((LAZY_64, True), (SEARCHING_64, False)):
         for S, H, causal, lens in cases:
             tiles = S // 128 + len(lens) if lens else -(-S // 128)
-            assert bool(rules.lazy_64(ctypes.c_int64(tiles * H), int(causal), int(lens is not None))) == lazy, (S, H)
+            mean = S // 128 // len(lens) if lens else tiles
+            assert bool(rules.lazy_64(ctypes.c_int64(tiles * H), int(causal), int(lens is not None), ctypes.c_int64(mean))) == lazy, (S, H)
 
 
 TWO, DEALT, QUEUED = 0, 1, 2   # enum Bwd64
