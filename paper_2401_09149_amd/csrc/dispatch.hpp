@@ -70,9 +70,10 @@ inline Bwd64 bwd64_route(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, bool cau
 // 2 x 4096 x 32 890 : 920, 14443 x 37 5860 : 6222.
 // Where a call has rounds enough the persistent kernels are ahead for every size but one tile per head, where a 256-row dQ item
 // is half empty (two : one, 102 x 689 x 24 2038 : 2556 us, 387 x 141 x 16, bidirectional, 1025 : 1293, 13880 x 19, bidirectional,
-// 5694 : 6072; one tile: 1211 x 9 x 32, 4 per group, 1657 : 1482, 587 x 3 x 16 487 : 436), so a workgroup that the hardware starts costs more around its item than
-// one that draws it.  Fitted to 2840 dense calls, 2124 of them of 128 to 16384 tokens and the others of 4 to 2000 batch
-// entries of up to 1200: 0.1 % slower than the better form on average, 10 % at most; of 2174 others twelve were 3 % or more
+// 5694 : 6072; one tile: 1211 x 9 x 32, 4 per group, 1657 : 1482, 587 x 3 x 16 487 : 436), so a workgroup that the hardware
+// starts costs more around its item than one that draws it.  Fitted to 2840 dense calls, 2124 of them of 128 to 16384 tokens
+// and the others of 4 to 2000 batch entries of up to 1200: 0.1 % slower than the better form on average, 10 % at most; of 2174
+// others twelve were 3 % or more
 // slower than two launches had been, 9 % at most (268 x 188 x 3, bidirectional).
 // Packed documents are priced by themselves (their items are short, and the longest of a call, whose lengths the host does
 // not know, counts as three times the mean, though not as more than the call): 1608 calls of 1024 to 65536
