@@ -356,6 +356,13 @@ __device__ __forceinline__ const char* uniform(const char* p) {
 
 __device__ __forceinline__ int64_t uniform(int64_t x) { return (int64_t)(uintptr_t)uniform((const char*)(uintptr_t)x); }
 
+// The lane of the wavefront, computed where it is asked for.
+__device__ __forceinline__ int lane_id() {
+  uint32_t lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return (int)lane;
+}
+
 __device__ __forceinline__ void async_copy16(uint32_t voffset, const char* sbase, uint32_t lds_addr) {
   sbase = uniform(sbase);
   lds_addr = uniform(lds_addr);

@@ -20,9 +20,12 @@ namespace ie {
 
 // FLIP: items flip_lo .. flip_hi - 1 run in the opposite order, eight at a time (AttnParams; a kernel of its own, because the
 // order costs a small launch 0.4 us, 4 %, before its first copy).
-// LAZY (head dimension 64): unmasked blocks after a row's first look for no maximum (below).
+// LAZY (head dimension 64): unmasked blocks after a row's first look for no maximum (below).  Launches that run it have more
+// items than the CUs have SIMDs to spare, so it keeps to 128 registers, for four workgroups to a CU instead of three: 4 x 2000 x
+// 16, bidirectional, 1024 items, 89 -> 85 us, causal 49.6 -> 46.3, 4 x 8192 x 16 1165 -> 1155.  With a maximum searched for, in
+// launches of fewer items, the tighter allocation is the slower one (2 x 1000 x 8 16.3 : 16.8).
 template <int D, bool FLIP, bool LAZY>
-__global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
+__global__ __launch_bounds__(kThreads, LAZY ? 4 : 2) void attn_fwd_kernel(AttnParams p) {
   constexpr int BM = 128, BN = 64;
   constexpr int NKS = D / 16;  // k-steps of the QK^T product
   constexpr int NDB = D / 32;  // 32-wide blocks of the head dimension in O^T
@@ -65,16 +68,16 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
   ld.load(lds0 + TILE_BYTES, vbase + key_tile_off(0), nk);
 
   // This lane's query row (clamped into the tile so that out-of-range lanes repeat the last row).
-  int64_t row = q0 + wv * 32 + n;
-  const bool row_ok = row < q_end;
-  if (!row_ok) row = q_end - 1;
-  const int row_rel = (int)(row - k_begin);  // position of the row among the document's keys
+  const int rows_rel_end = (int)(q_end - k_begin), wave_row_min = (int)(q0 - k_begin) + wv * 32;
+  int row_rel = wave_row_min + n;  // position of the row among the document's keys
+  if (row_rel >= rows_rel_end) row_rel = rows_rel_end - 1;
+  const int lim0 = (p.causal ? row_rel : nk - 1) - 4 * h;  // last visible key relative to the lane's first key of tile 0
 
   // Q fragments: B operand of S^T = K Q^T, column n = query, k = head-dim index.
   bf16x8 qf[NKS];
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks)
-    qf[ks] = *reinterpret_cast<const bf16x8*>(qbase + tok_off(p, row, q_stride * 2) + (ks * 16 + h * 8) * 2);
+    qf[ks] = *reinterpret_cast<const bf16x8*>(qbase + tok_off(p, k_begin + row_rel, q_stride * 2) + (ks * 16 + h * 8) * 2);
 
   // Per-lane LDS addresses inside stage 0; stage, tile and row-block offsets are immediates.
   const char* k_ptr[NKS];  // K tile, A operand: row = key n (+32 for the second block), chunk = 2ks + h
@@ -110,8 +113,6 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
 
-  const int wave_row_min = (int)(q0 - k_begin) + wv * 32;
-
   // One 64-key LDS tile is consumed as two 32-key blocks, each with its own softmax update.
   // `stage` is the byte offset of the stage holding tile kt; FULL_NEXT says that tile kt+1
   // exists and is complete (the common case, no per-lane address arithmetic).
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
     }
     // Mask: only tiles that reach past the wave's first row (causal) or past the last key.
     const bool need_mask = (p.causal && kb + BN - 1 > wave_row_min) || (kb + BN > nk);
-    const int lim = (p.causal ? row_rel : nk - 1) - kb - 4 * h;  // last visible key relative to the lane's first key
+    const int lim = lim0 - kb;
 
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -220,13 +221,19 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(AttnParams p) {
   }
   for (; kt < nkt; ++kt) tile_step(kt, (kt & 1) * STAGE_BYTES, std::false_type{});
 
-  // Epilogue: normalise, write O (bf16) and LSE (natural log).
+  // Epilogue: normalise, write O (bf16) and LSE (natural log).  (The lane is asked for again, so that neither its parts nor
+  // its row stay in registers through the loop.)
+  const int lane_e = lane_id(), h_e = lane_e >> 5;
+  row_rel = wave_row_min + (lane_e & 31);
+  const bool row_ok = row_rel < rows_rel_end;
+  if (!row_ok) row_rel = rows_rel_end - 1;
+  const int64_t row = k_begin + row_rel;
   const float l_full = halfwave_sum(l);
   const float inv_l = 1.0f / l_full;
   __bf16* orow = p.o_out + ((int64_t)tc.b * p.S * p.Hq + tc.h) * D + row * q_stride;
 #pragma unroll
-  for (int db = 0; db < NDB; ++db) store_block32_bf16(orow + 32 * db, oacc[db], inv_l, h, row_ok);
-  if (row_ok && h == 0) p.lse_out[((int64_t)tc.b * p.Hq + tc.h) * p.S + row] = (m * c + __builtin_amdgcn_logf(l_full)) * kLn2;
+  for (int db = 0; db < NDB; ++db) store_block32_bf16(orow + 32 * db, oacc[db], inv_l, h_e, row_ok);
+  if (row_ok && h_e == 0) p.lse_out[((int64_t)tc.b * p.Hq + tc.h) * p.S + row] = (m * c + __builtin_amdgcn_logf(l_full)) * kLn2;
 }
 
 // The same item (128 query rows, head dimension 128) for launches of a few items per CU, where a workgroup has its CU to
