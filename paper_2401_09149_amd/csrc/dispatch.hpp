@@ -189,6 +189,25 @@ inline bool fwd_flips(int64_t items, int64_t tiles, bool causal, bool packed, in
   return causal && !packed && tiles >= 8 && items > cus && items <= 8 * cus;
 }
 
+// Dense forward launches that the hardware deals out: how many of a head's tiles go head by head, the heaviest first (q_heavy in
+// decode_tile), before what is left goes tile by tile over all heads?  Tile by tile a launch of many heads streams every
+// head's K and V from memory once per tile; head by head the workgroups that run together share them in L2.  Items are equal
+// in bidirectional launches, so all of them go that way (378 x 975 x 4 heads 1396 -> 865 us, 4 x 4096 x 24 779 -> 742, 40 x
+// 1000 x 16 at head dimension 64 228 -> 196).  Causal ones end on the light tiles of all heads, and the items must be enough
+// for the rest to even out: tile by tile : head by head, D = 128, 9 to 16 tiles, 4 to 8 items per CU 1.04 on average, 8 to 12 0.93,
+// 16 to 24 0.87, more 0.79; 17 to 32 tiles 8 to 16 items 1.005, 16 to 24 0.96, more 0.85; D = 64, three to four workgroups to a CU, 9 to
+// 16 tiles 8 to 12 items 1.06, 12 to 16 0.96; two tiles 0.97 to 1.08 at any number.  (16 x 1024 x 32, 4 per group, 215 -> 190 us; 4 x
+// 4096 x 16, D = 64, 145 : 155.)  An odd number of tiles, because an even one shares a factor with the CUs and gives the
+// heaviest tiles to the same ones (causal, all of 3, 4, 6 and 8 tiles 0.87, 1.03, 0.88, 0.95).  4113 launches of 600 to 16000
+// items: 7 % faster on average.
+inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool packed, bool d64, int64_t cus) {
+  if (packed || tiles < 2 || items <= 2 * cus) return 0;
+  if (!causal) return (int)tiles;
+  if (tiles < 3 || items <= (tiles > 16 ? 16 : d64 ? 12 : 8) * cus) return 0;
+  const int64_t share = (tiles - tiles * 3 / 8) | 1;
+  return (int)(share < tiles ? share : tiles);
+}
+
 // Forward at head dimension 64: unmasked blocks without a search for their maximum (LAZY in attn_fwd.hip)?  Where a wave has
 // its SIMD to itself the search is the shorter way (lazy : search, 165 x 40 6.34 : 6.12 us, 2911 x 4 41.9 : 39.9, 5374 x 1 72.3 :
 // 68.9); with several waves per SIMD it is work that can be left out.  Lazy against search in 200 launches, on average:

@@ -21,6 +21,9 @@ extern "C" int fwd_128(int64_t B, int64_t S, int64_t Hq, int causal, int64_t doc
 extern "C" int deals(int64_t items, int one_list, int grouped, int stores) { return ie::dkdv_deals(items, one_list != 0, grouped != 0, stores != 0, 256); }
 extern "C" int flips(int64_t items, int64_t tiles, int causal, int packed) { return ie::fwd_flips(items, tiles, causal != 0, packed != 0, 256); }
 extern "C" int lazy_64(int64_t items, int causal, int packed, int64_t tiles) { return ie::fwd64_is_lazy(items, causal != 0, packed != 0, 256, tiles); }
+extern "C" int by_head(int64_t items, int64_t tiles, int causal, int packed, int d64) {
+  return ie::fwd_head_by_head(tiles, items, causal != 0, packed != 0, d64 != 0, 256);
+}
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
@@ -91,6 +94,15 @@ def test_fwd128_route(rules, B, S, Hq, causal, docs, narrow, route):
 def test_forward_order(rules, B, S, H, causal, packed, flips):
     i64, tiles = ctypes.c_int64, -(-S // 128)
     assert bool(rules.flips(i64(B * tiles * H), i64(tiles), causal, packed)) == flips
+
+
+@pytest.mark.parametrize("items,tiles,causal,packed,d64,share", [
+    (512, 8, 0, 0, 0, 0), (520, 8, 0, 0, 0, 8), (5000, 1, 0, 0, 0, 0), (5000, 2, 0, 0, 1, 2), (5000, 8, 0, 1, 0, 0),
+    (2048, 8, 1, 0, 0, 0), (2056, 8, 1, 0, 0, 5), (2056, 8, 1, 0, 1, 0), (3080, 8, 1, 0, 1, 5), (9000, 2, 1, 0, 0, 0),
+    (4096, 32, 1, 0, 0, 0), (4104, 17, 1, 0, 1, 11), (9000, 3, 1, 0, 0, 3), (9000, 4, 1, 0, 0, 3), (9000, 6, 1, 0, 0, 5), (9000, 5, 1, 1, 0, 0),
+])
+def test_forward_head_by_head(rules, items, tiles, causal, packed, d64, share):
+    assert rules.by_head(ctypes.c_int64(items), ctypes.c_int64(tiles), causal, packed, d64) == share
 
 
 @pytest.mark.parametrize("S,H,causal,packed,lazy", [

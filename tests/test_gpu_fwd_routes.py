@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 from oracle import attention as ora
 
-from parity_util import TOL_LSE, TOL_O, randn_bf16, to64
+from parity_util import TOL_LSE, TOL_O, compare_all, randn_bf16, to64
 
 pytestmark = pytest.mark.gpu
 
@@ -108,3 +108,31 @@ def test_items_in_the_opposite_order(D):
     finally:
         binding.ie_attn_set_tile_rows(before)
     assert torch.equal(o, torch.cat([a for a, _ in parts], 2)) and torch.equal(lse, torch.cat([b for _, b in parts], 1))
+
+
+@pytest.mark.parametrize("S,heads,D,causal,backward", [
+    (129, 520, 64, False, False), (200, 264, 128, False, True), (384, 400, 128, False, True),   # two and three tiles, all head by head
+    (300, 688, 128, True, False), (641, 352, 128, True, False), (513, 624, 64, True, False),    # three, six and five, odd shares
+])
+def test_many_heads_in_head_by_head_order(S, heads, D, causal, backward):
+    """Launches of many heads (fwd_head_by_head in csrc/dispatch.hpp; bidirectional at head dimension 128 the shared backward
+    launch too): the batch repeats two entries, of which the first two are compared with the oracle and the others, bit for
+    bit, with those two: every item has run, for its own rows."""
+    import torch
+    from paper_2401_09149_amd import binding
+    print(f"case S{S} heads {heads} D{D} {causal}", flush=True)
+    dev, H, U = "cuda:0", 8, 2
+    B = heads // H
+    small = [randn_bf16((U, S, H, D), 990 + j) for j in range(4)]
+    q, k, v, do = (x.to(dev).repeat((B + 1) // U, 1, 1, 1)[:B].contiguous() for x in small)
+    o, lse = binding.attn_fwd(q, k, v, D ** -0.5, causal)
+    got = (o, lse) + (binding.attn_bwd(q, k, v, o, do, lse, D ** -0.5, causal) if backward else ())
+    torch.cuda.synchronize()
+    for t in got:
+        for u in range(U):
+            assert torch.equal(t[u::U], t[u:u + 1].expand_as(t[u::U]))
+    if backward:
+        compare_all([t[:U] for t in got], ora.attn_fwd_bwd(*(to64(x) for x in small), D ** -0.5, causal))
+    else:
+        ro, rlse = ora.attn_fwd(*(to64(x) for x in small[:3]), D ** -0.5, causal)
+        assert np.abs(to64(o[:U]) - ro).max() <= TOL_O and np.abs(to64(lse[:U]) - rlse).max() <= TOL_LSE
