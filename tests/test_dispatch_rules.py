@@ -54,6 +54,8 @@ WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
     *((1, s, 2, 0, 0, 1, SEQ) for s in (897, 960, 1024, 1025)),   # the GPU test's sizes (test_gpu_fwd_routes.py)
     (2, 700, 3, 1, 0, 1, SEQ), (1, 1100, 4, 0, 0, 1, SEQ), (1, 2500, 2, 1, 4, 0, SEQ), (1, 2300, 2, 0, 4, 0, SEQ),
     (2, 430, 40, 1, 0, 1, NARROW),      # short items, a second round
+    (1, 3720, 16, 1, 2, 0, NARROW),     # a few long documents
+    (1, 7756, 4, 0, 6, 0, NARROW),
     (1, 3000, 16, 0, 0, 1, NARROW),
     (1, 3001, 32, 1, 0, 1, NARROW),
     (1, 4129, 17, 0, 0, 1, NARROW),     # a last round of a few items
