@@ -140,6 +140,8 @@ __global__ __launch_bounds__(kThreads, LAZY ? 4 : 2) void attn_fwd_kernel(AttnPa
       for (int ks = 0; ks < NKS; ++ks) {
         s = mfma32(lds_read8(k_ptr[ks], stage + 32 * j * ROW_BYTES), qf[ks], s);
       }
+      // (the compiler counts the wait states behind a chain along one of the ways through the branches below, not the shortest)
+      if (LAZY) asm volatile("s_nop 1" : "+v"(s));
 
       // V^T fragments of this block: requested now, consumed after the exponentials
       bf16x8 vfrag[2][NDB];
