@@ -265,7 +265,8 @@ constexpr TileCost kCost[kTiles] = {
     {32, 32, 4, {0.128f, 0.f, 0.f}, 0.49f, 0.95f, 0.00f}};
 
 // C[I][J] over a contraction of R; product: 0 forward, 1 dx, 2 dw.
-inline Tile pick_tile(int64_t I, int64_t J, int64_t R, int product, int64_t cus) {
+// `us`: the estimate.
+inline Tile pick_tile(int64_t I, int64_t J, int64_t R, int product, int64_t cus, float* us_out = nullptr) {
   const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
   Tile best = kPp256;
@@ -284,6 +285,37 @@ inline Tile pick_tile(int64_t I, int64_t J, int64_t R, int product, int64_t cus)
       us += last > c.write_us * part ? last : c.write_us * part;
     }
     if (k == 0 || us < best_us) { best = (Tile)k; best_us = us; }
+  }
+  if (us_out) *us_out = best_us;
+  return best;
+}
+
+// Forward product: tiles whose four waves share nothing (linear_own_kernel), where their estimated time is less than `other_us`,
+// that of pick_tile's choice?  They gain where a call is a few rounds of small tiles: contractions of 768 and more (a wave's ring
+// holds two of its steps, 512), 32 to 1536 tokens, the range measured (below 32 the 32 x 32 tiles, which read a weight once, were
+// ahead in all but a few).  Costs per 256-deep step, around a tile and of a launch (`kOther` of the others, whose estimates leave
+// it out) fitted to 434 measured calls, widths 512 to 22016: 4 % faster than without these tiles on average (half of the calls
+// take them), 0.4 % slower than the best choice, eleven calls 3 to 7 % slower than without.  200 tokens, 4096 x 4096 21.5 ->
+// 18.3 us, 12288 x 4096 43.5 -> 36.7, 4096 x 11008 50.8 -> 42.0.
+enum Own { kOwnNone, kOwn64, kOwn64x96, kOwn128x96, kOwns };
+struct OwnCost { int ti, tj; float step_us, tile_us, light, launch_us; };
+constexpr OwnCost kOwnCost[kOwns] = {
+    {0, 0, 0.f, 0.f, 0.f, 0.f}, {64, 64, 0.930f, 0.09f, 0.707f, 3.61f}, {64, 96, 1.249f, 0.08f, 0.780f, 3.59f}, {128, 96, 1.809f, 0.82f, 0.630f, 4.18f}};
+inline Own pick_own(int64_t I, int64_t J, int64_t R, int64_t cus, float other_us) {
+  constexpr float kOther = 3.f, kGain = 0.96f;
+  const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  if (R < 768 || I < 32 || I > 1536) return kOwnNone;
+  const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
+  Own best = kOwnNone;
+  float best_us = (other_us + kOther) * kGain;
+  for (int k = 1; k < kOwns; ++k) {
+    const OwnCost& c = kOwnCost[k];
+    const int64_t per = ceil_div(ceil_div(I, c.ti) * ceil_div(J, c.tj), 8);
+    const int64_t full = per / per_xcd, rest = per % per_xcd;
+    const float steps = (float)ceil_div(R, 256) * c.step_us;
+    float us = c.launch_us + (float)full * (steps + c.tile_us);
+    if (rest) us += steps * (c.light + (1.f - c.light) * (float)rest / (float)per_xcd) + c.tile_us;
+    if (us < best_us) { best = (Own)k; best_us = us; }
   }
   return best;
 }

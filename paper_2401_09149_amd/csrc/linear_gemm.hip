@@ -52,17 +52,17 @@ __device__ __forceinline__ uint32_t dswz(uint32_t r) { return (r >> 1) & 7u; }
 // instructions ahead of a step's LDS reads: dw 8192 tokens 3200 x 3200 209 -> 168 us and 12288 x 4096 668 -> 633, dx 4096
 // tokens 17152 x 3200 426 -> 355, forward 2048 tokens 9600 x 3200 139 -> 123, all with 256 x 256 tiles; dw 6144 tokens
 // 512 x 1344, 64 x 64 tiles, 37 -> 29.)  Instruction t of wave w is piece w + 8 t of the SUB * EXT / 8 pieces of 1 KiB, in LDS order.
-template <bool T, int EXT, int SUB>
+template <bool T, int EXT, int SUB, int WAVES = kWaves>
 struct TileCopy {
   static constexpr uint32_t PIECES = EXT / 8;         // 1 KiB pieces of one 64-deep tile
-  static constexpr int NI = SUB * PIECES / kWaves;
+  static constexpr int NI = SUB * PIECES / WAVES;
   static constexpr uint32_t CPR = T ? EXT / 8 : 8;    // 16-byte chunks per row
   static constexpr uint32_t RPP = 64 / CPR;           // rows per piece
   static constexpr int NV = SUB > 1 ? 1 : NI;         // (SUB > 1: a lane's instructions differ in the 64-deep tile only)
-  static_assert(SUB == 1 || kWaves % PIECES == 0, "");
+  static_assert(SUB == 1 || WAVES % PIECES == 0, "");
   uint32_t wave;
   uint32_t voff[NV];     // byte offset of this lane's 16 bytes of instruction t
-  __device__ __forceinline__ void init(int tid) { wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6); }
+  __device__ __forceinline__ void init(int tid) { wave = WAVES == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6); }
   // `valid`: rows (direct) or 16-byte chunks (transposed) that exist along the output index; what lies past them repeats
   // the last.  `first`: the tile starts at that row or chunk.
   __device__ __forceinline__ void set_tile(int tid, uint32_t pitch, int valid, uint32_t first = 0) {
@@ -70,7 +70,7 @@ struct TileCopy {
     auto clamp = [&](uint32_t x) __attribute__((always_inline)) { return x + first < last ? x + first : last; };
 #pragma unroll
     for (int t = 0; t < NV; ++t) {
-      const uint32_t r = lane / CPR + (wave + kWaves * t) % PIECES * RPP;
+      const uint32_t r = lane / CPR + (wave + WAVES * t) % PIECES * RPP;
       const uint32_t chunk = lane % CPR ^ (T ? (uint32_t)swz<EXT>((int)r) : dswz(r));
       voff[t] = T ? r * pitch + (clamp(chunk) << 4) : clamp(r) * pitch + (chunk << 4);
     }
@@ -79,15 +79,16 @@ struct TileCopy {
   // `sub_step`: bytes between them.
   __device__ __forceinline__ void issue(uint32_t lds, const char* g, int64_t sub_step = 0, int subs = 1) const {
 #pragma unroll
-    for (int t = 0; t < NI; ++t) {
-      const uint32_t piece = wave + kWaves * t;
-      const char* src = g;
-      if constexpr (SUB > 1) {
-        const uint32_t sub = piece / PIECES;
-        src += (int64_t)(sub < (uint32_t)subs ? sub : (uint32_t)subs - 1) * sub_step;
-      }
-      async_copy16(voff[NV == 1 ? 0 : t], src, lds + piece * 1024);
+    for (int t = 0; t < NI; ++t) issue_piece(t, lds, g, sub_step, subs);
+  }
+  __device__ __forceinline__ void issue_piece(int t, uint32_t lds, const char* g, int64_t sub_step = 0, int subs = 1) const {
+    const uint32_t piece = wave + WAVES * t;
+    const char* src = g;
+    if constexpr (SUB > 1) {
+      const uint32_t sub = piece / PIECES;
+      src += (int64_t)(sub < (uint32_t)subs ? sub : (uint32_t)subs - 1) * sub_step;
     }
+    async_copy16(voff[NV == 1 ? 0 : t], src, lds + piece * 1024);
   }
 };
 
@@ -502,6 +503,186 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_ring_kernel(GemmParams 
   }
 }
 
+// ---- forward product over few tokens: waves that share nothing ----------------------------------------
+// A small tile's step in the ring kernel is a chain of barrier, copies, LDS reads and products that eight waves walk
+// together, 0.23-0.28 us for 16 KiB.  Here each of four waves, one per SIMD, computes the whole tile over every fourth 64-deep
+// step, with a ring in LDS of its own: no barrier until the four partial sums are added (in fp32, in the order of the waves,
+// through the slots that each wave has read last), every byte is read from LDS once, and a step's fragments go to registers
+// in one go, so that its slots are filled again behind its own first products.
+// Bound: the loaded latency of the copies (2 us) over the 112-160 KiB that LDS has room for in flight, 55-65 GB/s per CU.  (L2 alone
+// delivers 105.  Fragments loaded from memory straight to registers take half the rate, whatever their number in flight; lines of
+// the weights touched 4 to 32 steps ahead make every tile slower.)  200 tokens: 4096 x 4096 21.5 -> 18.3 us, 4096 x 11008
+// 50.8 -> 42.0 (64 x 64), 12288 x 4096 43.5 -> 36.7 (128 x 96).
+template <int CI_, int CJ_, int NA_, int NB_>
+struct OwnCfg {
+  static constexpr int CI = CI_, CJ = CJ_, NA = NA_, NB = NB_, WAVES = 4;   // NA, NB: 64-deep steps of each operand in a wave's ring
+  static constexpr int NIB = CI / 32, NJB = CJ / 32, BLOCKS = NIB * NJB;
+  static constexpr int A_BYTES = CI * 128, B_BYTES = CJ * 128;              // one step of each operand
+  static constexpr int RING_BYTES = NA * A_BYTES + NB * B_BYTES, SMEM_BYTES = WAVES * RING_BYTES;
+  static constexpr int CA = CI / 8, CB = CJ / 8;                            // copy instructions of a step
+  // Copies younger than those of the step that comes next, A's or B's, whichever are the fewer.
+  static constexpr int YOUNGER = CB + (NA - 1) * (CA + CB) < (NB - 1) * (CA + CB) ? CB + (NA - 1) * (CA + CB) : (NB - 1) * (CA + CB);
+  // Blocks of partial sums that fit the two slots a wave has read last.
+  static constexpr int ROUNDS = (BLOCKS + NIB + NJB - 1) / (NIB + NJB), PER_ROUND = (BLOCKS + ROUNDS - 1) / ROUNDS;
+  static_assert(SMEM_BYTES <= 160 * 1024 && YOUNGER < 64 && NA <= NB, "");
+};
+
+template <typename C>
+__global__ __launch_bounds__(C::WAVES * 64, 1) void linear_own_kernel(GemmParams p) {
+  constexpr int CI = C::CI, CJ = C::CJ, NA = C::NA, NB = C::NB, NIB = C::NIB, NJB = C::NJB, W = C::WAVES;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  const int lstep = (int)(gridDim.x >> 3);
+  const int nr = (int)(p.R / 64);
+  const int mine = (nr - wv + W - 1) / W;   // steps of this wave per tile: wv, wv + 4, ...; NB at least
+
+  TileCopy<false, CI, 1, 1> ca;
+  TileCopy<false, CJ, 1, 1> cb;
+  ca.init(tid);
+  cb.init(tid);
+  char* const ring = smem + wv * C::RING_BYTES;
+  const uint32_t lds_a = lds_address(ring), lds_b = lds_a + NA * C::A_BYTES;
+
+  int l = (int)(blockIdx.x >> 3);
+  GemmTile cur = decode_gemm_tile<false, false, CI, CJ>(p, l);
+  if (!cur.valid) return;
+  const char* ga = cur.ga + wv * 128;   // the next steps to copy
+  const char* gb = cur.gb + wv * 128;
+  ca.set_tile(lane, (uint32_t)p.a_pitch, cur.a_valid);
+  cb.set_tile(lane, (uint32_t)p.b_pitch, cur.b_valid);
+  auto copy_a = [&](int slot) __attribute__((always_inline)) { ca.issue(lds_a + slot * C::A_BYTES, ga); ga += W * 128; };
+  auto copy_b = [&](int slot) __attribute__((always_inline)) { cb.issue(lds_b + slot * C::B_BYTES, gb); gb += W * 128; };
+#pragma unroll
+  for (int s = 0; s < NB; ++s) {
+    if (s >= NB - NA) copy_a(s - (NB - NA));
+    copy_b(s);
+  }
+
+  int sa = 0, sb = 0;   // slots of the step that comes next
+  for (int done = 1;; ++done) {   // `done`: tiles up to and with this one
+    f32x16 acc[NIB][NJB];
+#pragma unroll
+    for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+      for (int jb = 0; jb < NJB; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[ib][jb][r] = 0.0f;
+    // One step: its copies have landed (stores of an epilogue in between only tighten the wait), its fragments go to
+    // registers, and behind the first products its slots are filled again.
+    auto step = [&](auto with_copies) __attribute__((always_inline)) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::YOUNGER) : "memory");
+      const char* ta = ring + sa * C::A_BYTES;
+      const char* tb = ring + NA * C::A_BYTES + sb * C::B_BYTES;
+      bf16x8 fi[NIB][4], fj[NJB][4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+        for (int ib = 0; ib < NIB; ++ib) fi[ib][ks] = ring_frag<false, CI>(ta, lane, ib * 32, ks);
+#pragma unroll
+        for (int jb = 0; jb < NJB; ++jb) fj[jb][ks] = ring_frag<false, CJ>(tb, lane, jb * 32, ks);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      const uint32_t base_a = lds_a + sa * C::A_BYTES, base_b = lds_b + sb * C::B_BYTES;
+      constexpr int MF = 4 * NIB * NJB;
+      int t = 0;
+#pragma unroll
+      for (int x = 0; x < MF; ++x) {
+        const int ks = x / (NIB * NJB), ib = x / NJB % NIB, jb = x % NJB;
+        acc[ib][jb] = mfma32(fj[jb][ks], fi[ib][ks], acc[ib][jb]);
+        if (with_copies) {
+#pragma unroll
+          for (; t < (C::CA + C::CB) && t < x + 1; ++t) {
+            if (t < C::CA) ca.issue_piece(t, base_a, ga);
+            else cb.issue_piece(t - C::CA, base_b, gb);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (with_copies) {
+#pragma unroll
+        for (; t < (C::CA + C::CB); ++t) {
+          if (t < C::CA) ca.issue_piece(t, base_a, ga);
+          else cb.issue_piece(t - C::CA, base_b, gb);
+        }
+        ga += W * 128;
+        gb += W * 128;
+        sa = sa + 1 == NA ? 0 : sa + 1;
+        sb = sb + 1 == NB ? 0 : sb + 1;
+      }
+    };
+    for (int kt = NB; kt < mine; ++kt) step(std::true_type{});
+    // The copies of B are at the next tile now.  There is none: they repeat this one's last step, which nothing reads.
+    l += lstep;
+    const GemmTile next = decode_gemm_tile<false, false, CI, CJ>(p, l);
+    if (next.valid) {
+      cb.set_tile(lane, (uint32_t)p.b_pitch, next.b_valid);
+      gb = next.gb + wv * 128;
+    } else {
+      gb -= W * 128;
+    }
+#pragma unroll
+    for (int s = 0; s < NB; ++s) {
+      if (s == NB - NA) {   // and those of A
+        if (next.valid) {
+          ca.set_tile(lane, (uint32_t)p.a_pitch, next.a_valid);
+          ga = next.ga + wv * 128;
+        } else {
+          ga -= W * 128;
+        }
+      }
+      if (s == NB - 1) {
+        step(std::false_type{});
+      } else {
+        step(std::true_type{});
+        if (!next.valid) {
+          gb -= W * 128;
+          if (s >= NB - NA) ga -= W * 128;
+        }
+      }
+    }
+
+    // Partial sums through the slots that each wave has read last: [block of the round][quad q][lane] x 16 bytes, quad q of a
+    // block four consecutive columns 8 q + 4 h of row n; wave w adds the quads q = w, in the order of the waves.
+    auto block_at = [&](int k, int b) __attribute__((always_inline)) {   // block b of wave k
+      const int last = done * ((nr - k + W - 1) / W) - 1;
+      char* r = smem + k * C::RING_BYTES;
+      return reinterpret_cast<float*>(b < NIB ? r + last % NA * C::A_BYTES + b * 4096
+                                              : r + NA * C::A_BYTES + last % NB * C::B_BYTES + (b - NIB) * 4096) + lane * 4;
+    };
+#pragma unroll
+    for (int r0 = 0; r0 < C::BLOCKS; r0 += C::PER_ROUND) {
+#pragma unroll
+      for (int b = r0; b < r0 + C::PER_ROUND && b < C::BLOCKS; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& a = acc[b / NJB][b % NJB];
+          f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+          *reinterpret_cast<f32x4*>(block_at(wv, b - r0) + q * 256) = v;
+        }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+      for (int b = r0; b < r0 + C::PER_ROUND && b < C::BLOCKS; ++b) {
+        f32x4 sum = *reinterpret_cast<const f32x4*>(block_at(0, b - r0) + wv * 256);
+#pragma unroll
+        for (int k = 1; k < W; ++k) sum += *reinterpret_cast<const f32x4*>(block_at(k, b - r0) + wv * 256);
+        const int il = b / NJB * 32 + n, j = b % NJB * 32 + 8 * wv + 4 * h;
+        bf16x4 out = {(__bf16)sum[0], (__bf16)sum[1], (__bf16)sum[2], (__bf16)sum[3]};
+        if (il < cur.i_valid && j < cur.j_valid) *reinterpret_cast<bf16x4*>(p.c + (cur.i0 + il) * p.c_pitch + cur.j0 + j) = out;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // read by all: the next round, or the next copies
+    }
+    if (!next.valid) break;
+    copy_a(sa);
+    copy_b(sb);
+    sa = sa + 1 == NA ? 0 : sa + 1;
+    sb = sb + 1 == NB ? 0 : sb + 1;
+    cur = next;
+  }
+  async_wait_all();
+}
+
 constexpr int64_t kMaxDim = (int64_t)1 << 22;   // rows stay below 8 MiB: 256 rows of byte offsets fit 32 bits
 
 bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; }
@@ -514,7 +695,7 @@ int check_dims(int64_t M, int64_t N, int64_t K) {
 
 // Tiles, grid and launch of one kernel: one workgroup per CU at most, the tiles dealt to the XCDs in eighths.
 template <typename K>
-int launch_tiles(K kernel, GemmParams p, int ti, int tj, int smem, hipStream_t st) {
+int launch_tiles(K kernel, GemmParams p, int ti, int tj, int smem, hipStream_t st, int waves = kWaves) {
   int rc = set_smem(kernel, smem);
   if (rc) return rc;
   p.tiles_i = (int)ceil_div(p.I, ti);
@@ -528,7 +709,7 @@ int launch_tiles(K kernel, GemmParams p, int ti, int tj, int smem, hipStream_t s
   const int per = (p.tiles + 7) / 8;                      // tiles of one XCD's share
   const int per_xcd_wgs = cus / 8 < per ? cus / 8 : per;  // one workgroup per CU
   const unsigned grid = 8u * (unsigned)(per_xcd_wgs < 1 ? 1 : per_xcd_wgs);
-  kernel<<<dim3(grid), dim3(kWaves * 64), smem, st>>>(p);
+  kernel<<<dim3(grid), dim3(waves * 64), smem, st>>>(p);
   e = hipGetLastError();
   return e == hipSuccess ? IE_OK : hip_fail(e);
 }
@@ -545,12 +726,27 @@ int launch_ring(const GemmParams& p, hipStream_t st) {
   return launch_tiles(linear_ring_kernel<A_T, B_T, C>, p, C::CI, C::CJ, C::SMEM_BYTES, st);
 }
 
+template <typename C>
+int launch_own(const GemmParams& p, hipStream_t st) {
+  return launch_tiles(linear_own_kernel<C>, p, C::CI, C::CJ, C::SMEM_BYTES, st, C::WAVES);
+}
+
 template <bool A_T, bool B_T>
 int launch_gemm(const GemmParams& p, hipStream_t st) {
   hipError_t e;
   const int cus = cu_count(&e);
   if (e != hipSuccess) return hip_fail(e);
-  switch (pick_tile(p.I, p.J, p.R, A_T ? 2 : B_T ? 1 : 0, cus)) {
+  float us;
+  const Tile tile = pick_tile(p.I, p.J, p.R, A_T ? 2 : B_T ? 1 : 0, cus, &us);
+  if constexpr (!A_T && !B_T) {
+    switch (pick_own(p.I, p.J, p.R, cus, us)) {
+      case kOwn64: return launch_own<OwnCfg<64, 64, 2, 2>>(p, st);
+      case kOwn64x96: return launch_own<OwnCfg<64, 96, 2, 2>>(p, st);
+      case kOwn128x96: return launch_own<OwnCfg<128, 96, 1, 2>>(p, st);
+      default: break;
+    }
+  }
+  switch (tile) {
     case kRing256x128: return launch_ring<A_T, B_T, Ring256x128>(p, st);
     case kRing128x256: return launch_ring<A_T, B_T, Ring128x256>(p, st);
     case kRing128: return launch_ring<A_T, B_T, Ring128>(p, st);

@@ -27,6 +27,11 @@ extern "C" int by_head(int64_t items, int64_t tiles, int causal, int packed, int
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
+extern "C" int own(int64_t I, int64_t J, int64_t R) {
+  float us;
+  ie::pick_tile(I, J, R, 0, 256, &us);
+  return ie::pick_own(I, J, R, 256, us);
+}
 extern "C" int tile(int64_t I, int64_t J, int64_t R, int product) { return ie::pick_tile(I, J, R, product, 256); }
 """
 TILES = [(256, 256), (256, 128), (128, 256), (128, 128), (64, 128), (64, 64), (32, 32)]   # enum Tile
@@ -275,6 +280,26 @@ def linear_tile(rules, product, M, N, K):
 ])
 def test_linear_tile(rules, product, M, N, K, tile):
     assert linear_tile(rules, product, M, N, K) == tile
+
+
+def own(rules, M, N, K):
+    return rules.own(ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K))
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (200, 12288, 4096, 3), (200, 4096, 4096, 1), (200, 4096, 11008, 1), (200, 22016, 4096, 0),
+    (33, 4200, 704, 0), (31, 4200, 2048, 0), (1537, 2368, 2368, 0), (1, 22016, 4096, 0), (8192, 4096, 4096, 0),
+])
+def test_forward_tiles_of_independent_waves(rules, M, N, K, kernel):
+    assert own(rules, M, N, K) == kernel
+
+
+def test_gpu_cases_of_independent_waves(rules):
+    """They take the kernels they name; of the ring's 64 x 64 tiles a case is left to the forward product."""
+    from test_gpu_linear_tiles import FORWARD, OWN
+    assert [own(rules, M, N, K) for M, N, K, _ in OWN] == [k for *_, k in OWN]
+    ring = [t for M, N, K, t in FORWARD if own(rules, M, N, K) == 0]
+    assert set(ring) == set(TILES)
 
 
 def test_every_linear_route_has_a_gpu_case(rules):

@@ -47,3 +47,23 @@ def test_forward_tiles(M, N, K, tile):
 def test_backward_tiles(M, N, K, dx, dw):
     print(f"case M{M} N{N} K{K} {dx} {dw}", flush=True)
     run_all(M, N, K, seed=M + N + K, which=("dx", "dw") if dx else ("dw",))
+
+
+OWN = [   # M, N, K, kernel of enum Own: the forward tiles whose waves share nothing (pick_own in csrc/dispatch.hpp)
+    (33, 4200, 768, 1),       # three steps per wave, one tile per workgroup, ragged in both indices
+    (127, 8152, 768, 1),      # the 256th tile of 256
+    (191, 1520, 832, 1),      # thirteen steps: one wave has a fourth
+    (385, 4664, 960, 1),      # two rounds: the rings run on across tiles, with a step less in one wave
+    (65, 8264, 1088, 2),
+    (191, 23832, 768, 2),     # three rounds
+    (700, 1584, 832, 2),
+    (65, 16408, 960, 3),
+    (1100, 1872, 1152, 3),
+    (255, 12272, 768, 3),
+]
+
+
+@pytest.mark.parametrize("M,N,K,own", OWN)
+def test_forward_tiles_of_independent_waves(M, N, K, own):
+    print(f"case M{M} N{N} K{K} {own}", flush=True)
+    run_all(M, N, K, seed=M + N + K, which=("fwd",))
