@@ -492,7 +492,7 @@ struct TileCoord {
 // alternate (head = w % (B*H)).  `heavy_last` says whether high tile numbers carry the most work
 // (forward and dq: causal rows late in a document see more keys).
 // `scratch`: 2 * THREADS / 64 + 2 ints of LDS (THREADS = workgroup size).
-template <int TS, int THREADS = kThreads>
+template <int TS, int THREADS = kThreads, bool LIST_BY_HEAD = false>
 __device__ __forceinline__ TileCoord decode_tile(const AttnParams& p, int heads, bool heavy_last, int* scratch, int w, int tid) {
   constexpr int NW = THREADS / 64;
   TileCoord c;
@@ -509,8 +509,16 @@ __device__ __forceinline__ TileCoord decode_tile(const AttnParams& p, int heads,
     if (slot < heavy * hpx) { hh = xcd + 8 * (slot / heavy); t = slot % heavy; }
     else { const int r = slot - heavy * hpx; hh = xcd + 8 * (r % hpx); t = heavy + r / hpx; }
   } else {
-    hh = w % nH;
-    t = w / nH;
+    // One list: head by head in the forward's dealt launches only (LIST_BY_HEAD); the other kernels' items would only pay for the
+    // second division (35 x 293 x 27 backward 436 : 442 us).
+    const int by_head = LIST_BY_HEAD ? p.q_heavy * nH : 0;
+    if (LIST_BY_HEAD && w < by_head) {
+      hh = w / p.q_heavy;
+      t = w % p.q_heavy;
+    } else {
+      hh = (w - by_head) % nH;
+      t = (LIST_BY_HEAD ? p.q_heavy : 0) + (w - by_head) / nH;
+    }
   }
   if (heavy_last) t = p.tiles - 1 - t;
   c.b = hh / heads;

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kThreads, LAZY ? 4 : 2) void attn_fwd_kernel(AttnPa
 
   int item = (int)blockIdx.x;
   if (FLIP && item >= p.flip_lo && item < p.flip_hi) item = p.flip_lo + (((p.flip_hi - p.flip_lo) >> 3) - 1 - ((item - p.flip_lo) >> 3)) * 8 + (item & 7);
-  TileCoord tc = decode_tile<BM>(p, p.Hq, true, scratch, item, tid);
+  TileCoord tc = decode_tile<BM, kThreads, true>(p, p.Hq, true, scratch, item, tid);
   if (!tc.valid) return;
   const int g = tc.h / (p.Hq / p.Hkv);
   // Tile coordinates come through LDS where documents are packed, so the compiler takes them for per-lane values: as scalars

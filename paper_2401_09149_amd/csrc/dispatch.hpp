@@ -202,7 +202,9 @@ inline bool fwd_flips(int64_t items, int64_t tiles, bool causal, bool packed, in
 // 16 tiles 8 to 12 items 1.06, 12 to 16 0.96; two tiles 0.97 to 1.08 at any number.  (16 x 1024 x 32, 4 per group, 215 -> 190 us; 4 x
 // 4096 x 16, D = 64, 145 : 155.)  An odd number of tiles, because an even one shares a factor with the CUs and gives the
 // heaviest tiles to the same ones (causal, all of 3, 4, 6 and 8 tiles 0.87, 1.03, 0.88, 0.95).  4113 launches of 600 to 16000
-// items: 7 % faster on average.
+// items: 7 % faster on average.  Head counts that are no multiple of eight, whose heads are spread over all XCDs, gain where K and V
+// of all heads outgrow the last-level cache (83 x 544 x 36 769 -> 514 us, bidirectional 45 x 1792 x 20 2504 -> 1590): 2023 launches 4.5
+// % faster, the worst cells of the above (heads, items, tiles) 1.03.
 inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool packed, bool d64, int64_t cus) {
   if (packed || tiles < 2 || items <= 2 * cus) return 0;
   if (!causal) return (int)tiles;

@@ -110,18 +110,19 @@ def test_items_in_the_opposite_order(D):
     assert torch.equal(o, torch.cat([a for a, _ in parts], 2)) and torch.equal(lse, torch.cat([b for _, b in parts], 1))
 
 
-@pytest.mark.parametrize("S,heads,D,causal,backward", [
-    (129, 520, 64, False, False), (200, 264, 128, False, True), (384, 400, 128, False, True),   # two and three tiles, all head by head
-    (300, 688, 128, True, False), (641, 352, 128, True, False), (513, 624, 64, True, False),    # three, six and five, odd shares
+@pytest.mark.parametrize("S,heads,D,causal,backward,H", [
+    (129, 520, 64, False, False, 8), (200, 264, 128, False, True, 8), (384, 400, 128, False, True, 8),   # two and three tiles, all head by head
+    (300, 688, 128, True, False, 8), (641, 352, 128, True, False, 8), (513, 624, 64, True, False, 8),    # three, six and five, odd shares
+    (129, 521, 64, False, False, 1), (200, 265, 128, False, True, 5), (641, 351, 128, True, False, 3),   # one list of heads
 ])
-def test_many_heads_in_head_by_head_order(S, heads, D, causal, backward):
+def test_many_heads_in_head_by_head_order(S, heads, D, causal, backward, H):
     """Launches of many heads (fwd_head_by_head in csrc/dispatch.hpp; bidirectional at head dimension 128 the shared backward
     launch too): the batch repeats two entries, of which the first two are compared with the oracle and the others, bit for
     bit, with those two: every item has run, for its own rows."""
     import torch
     from paper_2401_09149_amd import binding
-    print(f"case S{S} heads {heads} D{D} {causal}", flush=True)
-    dev, H, U = "cuda:0", 8, 2
+    print(f"case S{S} heads {heads} D{D} {causal} H{H}", flush=True)
+    dev, U = "cuda:0", 2
     B = heads // H
     small = [randn_bf16((U, S, H, D), 990 + j) for j in range(4)]
     q, k, v, do = (x.to(dev).repeat((B + 1) // U, 1, 1, 1)[:B].contiguous() for x in small)
