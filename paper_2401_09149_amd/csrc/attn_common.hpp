@@ -482,7 +482,8 @@ struct TileCoord {
 // Tiles of `TS` tokens never straddle documents.  `w` is the item number a persistent workgroup
 // drew from its queue (tile_queue.hpp): item w belongs to the list of XCD w & 7 and is that
 // list's entry number w >> 3.  When B*H is a multiple of 8, list x holds the heads x, x+8, ... .
-// Its first part (empty where a workgroup gets two items at most, see tile_queue_prepare) walks the heads one after the
+// Its first part (empty where a workgroup gets two items at most, see tile_queue_prepare; launches without a queue:
+// fwd_head_by_head in dispatch.hpp) walks the heads one after the
 // other, the heavier 5/8 of each head's tiles from
 // the heaviest down: the workgroups of an XCD then stream the SAME head's K/V (or Q/dO) through
 // its L2 nearly in lock-step, and each is fetched from HBM once per group of co-resident tiles.

@@ -5,9 +5,10 @@
 // ("direct": x and w in the forward, dy in dx) or with its output index contiguous ("transposed":
 // w in dx, dy and x in dw), so kernel templates with two flags serve them.
 //
-// Two kernels share the tile order, the copies and the fragment layouts.  linear_pp_kernel computes 256 x 256 tiles of C
+// Three kernels share the tile order, the copies and the fragment layouts.  linear_pp_kernel computes 256 x 256 tiles of C
 // and is the faster one per product; linear_ring_kernel computes smaller ones, down to 32 x 32, for outputs that
-// do not fill the chip with large tiles (pick_tile in dispatch.hpp chooses).  In both a workgroup is 8 wavefronts (two per SIMD),
+// do not fill the chip with large tiles (pick_tile in dispatch.hpp chooses); linear_own_kernel serves the forward product over few
+// tokens (pick_own).  In the first two a workgroup is 8 wavefronts (two per SIMD),
 // one workgroup per CU, each walking its share of the tiles; operands reach LDS by asynchronous copies that run ahead
 // of the products across tile boundaries.  Tiles sit in LDS row-major with swizzled 16-byte chunks; a direct operand's
 // fragment is one 16-byte LDS read, a transposed operand's two transpose loads.  The products are formed transposed,
