@@ -202,12 +202,24 @@ inline bool fwd_flips(int64_t items, int64_t tiles, bool causal, bool packed, in
 // 16 tiles 8 to 12 items 1.06, 12 to 16 0.96; two tiles 0.97 to 1.08 at any number.  (16 x 1024 x 32, 4 per group, 215 -> 190 us; 4 x
 // 4096 x 16, D = 64, 145 : 155.)  An odd number of tiles, because an even one shares a factor with the CUs and gives the
 // heaviest tiles to the same ones (causal, all of 3, 4, 6 and 8 tiles 0.87, 1.03, 0.88, 0.95).  4113 launches of 600 to 16000
-// items: 7 % faster on average.  Head counts that are no multiple of eight, whose heads are spread over all XCDs, gain where K and V
-// of all heads outgrow the last-level cache (83 x 544 x 36 769 -> 514 us, bidirectional 45 x 1792 x 20 2504 -> 1590): 2023 launches 4.5
-// % faster, the worst cells of the above (heads, items, tiles) 1.03.
-inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool packed, bool d64, int64_t cus) {
+// items: 7 % faster on average.
+// `one_list`: head counts that are no multiple of eight, whose heads are spread over all XCDs.  They gain where K and V of all
+// heads (`kv_bytes`) outgrow the last-level cache (83 x 544 x 36 769 -> 514 us, bidirectional 45 x 1792 x 20 2504 -> 1590), or where a
+// launch is long for its heads.  Bidirectional, head by head over tile by tile, mean and largest of 2450 launches: two to four tiles, up
+// to 192 MiB 0.995, 1.13, more 0.81, 1.01; five to eight tiles, up to 3 items per CU 1.03, 1.18, up to 6 0.97, 1.11, more 0.87,
+// 1.06; nine to sixteen, up to 3 0.995, 1.07, more 0.89, 1.04; longer heads 0.91, 1.02 (5 x 896 x 20 56.8 : 62.8 us, 3 x 713 x 36 45.1
+// : 54.0, 25 x 192 x 28, 2 per group, 35.0 : 38.5).
+// `last_rows`: of a head's last tile.  Two tiles of which one is not half full are unequal, and the same CUs get the fuller ones
+// (lists, D = 128: up to 32 rows 1.03, 1.06, up to 64 0.97, 1.09, up to 96 0.92, 1.03, more 0.87; 54 x 163 x 32 74.8 : 80.9 us).
+inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool packed, bool d64, int64_t cus, bool one_list = false,
+                            int64_t kv_bytes = 0, int64_t last_rows = 128) {
   if (packed || tiles < 2 || items <= 2 * cus) return 0;
-  if (!causal) return (int)tiles;
+  if (!causal) {
+    if (one_list && tiles <= 4 && kv_bytes <= ((int64_t)192 << 20)) return 0;
+    if (one_list && tiles > 4 && tiles <= 16 && items <= (tiles <= 8 ? 6 : 3) * cus) return 0;
+    if (!d64 && tiles == 2 && last_rows <= 64) return 0;
+    return (int)tiles;
+  }
   if (tiles < 3 || items <= (tiles > 16 ? 16 : d64 ? 12 : 8) * cus) return 0;
   const int64_t share = (tiles - tiles * 3 / 8) | 1;
   return (int)(share < tiles ? share : tiles);

@@ -24,6 +24,10 @@ extern "C" int lazy_64(int64_t items, int causal, int packed, int64_t tiles) { r
 extern "C" int by_head(int64_t items, int64_t tiles, int causal, int packed, int d64) {
   return ie::fwd_head_by_head(tiles, items, causal != 0, packed != 0, d64 != 0, 256);
 }
+extern "C" int by_head_of(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t D) {
+  const int64_t tiles = (S + 127) / 128;
+  return ie::fwd_head_by_head(tiles, tiles * B * Hq, causal != 0, false, D == 64, 256, B * Hq % 8 != 0, B * S * Hkv * D * 4, S - (tiles - 1) * 128);
+}
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
 }
@@ -110,6 +114,53 @@ def test_forward_order(rules, B, S, H, causal, packed, flips):
 ])
 def test_forward_head_by_head(rules, items, tiles, causal, packed, d64, share):
     assert rules.by_head(ctypes.c_int64(items), ctypes.c_int64(tiles), causal, packed, d64) == share
+
+
+def by_head(rules, B, S, Hq, Hkv, causal, D):
+    return rules.by_head_of(*map(ctypes.c_int64, (B, S, Hq, Hkv)), causal, ctypes.c_int64(D))
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,causal,D,share", [
+    (43, 256, 31, 31, 0, 128, 0),       # one list, two to four tiles: K and V of all heads stay in the last-level cache
+    (25, 192, 28, 14, 0, 128, 0),
+    (17, 301, 12, 12, 0, 128, 0),
+    (45, 512, 4, 4, 0, 64, 0),
+    (1537, 256, 1, 1, 0, 128, 2),       # 192 MiB and more
+    (1535, 256, 1, 1, 0, 128, 0),
+    (3074, 256, 2, 1, 0, 128, 2),
+    (3, 713, 36, 36, 0, 128, 0),        # five to eight tiles, few items per CU
+    (5, 896, 20, 20, 0, 128, 0),
+    (6, 896, 30, 30, 0, 64, 0),
+    (307, 513, 1, 1, 0, 128, 0),
+    (309, 513, 1, 1, 0, 128, 5),
+    (86, 1152, 1, 1, 0, 64, 9),         # nine and more
+    (85, 1152, 1, 1, 0, 64, 0),
+    (31, 2176, 1, 1, 0, 128, 17),
+    (54, 163, 32, 32, 0, 128, 0),       # lists, two tiles of which one is not half full
+    (54, 192, 32, 32, 0, 128, 0),
+    (54, 193, 32, 32, 0, 128, 2),
+    (54, 163, 32, 32, 0, 64, 2),
+    (378, 975, 4, 4, 0, 128, 8),
+    (83, 544, 36, 36, 1, 128, 5),
+    (118, 2230, 5, 5, 1, 64, 13),
+])
+def test_forward_head_by_head_by_shape(rules, B, S, Hq, Hkv, causal, D, share):
+    assert by_head(rules, B, S, Hq, Hkv, causal, D) == share
+
+
+def test_gpu_cases_of_many_heads(rules):
+    """test_many_heads_in_head_by_head_order: the kernel with that order, the share of tiles it names and, with a backward
+    pass, the shared launch."""
+    from test_gpu_fwd_routes import MANY_HEADS
+    for S, heads, D, causal, backward, H, group, share in MANY_HEADS:
+        B, Hkv = heads // H, H // group
+        assert heads % H == 0 and by_head(rules, B, S, H, Hkv, causal, D) == share, (S, heads)
+        if D == 128:
+            assert rules.fwd_128(*map(ctypes.c_int64, (B, S, H)), causal, ctypes.c_int64(0), 1) == NARROW, (S, heads)   # (sizes alone: 4096 tokens and fewer)
+        if backward:
+            assert rules.one_launch_128(*map(ctypes.c_int64, (B, S, H, Hkv)), causal, ctypes.c_int64(0)) == 1, (S, heads)
+    assert {(D, causal, B_H % 8 != 0) for _, B_H, D, causal, _, _, _, share in MANY_HEADS if share} >= {
+        (64, False, False), (64, False, True), (64, True, False), (128, False, False), (128, False, True), (128, True, False), (128, True, True)}
 
 
 @pytest.mark.parametrize("S,H,causal,packed,lazy", [

@@ -110,21 +110,28 @@ def test_items_in_the_opposite_order(D):
     assert torch.equal(o, torch.cat([a for a, _ in parts], 2)) and torch.equal(lse, torch.cat([b for _, b in parts], 1))
 
 
-@pytest.mark.parametrize("S,heads,D,causal,backward,H", [
-    (129, 520, 64, False, False, 8), (200, 264, 128, False, True, 8), (384, 400, 128, False, True, 8),   # two and three tiles, all head by head
-    (300, 688, 128, True, False, 8), (641, 352, 128, True, False, 8), (513, 624, 64, True, False, 8),    # three, six and five, odd shares
-    (129, 521, 64, False, False, 1), (200, 265, 128, False, True, 5), (641, 351, 128, True, False, 3),   # one list of heads
-])
-def test_many_heads_in_head_by_head_order(S, heads, D, causal, backward, H):
+MANY_HEADS = [   # S, heads of all batch entries, D, causal, backward, heads, heads per kv head, tiles per head that go head by head
+    (129, 520, 64, False, False, 8, 1, 2), (200, 264, 128, False, True, 8, 1, 2), (384, 400, 128, False, True, 8, 1, 3),   # lists, all tiles
+    (300, 688, 128, True, False, 8, 1, 3), (641, 352, 128, True, False, 8, 1, 5), (513, 624, 64, True, False, 8, 1, 5),    # odd shares
+    (129, 521, 64, False, False, 1, 1, 0), (200, 265, 128, False, True, 5, 1, 0),   # one list of heads, tile by tile
+    (641, 351, 128, True, False, 3, 1, 5), (1152, 86, 64, False, False, 2, 1, 9), (513, 309, 128, False, True, 3, 1, 5),   # one list, head by head
+    (256, 1537, 128, False, False, 1, 1, 2),
+    (129, 520, 64, False, False, 8, 4, 2), (384, 400, 128, False, True, 8, 2, 3), (641, 352, 128, True, False, 8, 4, 5),   # grouped heads
+    (641, 354, 128, True, False, 6, 3, 5), (1152, 86, 64, False, False, 2, 2, 9),
+]
+
+
+@pytest.mark.parametrize("S,heads,D,causal,backward,H,group,share", MANY_HEADS)
+def test_many_heads_in_head_by_head_order(S, heads, D, causal, backward, H, group, share):
     """Launches of many heads (fwd_head_by_head in csrc/dispatch.hpp; bidirectional at head dimension 128 the shared backward
     launch too): the batch repeats two entries, of which the first two are compared with the oracle and the others, bit for
     bit, with those two: every item has run, for its own rows."""
     import torch
     from paper_2401_09149_amd import binding
-    print(f"case S{S} heads {heads} D{D} {causal} H{H}", flush=True)
+    print(f"case S{S} heads {heads} D{D} {causal} H{H} group {group}", flush=True)
     dev, U = "cuda:0", 2
     B = heads // H
-    small = [randn_bf16((U, S, H, D), 990 + j) for j in range(4)]
+    small = [randn_bf16((U, S, H if j in (0, 3) else H // group, D), 990 + j) for j in range(4)]
     q, k, v, do = (x.to(dev).repeat((B + 1) // U, 1, 1, 1)[:B].contiguous() for x in small)
     o, lse = binding.attn_fwd(q, k, v, D ** -0.5, causal)
     got = (o, lse) + (binding.attn_bwd(q, k, v, o, do, lse, D ** -0.5, causal) if backward else ())
