@@ -1581,9 +1581,7 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     kv.q_total = (int32_t)(tiles * p.B * p.Hkv);
     q.q_total = (int32_t)(tiles * p.B * p.Hq);
     int64_t grid = (int64_t)kv.q_total + q.q_total;
-    // Equal items go head by head, so that the workgroups that run together share a head's rows in L2 (fwd_head_by_head in
-    // dispatch.hpp; here 151 x 384 x 8 605 -> 534 us, 110 x 384 x 4 217 -> 192, at head dimension 64 1.00).
-    if (D == 128 && kOnce && !p.causal && !p.cu) kv.q_heavy = q.q_heavy = (int)tiles;
+    if (D == 128 && kOnce) kv.q_heavy = q.q_heavy = bwd_head_by_head(tiles, p.S - (tiles - 1) * 128, p.causal != 0, p.cu != nullptr);
     if constexpr (!kOnce) {
       const QueueLaunch qk = tile_queue_prepare(kv, p.ws_counters + kCountersDkdv, kv.q_total, kv.Hkv, per_cu, st, cleared_by_delta);
       if (qk.err != hipSuccess) return hip_fail(qk.err);

@@ -225,6 +225,14 @@ inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool pack
   return (int)(share < tiles ? share : tiles);
 }
 
+// Shared backward launch at head dimension 128, dealt out by the hardware: how many of a head's tiles go head by head?  All, where
+// items are equal, so that the workgroups that run together share a head's rows in L2 (151 x 384 x 8 605 -> 534 us, 110 x 384 x 4
+// 217 -> 192; at head dimension 64 1.00; one list of heads goes tile by tile whatever this says).  Two tiles of which one is not
+// three quarters full are no gain (295 calls: up to 96 rows 0.99, 1.05 at most, more 0.944, 0.99; 193 x 161 x 8, 4 per group, 243 : 252).
+inline int bwd_head_by_head(int64_t tiles, int64_t last_rows, bool causal, bool packed) {
+  return causal || packed || (tiles == 2 && last_rows <= 96) ? 0 : (int)tiles;
+}
+
 // Forward at head dimension 64: unmasked blocks without a search for their maximum (LAZY in attn_fwd.hip)?  Where a wave has
 // its SIMD to itself the search is the shorter way (lazy : search, 165 x 40 6.34 : 6.12 us, 2911 x 4 41.9 : 39.9, 5374 x 1 72.3 :
 // 68.9); with several waves per SIMD it is work that can be left out.  Lazy against search in 200 launches, on average:
