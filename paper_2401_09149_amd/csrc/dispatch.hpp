@@ -287,8 +287,7 @@ constexpr TileCost kCost[kTiles] = {
     {64, 64, 1, {0.254f, 0.281f, 0.264f}, 1.28f, 0.72f, 2.06f},
     {32, 32, 4, {0.128f, 0.f, 0.f}, 0.49f, 0.95f, 0.00f}};
 
-// C[I][J] over a contraction of R; product: 0 forward, 1 dx, 2 dw.
-// `us`: the estimate.
+// C[I][J] over a contraction of R; product: 0 forward, 1 dx, 2 dw.  `us_out`: the estimate.
 inline Tile pick_tile(int64_t I, int64_t J, int64_t R, int product, int64_t cus, float* us_out = nullptr) {
   const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
@@ -313,29 +312,37 @@ inline Tile pick_tile(int64_t I, int64_t J, int64_t R, int product, int64_t cus,
   return best;
 }
 
-// Forward product: tiles whose four waves share nothing (linear_own_kernel), where their estimated time is less than `other_us`,
-// that of pick_tile's choice?  They gain where a call is a few rounds of small tiles: contractions of 768 and more (a wave's ring
-// holds two of its steps, 512), 32 to 1536 tokens, the range measured (below 32 the 32 x 32 tiles, which read a weight once, were
-// ahead in all but a few).  Costs per 256-deep step, around a tile and of a launch (`kOther` of the others, whose estimates leave
-// it out) fitted to 434 measured calls, widths 512 to 22016: 4 % faster than without these tiles on average (half of the calls
-// take them), 0.4 % slower than the best choice, eleven calls 3 to 7 % slower than without.  200 tokens, 4096 x 4096 21.5 ->
-// 18.3 us, 12288 x 4096 43.5 -> 36.7, 4096 x 11008 50.8 -> 42.0.
+// Forward product: tiles whose four waves share nothing (linear_own_kernel), where their estimated time is less than that of
+// pick_tile's choice (`other_us`), by 3 %?  They gain where a call is a few rounds of small tiles with a long contraction.  Costs per
+// 256-deep step, around a tile and of a launch, fitted, as is what makes an estimate of pick_tile's a time (kOther and what follows
+// it), to 11200 calls, each on weights that come from memory and on weights that stay in the caches: 32 to 1536 tokens, widths 512 to
+// 131072, contractions of 768 to 32768, which is the range the rule is held to, but for contractions below 1024, where nothing is
+// gained (1.00).  `once`: with few row tiles most of a step's bytes are weights that are read from memory and by one tile; `empty`:
+// rows that do not exist repeat the last one and cost less.  (Without those terms, with costs from weights that stay in the caches, 537
+// of these calls were more than 3 % slower than without these tiles on weights from memory: 362 x 11088 x 768 13.5 : 16.7 us, 85 x
+// 33288 x 1792 31.2 : 37.5, 83 x 12360 x 9856 66.3 : 76.3, 113 x 33000 x 2496 44.1 : 52.6.)  Now two calls in five take them, for
+// 7 % less time on average (15 % with weights in the caches); 264 are more than 3 % slower than without (120), 24 (30) more than
+// 10 % (15 % at most: 199 x 6464 x 6720 42 : 48), and all calls are 0.4 % (0.8 %) slower than with the best choice.
 enum Own { kOwnNone, kOwn64, kOwn64x96, kOwn128x96, kOwns };
-struct OwnCost { int ti, tj; float step_us, tile_us, light, launch_us; };
-constexpr OwnCost kOwnCost[kOwns] = {
-    {0, 0, 0.f, 0.f, 0.f, 0.f}, {64, 64, 0.930f, 0.09f, 0.707f, 3.61f}, {64, 96, 1.249f, 0.08f, 0.780f, 3.59f}, {128, 96, 1.809f, 0.82f, 0.630f, 4.18f}};
-inline Own pick_own(int64_t I, int64_t J, int64_t R, int64_t cus, float other_us) {
-  constexpr float kOther = 3.f, kGain = 0.96f;
+struct OwnCost { int ti, tj; float step_us, tile_us, light, launch_us, once, empty; };
+constexpr OwnCost kOwnCost[kOwns] = {{0, 0, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f},
+                                     {64, 64, 0.779f, 0.944f, 0.701f, 2.623f, 0.564f, 0.398f},
+                                     {64, 96, 0.995f, 1.691f, 0.729f, 2.739f, 0.535f, 0.252f},
+                                     {128, 96, 1.448f, 4.213f, 0.609f, 2.181f, 0.427f, 0.419f}};
+// `other_rows`: rows of the tiles of pick_tile's choice.
+inline Own pick_own(int64_t I, int64_t J, int64_t R, int64_t cus, float other_us, int64_t other_rows) {
+  constexpr float kOther = 2.101f, kAll = 0.956f, kOnce = 0.216f, kEmpty = 0.161f, kGain = 0.97f;
   const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-  if (R < 768 || I < 32 || I > 1536) return kOwnNone;
+  const auto empty = [&](int64_t ti) { return 1.f - (float)I / (float)(ceil_div(I, ti) * ti); };   // share of the tiles' rows
+  if (I < 32 || I > 1536 || J < 512 || J > 131072 || R < 1024 || R > 32768) return kOwnNone;
   const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
   Own best = kOwnNone;
-  float best_us = (other_us + kOther) * kGain;
+  float best_us = (other_us + kOther) * (kAll + kOnce / (float)ceil_div(I, 64) - kEmpty * empty(other_rows)) * kGain;
   for (int k = 1; k < kOwns; ++k) {
     const OwnCost& c = kOwnCost[k];
-    const int64_t per = ceil_div(ceil_div(I, c.ti) * ceil_div(J, c.tj), 8);
+    const int64_t rows = ceil_div(I, c.ti), per = ceil_div(rows * ceil_div(J, c.tj), 8);
     const int64_t full = per / per_xcd, rest = per % per_xcd;
-    const float steps = (float)ceil_div(R, 256) * c.step_us;
+    const float steps = (float)ceil_div(R, 256) * c.step_us * (1.f + c.once / (float)rows - c.empty * empty(c.ti));
     float us = c.launch_us + (float)full * (steps + c.tile_us);
     if (rest) us += steps * (c.light + (1.f - c.light) * (float)rest / (float)per_xcd) + c.tile_us;
     if (us < best_us) { best = (Own)k; best_us = us; }

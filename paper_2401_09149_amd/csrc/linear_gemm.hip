@@ -512,8 +512,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void linear_ring_kernel(GemmParams 
 // in one go, so that its slots are filled again behind its own first products.
 // Bound: the loaded latency of the copies (2 us) over the 112-160 KiB that LDS has room for in flight, 55-65 GB/s per CU.  (L2 alone
 // delivers 105.  Fragments loaded from memory straight to registers take half the rate, whatever their number in flight; lines of
-// the weights touched 4 to 32 steps ahead make every tile slower.)  200 tokens: 4096 x 4096 21.5 -> 18.3 us, 4096 x 11008
-// 50.8 -> 42.0 (64 x 64), 12288 x 4096 43.5 -> 36.7 (128 x 96).
+// the weights touched 4 to 32 steps ahead make every tile slower.)  200 tokens, the ring kernel -> this one, weights in
+// the caches and from memory: 4096 x 4096 17.6 -> 14.4, 17.8 -> 16.9 us, 4096 x 11008 39.8 -> 33.9, 42.2 -> 42.1 (64 x 64), 12288 x
+// 4096 39.2 -> 29.7, 41.0 -> 35.4 (128 x 96).
 template <int CI_, int CJ_, int NA_, int NB_>
 struct OwnCfg {
   static constexpr int CI = CI_, CJ = CJ_, NA = NA_, NB = NB_, WAVES = 4;   // NA, NB: 64-deep steps of each operand in a wave's ring
@@ -740,7 +741,7 @@ int launch_gemm(const GemmParams& p, hipStream_t st) {
   float us;
   const Tile tile = pick_tile(p.I, p.J, p.R, A_T ? 2 : B_T ? 1 : 0, cus, &us);
   if constexpr (!A_T && !B_T) {
-    switch (pick_own(p.I, p.J, p.R, cus, us)) {
+    switch (pick_own(p.I, p.J, p.R, cus, us, kCost[tile].ti)) {
       case kOwn64: return launch_own<OwnCfg<64, 64, 2, 2>>(p, st);
       case kOwn64x96: return launch_own<OwnCfg<64, 96, 2, 2>>(p, st);
       case kOwn128x96: return launch_own<OwnCfg<128, 96, 1, 2>>(p, st);

@@ -37,8 +37,8 @@ extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, 
 }
 extern "C" int own(int64_t I, int64_t J, int64_t R) {
   float us;
-  ie::pick_tile(I, J, R, 0, 256, &us);
-  return ie::pick_own(I, J, R, 256, us);
+  const ie::Tile tile = ie::pick_tile(I, J, R, 0, 256, &us);
+  return ie::pick_own(I, J, R, 256, us, ie::kCost[tile].ti);
 }
 extern "C" int tile(int64_t I, int64_t J, int64_t R, int product) { return ie::pick_tile(I, J, R, product, 256); }
 """
@@ -356,18 +356,30 @@ def own(rules, M, N, K):
 
 @pytest.mark.parametrize("M,N,K,kernel", [
     (200, 12288, 4096, 3), (200, 4096, 4096, 1), (200, 4096, 11008, 1), (200, 22016, 4096, 0),
-    (33, 4200, 704, 0), (31, 4200, 2048, 0), (1537, 2368, 2368, 0), (1, 22016, 4096, 0), (8192, 4096, 4096, 0),
+    (31, 4096, 4096, 0), (1537, 2368, 2368, 0), (1, 22016, 4096, 0), (8192, 4096, 4096, 0),
+    (48, 6144, 1024, 1), (48, 6144, 960, 0), (60, 69632, 1280, 2), (60, 131080, 1280, 0), (600, 504, 8192, 0), (1111, 5328, 14848, 3),
+    (270, 10912, 32768, 3), (270, 10912, 32832, 0),
+    (362, 11088, 768, 0),      # few steps, several rounds
+    (318, 13312, 1024, 0), (131, 16128, 768, 0),
+    (85, 33288, 1792, 0),      # one row tile, two rounds of weights that are read once
+    (113, 33000, 2496, 0), (127, 39936, 2304, 0),
+    (83, 12360, 9856, 0),      # and one round of them
+    (84, 12544, 6912, 0),
+    (683, 3584, 768, 0),       # few steps
+    (132, 11776, 768, 0),
 ])
 def test_forward_tiles_of_independent_waves(rules, M, N, K, kernel):
     assert own(rules, M, N, K) == kernel
 
 
 def test_gpu_cases_of_independent_waves(rules):
-    """They take the kernels they name; of the ring's 64 x 64 tiles a case is left to the forward product."""
+    """They take the kernels they name, each also with more tiles than CUs; the ring's cases are left to the ring."""
     from test_gpu_linear_tiles import FORWARD, OWN
     assert [own(rules, M, N, K) for M, N, K, _ in OWN] == [k for *_, k in OWN]
-    ring = [t for M, N, K, t in FORWARD if own(rules, M, N, K) == 0]
-    assert set(ring) == set(TILES)
+    for kernel, (ti, tj) in {1: (64, 64), 2: (64, 96), 3: (128, 96)}.items():
+        assert any(k == kernel and -(-M // ti) * -(-N // tj) > 256 for M, N, _, k in OWN), kernel
+    assert {(k, K // 64 % 4 != 0) for _, _, K, k in OWN} >= {(1, True), (2, True), (3, True), (1, False), (2, False), (3, False)}
+    assert all(own(rules, M, N, K) == 0 for M, N, K, _ in FORWARD)
 
 
 def test_every_linear_route_has_a_gpu_case(rules):

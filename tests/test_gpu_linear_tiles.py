@@ -13,7 +13,8 @@ FORWARD = [   # M, N, K, tile
     (33, 2056, 320, (32, 32)),       # one step and a quarter
     (1, 9736, 768, (32, 32)),        # more tiles than CUs: the ring runs on across tiles
     (31, 9608, 576, (64, 64)),       # one tile row, ragged in both indices
-    (250, 4040, 2112, (64, 64)),
+    (250, 4040, 2112, (64, 64)),     # 33 steps, more row tiles than one
+    (1543, 520, 2112, (64, 64)),
     (129, 8200, 128, (64, 128)),     # fewer steps than ring stages
     (130, 20488, 320, (64, 128)),    # more tiles than CUs
     (255, 12296, 192, (128, 128)),
@@ -50,16 +51,18 @@ def test_backward_tiles(M, N, K, dx, dw):
 
 
 OWN = [   # M, N, K, kernel of enum Own: the forward tiles whose waves share nothing (pick_own in csrc/dispatch.hpp)
-    (33, 4200, 768, 1),       # three steps per wave, one tile per workgroup, ragged in both indices
-    (127, 8152, 768, 1),      # the 256th tile of 256
-    (191, 1520, 832, 1),      # thirteen steps: one wave has a fourth
-    (385, 4664, 960, 1),      # two rounds: the rings run on across tiles, with a step less in one wave
-    (65, 8264, 1088, 2),
-    (191, 23832, 768, 2),     # three rounds
-    (700, 1584, 832, 2),
-    (65, 16408, 960, 3),
-    (1100, 1872, 1152, 3),
-    (255, 12272, 768, 3),
+    (35, 4552, 1024, 1),      # four steps per wave, one tile per workgroup, ragged in both indices
+    (449, 2008, 1792, 1),     # the 256th tile of 256
+    (394, 624, 2112, 1),      # 33 steps: one wave has a ninth
+    (1478, 1296, 1280, 1),    # two rounds: the rings run on across tiles
+    (65, 8320, 1856, 2),
+    (33, 68312, 1728, 2),     # three rounds, with a step less in one wave
+    (604, 1608, 1024, 2),
+    (65, 16736, 1984, 3),
+    (1218, 1624, 1536, 3),
+    (130, 12224, 1536, 3),    # 256 tiles
+    (260, 11032, 5632, 3),    # two rounds: the rings, one step of A and two of B, run on across tiles
+    (266, 10912, 6336, 3),    # and with a step less in one wave
 ]
 
 
