@@ -1581,7 +1581,11 @@ static int launch_bwd_d(AttnParams p, int phases, hipStream_t st) {
     kv.q_total = (int32_t)(tiles * p.B * p.Hkv);
     q.q_total = (int32_t)(tiles * p.B * p.Hq);
     int64_t grid = (int64_t)kv.q_total + q.q_total;
-    if (D == 128 && kOnce) kv.q_heavy = q.q_heavy = bwd_head_by_head(tiles, p.S - (tiles - 1) * 128, p.causal != 0, p.cu != nullptr);
+    if (D == 128 && kOnce) {
+      const int cus = cu_count(&e);
+      if (e != hipSuccess) return hip_fail(e);
+      kv.q_heavy = q.q_heavy = bwd_head_by_head(tiles, p.S - (tiles - 1) * 128, q.q_total, p.causal != 0, p.cu != nullptr, cus);
+    }
     if constexpr (!kOnce) {
       const QueueLaunch qk = tile_queue_prepare(kv, p.ws_counters + kCountersDkdv, kv.q_total, kv.Hkv, per_cu, st, cleared_by_delta);
       if (qk.err != hipSuccess) return hip_fail(qk.err);

@@ -227,11 +227,15 @@ inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool pack
 }
 
 // Shared backward launch at head dimension 128, dealt out by the hardware: how many of a head's tiles go head by head?  All, where
-// items are equal, so that the workgroups that run together share a head's rows in L2 (151 x 384 x 8 605 -> 534 us, 110 x 384 x 4
-// 217 -> 192; at head dimension 64 1.00; one list of heads goes tile by tile whatever this says).  Two tiles of which one is not
-// three quarters full are no gain (295 calls: up to 96 rows 0.99, 1.05 at most, more 0.944, 0.99; 193 x 161 x 8, 4 per group, 243 : 252).
-inline int bwd_head_by_head(int64_t tiles, int64_t last_rows, bool causal, bool packed) {
-  return causal || packed || (tiles == 2 && last_rows <= 96) ? 0 : (int)tiles;
+// items are equal, so that the workgroups that run together share a head's rows in L2 (151 x 384 x 8 601 -> 531 us, 110 x 384 x 4
+// 210 -> 189; at head dimension 64 1.00; one list of heads goes tile by tile whatever this says).  Two tiles of which one is partly
+// full are unequal.  Head by head over tile by tile, by rows of the last tile, mean and largest of 1962 calls, with up to two dQ
+// items (`items`) per CU : with more: up to 64 rows 1.015, 1.10 : 0.997, 1.04; up to 96 1.00, 1.04 : 0.986, 1.02; more 0.994, 1.02 :
+// 0.976, 1.01 (15 x 202 x 24 103 : 107 us; 193 x 161 x 8, 4 per group, 271 : 261).
+inline int bwd_head_by_head(int64_t tiles, int64_t last_rows, int64_t items, bool causal, bool packed, int64_t cus) {
+  if (causal || packed) return 0;
+  if (tiles == 2 && (last_rows <= 64 || (last_rows <= 96 && items <= 2 * cus))) return 0;
+  return (int)tiles;
 }
 
 // Forward at head dimension 64: unmasked blocks without a search for their maximum (LAZY in attn_fwd.hip)?  Where a wave has

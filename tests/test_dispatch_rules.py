@@ -28,9 +28,9 @@ extern "C" int by_head_of(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int cau
   const int64_t tiles = (S + 127) / 128;
   return ie::fwd_head_by_head(tiles, tiles * B * Hq, causal != 0, false, D == 64, 256, B * Hq % 8 != 0, B * S * Hkv * D * 4, S - (tiles - 1) * 128);
 }
-extern "C" int bwd_by_head(int64_t S, int causal, int packed) {
+extern "C" int bwd_by_head(int64_t S, int64_t heads, int causal, int packed) {
   const int64_t tiles = (S + 127) / 128;
-  return ie::bwd_head_by_head(tiles, S - (tiles - 1) * 128, causal != 0, packed != 0);
+  return ie::bwd_head_by_head(tiles, S - (tiles - 1) * 128, tiles * heads, causal != 0, packed != 0, 256);
 }
 extern "C" int dq16(int64_t items_128, int64_t items_256, int wide, int causal, int packed) {
   return ie::dq128_on_16x16x32(items_128, items_256, wide != 0, causal != 0, packed != 0, 256);
@@ -157,11 +157,13 @@ def test_forward_head_by_head_by_shape(rules, B, S, Hq, Hkv, causal, D, share):
     assert by_head(rules, B, S, Hq, Hkv, causal, D) == share
 
 
-@pytest.mark.parametrize("S,causal,packed,share", [
-    (161, 0, 0, 0), (224, 0, 0, 0), (225, 0, 0, 2), (256, 0, 0, 2), (257, 0, 0, 3), (384, 0, 0, 3), (384, 1, 0, 0), (384, 0, 1, 0), (100, 0, 0, 1),
+@pytest.mark.parametrize("S,heads,causal,packed,share", [
+    (161, 1544, 0, 0, 0), (192, 1544, 0, 0, 0), (193, 1544, 0, 0, 2), (202, 360, 0, 0, 2),   # two tiles: 33 to 74 rows in the last, many items
+    (202, 256, 0, 0, 0), (224, 256, 0, 0, 0), (202, 264, 0, 0, 2),   # two dQ items per CU
+    (225, 64, 0, 0, 2), (256, 64, 0, 0, 2), (257, 64, 0, 0, 3), (384, 1208, 0, 0, 3), (384, 1208, 1, 0, 0), (384, 1208, 0, 1, 0), (100, 64, 0, 0, 1),
 ])
-def test_backward_head_by_head(rules, S, causal, packed, share):
-    assert rules.bwd_by_head(ctypes.c_int64(S), causal, packed) == share
+def test_backward_head_by_head(rules, S, heads, causal, packed, share):
+    assert rules.bwd_by_head(ctypes.c_int64(S), ctypes.c_int64(heads), causal, packed) == share
 
 
 def test_gpu_cases_of_many_heads(rules):
@@ -175,7 +177,7 @@ def test_gpu_cases_of_many_heads(rules):
             assert rules.fwd_128(*map(ctypes.c_int64, (B, S, H)), causal, ctypes.c_int64(0), 1) == NARROW, (S, heads)   # (sizes alone: 4096 tokens and fewer)
         if backward:
             assert rules.one_launch_128(*map(ctypes.c_int64, (B, S, H, Hkv)), causal, ctypes.c_int64(0)) == 1, (S, heads)
-    assert any(backward and heads % 8 == 0 and rules.bwd_by_head(ctypes.c_int64(S), causal, 0) > 1 for S, heads, _, causal, backward, *_ in MANY_HEADS)
+    assert any(backward and heads % 8 == 0 and rules.bwd_by_head(ctypes.c_int64(S), ctypes.c_int64(heads), causal, 0) > 1 for S, heads, _, causal, backward, *_ in MANY_HEADS)
     assert {(D, causal, B_H % 8 != 0) for _, B_H, D, causal, _, _, _, share in MANY_HEADS if share} >= {
         (64, False, False), (64, False, True), (64, True, False), (128, False, False), (128, False, True), (128, True, False), (128, True, True)}
 
