@@ -478,7 +478,7 @@ static int launch_fwd_d(AttnParams p, int cus, hipStream_t st) {
   const int64_t grid = tiles * p.B * p.Hq;
   if (grid >= ((int64_t)1 << 31)) return kErrShape;
   p.tiles = (int32_t)tiles;
-  p.q_heavy = fwd_head_by_head(tiles, grid, p.causal != 0, p.cu != nullptr, D == 64, cus, p.B * p.Hq % 8 != 0,
+  p.q_heavy = fwd_head_by_head(tiles, grid, p.causal != 0, p.cu != nullptr, D == 64, cus, p.B * p.Hq % 8 != 0, p.Hq / p.Hkv,
                                (int64_t)p.B * p.S * p.Hkv * D * 4, p.S - (tiles - 1) * 128);
   static KernelSetup setup;
   int per_cu = 1;

@@ -195,31 +195,40 @@ inline bool fwd_flips(int64_t items, int64_t tiles, bool causal, bool packed, in
 
 // Dense forward launches that the hardware deals out: how many of a head's tiles go head by head, the heaviest first (q_heavy in
 // decode_tile), before what is left goes tile by tile over all heads?  Tile by tile a launch of many heads streams every
-// head's K and V from memory once per tile; head by head the workgroups that run together share them in L2.  Items are equal
-// in bidirectional launches, so all of them go that way (378 x 975 x 4 heads 1396 -> 865 us, 4 x 4096 x 24 779 -> 742, 40 x
-// 1000 x 16 at head dimension 64 228 -> 196).  Causal ones end on the light tiles of all heads, and the items must be enough
+// head's K and V from memory once per tile; head by head the workgroups that run together share them in L2.
+// Bidirectional items are equal, so all tiles go that way.  Head by head over tile by tile in 17705 launches of more than two items per
+// CU, D = 128 and 64, in eight lists of heads and, where the heads are no multiple of eight, in one (`one_list`: a head's workgroups
+// are spread over all XCDs):
+//   K and V of all heads (`kv_bytes`) more than 192 MiB, which the last-level cache no longer holds: lists 0.77, 0.87, one list 0.81,
+//     0.93, hardly any launch slower (45 x 1792 x 20 2507 -> 1543 us, 159 x 190 x 24 236 -> 179);
+//   else lists 0.93, 0.97, but not two unequal tiles: one of up to 64 rows (`last_rows`) D = 128 1.03, up to 1.13, D = 64 of up to four
+//     items per CU 1.015, 1.06 (54 x 163 x 32 74.8 : 80.9 us);
+//   else one list, two tiles 1.06, 1.025, up to 1.2; three and four 1.016, 1.005, but D = 128, four heads per group and more, 0.93; five to
+//     eight up to six items per CU 1.03, 1.03, more, or at D = 128 with grouped heads more than three, 0.97, 0.98; nine to sixteen up to three
+//     items 0.98, 1.01 (up to 1.1 and 1.15), more 0.93, 0.97; longer heads 0.94, 0.975 (3 x 713 x 36 45.1 : 54.0).
+// 196 of the 17705 are more than 3 % slower than tile by tile, up to 8 %; all are 0.3 % slower than with the better order.
+// Causal launches end on the light tiles of all heads, and the items must be enough
 // for the rest to even out: tile by tile : head by head, D = 128, 9 to 16 tiles, 4 to 8 items per CU 1.04 on average, 8 to 12 0.93,
-// 16 to 24 0.87, more 0.79; 17 to 32 tiles 8 to 16 items 1.005, 16 to 24 0.96, more 0.85; D = 64, three to four workgroups to a CU, 9 to
-// 16 tiles 8 to 12 items 1.06, 12 to 16 0.96; two tiles 0.97 to 1.08 at any number.  (16 x 1024 x 32, 4 per group, 215 -> 190 us; 4 x
-// 4096 x 16, D = 64, 145 : 155.)  An odd number of tiles, because an even one shares a factor with the CUs and gives the
-// heaviest tiles to the same ones (causal, all of 3, 4, 6 and 8 tiles 0.87, 1.03, 0.88, 0.95).  4113 launches of 600 to 16000
-// items: 7 % faster on average.
-// `one_list`: head counts that are no multiple of eight, whose heads are spread over all XCDs.  They gain where K and V of all
-// heads (`kv_bytes`) outgrow the last-level cache (83 x 544 x 36 769 -> 514 us, bidirectional 45 x 1792 x 20 2504 -> 1590), or where a
-// launch is long for its heads.  Bidirectional, head by head over tile by tile, mean and largest of 2450 launches: two to four tiles, up
-// to 192 MiB 0.995, 1.13, more 0.81, 1.01; five to eight tiles, up to 3 items per CU 1.03, 1.18, up to 6 0.97, 1.11, more 0.87,
-// 1.06; nine to sixteen, up to 3 0.995, 1.07, more 0.89, 1.04; longer heads 0.91, 1.02 (5 x 896 x 20 56.8 : 62.8 us, 3 x 713 x 36 45.1
-// : 54.0, 25 x 192 x 28, 2 per group, 35.0 : 38.5).
-// `last_rows`: of a head's last tile.  Two tiles of which one is not half full are unequal, and the same CUs get the fuller ones
-// (lists, D = 128: up to 32 rows 1.03, 1.06, up to 64 0.97, 1.09, up to 96 0.92, 1.03, more 0.87; 54 x 163 x 32 74.8 : 80.9 us).
-inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool packed, bool d64, int64_t cus, bool one_list = false,
-                            int64_t kv_bytes = 0, int64_t last_rows = 128) {
+// 16 to 24 0.87, more 0.79; 17 to 32 tiles 8 to 16 items 1.005, 16 to 24 0.96, more 0.85; D = 64, 9 to
+// 16 tiles 8 to 12 items 1.06, 12 to 16 0.96; two tiles 0.97 to 1.08 at any number.  (16 x 1024 x 32, 4 per group, 211 -> 192 us; 83 x
+// 544 x 36 768 -> 505.)  An odd number of tiles, because an even one shares a factor with the CUs and gives the
+// heaviest tiles to the same ones (causal, all of 3, 4, 6 and 8 tiles 0.87, 1.03, 0.88, 0.95).
+inline int fwd_head_by_head(int64_t tiles, int64_t items, bool causal, bool packed, bool d64, int64_t cus, bool one_list, int64_t group,
+                            int64_t kv_bytes, int64_t last_rows) {
   if (packed || tiles < 2 || items <= 2 * cus) return 0;
   if (!causal) {
-    if (one_list && tiles <= 4 && kv_bytes <= ((int64_t)192 << 20)) return 0;
-    if (one_list && tiles > 4 && tiles <= 16 && items <= (tiles <= 8 ? 6 : 3) * cus) return 0;
-    if (!d64 && tiles == 2 && last_rows <= 64) return 0;
-    return (int)tiles;
+    if (kv_bytes > ((int64_t)192 << 20)) return (int)tiles;
+    int64_t least = 2;   // items per CU
+    if (tiles == 2) {
+      if (one_list || (!d64 && last_rows <= 64)) return 0;
+      if (d64) least = 4;
+    } else if (one_list && tiles <= 4) {
+      if (d64 || group < 4) return 0;
+      least = 3;
+    } else if (one_list && tiles <= 16) {
+      least = tiles > 8 || (!d64 && group > 1) ? 3 : 6;
+    }
+    return items > least * cus ? (int)tiles : 0;
   }
   if (tiles < 3 || items <= (tiles > 16 ? 16 : d64 ? 12 : 8) * cus) return 0;
   const int64_t share = (tiles - tiles * 3 / 8) | 1;

@@ -22,11 +22,11 @@ extern "C" int deals(int64_t items, int one_list, int grouped, int stores) { ret
 extern "C" int flips(int64_t items, int64_t tiles, int causal, int packed) { return ie::fwd_flips(items, tiles, causal != 0, packed != 0, 256); }
 extern "C" int lazy_64(int64_t items, int causal, int packed, int64_t tiles) { return ie::fwd64_is_lazy(items, causal != 0, packed != 0, 256, tiles); }
 extern "C" int by_head(int64_t items, int64_t tiles, int causal, int packed, int d64) {
-  return ie::fwd_head_by_head(tiles, items, causal != 0, packed != 0, d64 != 0, 256);
+  return ie::fwd_head_by_head(tiles, items, causal != 0, packed != 0, d64 != 0, 256, false, 1, 0, 128);
 }
 extern "C" int by_head_of(int64_t B, int64_t S, int64_t Hq, int64_t Hkv, int causal, int64_t D) {
   const int64_t tiles = (S + 127) / 128;
-  return ie::fwd_head_by_head(tiles, tiles * B * Hq, causal != 0, false, D == 64, 256, B * Hq % 8 != 0, B * S * Hkv * D * 4, S - (tiles - 1) * 128);
+  return ie::fwd_head_by_head(tiles, tiles * B * Hq, causal != 0, false, D == 64, 256, B * Hq % 8 != 0, Hq / Hkv, B * S * Hkv * D * 4, S - (tiles - 1) * 128);
 }
 extern "C" int bwd_by_head(int64_t S, int64_t heads, int causal, int packed) {
   const int64_t tiles = (S + 127) / 128;
@@ -149,6 +149,16 @@ def by_head(rules, B, S, Hq, Hkv, causal, D):
     (54, 192, 32, 32, 0, 128, 0),
     (54, 193, 32, 32, 0, 128, 2),
     (54, 163, 32, 32, 0, 64, 2),
+    (16, 163, 32, 32, 0, 64, 0),        # up to four items per CU at head dimension 64
+    (159, 190, 24, 24, 0, 128, 2),      # K and V of all heads outgrow the last-level cache
+    (82, 190, 24, 24, 0, 128, 0),
+    (69, 538, 4, 1, 0, 128, 5),         # one list, grouped heads
+    (49, 512, 4, 1, 0, 128, 4),
+    (47, 512, 4, 1, 0, 128, 0),
+    (49, 512, 4, 2, 0, 128, 0),
+    (49, 512, 4, 1, 0, 64, 0),
+    (39, 538, 4, 2, 0, 128, 5),
+    (39, 538, 4, 2, 0, 64, 0),
     (378, 975, 4, 4, 0, 128, 8),
     (83, 544, 36, 36, 1, 128, 5),
     (118, 2230, 5, 5, 1, 64, 13),

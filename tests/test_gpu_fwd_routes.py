@@ -118,6 +118,7 @@ MANY_HEADS = [   # S, heads of all batch entries, D, causal, backward, heads, he
     (256, 1537, 128, False, False, 1, 1, 2),
     (129, 520, 64, False, False, 8, 4, 2), (384, 400, 128, False, True, 8, 2, 3), (641, 352, 128, True, False, 8, 4, 5),   # grouped heads
     (641, 354, 128, True, False, 6, 3, 5), (1152, 86, 64, False, False, 2, 2, 9),
+    (400, 196, 128, False, False, 4, 4, 4), (140, 2816, 128, False, False, 8, 1, 2),   # grouped in one list; more K and V than caches hold
 ]
 
 
