@@ -134,10 +134,11 @@ inline bool dkdv_deals(int64_t items, bool one_list, bool grouped, bool stores_d
 // launch.hpp), left for another kernel where that is ahead by 4 % (bidirectional 8 %; kNarrow of more than eight dense items per CU
 // 10 %, for its price then runs into the power limit: 4 x 4621 x 36 wide 866 : narrow 917 us).  Packed documents longer than 12
 // tiles on average count 1.3 times in 128-row items (bidirectional, 10 tiles, 1.4: 50671 x 9 in 35 documents wide 792 : narrow
-// 873): their longest are longer than the mean says.  With up to five items per CU 1.15, bidirectional up to two 1.2, since the copies
-// of attn_fwd_kernel take their addresses from scalars (3720 x 16 in 2 76 : 58 us, bidirectional 7756 x 4 in 6 94 : 71): 1347 calls
-// change kernel and take 15 % less on average, one in eighty more than 3 % more, 12 % at most.  With more items what the same prices
-// move gains 0.5 % bidirectional and loses up to 20 % (12790 x 19 in 6 781 : 934), causal 4 % and up to 12 % (19894 x 17 in 9 704 : 791).
+// 873): their longest are longer than the mean says.  With up to twelve items per CU 1.15, bidirectional up to two 1.2, since the copies
+// of attn_fwd_kernel take their addresses from scalars (3720 x 16 in 2 69 : 52 us, bidirectional 7756 x 4 in 6 71 : 50).  Narrow over
+// wide where that decides: up to five items per CU (two) 1347 calls 0.85, one in eighty more than 3 % slower; causal with more
+// 6315 calls, of even, uniform, exponential and log-uniform lengths, 0.92, even ones 0.86, one in sixteen more than 3 % slower, 14 %
+// at most (19894 x 17 in 9 704 : 791); bidirectional with more random lengths 1.01, a third more than 3 % slower, 21 % at most.
 // Wide or narrow as sizes alone say : now: 8192 x 8 179 : 154 us, 8192 x 4 145 : 121, 6000 x 8 116 : 94, 4096 x 16 90 : 79,
 // 29952 x 1 595 : 419; packed 8000 x 100 in 63 documents 74 : 30, 2222 x 2 in 4 44 : 24, 16384 x 2 in 24 53 : 32.
 // `last`: a last bidirectional round that leaves a slot of every CU free (4129 x 17 wide 228 : narrow 196 us, 5747 x 14 299 :
@@ -173,7 +174,7 @@ inline Fwd128 fwd128_route(int64_t B, int64_t S, int64_t Hq, bool causal, int64_
     }
     return n > slots ? t + again : t;
   };
-  const bool few = n128 * heads <= (causal ? 5 : 2) * (double)cus;
+  const bool few = n128 * heads <= (causal ? 12 : 2) * (double)cus;
   const double margin = causal ? 1.04 : 1.08, spread = !num_docs ? 1.0 : causal ? (doc > 12 ? (few ? 1.15 : 1.3) : 1.0) : (doc > 10 ? (few ? 1.2 : 1.4) : 1.0);
   const double many = !num_docs && n128 * heads > 8 * (double)cus ? 1.1 : margin;
   const double wide = time(kWideCost, n256, doc + 1, mean + 0.5) * (prefer_narrow ? margin : 1.0);

@@ -71,8 +71,9 @@ WIDE, NARROW, SEQ = 0, 1, 2   # enum Fwd128
     (1, 7756, 4, 0, 6, 0, NARROW),
     (1, 12790, 19, 0, 6, 0, WIDE),      # and of more items
     (1, 21359, 17, 0, 12, 0, WIDE),
-    (1, 19894, 17, 1, 9, 0, WIDE),
-    (1, 11892, 15, 1, 4, 0, WIDE),
+    (1, 19894, 17, 1, 9, 0, NARROW),   # causal up to twelve items per CU
+    (1, 11892, 15, 1, 4, 0, NARROW),
+    (1, 24000, 17, 1, 9, 0, WIDE),
     (1, 18616, 8, 1, 8, 0, NARROW),
     (1, 3000, 16, 0, 0, 1, NARROW),
     (1, 3001, 32, 1, 0, 1, NARROW),
