@@ -47,7 +47,8 @@ struct AttnParams {
   float scale, scale_log2;  // scale_log2 = scale * log2(e)
   int32_t causal;
   int32_t tiles;            // tiles per head the grid was sized for (upper bound when packed)
-  int32_t q_heavy, q_per_xcd, q_total;  // persistent launches (tile_queue.hpp): tiles per head in a list's head-by-head part, items per XCD list (0: one list), items
+  int32_t q_heavy;          // tiles per head in a list's head-by-head part (decode_tile), with a queue or without
+  int32_t q_per_xcd, q_total;  // persistent launches (tile_queue.hpp): items per XCD list (0: one list), items
   __bf16* ds;               // optional workspace: dS written by the dK/dV kernel for the dQ kernel (see ds_matrix_offset), or NULL
   // Where token t of batch entry b lives in q/dq (pitch Hq*D) and k/v/dk/dv (pitch Hkv*D), see tok_off():
   // contiguous [B,S,heads,D] tensors, or the chunks of a sequence-parallel exchange buffer (one chunk per peer).
@@ -482,15 +483,15 @@ struct TileCoord {
 // Tiles of `TS` tokens never straddle documents.  `w` is the item number a persistent workgroup
 // drew from its queue (tile_queue.hpp): item w belongs to the list of XCD w & 7 and is that
 // list's entry number w >> 3.  When B*H is a multiple of 8, list x holds the heads x, x+8, ... .
-// Its first part (empty where a workgroup gets two items at most, see tile_queue_prepare; launches without a queue:
-// fwd_head_by_head in dispatch.hpp) walks the heads one after the
-// other, the heavier 5/8 of each head's tiles from
-// the heaviest down: the workgroups of an XCD then stream the SAME head's K/V (or Q/dO) through
-// its L2 nearly in lock-step, and each is fetched from HBM once per group of co-resident tiles.
-// Its last part holds the lighter 3/8 of the tiles of all its heads, interleaved by weight, so that
+// Its first part walks the heads one after the other, `q_heavy` tiles of each, the heaviest first: the workgroups of an
+// XCD then stream the SAME head's K/V (or Q/dO) through its L2 nearly in lock-step, and each is fetched from HBM once per
+// group of co-resident tiles.  Its last part holds what is left of all its heads, interleaved by weight, so that
 // the items still running when the lists run empty are small (the kernel ends when the slowest
-// workgroup does).  Otherwise (B*H not a multiple of 8) there is one list and heads simply
-// alternate (head = w % (B*H)).  `heavy_last` says whether high tile numbers carry the most work
+// workgroup does).  q_heavy is 0 (launches of few items: all tiles by weight), a share of a head's tiles (5/8 in launches with a
+// queue, tile_queue_prepare; an odd number near it in causal forwards that the hardware deals out, fwd_head_by_head in
+// dispatch.hpp) or all of them (equal items, fwd_head_by_head and bwd_head_by_head).  When B*H is not a multiple of 8
+// there is one list, in the same two parts with LIST_BY_HEAD; without it the heads simply alternate (head = w % (B*H)),
+// whatever q_heavy says.  `heavy_last` says whether high tile numbers carry the most work
 // (forward and dq: causal rows late in a document see more keys).
 // `scratch`: 2 * THREADS / 64 + 2 ints of LDS (THREADS = workgroup size).
 template <int TS, int THREADS = kThreads, bool LIST_BY_HEAD = false>

@@ -20,10 +20,10 @@ namespace ie {
 
 // FLIP: items flip_lo .. flip_hi - 1 run in the opposite order, eight at a time (AttnParams; a kernel of its own, because the
 // order costs a small launch 0.4 us, 4 %, before its first copy).
-// LAZY (head dimension 64): unmasked blocks after a row's first look for no maximum (below).  Launches that run it have more
-// items than the CUs have SIMDs to spare, so it keeps to 128 registers, for four workgroups to a CU instead of three: 4 x 2000 x
-// 16, bidirectional, 1024 items, 89 -> 85 us, causal 49.6 -> 46.3, 4 x 8192 x 16 1165 -> 1155.  With a maximum searched for, in
-// launches of fewer items, the tighter allocation is the slower one (2 x 1000 x 8 16.3 : 16.8).
+// LAZY (head dimension 64): unmasked blocks after a row's first look for no maximum (below).  It is held to 128 registers, for four
+// workgroups to a CU; since tile coordinates and copy addresses are scalars it takes 125 and the other form 128 without being
+// told to.  Both together, against three workgroups: 4 x 2000 x 16, 1024 items, 82.7 -> 77.0 us bidirectional, 49.7 -> 43.3 causal,
+// 4 x 8192 x 16 1156 -> 1089 and 588 -> 554.
 template <int D, bool FLIP, bool LAZY>
 __global__ __launch_bounds__(kThreads, LAZY ? 4 : 2) void attn_fwd_kernel(AttnParams p) {
   constexpr int BM = 128, BN = 64;
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kThreads, LAZY ? 4 : 2) void attn_fwd_kernel(AttnPa
   const int g = tc.h / (p.Hq / p.Hkv);
   // Tile coordinates come through LDS where documents are packed, so the compiler takes them for per-lane values: as scalars
   // they leave the loop's copies no vector arithmetic (282 of 1902 VALU instructions of the kernel at head dimension 128; 2 x
-  // 4096 x 32 287 -> 276 us, 3001 x 32, 4 per group, 86.3 -> 83.4; at 64, 4 x 2000 x 16, bidirectional, 88.6 -> 86.7).
+  // 4096 x 32 282 -> 273 us, 3001 x 32, 4 per group, 85.2 -> 82.5, packed 16384 x 8 in 40 documents 64.8 -> 61.7).
   const int64_t q0 = uniform(tc.t0), doc_end = uniform(tc.doc_end);
   const int64_t q_end = (q0 + BM < doc_end) ? q0 + BM : doc_end;  // one past the tile's last row
   const int64_t k_begin = uniform(tc.doc_begin);

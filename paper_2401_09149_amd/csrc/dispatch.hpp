@@ -250,9 +250,10 @@ inline int bwd_head_by_head(int64_t tiles, int64_t last_rows, int64_t items, boo
 
 // Forward at head dimension 64: unmasked blocks without a search for their maximum (LAZY in attn_fwd.hip)?  Where a wave has
 // its SIMD to itself the search is the shorter way (lazy : search, 165 x 40 6.34 : 6.12 us, 2911 x 4 41.9 : 39.9, 5374 x 1 72.3 :
-// 68.9); with several waves per SIMD it is work that can be left out.  Lazy against search in 200 launches, on average:
-// bidirectional, up to 256 items, 1.03, 256 to 384 0.995, 512 to 640 0.965, more 0.975; causal, where an item's mean is half its
-// longest, 256 to 384 1.03, 512 to 640 1.01, 640 to 800 1.00, more 0.98; packed 384 to 512 1.035, 800 to 1024 1.00, more 0.98.
+// 68.9); with several waves per SIMD it is work that can be left out.  Lazy against search in 7173 launches with four workgroups to a
+// CU, on average by items per CU: bidirectional one to two 0.986, more 0.975; causal, where an item's mean is half its longest, one
+// to two 1.07, two to three 1.035, to 3.5 1.00, more 0.98; packed causal as causal, packed bidirectional one to two 1.01, two to three
+// 0.984, more 0.98.
 // `tiles`: of a head, or of a packed call's mean document.  Items of a few tiles are mostly masked blocks and first ones, which
 // search either way (lazy : search in 340 launches of many: one tile 1.01, two to four causal 1.015, bidirectional 1.005, from
 // five on as above; packed 1.012, from two on 1.005, from four on 0.99).

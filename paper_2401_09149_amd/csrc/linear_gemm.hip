@@ -52,7 +52,8 @@ __device__ __forceinline__ uint32_t dswz(uint32_t r) { return (r >> 1) & 7u; }
 // else, whole tile or not.  (Worked out in every step, with a path of its own for whole tiles, they were some 180
 // instructions ahead of a step's LDS reads: dw 8192 tokens 3200 x 3200 209 -> 168 us and 12288 x 4096 668 -> 633, dx 4096
 // tokens 17152 x 3200 426 -> 355, forward 2048 tokens 9600 x 3200 139 -> 123, all with 256 x 256 tiles; dw 6144 tokens
-// 512 x 1344, 64 x 64 tiles, 37 -> 29.)  Instruction t of wave w is piece w + 8 t of the SUB * EXT / 8 pieces of 1 KiB, in LDS order.
+// 512 x 1344, 64 x 64 tiles, 37 -> 29.)  Instruction t of wave w is piece w + WAVES t of the
+// SUB * EXT / 8 pieces of 1 KiB, in LDS order.
 template <bool T, int EXT, int SUB, int WAVES = kWaves>
 struct TileCopy {
   static constexpr uint32_t PIECES = EXT / 8;         // 1 KiB pieces of one 64-deep tile
@@ -588,26 +589,18 @@ __global__ __launch_bounds__(C::WAVES * 64, 1) void linear_own_kernel(GemmParams
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       const uint32_t base_a = lds_a + sa * C::A_BYTES, base_b = lds_b + sb * C::B_BYTES;
       constexpr int MF = 4 * NIB * NJB;
-      int t = 0;
+      static_assert(MF >= C::CA + C::CB, "a copy behind each of the first products");
 #pragma unroll
       for (int x = 0; x < MF; ++x) {
         const int ks = x / (NIB * NJB), ib = x / NJB % NIB, jb = x % NJB;
         acc[ib][jb] = mfma32(fj[jb][ks], fi[ib][ks], acc[ib][jb]);
         if (with_copies) {
-#pragma unroll
-          for (; t < (C::CA + C::CB) && t < x + 1; ++t) {
-            if (t < C::CA) ca.issue_piece(t, base_a, ga);
-            else cb.issue_piece(t - C::CA, base_b, gb);
-          }
+          if (x < C::CA) ca.issue_piece(x, base_a, ga);
+          else if (x < C::CA + C::CB) cb.issue_piece(x - C::CA, base_b, gb);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
       if (with_copies) {
-#pragma unroll
-        for (; t < (C::CA + C::CB); ++t) {
-          if (t < C::CA) ca.issue_piece(t, base_a, ga);
-          else cb.issue_piece(t - C::CA, base_b, gb);
-        }
         ga += W * 128;
         gb += W * 128;
         sa = sa + 1 == NA ? 0 : sa + 1;

@@ -144,7 +144,7 @@ def check(code, labels):
     return faults
 
 
-@pytest.mark.parametrize("src", ["attn_fwd.hip", "attn_fwd_wide.hip", "attn_bwd.hip"])
+@pytest.mark.parametrize("src", ["attn_fwd.hip", "attn_fwd_wide.hip", "attn_bwd.hip", "linear_gemm.hip"])
 def test_no_instruction_reads_a_register_too_early(src, tmp_path):
     out = str(tmp_path / "kernels.s")
     flags = [f for f in build.FLAGS if not f.startswith("-Rpass")] + build.SOURCE_FLAGS.get(src, [])
