@@ -331,7 +331,8 @@ inline Tile pick_tile(int64_t I, int64_t J, int64_t R, int product, int64_t cus,
 // pick_tile's choice (`other_us`), by 3 %?  They gain where a call is a few rounds of small tiles with a long contraction.  Costs per
 // 256-deep step, around a tile and of a launch, fitted, as is what makes an estimate of pick_tile's a time (kOther and what follows
 // it), to 11200 calls, each on weights that come from memory and on weights that stay in the caches: 32 to 1536 tokens, widths 512 to
-// 131072, contractions of 768 to 32768, which is the range the rule is held to, but for contractions below 1024, where nothing is
+// 131072, contractions of 768 to 32768.  The rule is held to that and what 3200 calls showed around it: widths below 512 0.88, contractions up
+// to 65536 0.87 (29 of 488 more than 3 % slower), wider outputs 1.00 and not taken, as are contractions below 1024, where nothing is
 // gained (1.00).  `once`: with few row tiles most of a step's bytes are weights that are read from memory and by one tile; `empty`:
 // rows that do not exist repeat the last one and cost less.  (Without those terms, with costs from weights that stay in the caches, 537
 // of these calls were more than 3 % slower than without these tiles on weights from memory: 362 x 11088 x 768 13.5 : 16.7 us, 85 x
@@ -349,7 +350,7 @@ inline Own pick_own(int64_t I, int64_t J, int64_t R, int64_t cus, float other_us
   constexpr float kOther = 2.101f, kAll = 0.956f, kOnce = 0.216f, kEmpty = 0.161f, kGain = 0.97f;
   const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   const auto empty = [&](int64_t ti) { return 1.f - (float)I / (float)(ceil_div(I, ti) * ti); };   // share of the tiles' rows
-  if (I < 32 || I > 1536 || J < 512 || J > 131072 || R < 1024 || R > 32768) return kOwnNone;
+  if (I < 32 || I > 1536 || J > 131072 || R < 1024 || R > 65536) return kOwnNone;
   const int64_t per_xcd = cus >= 8 ? cus / 8 : 1;
   Own best = kOwnNone;
   float best_us = (other_us + kOther) * (kAll + kOnce / (float)ceil_div(I, 64) - kEmpty * empty(other_rows)) * kGain;

@@ -370,8 +370,8 @@ def own(rules, M, N, K):
 @pytest.mark.parametrize("M,N,K,kernel", [
     (200, 12288, 4096, 3), (200, 4096, 4096, 1), (200, 4096, 11008, 1), (200, 22016, 4096, 0),
     (31, 4096, 4096, 0), (1537, 2368, 2368, 0), (1, 22016, 4096, 0), (8192, 4096, 4096, 0),
-    (48, 6144, 1024, 1), (48, 6144, 960, 0), (60, 69632, 1280, 2), (60, 131080, 1280, 0), (600, 504, 8192, 0), (1111, 5328, 14848, 3),
-    (270, 10912, 32768, 3), (270, 10912, 32832, 0),
+    (48, 6144, 1024, 1), (48, 6144, 960, 0), (60, 69632, 1280, 2), (60, 131080, 1280, 0), (1111, 5328, 14848, 3),
+    (1200, 256, 4096, 1), (1500, 328, 8192, 1), (270, 10912, 65536, 3), (270, 10912, 65600, 0),
     (362, 11088, 768, 0),      # few steps, several rounds
     (318, 13312, 1024, 0), (131, 16128, 768, 0),
     (85, 33288, 1792, 0),      # one row tile, two rounds of weights that are read once

@@ -55,6 +55,7 @@ OWN = [   # M, N, K, kernel of enum Own: the forward tiles whose waves share not
     (449, 2008, 1792, 1),     # the 256th tile of 256
     (394, 624, 2112, 1),      # 33 steps: one wave has a ninth
     (1478, 1296, 1280, 1),    # two rounds: the rings run on across tiles
+    (1250, 264, 2112, 1),     # a narrow output
     (65, 8320, 1856, 2),
     (33, 68312, 1728, 2),     # three rounds, with a step less in one wave
     (604, 1608, 1024, 2),
